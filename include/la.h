@@ -69,7 +69,10 @@ typedef enum {
  *   BF16X6 : x = hi + mid + lo (three bf16 terms, 24 significant bits);
  *            products hh + hm + mh + mm + hl + lh.
  *   AUTO   : la_gemm -> BF16X3; la_polar -> per phase (see la_polar_opts):
- *            preconditioning and H at BF16X6, Newton-Schulz at BF16X3;
+ *            preconditioning and H at BF16X6 (from n = 192 as an equivalent of
+ *            it: each operand, times a power of two, as two fp16 terms of 23
+ *            bits together, products lh + hl + hh, whose measured error is no
+ *            larger; reported as BF16X6), Newton-Schulz at BF16X3;
  *            la_inverse -> BF16X3 steps and one BF16X6 step; la_matfunc_* ->
  *            BF16X6.
  * The paper's TPU "fp32" matmul is itself a bf16-based emulation at about

@@ -14,6 +14,14 @@ namespace la {
 hipError_t launch_gemm_fp32(const GemmDesc &d, hipStream_t s);
 hipError_t launch_gemm_x3(const GemmDesc &d, hipStream_t s);
 hipError_t launch_gemm_x6(const GemmDesc &d, hipStream_t s);
+hipError_t launch_gemm_f16(const GemmDesc &d, hipStream_t s);
+hipError_t launch_grouped_f16(int, int, int, const GemmDesc *, const GroupItem *, int, int,
+                              hipStream_t);
+hipError_t launch_pack_x3(const float *, int64_t, int, int64_t, int64_t, void *, hipStream_t);
+hipError_t launch_pack_f16(const float *, int64_t, int, int64_t, int64_t, float, void *,
+                           hipStream_t);
+hipError_t launch_gemm_packed_x3(const GemmDesc &d, hipStream_t s);
+hipError_t launch_gemm_packed_f16(const GemmDesc &d, hipStream_t s);
 hipError_t launch_grouped_fp32(int, int, int, const GemmDesc *, const GroupItem *, int, int,
                                hipStream_t);
 hipError_t launch_grouped_x3(int, int, int, const GemmDesc *, const GroupItem *, int, int,
@@ -30,12 +38,12 @@ int tile_n_x6(int);
 int tile_m(int prec, int small)
 {
     return prec == PREC_FP32 ? tile_m_fp32(small)
-                             : prec == PREC_BF16X3 ? tile_m_x3(small) : tile_m_x6(small);
+                             : prec == PREC_BF16X6 ? tile_m_x6(small) : tile_m_x3(small);
 }
 int tile_n(int prec, int small)
 {
     return prec == PREC_FP32 ? tile_n_fp32(small)
-                             : prec == PREC_BF16X3 ? tile_n_x3(small) : tile_n_x6(small);
+                             : prec == PREC_BF16X6 ? tile_n_x6(small) : tile_n_x3(small);
 }
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -78,6 +86,7 @@ hipError_t launch_gemm(int prec, const GemmDesc &d, hipStream_t s)
     case PREC_FP32: return launch_gemm_fp32(d, s);
     case PREC_BF16X3: return launch_gemm_x3(d, s);
     case PREC_BF16X6: return launch_gemm_x6(d, s);
+    case PREC_F16X3: return launch_gemm_f16(d, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -93,6 +102,27 @@ hipError_t launch_gemm_grouped(int prec, int akc, int bkc, int small, const Gemm
         return launch_grouped_x3(akc, bkc, small, probs, items, num_items, grid_size, s);
     case PREC_BF16X6:
         return launch_grouped_x6(akc, bkc, small, probs, items, num_items, grid_size, s);
+    case PREC_F16X3:
+        return launch_grouped_f16(akc, bkc, small, probs, items, num_items, grid_size, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_pack(int prec, const float *X, int64_t ld, int kc, int64_t rows, int64_t k,
+                       float sc, void *out, hipStream_t s)
+{
+    switch (prec) {
+    case PREC_BF16X3: return launch_pack_x3(X, ld, kc, rows, k, out, s);
+    case PREC_F16X3: return launch_pack_f16(X, ld, kc, rows, k, sc, out, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_gemm_packed(int prec, const GemmDesc &d, hipStream_t s)
+{
+    switch (prec) {
+    case PREC_BF16X3: return launch_gemm_packed_x3(d, s);
+    case PREC_F16X3: return launch_gemm_packed_f16(d, s);
     default: return hipErrorInvalidValue;
     }
 }

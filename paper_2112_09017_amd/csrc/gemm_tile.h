@@ -35,6 +35,8 @@ namespace dev {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -64,6 +66,8 @@ template <> struct Cfg<PREC_BF16X3> {
     static constexpr int BM = 256, BN = 256, BK = 32, WM = 2, WN = 2, OCC = 1, PIPE = 1, GOCC = 1;
     static constexpr int terms = 2, entry_bytes = 16;
 };
+// two fp16 terms: the tile, stage and register use of 3xBF16
+template <> struct Cfg<PREC_F16X3> : Cfg<PREC_BF16X3> {};
 template <> struct Cfg<PREC_BF16X6> {
     static constexpr int BM = 256, BN = 256, BK = 16, WM = 2, WN = 2, OCC = 1, PIPE = 2, GOCC = 1;
     static constexpr int terms = 3, entry_bytes = 16;
@@ -79,6 +83,7 @@ template <> struct Cfg<PREC_BF16X3 | kSmall> {
     static constexpr int BM = 128, BN = 128, BK = 32, WM = 2, WN = 2, OCC = 2, PIPE = 1, GOCC = 2;
     static constexpr int terms = 2, entry_bytes = 16;
 };
+template <> struct Cfg<PREC_F16X3 | kSmall> : Cfg<PREC_BF16X3 | kSmall> {};
 template <> struct Cfg<PREC_BF16X6 | kSmall> {
     // two register stages of three terms fit within the 256 registers of two
     // workgroups per CU (at most 212 used), so one workgroup's loads and split
@@ -98,6 +103,7 @@ template <> struct Cfg<PREC_BF16X3 | kPacked> {
     static constexpr int BM = 256, BN = 256, BK = 16, WM = 2, WN = 2, OCC = 1, PIPE = 0, GOCC = 1;
     static constexpr int terms = 2, entry_bytes = 16;
 };
+template <> struct Cfg<PREC_F16X3 | kPacked> : Cfg<PREC_BF16X3 | kPacked> {};
 
 // Workgroups per CU a kernel is compiled for: the tile class's OCC, except
 // that the small 6xBF16 tile with both operands k-major (its loader keeps a
@@ -133,10 +139,12 @@ __device__ __forceinline__ float bf_hi(uint32_t p) { return __uint_as_float(p & 
 // give non-finite, possibly NaN, outputs.)
 __device__ __forceinline__ float rest(float x, float t) { return x - t; }
 
-// Split 8 FP32 values into the LDS terms of the precision.
+// Split 8 FP32 values into the LDS terms of the precision (sc: the power of two
+// an operand of PREC_F16X3 is multiplied by first; exact, and not used by the
+// others).
 template <int PREC> struct Split;
 template <> struct Split<PREC_FP32> {
-    __device__ __forceinline__ static void run(const float *v, u32x4 *o)
+    __device__ __forceinline__ static void run(const float *v, u32x4 *o, float sc = 1.0f)
     {
         o[0] = u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]),
                      __float_as_uint(v[3])};
@@ -145,7 +153,7 @@ template <> struct Split<PREC_FP32> {
     }
 };
 template <> struct Split<PREC_BF16X3> {
-    __device__ __forceinline__ static void run(const float *v, u32x4 *o)
+    __device__ __forceinline__ static void run(const float *v, u32x4 *o, float sc = 1.0f)
     {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -157,8 +165,24 @@ template <> struct Split<PREC_BF16X3> {
         }
     }
 };
+template <> struct Split<PREC_F16X3> {
+    __device__ __forceinline__ static void run(const float *v, u32x4 *o, float sc = 1.0f)
+    {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const f32x2 x = {v[2 * p] * sc, v[2 * p + 1] * sc};
+            const f16x2 h = __builtin_convertvector(x, f16x2);
+            // the remainder x - hi, exact in FP32 (one mixed-precision fma each)
+            const f32x2 r = {__builtin_fmaf(v[2 * p], sc, -(float)h[0]),
+                             __builtin_fmaf(v[2 * p + 1], sc, -(float)h[1])};
+            const f16x2 l = __builtin_convertvector(r, f16x2);
+            o[0][p] = __builtin_bit_cast(uint32_t, h);
+            o[1][p] = __builtin_bit_cast(uint32_t, l);
+        }
+    }
+};
 template <> struct Split<PREC_BF16X6> {
-    __device__ __forceinline__ static void run(const float *v, u32x4 *o)
+    __device__ __forceinline__ static void run(const float *v, u32x4 *o, float sc = 1.0f)
     {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -234,6 +258,7 @@ struct Loader {
     static constexpr int UPT = (UNITS + NT - 1) / NT;
     static_assert(UNITS % NT == 0, "every thread must own whole units");
     float v[UPT][R][8];
+    float sc = 1.0f;  // the operand's factor before the split (PREC_F16X3)
     int off[UPT];  // element offset of the unit's first element from the stage base
 
     // (row, k8) of entry q of unit uid.  KC: within each 16 consecutive units
@@ -336,7 +361,7 @@ struct Loader {
         const int k8 = k8_of(uid);
         const int row = row_of(uid, q);
         u32x4 parts[C::terms * (C::entry_bytes / 16)];
-        Split<base_prec(PREC)>::run(v[u][q], parts);
+        Split<base_prec(PREC)>::run(v[u][q], parts, sc);
         if constexpr (base_prec(PREC) == PREC_FP32) {
             u32x4 *dst =
                 reinterpret_cast<u32x4 *>(base + entry_off<ROWS, KF, C::entry_bytes>(0, row, k8));
@@ -364,7 +389,7 @@ struct Loader {
             for (int q = 0; q < R; ++q) {
                 const int row = row_of(uid, q);
                 u32x4 parts[C::terms * (C::entry_bytes / 16)];
-                Split<base_prec(PREC)>::run(v[u][q], parts);
+                Split<base_prec(PREC)>::run(v[u][q], parts, sc);
                 if constexpr (base_prec(PREC) == PREC_FP32) {
                     u32x4 *dst = reinterpret_cast<u32x4 *>(
                         base + entry_off<ROWS, KF, C::entry_bytes>(0, row, k8));
@@ -390,11 +415,24 @@ template <> struct Products<PREC_BF16X3> {
     static constexpr int a[3] = {1, 0, 0};
     static constexpr int b[3] = {0, 1, 0};
 };
+template <> struct Products<PREC_F16X3> : Products<PREC_BF16X3> {};
 template <> struct Products<PREC_BF16X6> {
     static constexpr int n = 6;
     static constexpr int a[6] = {2, 0, 1, 1, 0, 0};
     static constexpr int b[6] = {0, 2, 1, 0, 1, 0};
 };
+
+// One 32 x 32 x 16 product on the matrix cores; fragments are kept as 16-byte
+// bf16 vectors whatever 16-bit type they hold.
+template <int PREC>
+__device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c)
+{
+    if constexpr (base_prec(PREC) == PREC_F16X3)
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a),
+                                                      __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
 
 // One K stage of MFMAs from LDS.  Fragment reads are issued in the order the
 // MFMAs first need them (the first MFMA waits for two reads, later ones for
@@ -462,8 +500,7 @@ __device__ __forceinline__ void compute_stage(const char *sA, const char *sB,
                 for (int i = 0; i < FM; ++i)
 #pragma unroll
                     for (int j = 0; j < FN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            a[i][P::a[p]], b[j][P::b[p]], acc[i][j], 0, 0, 0);
+                        acc[i][j] = mfma16<PREC>(a[i][P::a[p]], b[j][P::b[p]], acc[i][j]);
         }
     }
 }
@@ -535,8 +572,7 @@ __device__ __forceinline__ void compute_half_interleaved(const char *sA, const c
 #pragma clang loop unroll(full)
         for (int m = 0; m < NM; ++m) {
             const int p = m / (FM * FN), i = (m / FN) % FM, j = m % FN;
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][P::a[p]], b[j][P::b[p]],
-                                                               acc[i][j], 0, 0, 0);
+            acc[i][j] = mfma16<PREC>(a[i][P::a[p]], b[j][P::b[p]], acc[i][j]);
             if (m % GS == GS - 1) {
                 between(m / GS);
                 // split work of one entry: ~6 VALU per 2 values per term
@@ -598,12 +634,12 @@ __device__ __forceinline__ void stage_x3_pipe1(const char *sA, const char *sB,
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[i][1], b0[j][0], acc[i][j], 0, 0, 0);
+            acc[i][j] = mfma16<PR>(a0[i][1], b0[j][0], acc[i][j]);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[i][0], b0[j][1], acc[i][j], 0, 0, 0);
+            acc[i][j] = mfma16<PR>(a0[i][0], b0[j][1], acc[i][j]);
     __builtin_amdgcn_sched_barrier(0);
     read_a<PR>(a1, sA, 1, 1, wm, lane);   // second half: lo A, hi B first
     read_b<PR>(b1, sB, 0, 1, wn, lane);
@@ -611,7 +647,7 @@ __device__ __forceinline__ void stage_x3_pipe1(const char *sA, const char *sB,
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[i][0], b0[j][0], acc[i][j], 0, 0, 0);
+            acc[i][j] = mfma16<PR>(a0[i][0], b0[j][0], acc[i][j]);
     __builtin_amdgcn_sched_barrier(0);
     read_a<PR>(a1, sA, 0, 1, wm, lane);
     read_b<PR>(b1, sB, 1, 1, wn, lane);
@@ -621,7 +657,7 @@ __device__ __forceinline__ void stage_x3_pipe1(const char *sA, const char *sB,
     for (int m = 0; m < NM; ++m) {
         const int p = m / (FM * FN), i = (m / FN) % FM, j = m % FN;
         const int ta = p == 0 ? 1 : 0, tb = p == 1 ? 1 : 0;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[i][ta], b1[j][tb], acc[i][j], 0, 0, 0);
+        acc[i][j] = mfma16<PR>(a1[i][ta], b1[j][tb], acc[i][j]);
         if (m % GS == GS - 1) {
             between(m / GS);
 #pragma unroll
@@ -815,13 +851,13 @@ __device__ __forceinline__ void interleave_hint()
     using G = Geo<PREC>;
     using C = Cfg<PREC>;
     constexpr int BP = base_prec(PREC);
-    constexpr int NPROD = BP == PREC_FP32 ? 8 : BP == PREC_BF16X3 ? 3 : 6;
+    constexpr int NPROD = BP == PREC_FP32 ? 8 : C::terms == 2 ? 3 : 6;
     constexpr int NMFMA = G::FM * G::FN * NPROD * NKF;
     constexpr int NREAD = (G::FM + G::FN) * C::terms * (C::entry_bytes / 16) * NKF;
     // LDS writes of one stage: (rows of A + rows of B) x BK / 8 entries per
     // term, spread over the workgroup
     constexpr int NWRITE = (C::BM + C::BN) * (C::BK / 8) * C::terms * (C::entry_bytes / 16) / G::NT;
-    constexpr int VALU_PER = BP == PREC_FP32 ? 0 : BP == PREC_BF16X3 ? 4 : 2;
+    constexpr int VALU_PER = BP == PREC_FP32 ? 0 : C::terms == 2 ? 4 : 2;
     constexpr int W_EVERY = NMFMA / NWRITE > 0 ? NMFMA / NWRITE : 1;
     __builtin_amdgcn_sched_group_barrier(0x100, NREAD, 0);
 #pragma unroll
@@ -852,6 +888,8 @@ __device__ __forceinline__ void k_loop2(const GemmDesc &d, int64_t row0, int64_t
     using LB = Loader<C::BN, BK, G::NT, BKC>;
     LA la[2];
     LB lb[2];
+    la[0].sc = la[1].sc = d.scale_a;
+    lb[0].sc = lb[1].sc = d.scale_b;
     const int64_t nst = (d.K + BK - 1) / BK;
     const int64_t nfull = GUARD ? 0 : d.K / BK;
     if (nst == 0)
@@ -940,6 +978,8 @@ __device__ __forceinline__ void k_loop1(const GemmDesc &d, int64_t row0, int64_t
     constexpr int BK = C::BK;
     Loader<C::BM, BK, G::NT, AKC> la;
     Loader<C::BN, BK, G::NT, BKC> lb;
+    la.sc = d.scale_a;
+    lb.sc = d.scale_b;
     const int64_t nst = (d.K + BK - 1) / BK;
     const int64_t nfull = GUARD ? 0 : d.K / BK;
     if (nst == 0)
@@ -982,7 +1022,7 @@ __device__ __forceinline__ void k_loop1(const GemmDesc &d, int64_t row0, int64_t
             __builtin_amdgcn_sched_barrier(0);
             la.template store<PREC>(sn);
             lb.template store<PREC>(sn + G::a_bytes);
-        } else if constexpr (base_prec(PREC) == PREC_BF16X3) {
+        } else if constexpr (Cfg<PREC>::terms == 2) {
             stage_x3_pipe1<PREC, EA + EB_>(sc, sc + G::a_bytes, acc, wm, wn, lane, between);
         } else {
             compute_stage<PREC, 0, 1>(sc, sc + G::a_bytes, acc, wm, wn, lane);
@@ -1178,10 +1218,10 @@ __host__ __device__ inline int64_t packed_kstride(int64_t rbt)
     return (2 * rbt + kPackPadKiB) << 10;
 }
 
-template <bool KC>
+template <int PREC, bool KC>
 __global__ void __launch_bounds__(256) pack_x3_kernel(const float *__restrict__ X, int64_t ld,
                                                       int64_t R, int64_t K, int64_t kbt,
-                                                      int64_t rbt, int vec,
+                                                      int64_t rbt, int vec, float sc,
                                                       char *__restrict__ out)
 {
     __shared__ float tile[32][kPackSlabK + 1];
@@ -1241,7 +1281,7 @@ __global__ void __launch_bounds__(256) pack_x3_kernel(const float *__restrict__ 
             for (int j = 0; j < 8; ++j)
                 v[j] = tile[r][kk + j];
             u32x4 parts[2];
-            Split<PREC_BF16X3>::run(v, parts);
+            Split<PREC>::run(v, parts, sc);
             char *chunk = out + kb * packed_kstride(rbt) + ((rb * 2) << 10);
             *reinterpret_cast<u32x4 *>(chunk + lane * 16) = parts[0];
             *reinterpret_cast<u32x4 *>(chunk + 1024 + lane * 16) = parts[1];
@@ -1373,12 +1413,12 @@ __device__ __forceinline__ void packed_stage(int ss, int nst, f32x16 (&acc)[Geo<
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo[i], bhi[j], acc[i][j], 0, 0, 0);
+            acc[i][j] = mfma16<P>(alo[i], bhi[j], acc[i][j]);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi[i], blo[j], acc[i][j], 0, 0, 0);
+            acc[i][j] = mfma16<P>(ahi[i], blo[j], acc[i][j]);
     __builtin_amdgcn_sched_barrier(0);
     const bool more = ss + 1 < nst;
     const char *nst_ = smem + ((ss + 1) & (NS - 1)) * G::stage_bytes;
@@ -1399,7 +1439,7 @@ __device__ __forceinline__ void packed_stage(int ss, int nst, f32x16 (&acc)[Geo<
     for (int j = 0; j < FN; ++j) {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi[i], bhi[j], acc[i][j], 0, 0, 0);
+            acc[i][j] = mfma16<P>(ahi[i], bhi[j], acc[i][j]);
         if (more)
             bhi[j] = *reinterpret_cast<const bf16x8 *>(nst_ + G::a_bytes +
                                                        frag_off<C::BN, 1, 16>(0, wn * FN + j, 0, lane));
@@ -1612,8 +1652,9 @@ inline size_t packed_bytes(int64_t R, int64_t K)
     return rbt == 0 ? 0 : (size_t)kbt * (size_t)packed_kstride(rbt);
 }
 
-inline hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t R, int64_t K,
-                                 char *out, hipStream_t s)
+template <int PREC>
+hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t R, int64_t K, float sc,
+                          char *out, hipStream_t s)
 {
     const int64_t rbt = (R + kPackRows - 1) / kPackRows * (kPackRows / 32);
     const int64_t kbt = (K + 15) / 16;
@@ -1625,22 +1666,23 @@ inline hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t R, 
     const unsigned gy = (unsigned)(rbt < 65535 ? rbt : 65535);
     const int vec = ((uintptr_t)X % 16 == 0 && ld % 4 == 0) ? 1 : 0;
     if (kc)
-        hipLaunchKernelGGL((pack_x3_kernel<true>), dim3((unsigned)gx, gy), dim3(256), 0, s, X, ld,
-                           R, K, kbt, rbt, vec, out);
+        hipLaunchKernelGGL((pack_x3_kernel<PREC, true>), dim3((unsigned)gx, gy), dim3(256), 0, s, X,
+                           ld, R, K, kbt, rbt, vec, sc, out);
     else
-        hipLaunchKernelGGL((pack_x3_kernel<false>), dim3((unsigned)gx, gy), dim3(256), 0, s, X, ld,
-                           R, K, kbt, rbt, vec, out);
+        hipLaunchKernelGGL((pack_x3_kernel<PREC, false>), dim3((unsigned)gx, gy), dim3(256), 0, s, X,
+                           ld, R, K, kbt, rbt, vec, sc, out);
     return hipGetLastError();
 }
 
-inline hipError_t launch_packed_x3(const GemmDesc &d, hipStream_t s)
+template <int PREC>
+hipError_t launch_packed_x3(const GemmDesc &d, hipStream_t s)
 {
     if (d.num_tiles <= 0)
         return hipSuccess;
     const int sl = d.slices > 1 ? d.slices : 1;
     if (sl > 1 && (d.slice_k <= 0 || d.slice_k % 16 != 0 || sl > 65535))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL((gemm_packed_kernel<PREC_BF16X3 | kPacked>), dim3(d.num_tiles, sl),
+    hipLaunchKernelGGL((gemm_packed_kernel<PREC | kPacked>), dim3(d.num_tiles, sl),
                        dim3(256), 0, s, d);
     return hipGetLastError();
 }

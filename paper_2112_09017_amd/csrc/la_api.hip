@@ -166,12 +166,13 @@ struct PolarWs {
 };
 
 // Whether an M x N x K product takes the packed-operand kernel inside an
-// iteration: 3xBF16 on 256 x 256 tiles (at least 128 of them) with K >= 256,
-// as in la_gemm_ws.  The packed kernel computes every product exactly as the
-// unpacked one, so the choice never changes a result.
+// iteration: 3xBF16 or F16X3 on 256 x 256 tiles (at least 128 of them) with
+// K >= 256, as in la_gemm_ws.  The packed kernel computes every product exactly
+// as the unpacked one, so the choice never changes a result.
 static bool packs(int prec, int64_t M, int64_t N, int64_t K)
 {
-    return prec == PREC_BF16X3 && K >= 256 && ((M + 255) / 256) * ((N + 255) / 256) >= 128;
+    return (prec == PREC_BF16X3 || prec == PREC_F16X3) && K >= 256 &&
+           ((M + 255) / 256) * ((N + 255) / 256) >= 128;
 }
 
 // Bytes of the packed op(A) and op(B)^T of such a product (0 if it does not pack).
@@ -193,35 +194,41 @@ static hipError_t gemm_packed_or_plain(int prec, GemmDesc d, char *pk, hipStream
         char *pa = pk, *pb = pk + align_up256(packed_x3_bytes(d.M, d.K));
         hipError_t e = hipSuccess;
         if (!pre_a)
-            e = launch_pack_x3(d.A, d.lda, d.a_kcontig, d.M, d.K, pa, s);
+            e = launch_pack(prec, d.A, d.lda, d.a_kcontig, d.M, d.K, d.scale_a, pa, s);
         if (e == hipSuccess && !pre_b)
-            e = launch_pack_x3(d.B, d.ldb, d.b_kcontig, d.N, d.K, pb, s);
+            e = launch_pack(prec, d.B, d.ldb, d.b_kcontig, d.N, d.K, d.scale_b, pb, s);
         if (e != hipSuccess)
             return e;
         d.A = (const float *)(pre_a ? pre_a : pa);
         d.B = (const float *)(pre_b ? pre_b : pb);
-        return launch_gemm_packed_x3(d, s);
+        return launch_gemm_packed(prec, d, s);
     }
     return launch_gemm(prec, d, s);
 }
 
 // Whether a Gram X^T X (n x n, K = m) at prec runs on the packed-operand
-// kernel: 3xBF16 with at least 128 upper 256 x 256 tiles and K >= 256.  X^T is
+// kernel: 3xBF16 or F16X3 with at least 128 upper 256 x 256 tiles and K >= 256.  X^T is
 // packed once and serves as both operands.
 static bool gram_packs(int prec, int64_t m, int64_t n)
 {
     const int64_t nb = (n + 255) / 256;
-    return prec == PREC_BF16X3 && m >= 256 && nb * (nb + 1) / 2 >= 128;
+    return (prec == PREC_BF16X3 || prec == PREC_F16X3) && m >= 256 && nb * (nb + 1) / 2 >= 128;
 }
 
 // Packed copies the iteration keeps: X and P for a packed update, or X^T for
-// a packed Gram (the Gram's pack is consumed before the update packs).
+// a packed Gram (the Gram's pack is consumed before the update packs).  Steps
+// at 3xBF16 size the region; F16X3 steps (the same bytes) use it where it is
+// there and run unpacked otherwise, with the same result.
 static size_t packed_update_bytes(const PolarPlan &p)
 {
-    size_t b = std::max(pack_bytes(p.prec_pre, p.m, p.n, p.n), pack_bytes(p.prec_ns, p.m, p.n, p.n));
-    for (int pr : {p.prec_pre, p.prec_ns})
+    size_t b = 0;
+    for (int pr : {p.prec_pre, p.prec_ns}) {
+        if (pr != PREC_BF16X3)
+            continue;
+        b = std::max(b, pack_bytes(pr, p.m, p.n, p.n));
         if (gram_packs(pr, p.m, p.n))
             b = std::max(b, align_up256(packed_x3_bytes(p.n, p.m)));
+    }
     return b;
 }
 
@@ -304,10 +311,12 @@ static PolarWs carve(const PolarPlan &p, void *ws)
 // X1^T X2 for K x n operands X1, X2 (row-major, leading dimensions ld1, ld2)
 // as about `want` K-slices in one Gram-mode launch: slice y writes the upper
 // triangle (i <= j) of its n x n part, the sum over its k range, at
-// parts + y n^2.  *count receives the number of slices.
-static hipError_t gram_slices(int prec, const float *X1, int64_t ld1, const float *X2,
-                              int64_t ld2, int64_t K, int64_t n, int want, float *parts,
-                              int *count, hipStream_t s, char *pk = nullptr)
+// parts + y n^2.  *count receives the number of slices.  sc1, sc2: the
+// operands' factors where prec is F16X3.
+static hipError_t gram_slices(int prec, const float *X1, int64_t ld1, float sc1,
+                              const float *X2, int64_t ld2, float sc2, int64_t K, int64_t n,
+                              int want, float *parts, int *count, hipStream_t s,
+                              char *pk = nullptr)
 {
     GemmDesc d;
     memset(&d, 0, sizeof d);
@@ -325,6 +334,7 @@ static hipError_t gram_slices(int prec, const float *X1, int64_t ld1, const floa
     d.C = parts;
     d.ldc = n;
     d.alpha = 1.0f;
+    gemm_f16_scales(d, prec, sc1, sc2);
     gemm_finalize(d, prec);
     d.slices = slice_plan(K, want, &d.slice_k);
     d.slice_stride = n * n;
@@ -332,12 +342,12 @@ static hipError_t gram_slices(int prec, const float *X1, int64_t ld1, const floa
     if (pk && X1 == X2 && ld1 == ld2 && gram_packs(prec, K, n) && !d.small) {
         // X^T (n rows, K) packed once and read as both operands; the packed
         // kernel computes every product exactly as the unpacked one
-        hipError_t e = launch_pack_x3(X1, ld1, 0, n, K, pk, s);
+        hipError_t e = launch_pack(prec, X1, ld1, 0, n, K, d.scale_a, pk, s);
         if (e != hipSuccess)
             return e;
         d.A = (const float *)pk;
         d.B = (const float *)pk;
-        return launch_gemm_packed_x3(d, s);
+        return launch_gemm_packed(prec, d, s);
     }
     return launch_gemm(prec, d, s);
 }
@@ -366,6 +376,7 @@ static hipError_t gram_step(const PolarPlan &p, int prec, const float *X, int64_
         d.K = m;
         d.alpha = (float)alpha;
         d.gamma = (float)gamma;
+        gemm_f16_scales(d, prec, kIterScale, kIterScale);
         gemm_finalize(d, prec);
         return launch_gemm(prec, d, s);
     }
@@ -373,7 +384,8 @@ static hipError_t gram_step(const PolarPlan &p, int prec, const float *X, int64_
     // the upper triangle of its own n x n part, and the parts are added in
     // slice order in FP64
     int count = 0;
-    hipError_t e = gram_slices(prec, X, ldx, X, ldx, m, n, splits, w.parts, &count, s, w.pk);
+    hipError_t e = gram_slices(prec, X, ldx, kIterScale, X, ldx, kIterScale, m, n, splits, w.parts,
+                               &count, s, w.pk);
     if (e != hipSuccess)
         return e;
     return launch_splitk_sym_reduce(w.parts, n * n, count, n, alpha, gamma, P, n, s);
@@ -403,6 +415,7 @@ static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int6
         d.C = w.parts;
         d.ldc = n;
         d.alpha = 1.0f;
+        gemm_f16_scales(d, prec, kIterScale, kIterScale);
         gemm_finalize(d, prec);
         d.slices = slice_plan(n, splits, &d.slice_k);
         d.slice_stride = m * n;
@@ -423,6 +436,7 @@ static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int6
         d.beta = (float)beta;
     }
     d.partials = tiles;
+    gemm_f16_scales(d, prec, kIterScale, kIterScale);
     gemm_finalize(d, prec);
     if (ntiles)
         *ntiles = d.tiles_m * d.tiles_n;
@@ -434,15 +448,19 @@ static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int6
 // kMaxAccK rows of the K = m sum), and the 2 s slices are added in FP64 with
 // the factor 1/2 and written to both triangles, so H is exactly symmetric.
 static hipError_t h_step(const PolarPlan &p, const float *U, int64_t ldu, const float *A,
-                         int64_t lda, float *H, int64_t ldh, const PolarWs &w, hipStream_t s)
+                         int64_t lda, double fro, float *H, int64_t ldh, const PolarWs &w,
+                         hipStream_t s)
 {
     const int64_t n = p.n;
     const int want = h_splits(p);
+    float sc = 1.0f;
+    const int prec = h_prec(p.prec_h, fro, &sc);
     int c1 = 0, c2 = 0;
-    hipError_t e = gram_slices(p.prec_h, U, ldu, A, lda, p.m, n, want, w.parts, &c1, s);
+    hipError_t e = gram_slices(prec, U, ldu, kIterScale, A, lda, sc, p.m, n, want, w.parts, &c1, s);
     if (e != hipSuccess)
         return e;
-    e = gram_slices(p.prec_h, A, lda, U, ldu, p.m, n, want, w.parts + (size_t)c1 * n * n, &c2, s);
+    e = gram_slices(prec, A, lda, sc, U, ldu, kIterScale, p.m, n, want,
+                    w.parts + (size_t)c1 * n * n, &c2, s);
     if (e != hipSuccess)
         return e;
     return launch_splitk_sym_reduce(w.parts, n * n, c1 + c2, n, 0.5, 0.0, H, ldh, s);
@@ -853,7 +871,8 @@ la_status la_pack_bf16x3(la_context *ctx, int kc, int64_t rows, int64_t k, const
         return LA_ERR_INVALID_ARG;
     }
     LA_HIP(hipSetDevice(ctx->device), "la_pack_bf16x3: hipSetDevice");
-    LA_HIP(launch_pack_x3(X, ld, kc ? 1 : 0, rows, k, packed, (hipStream_t)hip_stream),
+    LA_HIP(launch_pack(PREC_BF16X3, X, ld, kc ? 1 : 0, rows, k, 1.0f, packed,
+                       (hipStream_t)hip_stream),
            "la_pack_bf16x3: launch");
     return LA_OK;
 }
@@ -902,7 +921,7 @@ la_status la_gemm_packed(la_context *ctx, int64_t m, int64_t n, int64_t k, float
     d.tiles_m = (int)((m + 255) / 256);
     d.tiles_n = (int)((n + 255) / 256);
     d.num_tiles = d.tiles_m * d.tiles_n;
-    LA_HIP(launch_gemm_packed_x3(d, (hipStream_t)hip_stream), "la_gemm_packed: launch");
+    LA_HIP(launch_gemm_packed(PREC_BF16X3, d, (hipStream_t)hip_stream), "la_gemm_packed: launch");
     return LA_OK;
 }
 
@@ -951,14 +970,14 @@ la_status la_gemm_ws(la_context *ctx, int trans_a, int trans_b, int64_t m, int64
     }
     char *wa = (char *)workspace, *wb = wa + pa;
     // op(A) rows are the output rows; op(B)^T rows are the output columns
-    LA_HIP(launch_pack_x3(A, lda, trans_a ? 0 : 1, m, k, wa, s), "la_gemm_ws: pack A");
-    LA_HIP(launch_pack_x3(B, ldb, trans_b ? 1 : 0, n, k, wb, s), "la_gemm_ws: pack B");
+    LA_HIP(launch_pack(PREC_BF16X3, A, lda, trans_a ? 0 : 1, m, k, 1.0f, wa, s), "la_gemm_ws: pack A");
+    LA_HIP(launch_pack(PREC_BF16X3, B, ldb, trans_b ? 1 : 0, n, k, 1.0f, wb, s), "la_gemm_ws: pack B");
     d.A = (const float *)wa;
     d.B = (const float *)wb;
     d.tiles_m = (int)((m + 255) / 256);
     d.tiles_n = (int)((n + 255) / 256);
     d.num_tiles = d.tiles_m * d.tiles_n;
-    LA_HIP(launch_gemm_packed_x3(d, s), "la_gemm_ws: launch");
+    LA_HIP(launch_gemm_packed(PREC_BF16X3, d, s), "la_gemm_ws: launch");
     return LA_OK;
 }
 
@@ -1058,9 +1077,9 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
 
     la_polar_info inf;
     memset(&inf, 0, sizeof inf);
-    inf.prec_precond = p.prec_pre;
-    inf.prec_ns = p.prec_ns;
-    inf.prec_h = p.prec_h;
+    inf.prec_precond = public_prec(p.prec_pre);
+    inf.prec_ns = public_prec(p.prec_ns);
+    inf.prec_h = public_prec(p.prec_h);
     inf.last_delta = INFINITY;
     inf.stop_reason = 2;
 
@@ -1136,7 +1155,7 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
         LA_HIP(launch_copy(buf[cur], ld[cur], U, ldu, m, n, s), "la_polar: copy");
 
     if (H)
-        LA_HIP(h_step(p, U, ldu, A, lda, H, ldh, w, s), "la_polar: H");
+        LA_HIP(h_step(p, U, ldu, A, lda, fro, H, ldh, w, s), "la_polar: H");
     LA_HIP(hipStreamSynchronize(s), "la_polar: final sync");
     if (info)
         *info = inf;
@@ -1250,7 +1269,7 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
     int cur = 0;
     LA_HIP(launch_transpose_scale(A, lda, buf[cur], ld[cur], n, m, a, s), "la_inverse: X0");
     if (w.pka)   // A as op(A) of A X (k contiguous) or as op(B)^T of X A (k-major)
-        LA_HIP(launch_pack_x3(A, lda, p.wide ? 1 : 0, p.r, p.wide ? p.m : p.n, w.pka, s),
+        LA_HIP(launch_pack(p.prec, A, lda, p.wide ? 1 : 0, p.r, p.wide ? p.m : p.n, 1.0f, w.pka, s),
                "la_inverse: pack A");
 
     const double scale = p.literal ? 1.0 : sqrt(a);

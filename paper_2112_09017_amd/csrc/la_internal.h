@@ -36,6 +36,9 @@ struct GemmDesc {
     int64_t lda, ldb, ldc, lde;
     int64_t M, N, K;
     float alpha, beta, gamma;
+    // PREC_F16X3: powers of two op(A) and op(B) are multiplied by before their
+    // split (the caller divides alpha by their product: gemm_f16_scales)
+    float scale_a, scale_b;
     int a_kcontig, b_kcontig;
     int gram;
     int gram_upper;    // gram: write only the upper triangle (no mirror)
@@ -64,6 +67,18 @@ void gemm_finalize(GemmDesc &d, int prec);
 // and the tile counts that follow from it; the products are the same either way.
 void gemm_set_class(GemmDesc &d, int prec, int small);
 
+// Sets the factors of a PREC_F16X3 product (powers of two sa, sb with |sa a| and
+// |sb b| below the fp16 range for every entry of its operands) and takes them
+// out of alpha again; other precisions are left as they are.
+inline void gemm_f16_scales(GemmDesc &d, int prec, float sa, float sb)
+{
+    if (prec == PREC_F16X3) {
+        d.scale_a = sa;
+        d.scale_b = sb;
+        d.alpha /= sa * sb;
+    }
+}
+
 hipError_t launch_gemm(int prec, const GemmDesc &d, hipStream_t s);
 
 // MI355X dispatches consecutive workgroups round-robin over its 8 XCDs.
@@ -85,16 +100,17 @@ hipError_t launch_gemm_grouped(int prec, int a_kcontig, int b_kcontig, int small
                                const GroupItem *items_dev, int num_items,
                                int grid_size, hipStream_t s);
 
-// Packed 3xBF16 operands (gemm_x3.hip): op(X) (rows x k; kc: k contiguous,
+// Packed operands of two 16-bit terms (gemm_x3.hip: 3xBF16, gemm_f16x3.hip:
+// F16X3, whose entries are multiplied by sc before the split): op(X) (rows x k; kc: k contiguous,
 // X[r * ld + k], else X[k * ld + r]) split into bf16 hi/lo terms and laid out
 // in the GEMM's LDS fragment order, zero-padded to 256 rows and 16 k.
 size_t packed_x3_bytes(int64_t rows, int64_t k);
-hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t rows, int64_t k, void *out,
-                          hipStream_t s);
+hipError_t launch_pack(int prec, const float *X, int64_t ld, int kc, int64_t rows, int64_t k,
+                       float sc, void *out, hipStream_t s);
 // GEMM on packed operands: d.A and d.B point at packed op(A) (M x K) and
 // packed op(B)^T (N x K); 256 x 256 tiles (d.small must be 0).  Computes the
-// same products in the same order as the 3xBF16 kernel of launch_gemm.
-hipError_t launch_gemm_packed_x3(const GemmDesc &d, hipStream_t s);
+// same products in the same order as launch_gemm's kernel of that precision.
+hipError_t launch_gemm_packed(int prec, const GemmDesc &d, hipStream_t s);
 
 // C (rows x cols, ldc) <- C - Y Z with Y (rows x K, k contiguous, ldy) and
 // Z (K x cols, ldz), K <= 128 (qr_update.hip): the short-K update of

@@ -66,9 +66,9 @@ constexpr int kMaxSlots = 4096;
 // from larger ones.
 constexpr int kMaxBands = 2;
 constexpr double kBandWork = 2048.0 * 2048.0 * 2048.0;
-// launch groups of one staging pass: 3 precisions x 2 tile classes x 2 phases,
-// each with its descriptors and its items padded to kAlign
-constexpr int kMaxGroups = 12;
+// launch groups of one staging pass: 4 product arithmetics x 2 tile classes x 2
+// phases, each with its descriptors and its items padded to kAlign
+constexpr int kMaxGroups = 16;
 static_assert(2 * kMaxSlots * sizeof(double) <= kRedBytes, "norms of one tick");
 static_assert(2 * sizeof(ReduceItem) <= sizeof(GemmDesc), "reduce items in a descriptor slot");
 
@@ -170,8 +170,10 @@ void add_problem(std::vector<Launch> &ls, int prec, int akc, int bkc, const Gemm
         L->items.push_back(GroupItem{pid, t});
 }
 
+// sc1, sc2: the operands' factors where prec is F16X3
 GemmDesc gram_desc(const float *X1, const float *X2, float *C, int64_t m, int64_t n,
-                   float alpha, float gamma, int upper, int prec)
+                   float alpha, float gamma, int upper, int prec, float sc1 = kIterScale,
+                   float sc2 = kIterScale)
 {
     GemmDesc d;
     memset(&d, 0, sizeof d);
@@ -188,11 +190,13 @@ GemmDesc gram_desc(const float *X1, const float *X2, float *C, int64_t m, int64_
     d.gamma = gamma;
     d.gram = 1;
     d.gram_upper = upper;
+    gemm_f16_scales(d, prec, sc1, sc2);
     gemm_finalize(d, prec);
     return d;
 }
 
-GemmDesc update_desc(const float *X, const float *P, float *Xn, int64_t m, int64_t n, int prec)
+GemmDesc update_desc(const float *X, const float *P, float *Xn, int64_t m, int64_t n,
+                     float alpha, int prec)
 {
     GemmDesc d;
     memset(&d, 0, sizeof d);
@@ -206,6 +210,8 @@ GemmDesc update_desc(const float *X, const float *P, float *Xn, int64_t m, int64
     d.M = m;
     d.N = n;
     d.K = n;
+    d.alpha = alpha;
+    gemm_f16_scales(d, prec, kIterScale, kIterScale);
     gemm_finalize(d, prec);
     return d;
 }
@@ -261,7 +267,7 @@ struct HipExec {
             if (!pr)
                 continue;
             const GemmDesc g = gram_desc(nullptr, nullptr, nullptr, r.m, r.n, 1.0f, 0.0f, 0, pr);
-            const GemmDesc u = update_desc(nullptr, nullptr, nullptr, r.m, r.n, pr);
+            const GemmDesc u = update_desc(nullptr, nullptr, nullptr, r.m, r.n, 1.0f, pr);
             it = std::max(it, (size_t)g.num_tiles + (size_t)u.num_tiles);
         }
         const GemmDesc h = gram_desc(nullptr, nullptr, nullptr, r.m, r.n, 1.0f, 0.0f, 1,
@@ -453,16 +459,14 @@ struct HipExec {
             const int prec = r->step_prec();
             GemmDesc gd = gram_desc(d->X[d->cur], d->X[d->cur], d->P, r->m, r->n,
                                     pre ? (float)(-p.c) : -1.0f, 1.0f, 0, prec);
-            GemmDesc ud = update_desc(d->X[d->cur], d->P, d->X[d->cur ^ 1], r->m, r->n, prec);
+            GemmDesc ud = update_desc(d->X[d->cur], d->P, d->X[d->cur ^ 1], r->m, r->n,
+                                      pre ? (float)p.a : 0.5f, prec);
             if (all_large) {
                 gemm_set_class(gd, prec, 0);
                 gemm_set_class(ud, prec, 0);
             }
             add_problem(grams, prec, 0, 0, gd);
-            if (pre) {
-                ud.alpha = (float)p.a;
-            } else {
-                ud.alpha = 0.5f;
+            if (!pre) {
                 ud.beta = 1.0f;
                 ud.E = d->X[d->cur];
                 ud.lde = r->n;
@@ -524,11 +528,14 @@ struct HipExec {
         for (serve::Req *r : done) {
             DevReq *d = (DevReq *)r->x;
             const float *U = d->X[d->cur];
-            add_problem(hs, r->plan.prec_h, 0, 0,
-                        gram_desc(U, d->A, d->X[d->cur ^ 1], r->m, r->n, 1.0f, 0.0f, 1,
-                                  r->plan.prec_h));
-            add_problem(hs, r->plan.prec_h, 0, 0,
-                        gram_desc(d->A, U, d->P, r->m, r->n, 1.0f, 0.0f, 1, r->plan.prec_h));
+            float sc = 1.0f;
+            const int prec = h_prec(r->plan.prec_h, r->info.fro_norm_a, &sc);
+            add_problem(hs, prec, 0, 0,
+                        gram_desc(U, d->A, d->X[d->cur ^ 1], r->m, r->n, 1.0f, 0.0f, 1, prec,
+                                  kIterScale, sc));
+            add_problem(hs, prec, 0, 0,
+                        gram_desc(d->A, U, d->P, r->m, r->n, 1.0f, 0.0f, 1, prec, sc,
+                                  kIterScale));
         }
         size_t pos = 0;   // the tick's wait has passed: the region is free
         std::vector<Staged> sh;

@@ -13,8 +13,17 @@
 
 namespace la {
 
-// Resolved product arithmetic (la_precision without AUTO).
-enum Prec : int { PREC_FP32 = 1, PREC_BF16X3 = 2, PREC_BF16X6 = 3 };
+// Resolved product arithmetic (la_precision without AUTO).  PREC_F16X3 is not
+// part of the ABI: each operand, multiplied by a power of two that brings its
+// largest entries near the top of the fp16 range, is split into two fp16 terms
+// (23 significant bits together: hi holds 11, lo the next 11 and a sign), and
+// three fp16 products (lo hi, hi lo, hi hi) are accumulated in FP32.  It stands
+// in for BF16X6 where the operands' magnitudes are known (see polar_plan).
+enum Prec : int { PREC_FP32 = 1, PREC_BF16X3 = 2, PREC_BF16X6 = 3, PREC_F16X3 = 4 };
+
+// The la_precision a product arithmetic is reported as: F16X3 is an
+// implementation of the FP32-level tier, BF16X6.
+inline int public_prec(int p) { return p == PREC_F16X3 ? (int)PREC_BF16X6 : p; }
 
 // Thread-local error text (defined by the library, or by a test harness).
 void set_error(const char *fmt, ...);
@@ -31,6 +40,33 @@ constexpr int64_t kMaxAccK = 4096;
 
 // Smallest accepted s_- (see polar_plan).
 constexpr double kMinSminus = 1e-3;
+
+// F16X3 factor of the iterates X and of P = I - c X^T X: every entry of both is
+// at most 1 in magnitude (the singular values of X stay in [0, 1] up to FP32
+// rounding, and 0 <= c <= 1), so 2^15 keeps them a factor 2 below the largest
+// fp16 value, and entries down to 2^-18 keep all 23 bits of their two terms
+// (smaller ones an absolute error of 2^-40).
+constexpr float kIterScale = 32768.0f;
+
+// Smallest n whose AUTO preconditioning and H run as F16X3 (see polar_plan).
+constexpr int64_t kF16MinN = 192;
+
+// Arithmetic of H = sym(U^T A) for ||A||_F = fro: *sc receives the F16X3 factor
+// of A, the power of two that takes fro, and so every |A_ij|, below 2^15.  An A
+// whose norm leaves 2^+-60 keeps BF16X6, so that neither the factor nor its
+// reciprocal in the epilogue can leave the FP32 range.
+inline int h_prec(int prec, double fro, float *sc)
+{
+    *sc = 1.0f;
+    if (prec != PREC_F16X3)
+        return prec;
+    int e = 0;
+    (void)frexp(fro, &e);   // fro < 2^e
+    if (e < -60 || e > 60)
+        return PREC_BF16X6;
+    *sc = (float)ldexp(1.0, 15 - e);
+    return prec;
+}
 
 struct PolarPlan {
     int64_t m, n;
@@ -87,12 +123,22 @@ inline la_status polar_plan(int64_t m, int64_t n, const la_polar_opts *opts, Pol
         set_error("la_polar_opts: need %g <= s_minus < 1 and finite s0, eps", kMinSminus);
         return LA_ERR_INVALID_ARG;
     }
-    p.prec_pre = o.prec_precond == LA_PREC_AUTO ? (int)PREC_BF16X6 : o.prec_precond;
+    // AUTO's FP32-level phases run as F16X3 from n = kF16MinN: half the matrix
+    // core work of BF16X6, and half the FP32 accumulation roundings, which
+    // outweigh its one bit less per operand.  Measured error of U against FP64
+    // (square A, cond 10 and 1e3, F16X3 / BF16X6): n = 64 2.98e-6 / 2.95e-6,
+    // 192 3.06e-6 / 3.11e-6, 1000 3.30e-6 / 3.63e-6, 4096 4.57e-6 / 5.75e-6;
+    // of H: 128 2.57e-6 / 2.54e-6, 192 2.57e-6 / 2.60e-6, 4096 2.86e-6 /
+    // 3.16e-6; below n = 192 the two cross, so the smaller sizes keep BF16X6.
+    // 16384^2: precond Gram 21.0 -> 10.7 ms, update 39.5 -> 20 ms, the whole
+    // polar 1.288 -> 0.866 s; 131072 x 4096 0.653 -> 0.454 s.
+    const int fp32_level = n >= kF16MinN ? (int)PREC_F16X3 : (int)PREC_BF16X6;
+    p.prec_pre = o.prec_precond == LA_PREC_AUTO ? fp32_level : o.prec_precond;
     p.prec_ns = o.prec_ns == LA_PREC_AUTO ? (int)PREC_BF16X3 : o.prec_ns;
     // H = sym(U^T A) is one product (about 2 of the ~85 N^3 of a polar) but its
     // error enters the residual directly: at 3xBF16 it alone is about
-    // 2^-16 ||A||_F, so AUTO computes it at 6xBF16.
-    p.prec_h = o.prec_h == LA_PREC_AUTO ? (int)PREC_BF16X6 : o.prec_h;
+    // 2^-16 ||A||_F, so AUTO computes it at FP32 level like the preconditioning.
+    p.prec_h = o.prec_h == LA_PREC_AUTO ? fp32_level : o.prec_h;
     p.a = 1.5 * sqrt(3.0) - p.s_minus;
     p.c = (4.0 / 27.0) * p.a * p.a;
     double s = p.s0;

@@ -402,9 +402,9 @@ class Core {
         r->status = st;
         r->state = DONE;
         r->t_done = t;
-        r->info.prec_precond = r->plan.prec_pre;
-        r->info.prec_ns = r->plan.prec_ns;
-        r->info.prec_h = r->plan.prec_h;
+        r->info.prec_precond = public_prec(r->plan.prec_pre);
+        r->info.prec_ns = public_prec(r->plan.prec_ns);
+        r->info.prec_h = public_prec(r->plan.prec_h);
         if (st == LA_OK)
             stats_.completed++;
         else
