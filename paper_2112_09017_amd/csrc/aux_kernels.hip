@@ -28,27 +28,42 @@ hipError_t launch_grouped_x3(int, int, int, const GemmDesc *, const GroupItem *,
                              hipStream_t);
 hipError_t launch_grouped_x6(int, int, int, const GemmDesc *, const GroupItem *, int, int,
                              hipStream_t);
-int tile_m_fp32(int);
-int tile_n_fp32(int);
-int tile_m_x3(int);
-int tile_n_x3(int);
-int tile_m_x6(int);
-int tile_n_x6(int);
 
-int tile_m(int prec, int small)
+int tile_m(int, int cls)
 {
-    return prec == PREC_FP32 ? tile_m_fp32(small)
-                             : prec == PREC_BF16X6 ? tile_m_x6(small) : tile_m_x3(small);
+    return cls == kClassLarge ? 256 : cls == kClassSmall ? 128 : cls == kClassDirect64 ? 64 : 32;
 }
-int tile_n(int prec, int small)
-{
-    return prec == PREC_FP32 ? tile_n_fp32(small)
-                             : prec == PREC_BF16X6 ? tile_n_x6(small) : tile_n_x3(small);
-}
+int tile_n(int prec, int cls) { return tile_m(prec, cls); }
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-void gemm_finalize(GemmDesc &d, int prec)
+// Tile class of a product, by its shape alone.  Measured (us, n^3 products,
+// 3xBF16 / 6xBF16; small = 128 x 128 tiles through LDS): 256: direct32 9 / 9
+// (the host's launch rate), direct64 10 / 10, small 17 / 20; 512: 9 / 10, 12 /
+// 13, 25 / 29; 768: 19 / 20, 17 / 19, 36 / 41; 1000: 26 / 28, 20 / 25, 98 /
+// 110; 1536: 84 / 87, 63 / 76, 69 / 78; 2048: 166 / 176, 98 / 121, 90 / 105.
+// So: large tiles once they give half the CUs one; else 32 x 32 tiles while one
+// round of workgroups holds them, 64 x 64 tiles up to 2.5 rounds, small tiles
+// between.
+static int gemm_class(const GemmDesc &d, int prec)
+{
+    auto tiles = [&](int64_t t) {
+        const int64_t tm = (d.M + t - 1) / t, tn = (d.N + t - 1) / t;
+        return d.gram ? tn * (tn + 1) / 2 : tm * tn;
+    };
+    constexpr int64_t kCus = 256;
+    if (tiles(256) >= kCus / 2)
+        return kClassLarge;
+    // the direct kernels keep 32-bit byte offsets within an operand
+    constexpr int64_t kMaxElems = (int64_t)1 << 29;
+    const int64_t ea = d.a_kcontig ? d.M * d.lda : d.M + 8 * d.lda;
+    const int64_t eb = d.b_kcontig ? d.N * d.ldb : d.N + 8 * d.ldb;
+    if (ea >= kMaxElems || eb >= kMaxElems || 2 * tiles(64) > 5 * kCus)
+        return kClassSmall;
+    return tiles(32) <= kCus || d.M < 2 || d.N < 2 ? kClassDirect32 : kClassDirect64;
+}
+
+void gemm_finalize(GemmDesc &d, int prec, bool staged)
 {
     // The interior loader keeps 32-bit element offsets of up to 255 rows (or 24
     // k rows) from a 64-bit stage base; an operand with a longer leading
@@ -56,20 +71,14 @@ void gemm_finalize(GemmDesc &d, int prec)
     constexpr int64_t kMaxFastLd = (int64_t)1 << 23;
     d.vec_a = aligned16(d.A) && (d.lda % 4 == 0) && d.lda < kMaxFastLd;
     d.vec_b = aligned16(d.B) && (d.ldb % 4 == 0) && d.ldb < kMaxFastLd;
-    // small tiles when large ones would leave most CUs idle
-    {
-        const int64_t lm = (d.M + tile_m(prec) - 1) / tile_m(prec);
-        const int64_t ln = (d.N + tile_n(prec) - 1) / tile_n(prec);
-        const int64_t large = d.gram ? ln * (ln + 1) / 2 : lm * ln;
-        d.small = large < 128 ? 1 : 0;
-    }
-    gemm_set_class(d, prec, d.small);
+    const int cls = gemm_class(d, prec);
+    gemm_set_class(d, prec, staged && is_direct(cls) ? kClassSmall : cls);
 }
 
-void gemm_set_class(GemmDesc &d, int prec, int small)
+void gemm_set_class(GemmDesc &d, int prec, int cls)
 {
-    d.small = small;
-    const int bm = tile_m(prec, d.small), bn = tile_n(prec, d.small);
+    d.small = cls;
+    const int bm = tile_m(prec, cls), bn = tile_n(prec, cls);
     d.tiles_m = (int)((d.M + bm - 1) / bm);
     d.tiles_n = (int)((d.N + bn - 1) / bn);
     if (d.gram)
@@ -78,6 +87,23 @@ void gemm_set_class(GemmDesc &d, int prec, int small)
         d.num_tiles = d.tiles_m * d.tiles_n;
     if (d.M == 0 || d.N == 0)
         d.num_tiles = 0;
+}
+
+size_t gemm_max_tiles(int prec, int64_t M, int64_t N, int64_t K)
+{
+    // of the class taken with dense operands, and of the small class, which
+    // stands in for a direct one where a leading dimension is too long for it
+    GemmDesc d{};
+    d.M = M;
+    d.N = N;
+    d.K = K;
+    d.lda = K;
+    d.ldb = N;
+    d.a_kcontig = 1;
+    gemm_finalize(d, prec);
+    const size_t dense = (size_t)d.tiles_m * d.tiles_n;
+    gemm_set_class(d, prec, kClassSmall);
+    return std::max(dense, (size_t)d.tiles_m * d.tiles_n);
 }
 
 hipError_t launch_gemm(int prec, const GemmDesc &d, hipStream_t s)
@@ -91,19 +117,19 @@ hipError_t launch_gemm(int prec, const GemmDesc &d, hipStream_t s)
     }
 }
 
-hipError_t launch_gemm_grouped(int prec, int akc, int bkc, int small, const GemmDesc *probs,
+hipError_t launch_gemm_grouped(int prec, int akc, int bkc, int cls, const GemmDesc *probs,
                                const GroupItem *items, int num_items, int grid_size,
                                hipStream_t s)
 {
     switch (prec) {
     case PREC_FP32:
-        return launch_grouped_fp32(akc, bkc, small, probs, items, num_items, grid_size, s);
+        return launch_grouped_fp32(akc, bkc, cls, probs, items, num_items, grid_size, s);
     case PREC_BF16X3:
-        return launch_grouped_x3(akc, bkc, small, probs, items, num_items, grid_size, s);
+        return launch_grouped_x3(akc, bkc, cls, probs, items, num_items, grid_size, s);
     case PREC_BF16X6:
-        return launch_grouped_x6(akc, bkc, small, probs, items, num_items, grid_size, s);
+        return launch_grouped_x6(akc, bkc, cls, probs, items, num_items, grid_size, s);
     case PREC_F16X3:
-        return launch_grouped_f16(akc, bkc, small, probs, items, num_items, grid_size, s);
+        return launch_grouped_f16(akc, bkc, cls, probs, items, num_items, grid_size, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -1,19 +1,19 @@
-// Instantiates the tile GEMM (gemm_tile.h) for F16X3 (two scaled fp16 terms per
-// operand, three products), both tile classes and the packed operands; kept in
+// Instantiates the GEMM kernels (gemm_tile.h, gemm_direct.h) for F16X3 (two scaled fp16 terms per
+// operand, three products), all tile classes and the packed operands; kept in
 // its own translation unit so the precisions compile in parallel.
-#include "gemm_tile.h"
+#include "gemm_direct.h"
 
 namespace la {
 
 hipError_t launch_gemm_f16(const GemmDesc &d, hipStream_t s)
 {
-    return dev::launch_t<PREC_F16X3>(d, s);
+    return dev::launch_any<PREC_F16X3>(d, s);
 }
 
-hipError_t launch_grouped_f16(int akc, int bkc, int small, const GemmDesc *probs,
+hipError_t launch_grouped_f16(int akc, int bkc, int cls, const GemmDesc *probs,
                               const GroupItem *items, int num_items, int grid_size, hipStream_t s)
 {
-    return dev::launch_grouped_t<PREC_F16X3>(akc, bkc, small, probs, items, num_items, grid_size, s);
+    return dev::launch_grouped_any<PREC_F16X3>(akc, bkc, cls, probs, items, num_items, grid_size, s);
 }
 
 hipError_t launch_pack_f16(const float *X, int64_t ld, int kc, int64_t rows, int64_t k, float sc,
@@ -24,7 +24,7 @@ hipError_t launch_pack_f16(const float *X, int64_t ld, int kc, int64_t rows, int
 
 hipError_t launch_gemm_packed_f16(const GemmDesc &d, hipStream_t s)
 {
-    return dev::launch_packed_x3<PREC_F16X3>(d, s);
+    return dev::launch_packed_any<PREC_F16X3>(d, s);
 }
 
 }  // namespace la

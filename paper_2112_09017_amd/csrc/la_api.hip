@@ -266,11 +266,8 @@ static size_t parts_floats(const PolarPlan &p)
 static size_t max_update_tiles(const PolarPlan &p)
 {
     size_t t = (size_t)splitk_update_num_partials();
-    for (int pr : {PREC_FP32, PREC_BF16X3, PREC_BF16X6}) {
-        const size_t tm = (size_t)((p.m + tile_m(pr, 1) - 1) / tile_m(pr, 1));
-        const size_t tn = (size_t)((p.n + tile_n(pr, 1) - 1) / tile_n(pr, 1));
-        t = std::max(t, tm * tn);
-    }
+    for (int pr : {PREC_FP32, PREC_BF16X3, PREC_BF16X6, PREC_F16X3})
+        t = std::max(t, gemm_max_tiles(pr, p.m, p.n, p.n));
     return t;
 }
 
@@ -521,11 +518,8 @@ static la_status inverse_plan(int64_t n, int64_t m, const la_inverse_opts *opts,
 static size_t inverse_max_tiles(const InvPlan &p)
 {
     size_t t = 0;
-    for (int pr : {PREC_FP32, PREC_BF16X3, PREC_BF16X6}) {
-        const size_t tm = (size_t)((p.m + tile_m(pr, 1) - 1) / tile_m(pr, 1));
-        const size_t tn = (size_t)((p.n + tile_n(pr, 1) - 1) / tile_n(pr, 1));
-        t = std::max(t, tm * tn);
-    }
+    for (int pr : {PREC_FP32, PREC_BF16X3, PREC_BF16X6})
+        t = std::max(t, gemm_max_tiles(pr, p.m, p.n, p.wide ? p.n : p.m));
     return t;
 }
 
@@ -662,6 +656,18 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
     gemm_finalize(u, prec);
     *ntiles = u.tiles_m * u.tiles_n;
     return gemm_packed_or_plain(prec, u, w.pk, s);
+}
+
+// Tile class of a product of packed operands: the direct class la_gemm would
+// take for the shape with dense operands (the same sums), else 256 x 256 tiles.
+static void gemm_packed_class(GemmDesc &d)
+{
+    GemmDesc t = d;
+    t.lda = std::max<int64_t>(d.K, 1);
+    t.ldb = std::max<int64_t>(d.K, 1);
+    t.a_kcontig = t.b_kcontig = 1;
+    gemm_finalize(t, PREC_BF16X3);
+    gemm_set_class(d, PREC_BF16X3, is_direct(t.small) ? t.small : kClassLarge);
 }
 
 // Validation and descriptor of a la_gemm-style call.  *empty: nothing to do
@@ -918,9 +924,9 @@ la_status la_gemm_packed(la_context *ctx, int64_t m, int64_t n, int64_t k, float
         d.lde = ldc;
         d.beta = beta;
     }
-    d.tiles_m = (int)((m + 255) / 256);
-    d.tiles_n = (int)((n + 255) / 256);
-    d.num_tiles = d.tiles_m * d.tiles_n;
+    // the class la_gemm takes for this shape (dense operands), so that the sums
+    // are the same; the 128 x 128 class adds as the large tiles do
+    gemm_packed_class(d);
     LA_HIP(launch_gemm_packed(PREC_BF16X3, d, (hipStream_t)hip_stream), "la_gemm_packed: launch");
     return LA_OK;
 }
@@ -974,9 +980,6 @@ la_status la_gemm_ws(la_context *ctx, int trans_a, int trans_b, int64_t m, int64
     LA_HIP(launch_pack(PREC_BF16X3, B, ldb, trans_b ? 1 : 0, n, k, 1.0f, wb, s), "la_gemm_ws: pack B");
     d.A = (const float *)wa;
     d.B = (const float *)wb;
-    d.tiles_m = (int)((m + 255) / 256);
-    d.tiles_n = (int)((n + 255) / 256);
-    d.num_tiles = d.tiles_m * d.tiles_n;
     LA_HIP(launch_gemm_packed(PREC_BF16X3, d, s), "la_gemm_ws: launch");
     return LA_OK;
 }

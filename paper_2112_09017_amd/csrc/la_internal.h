@@ -45,7 +45,7 @@ struct GemmDesc {
     int vec_a, vec_b;  // operand addresses allow 16-byte vector loads
     int tiles_m, tiles_n;
     int num_tiles;     // tiles launched (upper triangle only for gram)
-    int small;         // 128 x 128 tiles (chosen from the problem's own shape)
+    int small;         // tile class (chosen from the problem's own shape)
     int quarters;      // small tiles covering large Gram tiles tail_first.. (4 per tile)
     int tail_first;
     // split-K slices in one launch: slice y takes k in [y slice_k, min(K,
@@ -55,17 +55,27 @@ struct GemmDesc {
     int64_t slice_k, slice_stride;
 };
 
-// Tile geometry of each precision and tile class.  Both tile classes use the
-// same K stages and product order, so the choice (made from the problem's own
-// shape only) never changes a result.
-int tile_m(int prec, int small = 0);
-int tile_n(int prec, int small = 0);
+// Tile classes.  Large (256 x 256) and small (128 x 128) tiles (gemm_tile.h) use
+// the same K stages and product order, so the choice between these two never
+// changes a result.  The direct classes (gemm_direct.h: 64 x 64 and 32 x 32
+// tiles whose waves split K) each add in an order of their own, the same on
+// packed operands.  The class follows from the problem's own shape, so a
+// problem's result does not depend on what it is launched with.
+constexpr int kClassLarge = 0, kClassSmall = 1, kClassDirect64 = 2, kClassDirect32 = 3;
+inline bool is_direct(int cls) { return cls >= kClassDirect64; }
 
-// Fills the derived fields (tile class, vec flags, tile counts) of d.
-void gemm_finalize(GemmDesc &d, int prec);
-// Sets d's tile class (small: 128 x 128, else the precision's large tiles)
-// and the tile counts that follow from it; the products are the same either way.
-void gemm_set_class(GemmDesc &d, int prec, int small);
+// Tile geometry of each precision and tile class.
+int tile_m(int prec, int cls = 0);
+int tile_n(int prec, int cls = 0);
+
+// Fills the derived fields (tile class, vec flags, tile counts) of d.  staged:
+// never a direct class (launches of the persistent grouped kernel).
+void gemm_finalize(GemmDesc &d, int prec, bool staged = false);
+// Sets d's tile class and the tile counts that follow from it.
+void gemm_set_class(GemmDesc &d, int prec, int cls);
+// Most output tiles an M x N x K product (not a Gram) can take: the partials
+// its step norm needs.
+size_t gemm_max_tiles(int prec, int64_t M, int64_t N, int64_t K);
 
 // Sets the factors of a PREC_F16X3 product (powers of two sa, sb with |sa a| and
 // |sb b| below the fp16 range for every entry of its operands) and takes them
@@ -95,7 +105,7 @@ struct GroupItem {
     int prob;
     int tile;   // linear tile index within the problem
 };
-hipError_t launch_gemm_grouped(int prec, int a_kcontig, int b_kcontig, int small,
+hipError_t launch_gemm_grouped(int prec, int a_kcontig, int b_kcontig, int cls,
                                const GemmDesc *probs_dev,
                                const GroupItem *items_dev, int num_items,
                                int grid_size, hipStream_t s);
@@ -108,8 +118,8 @@ size_t packed_x3_bytes(int64_t rows, int64_t k);
 hipError_t launch_pack(int prec, const float *X, int64_t ld, int kc, int64_t rows, int64_t k,
                        float sc, void *out, hipStream_t s);
 // GEMM on packed operands: d.A and d.B point at packed op(A) (M x K) and
-// packed op(B)^T (N x K); 256 x 256 tiles (d.small must be 0).  Computes the
-// same products in the same order as launch_gemm's kernel of that precision.
+// packed op(B)^T (N x K), on 256 x 256 tiles or a direct class (d.small).
+// Computes the same products in the same order as launch_gemm's kernel of that precision.
 hipError_t launch_gemm_packed(int prec, const GemmDesc &d, hipStream_t s);
 
 // C (rows x cols, ldc) <- C - Y Z with Y (rows x K, k contiguous, ldy) and

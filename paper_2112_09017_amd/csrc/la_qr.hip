@@ -1131,7 +1131,7 @@ int splits_for(int prec, int64_t rows, int64_t cols, int64_t K, int num_cus, int
     d.ldc = cols;
     d.a_kcontig = 0;
     d.b_kcontig = 0;
-    gemm_finalize(d, prec);
+    gemm_finalize(d, prec, true);
     const int64_t tiles = std::max<int64_t>(1, (int64_t)d.tiles_m * d.tiles_n);
     int64_t sp = (2 * num_cus + tiles - 1) / tiles;
     sp = std::min<int64_t>(sp, std::max<int64_t>(1, K / min_slice));
@@ -1188,7 +1188,7 @@ void add_split(SplitBatch &sb, int prec, const float *X, int64_t ldx, const floa
         d.N = cols;
         d.K = kl > 0 ? kl : 0;
         d.alpha = 1.0f;
-        gemm_finalize(d, prec);
+        gemm_finalize(d, prec, true);
         g.small = d.small;   // the same for every slice (it depends on M and N only)
         const int pid = (int)sb.probs.size() - g.first_prob;
         sb.probs.push_back(d);

@@ -66,16 +66,19 @@ constexpr int kMaxSlots = 4096;
 // from larger ones.
 constexpr int kMaxBands = 2;
 constexpr double kBandWork = 2048.0 * 2048.0 * 2048.0;
-// launch groups of one staging pass: 4 product arithmetics x 2 tile classes x 2
+// launch groups of one staging pass: 4 product arithmetics x 4 tile classes x 2
 // phases, each with its descriptors and its items padded to kAlign
-constexpr int kMaxGroups = 16;
+constexpr int kMaxGroups = 32;
 static_assert(2 * kMaxSlots * sizeof(double) <= kRedBytes, "norms of one tick");
 static_assert(2 * sizeof(ReduceItem) <= sizeof(GemmDesc), "reduce items in a descriptor slot");
 
 size_t up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
 // Pinned host buffers reused across requests (power-of-two size classes), so a
-// submit does not pay for a pinned allocation once the pool has warmed up.
+// submit does not pay for a pinned allocation once the pool has warmed up.  A
+// class that has run out grows by as many buffers as it has (in one allocation
+// of at most kSlabBytes), so a burst of submits waits for few allocations: 8 MiB
+// of pinned memory takes 1.4 ms, a submit without it 0.26 ms (1024^2).
 class PinnedPool {
   public:
     ~PinnedPool()
@@ -96,10 +99,18 @@ class PinnedPool {
             fl.pop_back();
             return p;
         }
+        size_t &have = count_[c];
+        size_t grow = std::max<size_t>(1, std::min(have, kSlabBytes / c));
         void *p = nullptr;
-        if (hipHostMalloc(&p, c, hipHostMallocDefault) != hipSuccess)
-            return nullptr;
+        while (hipHostMalloc(&p, grow * c, hipHostMallocDefault) != hipSuccess) {
+            if (grow == 1)
+                return nullptr;
+            grow = 1;
+        }
         all_.push_back(p);
+        have += grow;
+        for (size_t i = 1; i < grow; ++i)
+            fl.push_back((char *)p + i * c);
         return p;
     }
     void put(void *p, size_t cls)
@@ -112,8 +123,10 @@ class PinnedPool {
 
   private:
     std::mutex mu_;
+    static constexpr size_t kSlabBytes = (size_t)32 << 20;
     std::map<size_t, std::vector<void *>> free_;
-    std::vector<void *> all_;
+    std::map<size_t, size_t> count_;   // buffers of each class, free or not
+    std::vector<void *> all_;          // allocations
 };
 
 // Device and host state of one request.
@@ -130,14 +143,13 @@ struct DevReq {
 size_t max_tiles(int64_t m, int64_t n)
 {
     size_t t = 0;
-    for (int pr : {PREC_FP32, PREC_BF16X3, PREC_BF16X6})
-        t = std::max(t, (size_t)((m + tile_m(pr, 1) - 1) / tile_m(pr, 1)) *
-                            (size_t)((n + tile_n(pr, 1) - 1) / tile_n(pr, 1)));
+    for (int pr : {PREC_FP32, PREC_BF16X3, PREC_BF16X6, PREC_F16X3})
+        t = std::max(t, gemm_max_tiles(pr, m, n, n));
     return t;
 }
 
 struct Launch {
-    int prec, akc, bkc, small;
+    int prec, akc, bkc, cls;
     std::vector<GemmDesc> probs;
     std::vector<GroupItem> items;
 };
@@ -158,7 +170,7 @@ void add_problem(std::vector<Launch> &ls, int prec, int akc, int bkc, const Gemm
 {
     Launch *L = nullptr;
     for (auto &x : ls)
-        if (x.prec == prec && x.akc == akc && x.bkc == bkc && x.small == d.small)
+        if (x.prec == prec && x.akc == akc && x.bkc == bkc && x.cls == d.small)
             L = &x;
     if (!L) {
         ls.push_back(Launch{prec, akc, bkc, d.small, {}, {}});
@@ -406,7 +418,7 @@ struct HipExec {
         for (size_t i = 0; i < st.size() && e == hipSuccess; ++i) {
             const Launch &L = *st[i].L;
             hipStream_t s = i == 0 ? stream : side[(i - 1) % kSide];
-            e = launch_gemm_grouped(L.prec, L.akc, L.bkc, L.small, st[i].dd, st[i].di,
+            e = launch_gemm_grouped(L.prec, L.akc, L.bkc, L.cls, st[i].dd, st[i].di,
                                     (int)L.items.size(), 0, s);
         }
         for (int k = 0; k < used && e == hipSuccess; ++k) {
@@ -461,10 +473,11 @@ struct HipExec {
                                     pre ? (float)(-p.c) : -1.0f, 1.0f, 0, prec);
             GemmDesc ud = update_desc(d->X[d->cur], d->P, d->X[d->cur ^ 1], r->m, r->n,
                                       pre ? (float)p.a : 0.5f, prec);
-            if (all_large) {
-                gemm_set_class(gd, prec, 0);
-                gemm_set_class(ud, prec, 0);
-            }
+            // (a direct class adds in another order: those keep theirs)
+            if (all_large && !is_direct(gd.small))
+                gemm_set_class(gd, prec, kClassLarge);
+            if (all_large && !is_direct(ud.small))
+                gemm_set_class(ud, prec, kClassLarge);
             add_problem(grams, prec, 0, 0, gd);
             if (!pre) {
                 ud.beta = 1.0f;
