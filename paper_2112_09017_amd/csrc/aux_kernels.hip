@@ -37,14 +37,21 @@ int tile_n(int prec, int cls) { return tile_m(prec, cls); }
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Tile class of a product, by its shape alone.  Measured (us, n^3 products,
-// 3xBF16 / 6xBF16; small = 128 x 128 tiles through LDS): 256: direct32 9 / 9
-// (the host's launch rate), direct64 10 / 10, small 17 / 20; 512: 9 / 10, 12 /
-// 13, 25 / 29; 768: 19 / 20, 17 / 19, 36 / 41; 1000: 26 / 28, 20 / 25, 98 /
-// 110; 1536: 84 / 87, 63 / 76, 69 / 78; 2048: 166 / 176, 98 / 121, 90 / 105.
-// So: large tiles once they give half the CUs one; else 32 x 32 tiles while one
-// round of workgroups holds them, 64 x 64 tiles up to 2.5 rounds, small tiles
-// between.
+// Tile class of a product, by its shape alone.  Measured (ns per unit of K,
+// 3xBF16 / 6xBF16 / FP32; the last round of workgroups counts as a whole one):
+//   direct64, up to 512 tiles 28 / 35 / 59, 1024 47 / 56 / 107, 1536 62 / 71 /
+//     131, 2048 79 / 93 / 156, 2560 96 / 118 / 203;
+//   small, up to 256 tiles 43 / 52 / 84, 512 57 / 85 / 160, 768 91 / 127 / 234;
+//   large, up to 256 tiles 92 / 135 / 271.
+// n^3 products (us, 3xBF16): 256 direct32 9 (the host's launch rate), direct64
+// 10, small 17; 640 11, 14, 31; 768 19, 17, 36; 1000 26, 20, 65; 1536 84, 63, 69;
+// 2048 166, 97, 90; 3000: small 274, large 277.
+// So: 32 x 32 tiles while one round of workgroups holds them, 64 x 64 tiles up
+// to 2.5 rounds of one per CU and, for the precisions whose small tiles do not
+// gain from a second workgroup per CU, from 4 to 6 rounds; large tiles once
+// they give half the CUs one; small tiles between.  A matrix with a side below
+// 128 is all edge to the staged classes and always direct, and large tiles
+// need both sides to hold one.
 static int gemm_class(const GemmDesc &d, int prec)
 {
     auto tiles = [&](int64_t t) {
@@ -52,25 +59,32 @@ static int gemm_class(const GemmDesc &d, int prec)
         return d.gram ? tn * (tn + 1) / 2 : tm * tn;
     };
     constexpr int64_t kCus = 256;
-    if (tiles(256) >= kCus / 2)
+    const int64_t side = std::min(d.M, d.N);
+    if (side >= 256 && tiles(256) >= kCus / 2)
         return kClassLarge;
     // the direct kernels keep 32-bit byte offsets within an operand
     constexpr int64_t kMaxElems = (int64_t)1 << 29;
     const int64_t ea = d.a_kcontig ? d.M * d.lda : d.M + 8 * d.lda;
     const int64_t eb = d.b_kcontig ? d.N * d.ldb : d.N + 8 * d.ldb;
-    if (ea >= kMaxElems || eb >= kMaxElems || 2 * tiles(64) > 5 * kCus)
+    if (ea >= kMaxElems || eb >= kMaxElems)
         return kClassSmall;
-    return tiles(32) <= kCus || d.M < 2 || d.N < 2 ? kClassDirect32 : kClassDirect64;
+    if (tiles(32) <= kCus || side < 2)
+        return kClassDirect32;
+    const int64_t t64 = tiles(64);
+    const bool one_deep = prec == PREC_BF16X6 || prec == PREC_FP32;
+    if (side < 128 || 2 * t64 <= 5 * kCus || (one_deep && t64 > 4 * kCus && t64 <= 6 * kCus))
+        return kClassDirect64;
+    return kClassSmall;
 }
 
 void gemm_finalize(GemmDesc &d, int prec, bool staged)
 {
-    // The interior loader keeps 32-bit element offsets of up to 255 rows (or 24
+    // The unguarded loader keeps 32-bit element offsets of up to 255 rows (or 24
     // k rows) from a 64-bit stage base; an operand with a longer leading
     // dimension takes the guarded loader, which indexes in 64 bits.
     constexpr int64_t kMaxFastLd = (int64_t)1 << 23;
-    d.vec_a = aligned16(d.A) && (d.lda % 4 == 0) && d.lda < kMaxFastLd;
-    d.vec_b = aligned16(d.B) && (d.ldb % 4 == 0) && d.ldb < kMaxFastLd;
+    d.vec_a = d.lda < kMaxFastLd;
+    d.vec_b = d.ldb < kMaxFastLd;
     const int cls = gemm_class(d, prec);
     gemm_set_class(d, prec, staged && is_direct(cls) ? kClassSmall : cls);
 }

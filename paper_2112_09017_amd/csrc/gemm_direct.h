@@ -39,10 +39,6 @@ template <> struct DirectCfg<kClassDirect32> {
     static constexpr int FM = 1, FN = 1, KW = 8, WPE = 4;
 };
 
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
-typedef const __attribute__((address_space(1))) f32x4u gf32x4u;
-typedef const __attribute__((address_space(1))) f32x2u gf32x2u;
 typedef const __attribute__((address_space(1))) char gchar;
 
 // op(X) rows of a wave's F 32-row blocks and one 16-k step: lane l holds, for

@@ -237,16 +237,21 @@ __device__ __forceinline__ __attribute__((address_space(1))) T *gmem(T *p)
 {
     return (__attribute__((address_space(1))) T *)p;
 }
-typedef const __attribute__((address_space(1))) f32x4 gf32x4;
-typedef const __attribute__((address_space(1))) f32x2 gf32x2;
+// vectors that need the 4-byte alignment of a float only (one load instruction
+// all the same: the memory pipe takes any dword-aligned address)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef const __attribute__((address_space(1))) f32x4u gf32x4u;
+typedef const __attribute__((address_space(1))) f32x2u gf32x2u;
 
 // Loads one K stage of op(X) rows [r0, r0+ROWS) x k [k0, k0+BK) into
 // registers.  KC: k is contiguous in memory (X[r * ld + k]); otherwise the
 // row index is (X[k * ld + r]).  Work unit = 8 k x R rows: R float4 pairs
 // (KC) or 8 float-R vectors (row-contiguous), R = 4 or 2 so that every
-// thread has work.  Interior stages use load_fast (no bounds checks, loop-
-// invariant 32-bit offsets from a uniform stage base); edge tiles and the K
-// tail use load_guarded.
+// thread has work.  Whole stages use load_fast (no bounds checks, loop-
+// invariant 32-bit offsets from a uniform stage base, any 4-byte alignment);
+// the K tail, and tiles of an operand with fewer rows than the tile, use
+// load_guarded.
 template <int ROWS, int BK, int NT, bool KC>
 struct Loader {
     // up to 4 rows per unit, fewer when the stage is too small to give every
@@ -289,7 +294,7 @@ struct Loader {
         }
     }
 
-    // base = &op(X)(r0, k0) (uniform), stage fully in bounds, 16-byte aligned.
+    // base = &op(X)(r0, k0) (uniform), stage fully in bounds.
     __device__ __forceinline__ void load_fast(const float *__restrict__ base, int64_t ld)
     {
 #pragma unroll
@@ -297,7 +302,7 @@ struct Loader {
             if constexpr (KC) {
 #pragma unroll
                 for (int q = 0; q < R; ++q) {
-                    gf32x4 *p = reinterpret_cast<gf32x4 *>(
+                    gf32x4u *p = reinterpret_cast<gf32x4u *>(
                         gmem(base) + off[u] + (int64_t)q * (ROWS / R) * ld);
                     const f32x4 a = p[0], b = p[1];
 #pragma unroll
@@ -311,12 +316,12 @@ struct Loader {
                 for (int j = 0; j < 8; ++j) {
                     const auto p = gmem(base) + off[u] + (int64_t)j * ld;
                     if constexpr (R == 4) {
-                        const f32x4 a = *reinterpret_cast<gf32x4 *>(p);
+                        const f32x4 a = *reinterpret_cast<gf32x4u *>(p);
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
                             v[u][q][j] = a[q];
                     } else if constexpr (R == 2) {
-                        const f32x2 a = *reinterpret_cast<gf32x2 *>(p);
+                        const f32x2 a = *reinterpret_cast<gf32x2u *>(p);
                         v[u][0][j] = a[0];
                         v[u][1][j] = a[1];
                     } else {
@@ -762,7 +767,7 @@ __device__ __forceinline__ void round_tile_coords(const GemmDesc &d, int &tm, in
 
 // Epilogue of one tile: out = alpha acc + beta E + gamma I, written to C (and
 // mirrored for a full Gram), with the FP64 sum of (out - E)^2 for the step
-// norm.  Each 32 x 32 block's 16 addend values per lane are loaded together,
+// norm.  row0, col0: the first row and column acc holds.  Each 32 x 32 block's 16 addend values per lane are loaded together,
 // before any of the block's stores (C may alias E, so a load placed after a
 // store would have to wait for it), and one explicit wait for them follows:
 // without it the per-element bounds branches make the compiler wait for every
@@ -770,12 +775,15 @@ __device__ __forceinline__ void round_tile_coords(const GemmDesc &d, int &tm, in
 template <int PREC>
 __device__ __forceinline__ void epilogue(const GemmDesc &d,
                                          f32x16 (&acc)[Geo<PREC>::FM][Geo<PREC>::FN],
-                                         int tm, int tn, int wm, int wn, int lane,
-                                         double *red)
+                                         int64_t row0, int64_t col0, int tm, int tn, int wm,
+                                         int wn, int lane, double *red)
 {
     using G = Geo<PREC>;
-    const int64_t rb = (int64_t)tm * Cfg<PREC>::BM + wm * G::TM + (lane >> 5) * 4;
-    const int64_t cb = (int64_t)tn * Cfg<PREC>::BN + wn * G::TN + (lane & 31);
+    const int64_t rb = row0 + wm * G::TM + (lane >> 5) * 4;
+    const int64_t cb = col0 + wn * G::TN + (lane & 31);
+    // rows and columns before the tile's own belong to its neighbours (row0 /
+    // col0 moved back inside the matrix)
+    const int64_t rlo = (int64_t)tm * Cfg<PREC>::BM, clo = (int64_t)tn * Cfg<PREC>::BN;
     double ss = 0.0;
     const bool want_ss = d.partials != nullptr;
 #pragma clang loop unroll(full)
@@ -798,7 +806,7 @@ __device__ __forceinline__ void epilogue(const GemmDesc &d,
 #pragma clang loop unroll(full)
             for (int e = 0; e < 16; ++e) {
                 const int64_t row = rb + i * 32 + (e >> 2) * 8 + (e & 3);
-                if (row >= d.M || col >= d.N || (d.gram && row > col))
+                if (row < rlo || row >= d.M || col < clo || col >= d.N || (d.gram && row > col))
                     continue;
                 float val = d.alpha * acc[i][j][e];
                 float evv = 0.0f;
@@ -874,8 +882,8 @@ __device__ __forceinline__ void interleave_hint()
 // stage s run from LDS buffer s%2, the registers holding stage s+1 (loaded
 // one stage earlier) are split into LDS buffer (s+1)%2, and stage s+2 is
 // being loaded into the other register set.  GUARD: every load is bounds
-// checked (edge tiles, unaligned operands); otherwise stages [0, K / BK) use
-// unguarded vector loads and only a partial last stage is guarded.
+// checked; otherwise stages [0, K / BK) use unguarded vector loads and only a
+// partial last stage is guarded.
 template <int PREC, bool AKC, bool BKC, bool GUARD>
 __device__ __forceinline__ void k_loop2(const GemmDesc &d, int64_t row0, int64_t col0,
                                         f32x16 (&acc)[Geo<PREC>::FM][Geo<PREC>::FN],
@@ -1078,7 +1086,15 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc &d, int tm, int tn, cha
     using G = Geo<PREC>;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int wm = w / C::WN, wn = w % C::WN;
-    const int64_t row0 = (int64_t)tm * C::BM, col0 = (int64_t)tn * C::BN;
+    // A last tile that would reach past the edge is moved back inside the matrix:
+    // it computes some of its neighbour's elements again (the same bits, not
+    // stored), and every load stays in bounds without a check.
+    int64_t row0 = (int64_t)tm * C::BM, col0 = (int64_t)tn * C::BN;
+    const bool interior = d.M >= C::BM && d.N >= C::BN && d.vec_a && d.vec_b;
+    if (interior) {
+        row0 = row0 < d.M - C::BM ? row0 : d.M - C::BM;
+        col0 = col0 < d.N - C::BN ? col0 : d.N - C::BN;
+    }
 
     f32x16 acc[G::FM][G::FN];
 #pragma clang loop unroll(full)
@@ -1087,12 +1103,11 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc &d, int tm, int tn, cha
         for (int j = 0; j < G::FN; ++j)
             acc[i][j] = f32x16{};
 
-    const bool interior = row0 + C::BM <= d.M && col0 + C::BN <= d.N && d.vec_a && d.vec_b;
     if (interior)
         k_loop<PREC, AKC, BKC, false, GROUPED>(d, row0, col0, acc, smem, wm, wn, lane);
     else
         k_loop<PREC, AKC, BKC, true, GROUPED>(d, row0, col0, acc, smem, wm, wn, lane);
-    epilogue<PREC>(d, acc, tm, tn, wm, wn, lane, red);
+    epilogue<PREC>(d, acc, row0, col0, tm, tn, wm, wn, lane, red);
 }
 
 // ---------------------------------------------------------------- kernels
@@ -1221,7 +1236,7 @@ __host__ __device__ inline int64_t packed_kstride(int64_t rbt)
 template <int PREC, bool KC>
 __global__ void __launch_bounds__(256) pack_x3_kernel(const float *__restrict__ X, int64_t ld,
                                                       int64_t R, int64_t K, int64_t kbt,
-                                                      int64_t rbt, int vec, float sc,
+                                                      int64_t rbt, float sc,
                                                       char *__restrict__ out)
 {
     __shared__ float tile[32][kPackSlabK + 1];
@@ -1230,8 +1245,7 @@ __global__ void __launch_bounds__(256) pack_x3_kernel(const float *__restrict__ 
         const int64_t r0 = rb * 32, k0 = (int64_t)blockIdx.x * kPackSlabK;
         // stage 32 rows x 128 k through LDS, 4 consecutive elements of the
         // contiguous direction per thread and load (consecutive threads read
-        // consecutive 16 bytes); zero outside R x K.  vec: the operand allows
-        // 16-byte loads (aligned base, ld a multiple of 4)
+        // consecutive 16 bytes, at any 4-byte alignment); zero outside R x K
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int i = t + 256 * u;            // 1024 groups of 4 elements
@@ -1246,8 +1260,8 @@ __global__ void __launch_bounds__(256) pack_x3_kernel(const float *__restrict__ 
             const int64_t gr = r0 + r, gk = k0 + k;
             float v[4];
             const bool full = KC ? (gr < R && gk + 3 < K) : (gk < K && gr + 3 < R);
-            if (vec && full) {
-                const f32x4 q = *reinterpret_cast<const f32x4 *>(KC ? X + gr * ld + gk
+            if (full) {
+                const f32x4 q = *reinterpret_cast<const f32x4u *>(KC ? X + gr * ld + gk
                                                                     : X + gk * ld + gr);
                 v[0] = q[0];
                 v[1] = q[1];
@@ -1501,7 +1515,8 @@ __global__ void __launch_bounds__(256, 1) gemm_packed_kernel(GemmDesc d)
     for (int s = 0; s < nst; ++s)
         packed_stage<P>(s, nst, acc, alo, bhi, smem, smem_lds, pa, pb, rbta, rbtb, rba, rbb, w, wm,
                         wn, lane);
-    epilogue<P>(d, acc, tm, tn, wm, wn, lane, red);
+    epilogue<P>(d, acc, (int64_t)tm * Cfg<P>::BM, (int64_t)tn * Cfg<P>::BN, tm, tn, wm, wn, lane,
+                red);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1664,13 +1679,12 @@ hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t R, int64_t
     if (gx > 0x7fffffff)
         return hipErrorInvalidValue;
     const unsigned gy = (unsigned)(rbt < 65535 ? rbt : 65535);
-    const int vec = ((uintptr_t)X % 16 == 0 && ld % 4 == 0) ? 1 : 0;
     if (kc)
         hipLaunchKernelGGL((pack_x3_kernel<PREC, true>), dim3((unsigned)gx, gy), dim3(256), 0, s, X,
-                           ld, R, K, kbt, rbt, vec, sc, out);
+                           ld, R, K, kbt, rbt, sc, out);
     else
         hipLaunchKernelGGL((pack_x3_kernel<PREC, false>), dim3((unsigned)gx, gy), dim3(256), 0, s, X,
-                           ld, R, K, kbt, rbt, vec, sc, out);
+                           ld, R, K, kbt, rbt, sc, out);
     return hipGetLastError();
 }
 

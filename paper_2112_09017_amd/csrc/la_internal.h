@@ -42,7 +42,7 @@ struct GemmDesc {
     int a_kcontig, b_kcontig;
     int gram;
     int gram_upper;    // gram: write only the upper triangle (no mirror)
-    int vec_a, vec_b;  // operand addresses allow 16-byte vector loads
+    int vec_a, vec_b;  // the operand's leading dimension suits the loader's 32-bit offsets
     int tiles_m, tiles_n;
     int num_tiles;     // tiles launched (upper triangle only for gram)
     int small;         // tile class (chosen from the problem's own shape)

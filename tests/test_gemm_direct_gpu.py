@@ -64,6 +64,26 @@ def test_edges_against_oracle(la, prec, ta, tb, mnk):
             assert np.linalg.norm(got - ref) <= tol * nrm, (pad, alpha, beta)
 
 
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("mnk", [(2049, 2050, 33), (2100, 2177, 100), (129, 20000, 70),
+                                 (257, 33000, 48), (3001, 2999, 40)])
+def test_staged_tiles_at_the_edges(la, prec, mnk):
+    """Staged tiles whose last row and column of tiles are moved back inside the
+    matrix, with odd leading dimensions and offsets and C updated in place
+    (beta): integers, so exact, elements shared by two tiles counted once."""
+    m, n, k = mnk
+    for ta, tb in ((False, False), (True, True)):
+        Av, A = operand((m, k), ta, 61, 1, True)
+        Bv, B = operand((k, n), tb, 62, 3, True)
+        C0 = la_inputs.integer_matrix((m, n), 63)
+        C = torch.from_numpy(C0).to("cuda")
+        la.gemm(Av, Bv, C, alpha=1.0, beta=-2.0, prec=la.Precision[prec])
+        ref = (torch.from_numpy(A.copy()).to("cuda").double() @
+               torch.from_numpy(B.copy()).to("cuda").double()) - 2.0 * torch.from_numpy(C0).to("cuda")
+        torch.cuda.synchronize()
+        assert torch.equal(C.double(), ref)
+
+
 @pytest.mark.parametrize("mnk", [(96, 70, 50), (513, 512, 257), (1100, 1000, 333)])
 def test_packed_operands_bitwise(la, mnk):
     """la_gemm_packed adds as la_gemm does in both direct classes."""
