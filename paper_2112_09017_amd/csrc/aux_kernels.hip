@@ -37,6 +37,14 @@ int tile_n(int prec, int cls) { return tile_m(prec, cls); }
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+bool direct_fits(const GemmDesc &d)
+{
+    constexpr int64_t kMaxElems = (int64_t)1 << 29;
+    const int64_t ea = d.a_kcontig ? d.M * d.lda : d.M + 8 * d.lda;
+    const int64_t eb = d.b_kcontig ? d.N * d.ldb : d.N + 8 * d.ldb;
+    return ea < kMaxElems && eb < kMaxElems;
+}
+
 // Tile class of a product, by its shape alone.  Measured (ns per unit of K,
 // 3xBF16 / 6xBF16 / FP32; the last round of workgroups counts as a whole one):
 //   direct64, up to 512 tiles 28 / 35 / 59, 1024 47 / 56 / 107, 1536 62 / 71 /
@@ -62,11 +70,7 @@ static int gemm_class(const GemmDesc &d, int prec)
     const int64_t side = std::min(d.M, d.N);
     if (side >= 256 && tiles(256) >= kCus / 2)
         return kClassLarge;
-    // the direct kernels keep 32-bit byte offsets within an operand
-    constexpr int64_t kMaxElems = (int64_t)1 << 29;
-    const int64_t ea = d.a_kcontig ? d.M * d.lda : d.M + 8 * d.lda;
-    const int64_t eb = d.b_kcontig ? d.N * d.ldb : d.N + 8 * d.ldb;
-    if (ea >= kMaxElems || eb >= kMaxElems)
+    if (!direct_fits(d))
         return kClassSmall;
     if (tiles(32) <= kCus || side < 2)
         return kClassDirect32;
@@ -77,7 +81,7 @@ static int gemm_class(const GemmDesc &d, int prec)
     return kClassSmall;
 }
 
-void gemm_finalize(GemmDesc &d, int prec, bool staged)
+void gemm_finalize(GemmDesc &d, int prec)
 {
     // The unguarded loader keeps 32-bit element offsets of up to 255 rows (or 24
     // k rows) from a 64-bit stage base; an operand with a longer leading
@@ -85,8 +89,7 @@ void gemm_finalize(GemmDesc &d, int prec, bool staged)
     constexpr int64_t kMaxFastLd = (int64_t)1 << 23;
     d.vec_a = d.lda < kMaxFastLd;
     d.vec_b = d.ldb < kMaxFastLd;
-    const int cls = gemm_class(d, prec);
-    gemm_set_class(d, prec, staged && is_direct(cls) ? kClassSmall : cls);
+    gemm_set_class(d, prec, gemm_class(d, prec));
 }
 
 void gemm_set_class(GemmDesc &d, int prec, int cls)

@@ -68,9 +68,10 @@ inline bool is_direct(int cls) { return cls >= kClassDirect64; }
 int tile_m(int prec, int cls = 0);
 int tile_n(int prec, int cls = 0);
 
-// Fills the derived fields (tile class, vec flags, tile counts) of d.  staged:
-// never a direct class (launches of the persistent grouped kernel).
-void gemm_finalize(GemmDesc &d, int prec, bool staged = false);
+// Fills the derived fields (tile class, vec flags, tile counts) of d.
+void gemm_finalize(GemmDesc &d, int prec);
+// Whether d's operands suit the direct kernels' 32-bit byte offsets.
+bool direct_fits(const GemmDesc &d);
 // Sets d's tile class and the tile counts that follow from it.
 void gemm_set_class(GemmDesc &d, int prec, int cls);
 // Most output tiles an M x N x K product (not a Gram) can take: the partials

@@ -1115,24 +1115,25 @@ hipError_t wy_run(int64_t m, int nc, const float *Q, int64_t ldq, float *W, int6
 
 size_t wy_bytes(int nc) { return al((size_t)nc * nc * sizeof(float)) + 256; }
 
+// Tile class of a split product X^T V, rows x cols with K slices: direct, so
+// that a panel of 64 columns has no idle half tile and each workgroup's share
+// of K is a few steps per wave.  32 x 32 tiles while they cover the output in
+// four (the next panel's product: the slices give the chip enough workgroups
+// and the launch is on the critical path), 64 x 64 tiles else.  An operand too
+// long for the direct kernels' offsets keeps the staged small tiles.
+int split_class(const GemmDesc &d)
+{
+    if (!direct_fits(d))
+        return kClassSmall;
+    return (d.M <= 64 && d.N <= 64) || d.M < 2 || d.N < 2 ? kClassDirect32 : kClassDirect64;
+}
+
 // Split count for a GEMM whose output (rows x cols) is small beside its K:
 // enough slices to give every compute unit about two tiles, each slice at
 // least min_slice deep, at most max_splits.
-int splits_for(int prec, int64_t rows, int64_t cols, int64_t K, int num_cus, int max_splits,
-               int64_t min_slice)
+int splits_for(int64_t tiles, int64_t K, int num_cus, int max_splits, int64_t min_slice)
 {
-    GemmDesc d;
-    memset(&d, 0, sizeof d);
-    d.M = rows;
-    d.N = cols;
-    d.K = K;
-    d.lda = K;
-    d.ldb = cols;
-    d.ldc = cols;
-    d.a_kcontig = 0;
-    d.b_kcontig = 0;
-    gemm_finalize(d, prec, true);
-    const int64_t tiles = std::max<int64_t>(1, (int64_t)d.tiles_m * d.tiles_n);
+    tiles = std::max<int64_t>(1, tiles);
     int64_t sp = (2 * num_cus + tiles - 1) / tiles;
     sp = std::min<int64_t>(sp, std::max<int64_t>(1, K / min_slice));
     return (int)std::max<int64_t>(1, std::min<int64_t>(sp, max_splits));
@@ -1140,12 +1141,12 @@ int splits_for(int prec, int64_t rows, int64_t cols, int64_t K, int num_cus, int
 
 // Split-K GEMMs Z (rows x cols, ld cols) = X^T V with X (K x rows, ldx) and
 // V (K x cols, ldv): the slices are independent problems of one grouped
-// persistent launch (so they run side by side), each writing its own slice
+// launch (so they run side by side), each writing its own slice
 // of parts (max_splits x rows x cols scratch), summed in slice order.  The
 // descriptors of every such product of a factorisation are built on the host
 // first and uploaded once.
 struct SplitGemm {
-    int first_prob, first_item, num_items, splits, small;
+    int first_prob, first_item, num_items, splits, cls;
     float *Z, *parts;
     int64_t rows, cols;
 };
@@ -1160,7 +1161,19 @@ void add_split(SplitBatch &sb, int prec, const float *X, int64_t ldx, const floa
                int64_t rows, int64_t cols, int64_t K, float *Z, float *parts, int num_cus,
                int max_splits, int64_t min_slice)
 {
-    const int splits = splits_for(prec, rows, cols, K, num_cus, max_splits, min_slice);
+    GemmDesc d;
+    memset(&d, 0, sizeof d);
+    d.lda = ldx;
+    d.a_kcontig = 0;
+    d.ldb = ldv;
+    d.b_kcontig = 0;
+    d.ldc = cols;
+    d.M = rows;
+    d.N = cols;
+    d.alpha = 1.0f;
+    gemm_finalize(d, prec);
+    gemm_set_class(d, prec, split_class(d));
+    const int splits = splits_for(d.num_tiles, K, num_cus, max_splits, min_slice);
     const int64_t ks = (K + splits - 1) / splits;
     SplitGemm g;
     g.first_prob = (int)sb.probs.size();
@@ -1170,26 +1183,14 @@ void add_split(SplitBatch &sb, int prec, const float *X, int64_t ldx, const floa
     g.parts = parts;
     g.rows = rows;
     g.cols = cols;
-    g.small = 0;
+    g.cls = d.small;
     for (int sp = 0; sp < splits; ++sp) {
         const int64_t k0 = sp * ks;
         const int64_t kl = std::min<int64_t>(ks, K - k0);
-        GemmDesc d;
-        memset(&d, 0, sizeof d);
         d.A = X + k0 * ldx;
-        d.lda = ldx;
-        d.a_kcontig = 0;
         d.B = V + k0 * ldv;
-        d.ldb = ldv;
-        d.b_kcontig = 0;
         d.C = splits == 1 ? Z : parts + (size_t)sp * rows * cols;
-        d.ldc = cols;
-        d.M = rows;
-        d.N = cols;
         d.K = kl > 0 ? kl : 0;
-        d.alpha = 1.0f;
-        gemm_finalize(d, prec, true);
-        g.small = d.small;   // the same for every slice (it depends on M and N only)
         const int pid = (int)sb.probs.size() - g.first_prob;
         sb.probs.push_back(d);
         for (int tt = 0; tt < d.num_tiles; ++tt)
@@ -1199,20 +1200,21 @@ void add_split(SplitBatch &sb, int prec, const float *X, int64_t ldx, const floa
     sb.gemms.push_back(g);
 }
 
-// Upper bound of the items one split product of `cols` output columns adds
-// (rows <= 128, so one tile row): splits * tiles <= 2 num_cus + tiles, and
-// at most kMaxSplits * tiles; num_cus is taken as at most 1024.
-size_t split_items_bound(int64_t cols)
+// Upper bound of the items one split product of b x cols adds, in the class
+// with the most tiles: splits * tiles <= 2 num_cus + tiles, and at most
+// kMaxSplits * tiles; num_cus is taken as at most 1024.
+size_t split_items_bound(int b, int64_t cols)
 {
-    const size_t tiles = (size_t)((cols + 127) / 128);
-    return std::min<size_t>(kMaxSplits * tiles, 2048 + tiles);
+    const size_t tiles = (size_t)((b + 63) / 64) * (size_t)((cols + 63) / 64);
+    return std::max<size_t>(std::min<size_t>(kMaxSplits * tiles, 2048 + tiles),
+                            kMaxSplits * 4);   // one of at most four 32 x 32 tiles
 }
 
 hipError_t run_split(int prec, const SplitBatch &sb, int which, const GemmDesc *probs_dev,
                      const GroupItem *items_dev, int num_cus, hipStream_t s)
 {
     const SplitGemm &g = sb.gemms[which];
-    hipError_t e = launch_gemm_grouped(prec, 0, 0, g.small, probs_dev + g.first_prob,
+    hipError_t e = launch_gemm_grouped(prec, 0, 0, g.cls, probs_dev + g.first_prob,
                                        items_dev + g.first_item, g.num_items, num_cus, s);
     if (e != hipSuccess || g.splits == 1)
         return e;
@@ -1272,12 +1274,12 @@ CaqrWs caqr_ws(int64_t m, int64_t n, int b, int want_q)
     // split-K descriptors: next-panel and trailing products of every panel,
     // and the Q pass
     const int64_t np = (n + b - 1) / b;
-    // (a next-panel product has one tile row and one tile column, b <= 128)
+    // (a next-panel product has at most four tiles, b <= 128)
     const size_t nwide = (size_t)np * (want_q ? 2 : 1);
     w.probs = o;
     o += al(((size_t)np * sp_next + nwide * sp_wide) * sizeof(GemmDesc));
     w.items = o;
-    o += al(((size_t)np * sp_next + nwide * split_items_bound(n)) * sizeof(GroupItem));
+    o += al(((size_t)np * sp_next * 4 + nwide * split_items_bound(b, n)) * sizeof(GroupItem));
     w.bytes = o;
     return w;
 }
