@@ -15,18 +15,18 @@ hipError_t launch_gemm_fp32(const GemmDesc &d, hipStream_t s);
 hipError_t launch_gemm_x3(const GemmDesc &d, hipStream_t s);
 hipError_t launch_gemm_x6(const GemmDesc &d, hipStream_t s);
 hipError_t launch_gemm_f16(const GemmDesc &d, hipStream_t s);
-hipError_t launch_grouped_f16(int, int, int, const GemmDesc *, const GroupItem *, int, int,
+hipError_t launch_grouped_f16(int, int, int, const GemmDesc *, const GroupItem *, int,
                               hipStream_t);
 hipError_t launch_pack_x3(const float *, int64_t, int, int64_t, int64_t, void *, hipStream_t);
 hipError_t launch_pack_f16(const float *, int64_t, int, int64_t, int64_t, float, void *,
                            hipStream_t);
 hipError_t launch_gemm_packed_x3(const GemmDesc &d, hipStream_t s);
 hipError_t launch_gemm_packed_f16(const GemmDesc &d, hipStream_t s);
-hipError_t launch_grouped_fp32(int, int, int, const GemmDesc *, const GroupItem *, int, int,
+hipError_t launch_grouped_fp32(int, int, int, const GemmDesc *, const GroupItem *, int,
                                hipStream_t);
-hipError_t launch_grouped_x3(int, int, int, const GemmDesc *, const GroupItem *, int, int,
+hipError_t launch_grouped_x3(int, int, int, const GemmDesc *, const GroupItem *, int,
                              hipStream_t);
-hipError_t launch_grouped_x6(int, int, int, const GemmDesc *, const GroupItem *, int, int,
+hipError_t launch_grouped_x6(int, int, int, const GemmDesc *, const GroupItem *, int,
                              hipStream_t);
 
 int tile_m(int, int cls)
@@ -135,18 +135,17 @@ hipError_t launch_gemm(int prec, const GemmDesc &d, hipStream_t s)
 }
 
 hipError_t launch_gemm_grouped(int prec, int akc, int bkc, int cls, const GemmDesc *probs,
-                               const GroupItem *items, int num_items, int grid_size,
-                               hipStream_t s)
+                               const GroupItem *items, int num_items, hipStream_t s)
 {
     switch (prec) {
     case PREC_FP32:
-        return launch_grouped_fp32(akc, bkc, cls, probs, items, num_items, grid_size, s);
+        return launch_grouped_fp32(akc, bkc, cls, probs, items, num_items, s);
     case PREC_BF16X3:
-        return launch_grouped_x3(akc, bkc, cls, probs, items, num_items, grid_size, s);
+        return launch_grouped_x3(akc, bkc, cls, probs, items, num_items, s);
     case PREC_BF16X6:
-        return launch_grouped_x6(akc, bkc, cls, probs, items, num_items, grid_size, s);
+        return launch_grouped_x6(akc, bkc, cls, probs, items, num_items, s);
     case PREC_F16X3:
-        return launch_grouped_f16(akc, bkc, cls, probs, items, num_items, grid_size, s);
+        return launch_grouped_f16(akc, bkc, cls, probs, items, num_items, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -228,6 +227,66 @@ __global__ void __launch_bounds__(kThreads) reduce_fixed_kernel(const double *__
         out[0] = s;
 }
 
+// reduce_fixed_kernel's sum, then the state of an iteration (see StepState).
+__device__ double fixed_sum(const double *parts, int64_t count, double *sh)
+{
+    double acc = 0.0;
+    for (int64_t i = threadIdx.x; i < count; i += kThreads)
+        acc += parts[i];
+    return block_sum(acc, sh);
+}
+
+__device__ void reset_state(StepState *st, double norm2, bool ok)
+{
+    st->norm2 = norm2;
+    st->delta = INFINITY;
+    st->prev = INFINITY;
+    st->stop = ok ? 0 : 1;
+    st->steps = 0;
+    st->reason = ok ? 2 : 3;
+}
+
+__global__ void __launch_bounds__(kThreads) norm_state_kernel(const double *__restrict__ parts,
+                                                              int64_t count, StepState *st)
+{
+    __shared__ double sh[kThreads / 64];
+    const double s = fixed_sum(parts, count, sh);
+    if (threadIdx.x == 0) {
+        const double nrm = sqrt(s);
+        reset_state(st, s, nrm > 0.0 && isfinite(nrm));
+    }
+}
+
+__global__ void clear_state_kernel(StepState *st) { reset_state(st, 0.0, true); }
+
+__global__ void __launch_bounds__(kThreads) step_state_kernel(const double *__restrict__ parts,
+                                                              int64_t count, StepState *st,
+                                                              StepTest t)
+{
+    __shared__ double sh[kThreads / 64];
+    if (st->stop)
+        return;
+    const double s = fixed_sum(parts, count, sh);
+    if (threadIdx.x == 0) {
+        const double delta = t.scale * sqrt(s);
+        const int steps = st->steps + 1;
+        int stop = 1, reason = 2;
+        if (!isfinite(delta))
+            reason = 3;
+        else if (delta <= (t.tol_doubles ? ldexp(t.tol, steps) : t.tol))
+            reason = 0;
+        else if (delta < t.stag_below && delta > 0.5 * st->prev)
+            reason = 1;
+        else
+            stop = steps >= t.max_steps;
+        st->prev = delta;
+        st->delta = delta;
+        st->steps = steps;
+        st->reason = reason;
+        st->stop = stop;
+    }
+}
+
 __global__ void __launch_bounds__(kThreads) reduce_grouped_kernel(const ReduceItem *__restrict__ items)
 {
     __shared__ double sh[kThreads / 64];
@@ -253,8 +312,11 @@ __global__ void scale_kernel(const float *__restrict__ X, int64_t ldx, float *__
 // rounded as on the host).
 __global__ void scale_by_norm_kernel(const float *__restrict__ X, int64_t ldx,
                                      float *__restrict__ Y, int64_t ldy, int64_t m, int64_t n,
-                                     const double *__restrict__ nrm2)
+                                     const double *__restrict__ nrm2,
+                                     const int *__restrict__ stop)
 {
+    if (stop && *stop)
+        return;
     const double nrm = sqrt(*nrm2);
     for (int64_t r = blockIdx.y; r < m; r += gridDim.y)
         for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n;
@@ -511,6 +573,25 @@ hipError_t launch_reduce_fixed(const double *parts, int64_t count, double *out, 
     return hipGetLastError();
 }
 
+hipError_t launch_norm_state(const double *parts, int64_t count, StepState *st, hipStream_t s)
+{
+    hipLaunchKernelGGL(norm_state_kernel, dim3(1), dim3(kThreads), 0, s, parts, count, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear_state(StepState *st, hipStream_t s)
+{
+    hipLaunchKernelGGL(clear_state_kernel, dim3(1), dim3(1), 0, s, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_step_state(const double *parts, int64_t count, StepState *st,
+                             const StepTest &test, hipStream_t s)
+{
+    hipLaunchKernelGGL(step_state_kernel, dim3(1), dim3(kThreads), 0, s, parts, count, st, test);
+    return hipGetLastError();
+}
+
 hipError_t launch_reduce_grouped(const ReduceItem *items, int n, hipStream_t s)
 {
     if (n <= 0)
@@ -530,12 +611,12 @@ hipError_t launch_scale(const float *X, int64_t ldx, float *Y, int64_t ldy, int6
 }
 
 hipError_t launch_scale_by_norm(const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t m,
-                                int64_t n, const double *nrm2, hipStream_t s)
+                                int64_t n, const double *nrm2, hipStream_t s, const int *stop)
 {
     if (m == 0 || n == 0)
         return hipSuccess;
     hipLaunchKernelGGL(scale_by_norm_kernel, grid2d(m, n), dim3(kThreads), 0, s, X, ldx, Y, ldy,
-                       m, n, nrm2);
+                       m, n, nrm2, stop);
     return hipGetLastError();
 }
 

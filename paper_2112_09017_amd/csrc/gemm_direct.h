@@ -205,7 +205,7 @@ __device__ __forceinline__ void direct_step(const float (&va)[FM][8], const floa
 template <class OA, class OB, int FM, int FN, int KW>
 __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)[FM][FN],
                                                 int64_t row0, int64_t col0, int tm, int tn, int w,
-                                                int lane, float *red, double *red8)
+                                                int lane, int stop, float *red, double *red8)
 {
     constexpr int NE = FM * FN * 16, EPW = NE / KW, HW = KW / 2;
     auto at = [&](int v, int el) -> float & { return red[(v * NE + el) * 64 + lane]; };
@@ -230,6 +230,8 @@ __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)
             s += at(v, w * EPW + q);
         out[q] = s;
     }
+    if (stop)
+        return;   // uniform over the launch
     const bool want_ss = d.partials != nullptr;
     double ss = 0.0;
     float ev[EPW];
@@ -297,6 +299,8 @@ __device__ __forceinline__ void direct_tile(const GemmDesc &d, int tm, int tn, i
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t row0 = (int64_t)tm * (32 * FM), col0 = (int64_t)tn * (32 * FN);
+    // read here, used by the epilogue: its latency is not waited for
+    const int stop = d.stop ? *gmem(d.stop) : 0;
     DirectOperand<AKC, FM> oa;
     DirectOperand<BKC, FN> ob;
     oa.init(d.A, d.lda, d.M, row0, lane);
@@ -343,7 +347,7 @@ __device__ __forceinline__ void direct_tile(const GemmDesc &d, int tm, int tn, i
         if (i + s < cnt)
             direct_step<PREC, FM, FN>(va[s], vb[s], d.scale_a, d.scale_b, acc);
     direct_epilogue<DirectOperand<AKC, FM>, DirectOperand<BKC, FN>, FM, FN, KW>(
-        d, acc, row0, col0, tm, tn, w, lane, red, red8);
+        d, acc, row0, col0, tm, tn, w, lane, stop, red, red8);
 }
 
 template <int CLS> constexpr int direct_red_floats()
@@ -447,7 +451,7 @@ __global__ void __launch_bounds__(DirectCfg<CLS>::KW * 64, DirectCfg<CLS>::WPE)
     if (i < cnt)
         direct_mfma<PREC, FM, FN>(a[0], b[0], acc);
     direct_epilogue<DirectOperand<true, FM>, DirectOperand<true, FN>, FM, FN, KW>(
-        d, acc, row0, col0, tm, tn, w, lane, red, red8);
+        d, acc, row0, col0, tm, tn, w, lane, 0, red, red8);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -508,7 +512,7 @@ hipError_t launch_direct_items(int akc, int bkc, const GemmDesc *probs, const Gr
 
 template <int PREC>
 hipError_t launch_grouped_any(int akc, int bkc, int small, const GemmDesc *probs,
-                              const GroupItem *items, int num_items, int grid_size, hipStream_t s)
+                              const GroupItem *items, int num_items, hipStream_t s)
 {
     if (num_items <= 0)
         return hipSuccess;
@@ -516,7 +520,7 @@ hipError_t launch_grouped_any(int akc, int bkc, int small, const GemmDesc *probs
         return launch_direct_items<PREC, kClassDirect64>(akc, bkc, probs, items, num_items, s);
     if (small == kClassDirect32)
         return launch_direct_items<PREC, kClassDirect32>(akc, bkc, probs, items, num_items, s);
-    return launch_grouped_t<PREC>(akc, bkc, small, probs, items, num_items, grid_size, s);
+    return launch_grouped_t<PREC>(akc, bkc, small, probs, items, num_items, s);
 }
 
 // Packed operands on the tile class of d.

@@ -11,9 +11,9 @@ hipError_t launch_gemm_f16(const GemmDesc &d, hipStream_t s)
 }
 
 hipError_t launch_grouped_f16(int akc, int bkc, int cls, const GemmDesc *probs,
-                              const GroupItem *items, int num_items, int grid_size, hipStream_t s)
+                              const GroupItem *items, int num_items, hipStream_t s)
 {
-    return dev::launch_grouped_any<PREC_F16X3>(akc, bkc, cls, probs, items, num_items, grid_size, s);
+    return dev::launch_grouped_any<PREC_F16X3>(akc, bkc, cls, probs, items, num_items, s);
 }
 
 hipError_t launch_pack_f16(const float *X, int64_t ld, int kc, int64_t rows, int64_t k, float sc,

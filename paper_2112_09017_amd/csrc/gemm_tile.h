@@ -59,37 +59,36 @@ template <int PREC> struct Cfg;
 // the second 16-k half of the current stage.  PIPE 2: two register stages,
 // BK = 16, the split of stage s+1 runs under the MFMAs of stage s.
 template <> struct Cfg<PREC_FP32> {
-    static constexpr int BM = 256, BN = 256, BK = 32, WM = 2, WN = 2, OCC = 1, PIPE = 1, GOCC = 1;
+    static constexpr int BM = 256, BN = 256, BK = 32, WM = 2, WN = 2, OCC = 1, PIPE = 1;
     static constexpr int terms = 1, entry_bytes = 32;
 };
 template <> struct Cfg<PREC_BF16X3> {
-    static constexpr int BM = 256, BN = 256, BK = 32, WM = 2, WN = 2, OCC = 1, PIPE = 1, GOCC = 1;
+    static constexpr int BM = 256, BN = 256, BK = 32, WM = 2, WN = 2, OCC = 1, PIPE = 1;
     static constexpr int terms = 2, entry_bytes = 16;
 };
 // two fp16 terms: the tile, stage and register use of 3xBF16
 template <> struct Cfg<PREC_F16X3> : Cfg<PREC_BF16X3> {};
 template <> struct Cfg<PREC_BF16X6> {
-    static constexpr int BM = 256, BN = 256, BK = 16, WM = 2, WN = 2, OCC = 1, PIPE = 2, GOCC = 1;
+    static constexpr int BM = 256, BN = 256, BK = 16, WM = 2, WN = 2, OCC = 1, PIPE = 2;
     static constexpr int terms = 3, entry_bytes = 16;
 };
 // 128 x 128 tiles (64 x 64 per wave), two workgroups per CU: problems too
 // small to give every CU a 256 x 256 tile.  Same BK and product order as the
 // large tiles, so every output element is computed identically.
 template <> struct Cfg<PREC_FP32 | kSmall> {
-    static constexpr int BM = 128, BN = 128, BK = 32, WM = 2, WN = 2, OCC = 2, PIPE = 1, GOCC = 2;
+    static constexpr int BM = 128, BN = 128, BK = 32, WM = 2, WN = 2, OCC = 2, PIPE = 1;
     static constexpr int terms = 1, entry_bytes = 32;
 };
 template <> struct Cfg<PREC_BF16X3 | kSmall> {
-    static constexpr int BM = 128, BN = 128, BK = 32, WM = 2, WN = 2, OCC = 2, PIPE = 1, GOCC = 2;
+    static constexpr int BM = 128, BN = 128, BK = 32, WM = 2, WN = 2, OCC = 2, PIPE = 1;
     static constexpr int terms = 2, entry_bytes = 16;
 };
 template <> struct Cfg<PREC_F16X3 | kSmall> : Cfg<PREC_BF16X3 | kSmall> {};
 template <> struct Cfg<PREC_BF16X6 | kSmall> {
     // two register stages of three terms fit within the 256 registers of two
     // workgroups per CU (at most 212 used), so one workgroup's loads and split
-    // overlap the other's MFMAs; the grouped kernel (one register stage) runs two
-    // per CU too
-    static constexpr int BM = 128, BN = 128, BK = 16, WM = 2, WN = 2, OCC = 2, PIPE = 2, GOCC = 2;
+    // overlap the other's MFMAs
+    static constexpr int BM = 128, BN = 128, BK = 16, WM = 2, WN = 2, OCC = 2, PIPE = 2;
     static constexpr int terms = 3, entry_bytes = 16;
 };
 
@@ -100,7 +99,7 @@ template <> struct Cfg<PREC_BF16X6 | kSmall> {
 constexpr int kPacked = 32;
 constexpr int kPackStages = 4;
 template <> struct Cfg<PREC_BF16X3 | kPacked> {
-    static constexpr int BM = 256, BN = 256, BK = 16, WM = 2, WN = 2, OCC = 1, PIPE = 0, GOCC = 1;
+    static constexpr int BM = 256, BN = 256, BK = 16, WM = 2, WN = 2, OCC = 1, PIPE = 0;
     static constexpr int terms = 2, entry_bytes = 16;
 };
 template <> struct Cfg<PREC_F16X3 | kPacked> : Cfg<PREC_BF16X3 | kPacked> {};
@@ -1064,21 +1063,18 @@ __device__ __forceinline__ void k_loop1(const GemmDesc &d, int64_t row0, int64_t
     }
 }
 
-// GROUPED: the persistent kernel keeps extra state live across tiles; where
-// two register stages would spill there, one stage is used (same arithmetic,
-// same k order, so identical results).
-template <int PREC, bool AKC, bool BKC, bool GUARD, bool GROUPED = false>
+template <int PREC, bool AKC, bool BKC, bool GUARD>
 __device__ __forceinline__ void k_loop(const GemmDesc &d, int64_t row0, int64_t col0,
                                        f32x16 (&acc)[Geo<PREC>::FM][Geo<PREC>::FN],
                                        char *smem, int wm, int wn, int lane)
 {
-    if constexpr (Cfg<PREC>::PIPE == 1 || GROUPED)
+    if constexpr (Cfg<PREC>::PIPE == 1)
         k_loop1<PREC, AKC, BKC, GUARD>(d, row0, col0, acc, smem, wm, wn, lane);
     else
         k_loop2<PREC, AKC, BKC, GUARD>(d, row0, col0, acc, smem, wm, wn, lane);
 }
 
-template <int PREC, bool AKC, bool BKC, bool GROUPED = false>
+template <int PREC, bool AKC, bool BKC>
 __device__ __forceinline__ void gemm_tile(const GemmDesc &d, int tm, int tn, char *smem,
                                           double *red)
 {
@@ -1104,9 +1100,9 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc &d, int tm, int tn, cha
             acc[i][j] = f32x16{};
 
     if (interior)
-        k_loop<PREC, AKC, BKC, false, GROUPED>(d, row0, col0, acc, smem, wm, wn, lane);
+        k_loop<PREC, AKC, BKC, false>(d, row0, col0, acc, smem, wm, wn, lane);
     else
-        k_loop<PREC, AKC, BKC, true, GROUPED>(d, row0, col0, acc, smem, wm, wn, lane);
+        k_loop<PREC, AKC, BKC, true>(d, row0, col0, acc, smem, wm, wn, lane);
     epilogue<PREC>(d, acc, row0, col0, tm, tn, wm, wn, lane, red);
 }
 
@@ -1160,31 +1156,8 @@ __global__ void __launch_bounds__(Geo<PREC>::NT, (kernel_occ<PREC, AKC, BKC>()))
     gemm_tile<PREC, AKC, BKC>(d, tm, tn, smem, red);
 }
 
-// Persistent grouped kernel: workgroup b runs items b, b + grid, ...; each
-// item is one tile of one problem, computed exactly as gemm_kernel would.  A
-// capped grid leaves CUs to work on other streams (the panel chain of CAQR).
-template <int PREC, bool AKC, bool BKC>
-__global__ void __launch_bounds__(Geo<PREC>::NT, Cfg<PREC>::GOCC)
-    gemm_grouped_kernel(const GemmDesc *__restrict__ probs, const GroupItem *__restrict__ items,
-                        int num_items)
-{
-    __shared__ __attribute__((aligned(16))) char smem[2 * Geo<PREC>::stage_bytes];
-    __shared__ double red[Cfg<PREC>::WM * Cfg<PREC>::WN];
-    for (int it = blockIdx.x; it < num_items; it += gridDim.x) {
-        const GroupItem gi = items[it];
-        if (gi.prob < 0)
-            continue;   // empty item (uniform over the workgroup)
-        const GemmDesc d = probs[gi.prob];
-        int tm, tn;
-        tile_coords(d, gi.tile, tm, tn);
-        gemm_tile<PREC, AKC, BKC, true>(d, tm, tn, smem, red);
-        __syncthreads();
-    }
-}
-
-// Grouped kernel, one workgroup per item: workgroup b computes item b exactly
-// as gemm_kernel would (the same loop, so the same bits as the persistent
-// kernel too); workgroup b runs on XCD b % kXcds, so the caller places the
+// Grouped kernel: workgroup b computes item b, one tile of one problem, exactly
+// as gemm_kernel would; it runs on XCD b % kXcds, so the caller places the
 // items on the XCDs by their position in the list.
 template <int PREC, bool AKC, bool BKC>
 __global__ void __launch_bounds__(Geo<PREC>::NT, (kernel_occ<PREC, AKC, BKC>()))
@@ -1615,48 +1588,34 @@ hipError_t launch_t(const GemmDesc &d, hipStream_t s)
     return d.small ? launch_one<PREC | kSmall>(d, s) : launch_one<PREC>(d, s);
 }
 
-// grid_size is the number of CUs; small tiles run two workgroups per CU.
-template <int PREC, bool AKC, bool BKC>
-void launch_grouped_kern(bool persist, dim3 grid, dim3 block, hipStream_t s,
-                         const GemmDesc *probs, const GroupItem *items, int num_items)
-{
-    if (persist)
-        hipLaunchKernelGGL((gemm_grouped_kernel<PREC, AKC, BKC>), grid, block, 0, s, probs,
-                           items, num_items);
-    else
-        hipLaunchKernelGGL((gemm_items_kernel<PREC, AKC, BKC>), grid, block, 0, s, probs, items,
-                           num_items);
-}
-
 template <int PREC>
 hipError_t launch_grouped_one(int akc, int bkc, const GemmDesc *probs, const GroupItem *items,
-                              int num_items, int grid_size, hipStream_t s)
+                              int num_items, hipStream_t s)
 {
-    // grid_size > 0: persistent workgroups, at most grid_size per GOCC; else
-    // one workgroup per item
-    const bool persist = grid_size > 0;
-    grid_size *= Cfg<PREC>::GOCC;
-    dim3 grid(persist && grid_size < num_items ? grid_size : num_items), block(Geo<PREC>::NT);
+    const dim3 grid(num_items), block(Geo<PREC>::NT);
     if (akc && bkc)
-        launch_grouped_kern<PREC, true, true>(persist, grid, block, s, probs, items, num_items);
+        hipLaunchKernelGGL((gemm_items_kernel<PREC, true, true>), grid, block, 0, s, probs, items,
+                           num_items);
     else if (akc)
-        launch_grouped_kern<PREC, true, false>(persist, grid, block, s, probs, items, num_items);
+        hipLaunchKernelGGL((gemm_items_kernel<PREC, true, false>), grid, block, 0, s, probs, items,
+                           num_items);
     else if (bkc)
-        launch_grouped_kern<PREC, false, true>(persist, grid, block, s, probs, items, num_items);
+        hipLaunchKernelGGL((gemm_items_kernel<PREC, false, true>), grid, block, 0, s, probs, items,
+                           num_items);
     else
-        launch_grouped_kern<PREC, false, false>(persist, grid, block, s, probs, items, num_items);
+        hipLaunchKernelGGL((gemm_items_kernel<PREC, false, false>), grid, block, 0, s, probs,
+                           items, num_items);
     return hipGetLastError();
 }
 
 template <int PREC>
 hipError_t launch_grouped_t(int akc, int bkc, int small, const GemmDesc *probs,
-                            const GroupItem *items, int num_items, int grid_size, hipStream_t s)
+                            const GroupItem *items, int num_items, hipStream_t s)
 {
     if (num_items <= 0)
         return hipSuccess;
-    return small ? launch_grouped_one<PREC | kSmall>(akc, bkc, probs, items, num_items,
-                                                     grid_size, s)
-                 : launch_grouped_one<PREC>(akc, bkc, probs, items, num_items, grid_size, s);
+    return small ? launch_grouped_one<PREC | kSmall>(akc, bkc, probs, items, num_items, s)
+                 : launch_grouped_one<PREC>(akc, bkc, probs, items, num_items, s);
 }
 
 // Packed operand bytes for R rows and inner dimension K.

@@ -11,9 +11,9 @@ hipError_t launch_gemm_x6(const GemmDesc &d, hipStream_t s)
 }
 
 hipError_t launch_grouped_x6(int akc, int bkc, int cls, const GemmDesc *probs,
-                             const GroupItem *items, int num_items, int grid_size, hipStream_t s)
+                             const GroupItem *items, int num_items, hipStream_t s)
 {
-    return dev::launch_grouped_any<PREC_BF16X6>(akc, bkc, cls, probs, items, num_items, grid_size, s);
+    return dev::launch_grouped_any<PREC_BF16X6>(akc, bkc, cls, probs, items, num_items, s);
 }
 
 }  // namespace la

@@ -12,7 +12,8 @@
 // Each step is two launches: the symmetric Gram (only upper tiles, the
 // polynomial coefficients applied in its epilogue) and the product with the
 // update applied in the epilogue.  The only host synchronisation per step is
-// the 8-byte readback of ||U' - U||_F^2 for the data-dependent stop test.
+// the 8-byte readback of ||U' - U||_F^2 for the data-dependent stop test; small
+// problems queue their steps in batches instead, with the test on the device.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -392,7 +393,8 @@ static hipError_t gram_step(const PolarPlan &p, int prec, const float *X, int64_
 // *ntiles receives their count).
 static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int64_t ldx,
                               const float *P, double alpha, double beta, float *Xn, int64_t ldxn,
-                              double *tiles, int *ntiles, const PolarWs &w, hipStream_t s)
+                              double *tiles, int *ntiles, const PolarWs &w, hipStream_t s,
+                              const int *stop = nullptr)
 {
     const int64_t m = p.m, n = p.n;
     GemmDesc d;
@@ -433,11 +435,42 @@ static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int6
         d.beta = (float)beta;
     }
     d.partials = tiles;
+    d.stop = stop;
     gemm_f16_scales(d, prec, kIterScale, kIterScale);
     gemm_finalize(d, prec);
     if (ntiles)
         *ntiles = d.tiles_m * d.tiles_n;
     return gemm_packed_or_plain(prec, d, w.pk, s);
+}
+
+// Newton-Schulz (inversion) steps queued before the first look at the stop test, and
+// between later ones: well-conditioned inputs stop within the first batch.
+constexpr int kFirstBatch = 10, kNextBatch = 4;
+constexpr int kFirstInvBatch = 16;
+
+// Whether every step of p runs on the direct kernels (X in either buffer):
+// launches short enough that the host's turn between steps would take longer,
+// so the steps are queued ahead of their stop test.  (With polish the step
+// after the stop differs, so those wait.)
+static bool queues_ahead(const PolarPlan &p, int64_t ldu)
+{
+    if (p.polish || update_splits(p) > 1)
+        return false;
+    for (int64_t ld : {p.n, ldu})
+        for (int pr : {p.prec_pre, p.prec_ns}) {
+            GemmDesc d;
+            memset(&d, 0, sizeof d);
+            d.lda = ld;
+            d.a_kcontig = 1;
+            d.ldb = p.n;
+            d.M = p.m;
+            d.N = p.n;
+            d.K = p.n;
+            gemm_finalize(d, pr);
+            if (!is_direct(d.small))
+                return false;
+        }
+    return true;
 }
 
 // H = (U^T A + A^T U) / 2 in one symmetric pass: the upper triangle of U^T A
@@ -586,11 +619,32 @@ static InvWs inverse_carve(const InvPlan &p, void *ws)
     return w;
 }
 
+// Whether the steps' updates run on the direct kernels (X in either buffer), so
+// that they are queued ahead of their stop test as la_polar's are.
+static bool queues_ahead(const InvPlan &p, int64_t ldx)
+{
+    for (int64_t ld : {p.n, ldx}) {
+        GemmDesc u;
+        memset(&u, 0, sizeof u);
+        u.M = p.m;
+        u.N = p.n;
+        u.K = p.wide ? p.n : p.m;
+        u.lda = p.wide ? ld : p.r;
+        u.ldb = p.wide ? p.r : ld;
+        u.a_kcontig = 1;
+        gemm_finalize(u, p.prec);
+        if (!is_direct(u.small))
+            return false;
+    }
+    return true;
+}
+
 // One step X' = X + X (I - A X)  (wide / square)  or  X + (I - X A) X  (tall),
 // with FP64 per-tile partials of (X' - X)^2 in w.tiles.
 static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64_t lda,
                                const float *X, int64_t ldx, float *Xn, int64_t ldxn,
-                               const InvWs &w, int *ntiles, hipStream_t s)
+                               const InvWs &w, int *ntiles, hipStream_t s,
+                               const int *stop = nullptr)
 {
     GemmDesc d;
     memset(&d, 0, sizeof d);
@@ -653,6 +707,7 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
         u.b_kcontig = 0;
         u.K = p.m;
     }
+    u.stop = stop;
     gemm_finalize(u, prec);
     *ntiles = u.tiles_m * u.tiles_n;
     return gemm_packed_or_plain(prec, u, w.pk, s);
@@ -1086,34 +1141,50 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
     inf.last_delta = INFINITY;
     inf.stop_reason = 2;
 
-    // ||A||_F in FP64
-    double h2[2];
-    LA_HIP(launch_sumsq(A, m, n, lda, w.sumsq, s), "la_polar: norm");
-    LA_HIP(launch_reduce_fixed(w.sumsq, sumsq_num_partials(), w.scal, s), "la_polar: norm");
-    LA_HIP(hipMemcpyAsync(h2, w.scal, sizeof(double), hipMemcpyDeviceToHost, s),
-           "la_polar: readback");
-    LA_HIP(hipStreamSynchronize(s), "la_polar: sync");
-    const double fro = sqrt(h2[0]);
-    inf.fro_norm_a = fro;
-    if (!(fro > 0.0) || !isfinite(fro)) {
-        if (info)
-            *info = inf;
-        set_error("la_polar: ||A||_F = %g (zero or not finite)", fro);
-        return LA_ERR_NONFINITE;
-    }
-
     // ping-pong between U (ld ldu) and the workspace copy (ld n)
     float *buf[2] = {U, w.X};
     int64_t ld[2] = {ldu, n};
     int cur = 0;
-    LA_HIP(launch_scale(A, lda, buf[cur], ld[cur], m, n, fro, s), "la_polar: scale");
+    double h2[2];
+    double fro = 0.0;
+    StopState stop;
+    bool converged = false, finite = true;
+
+    LA_HIP(launch_sumsq(A, m, n, lda, w.sumsq, s), "la_polar: norm");
+    const bool ahead = queues_ahead(p, ldu);
+    StepState *st = (StepState *)w.scal;
+    const int *dev_stop = nullptr;
+    auto bad_norm = [&]() {
+        if (info)
+            *info = inf;
+        set_error("la_polar: ||A||_F = %g (zero or not finite)", fro);
+        return LA_ERR_NONFINITE;
+    };
+    if (ahead) {
+        // the norm stays on the device; an A without one stops every later write
+        LA_HIP(launch_norm_state(w.sumsq, sumsq_num_partials(), st, s), "la_polar: norm");
+        dev_stop = &st->stop;
+        LA_HIP(launch_scale_by_norm(A, lda, buf[cur], ld[cur], m, n, &st->norm2, s, dev_stop),
+               "la_polar: scale");
+    } else {
+        // ||A||_F in FP64
+        LA_HIP(launch_reduce_fixed(w.sumsq, sumsq_num_partials(), w.scal, s), "la_polar: norm");
+        LA_HIP(hipMemcpyAsync(h2, w.scal, sizeof(double), hipMemcpyDeviceToHost, s),
+               "la_polar: readback");
+        LA_HIP(hipStreamSynchronize(s), "la_polar: sync");
+        fro = sqrt(h2[0]);
+        inf.fro_norm_a = fro;
+        if (!(fro > 0.0) || !isfinite(fro))
+            return bad_norm();
+        LA_HIP(launch_scale(A, lda, buf[cur], ld[cur], m, n, fro, s), "la_polar: scale");
+    }
 
     // preconditioning: U <- a U (I - c U^T U), c = (4/27) a^2
     for (int i = 0; i < p.k_pre; ++i) {
         LA_HIP(gram_step(p, p.prec_pre, buf[cur], ld[cur], -p.c, 1.0, w.P, w, s),
                "la_polar: precondition gram");
         LA_HIP(update_step(p, p.prec_pre, buf[cur], ld[cur], w.P, p.a, 0.0, buf[cur ^ 1],
-                           ld[cur ^ 1], nullptr, nullptr, w, s),
+                           ld[cur ^ 1], nullptr, nullptr, w, s, dev_stop),
                "la_polar: precondition update");
         cur ^= 1;
         inf.iters_precond++;
@@ -1121,9 +1192,51 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
 
     // Newton-Schulz: U' = U + U (I - U^T U) / 2, delta = ||U' - U||_F, until the
     // stop test (polar_host.h); a polish step runs at BF16X6
-    StopState stop;
-    bool converged = false;
-    for (;;) {
+    if (ahead) {
+        // Steps are queued in batches; the device applies the stop test after
+        // each, and from the stop on leaves the iterates alone.  256^2: 20 us
+        // of readback and wait per step saved, 540 -> 360 us for the polar
+        // (9 steps), at 10 us per step queued in vain.
+        StepTest t;
+        t.scale = 1.0;
+        t.tol = (double)std::max(m, n) * p.eps;
+        t.tol_doubles = 0;
+        t.stag_below = p.stagnation ? 1e-2 * sqrt((double)n) : 0.0;
+        t.max_steps = p.max_iter;
+        const int start = cur;
+        StepState h;
+        int queued = 0, batch = kFirstBatch;
+        do {
+            for (const int to = std::min(queued + batch, p.max_iter); queued < to; ++queued) {
+                int ntiles = 0;
+                LA_HIP(gram_step(p, p.prec_ns, buf[cur], ld[cur], -1.0, 1.0, w.P, w, s),
+                       "la_polar: NS gram");
+                LA_HIP(update_step(p, p.prec_ns, buf[cur], ld[cur], w.P, 0.5, 1.0, buf[cur ^ 1],
+                                   ld[cur ^ 1], w.tiles, &ntiles, w, s, dev_stop),
+                       "la_polar: NS update");
+                LA_HIP(launch_step_state(w.tiles, ntiles, st, t, s), "la_polar: delta");
+                cur ^= 1;
+            }
+            batch = kNextBatch;
+            LA_HIP(hipMemcpyAsync(&h, st, sizeof h, hipMemcpyDeviceToHost, s),
+                   "la_polar: readback");
+            LA_HIP(hipStreamSynchronize(s), "la_polar: sync");
+        } while (!h.stop);
+        fro = sqrt(h.norm2);
+        inf.fro_norm_a = fro;
+        if (!(fro > 0.0) || !isfinite(fro)) {
+            inf.iters_precond = 0;
+            return bad_norm();
+        }
+        cur = (start + h.steps) & 1;
+        inf.iters_ns = h.steps;
+        inf.last_delta = h.delta;
+        finite = h.reason != 3;
+        converged = h.reason < 2;
+        if (finite)
+            inf.stop_reason = h.reason;
+    }
+    while (!ahead) {
         const int prec = stop.stopped ? PREC_BF16X6 : p.prec_ns;
         int ntiles = 0;
         LA_HIP(gram_step(p, prec, buf[cur], ld[cur], -1.0, 1.0, w.P, w, s),
@@ -1140,10 +1253,8 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
         const double delta = sqrt(h2[1]);
         inf.last_delta = delta;
         if (!isfinite(delta)) {
-            if (info)
-                *info = inf;
-            set_error("la_polar: step norm is not finite");
-            return LA_ERR_NONFINITE;
+            finite = false;
+            break;
         }
         const StopDecision d = stop_test(p, m, n, delta, stop, inf.iters_ns);
         inf.stop_reason = stop.reason;
@@ -1153,6 +1264,12 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
         }
         if (d == STOP_CAP)
             break;
+    }
+    if (!finite) {
+        if (info)
+            *info = inf;
+        set_error("la_polar: step norm is not finite");
+        return LA_ERR_NONFINITE;
     }
     if (cur != 0)
         LA_HIP(launch_copy(buf[cur], ld[cur], U, ldu, m, n, s), "la_polar: copy");
@@ -1278,8 +1395,46 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
     const double scale = p.literal ? 1.0 : sqrt(a);
     double eps = p.eps;
     const int total = p.max_iter + (p.polish ? 1 : 0);
-    bool stopped = false;
-    for (int it = 0; it < total; ++it) {
+    bool stopped = false, finite = true;
+    int it = 0;
+    if (queues_ahead(p, ldx)) {
+        // steps queued in batches, the stop test on the device (as in la_polar)
+        StepTest t;
+        t.scale = scale;
+        t.tol = p.eps;
+        t.tol_doubles = 1;
+        t.stag_below = 0.0;
+        t.max_steps = p.max_iter;
+        StepState *st = (StepState *)w.scal;
+        StepState h;
+        LA_HIP(launch_clear_state(st, s), "la_inverse: state");
+        int queued = 0, batch = kFirstInvBatch;
+        do {
+            for (const int to = std::min(queued + batch, p.max_iter); queued < to; ++queued) {
+                int ntiles = 0;
+                const int from = queued & 1;
+                LA_HIP(inverse_step(p, p.prec, A, lda, buf[from], ld[from], buf[from ^ 1],
+                                    ld[from ^ 1], w, &ntiles, s, &st->stop),
+                       "la_inverse: step");
+                LA_HIP(launch_step_state(w.tiles, ntiles, st, t, s), "la_inverse: delta");
+            }
+            batch = kNextBatch;
+            LA_HIP(hipMemcpyAsync(&h, st, sizeof h, hipMemcpyDeviceToHost, s),
+                   "la_inverse: readback");
+            LA_HIP(hipStreamSynchronize(s), "la_inverse: sync");
+        } while (!h.stop);
+        cur = h.steps & 1;
+        inf.iters = h.steps;
+        finite = h.reason != 3;
+        stopped = h.reason == 0;
+        if (finite) {
+            inf.last_delta = h.delta;
+            inf.last_tol = ldexp(p.eps, h.steps);
+            inf.stop_reason = h.reason;
+        }
+        it = stopped && p.polish ? h.steps : total;   // what is left: the polish step
+    }
+    for (; it < total && finite; ++it) {
         const bool polishing = stopped;
         const int prec = polishing ? PREC_BF16X6 : p.prec;
         int ntiles = 0;
@@ -1294,10 +1449,8 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
         inf.iters++;
         const double delta = scale * sqrt(h2[1]);
         if (!isfinite(delta)) {
-            if (info)
-                *info = inf;
-            set_error("la_inverse: step norm is not finite");
-            return LA_ERR_NONFINITE;
+            finite = false;
+            break;
         }
         if (polishing)
             break;
@@ -1312,6 +1465,12 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
             break;
         if (!stopped && it + 1 >= p.max_iter)
             break;
+    }
+    if (!finite) {
+        if (info)
+            *info = inf;
+        set_error("la_inverse: step norm is not finite");
+        return LA_ERR_NONFINITE;
     }
     if (cur != 0)
         LA_HIP(launch_copy(buf[cur], ld[cur], X, ldx, m, n, s), "la_inverse: copy");

@@ -53,6 +53,9 @@ struct GemmDesc {
     // 32, so every slice but the last is whole K stages)
     int slices;
     int64_t slice_k, slice_stride;
+    // direct classes: optional device word; while it is not 0 the launch leaves
+    // its output as it is (a step queued past the iteration's stop)
+    const int *stop;
 };
 
 // Tile classes.  Large (256 x 256) and small (128 x 128) tiles (gemm_tile.h) use
@@ -96,20 +99,17 @@ hipError_t launch_gemm(int prec, const GemmDesc &d, hipStream_t s);
 constexpr int kXcds = 8;
 
 // Grouped launch: every item is one output tile of one problem; all problems
-// share precision and operand layouts.  probs / items live in device memory.
-// grid_size > 0: that many persistent workgroups per CU-occupancy slot at
-// most (the items loop over them, leaving CUs to other streams); 0: one
-// workgroup per item, item b on workgroup b, hence on XCD b % kXcds.  The
-// results are the same bits either way.  An item with prob < 0 is empty
-// (padding of a list laid out for the XCDs).
+// share precision, operand layouts and tile class.  probs / items live in
+// device memory.  One workgroup per item, item b on workgroup b, hence on XCD
+// b % kXcds.  An item with prob < 0 is empty (padding of a list laid out for
+// the XCDs).
 struct GroupItem {
     int prob;
     int tile;   // linear tile index within the problem
 };
 hipError_t launch_gemm_grouped(int prec, int a_kcontig, int b_kcontig, int cls,
                                const GemmDesc *probs_dev,
-                               const GroupItem *items_dev, int num_items,
-                               int grid_size, hipStream_t s);
+                               const GroupItem *items_dev, int num_items, hipStream_t s);
 
 // Packed operands of two 16-bit terms (gemm_x3.hip: 3xBF16, gemm_f16x3.hip:
 // F16X3, whose entries are multiplied by sc before the split): op(X) (rows x k; kc: k contiguous,
@@ -143,9 +143,31 @@ hipError_t launch_reduce_fixed(const double *parts, int64_t count, double *out,
 // power of two leaves Y bitwise unchanged).
 hipError_t launch_scale(const float *X, int64_t ldx, float *Y, int64_t ldy,
                         int64_t m, int64_t n, double nrm, hipStream_t s);
-// The same with nrm = sqrt(*nrm2) read on the device (no host round trip).
+// The same with nrm = sqrt(*nrm2) read on the device (no host round trip); Y
+// stays as it is if stop is given and *stop is not 0.
 hipError_t launch_scale_by_norm(const float *X, int64_t ldx, float *Y, int64_t ldy,
-                                int64_t m, int64_t n, const double *nrm2, hipStream_t s);
+                                int64_t m, int64_t n, const double *nrm2, hipStream_t s,
+                                const int *stop = nullptr);
+// State of an iteration whose steps are queued ahead of their stop test, in
+// device memory.  launch_norm_state: norm2 = the sum of the partials; stop = 1
+// (reason 3) unless sqrt(norm2) is positive and finite.  launch_step_state,
+// after a step: nothing once stopped, else steps += 1, delta = scale *
+// sqrt(sum of the partials) and the driver's stop test in FP64: not finite
+// (reason 3); delta <= the tolerance, tol, or tol 2^steps if tol_doubles
+// (reason 0); delta < stag_below and delta > half the one before (reason 1;
+// stag_below <= 0: off); steps = max_steps (reason 2).
+struct StepState {
+    double norm2, delta, prev, pad0;
+    int stop, steps, reason, pad1;
+};
+struct StepTest {
+    double scale, tol, stag_below;
+    int tol_doubles, max_steps;
+};
+hipError_t launch_norm_state(const double *parts, int64_t count, StepState *st, hipStream_t s);
+hipError_t launch_clear_state(StepState *st, hipStream_t s);
+hipError_t launch_step_state(const double *parts, int64_t count, StepState *st,
+                             const StepTest &test, hipStream_t s);
 // X = A^T / a (FP64 division, rounded once); A is n x m, X is m x n.
 hipError_t launch_transpose_scale(const float *A, int64_t lda, float *X, int64_t ldx,
                                   int64_t n, int64_t m, double a, hipStream_t s);

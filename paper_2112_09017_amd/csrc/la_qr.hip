@@ -1211,11 +1211,11 @@ size_t split_items_bound(int b, int64_t cols)
 }
 
 hipError_t run_split(int prec, const SplitBatch &sb, int which, const GemmDesc *probs_dev,
-                     const GroupItem *items_dev, int num_cus, hipStream_t s)
+                     const GroupItem *items_dev, hipStream_t s)
 {
     const SplitGemm &g = sb.gemms[which];
     hipError_t e = launch_gemm_grouped(prec, 0, 0, g.cls, probs_dev + g.first_prob,
-                                       items_dev + g.first_item, g.num_items, num_cus, s);
+                                       items_dev + g.first_item, g.num_items, s);
     if (e != hipSuccess || g.splits == 1)
         return e;
     hipLaunchKernelGGL(sum_slices_kernel, dim3(grid1d(g.rows * g.cols)), dim3(256), 0, s,
@@ -1553,14 +1553,14 @@ la_status la_caqr(la_context *ctx, int64_t m, int64_t n, float *A, int64_t lda, 
                 trail_pending = false;
             }
             // next panel's columns <- Q_f^T (...) = (...) - Y (W^T (...))
-            LA_HIP(run_split(pr, sb, zn[jp], probs_dev, items_dev, ctx->num_cus, s),
+            LA_HIP(run_split(pr, sb, zn[jp], probs_dev, items_dev, s),
                    "la_caqr: W^T A_next");
             LA_HIP(gemm_sub(pr, Y, ldwy, Z0, ml, nc2, nc, A + c * lda + nx, lda, s),
                    "la_caqr: next-panel update");
         }
         if (rest < n) {
             LA_HIP(hipStreamWaitEvent(la.s1, la.wy_ready, 0), "la_caqr: wait");
-            LA_HIP(run_split(pr, sb, zt[jp], probs_dev, items_dev, ctx->num_cus, la.s1),
+            LA_HIP(run_split(pr, sb, zt[jp], probs_dev, items_dev, la.s1),
                    "la_caqr: W^T A_rest");
             LA_HIP(gemm_sub(pr, Y, ldwy, Z1, ml, n - rest, nc, A + c * lda + rest, lda, la.s1),
                    "la_caqr: trailing update");
@@ -1579,7 +1579,7 @@ la_status la_caqr(la_context *ctx, int64_t m, int64_t n, float *A, int64_t lda, 
             const int nc = (int)std::min<int64_t>(b, n - c);
             float *Qc = Q + c * ldq + c;
             // Q[c:, c:] <- Q_f Q[c:, c:] = Q[c:, c:] - W (Y^T Q[c:, c:])
-            LA_HIP(run_split(pr, sb, zq[jp], probs_dev, items_dev, ctx->num_cus, s),
+            LA_HIP(run_split(pr, sb, zq[jp], probs_dev, items_dev, s),
                    "la_caqr: Y^T Q");
             LA_HIP(gemm_sub(pr, wpan(jp), n, Z1, ml, n - c, nc, Qc, ldq, s), "la_caqr: Q");
         }
