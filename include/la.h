@@ -184,7 +184,7 @@ typedef struct {
 /* Bytes of device workspace la_polar needs for an m x n input (0 on bad
  * arguments).  opts may be NULL.  It holds the second iterate (m n floats),
  * P (n^2), split-K Gram parts for tall inputs (up to 16 n^2), FP64 partials,
- * and, when a step runs at 3xBF16 on 256 x 256 tiles, packed copies of the
+ * and, when a step runs at 3xBF16 on staged tiles, packed copies of the
  * iterate and of P for the update (about m n + n^2 floats). */
 size_t la_polar_workspace_size(int64_t m, int64_t n, const la_polar_opts *opts);
 

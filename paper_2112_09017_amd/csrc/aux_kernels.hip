@@ -106,6 +106,48 @@ void gemm_set_class(GemmDesc &d, int prec, int cls)
         d.num_tiles = 0;
 }
 
+// Tile side of a product on packed operands, from the rounds of workgroups its
+// tiles take.  Measured, ns per unit of K (n^3 products): 256 x 256 tiles (one
+// workgroup per CU) 70-80 per round of 256; 192 x 192 48-51 per round of 256; 128
+// x 128 (two per CU) 28 up to 256 tiles, 38 / 40 / 44 at 324 / 400 / 484, 63 / 77
+// / 85 at 576 / 784 / 1024, 120 / 187 / 260 / 339 at 1369 / 2209 / 3025 / 4096.
+// (3000^3: 256 tiles 206 us, 192 153, 128 188; 7000^3: 2071, 1995, 1820; 8192^3:
+// 2539, 3216, 2774.)  The larger tile unless a smaller one is 3% better: it
+// reads its operands less often.  A product of the small class keeps its 128 x
+// 128 tiles, so that its step norm is summed the same way without a pack.
+static int packed_tile(const GemmDesc &d, int cls)
+{
+    if (cls == kClassSmall)
+        return 128;
+    auto count = [&](int64_t t) {
+        const int64_t tm = (d.M + t - 1) / t, tn = (d.N + t - 1) / t;
+        return (d.gram ? tn * (tn + 1) / 2 : tm * tn) * std::max(d.slices, 1);
+    };
+    auto rounds = [](int64_t t) { return (double)((t + 255) / 256); };
+    const int64_t t128 = count(128), rem = t128 % 512;
+    const double c256 = 73.0 * rounds(count(256)), c192 = 49.0 * rounds(count(192));
+    const double c128 = 43.5 * (double)(t128 / 512) +
+                        (rem == 0 ? 0.0 : 28.5 + 15.0 * (double)std::max<int64_t>(0, rem - 256) / 256.0);
+    int side = 256;
+    double best = c256;
+    if (c192 < 0.97 * best) {
+        side = 192;
+        best = c192;
+    }
+    return c128 < 0.97 * best ? 128 : side;
+}
+
+void gemm_set_packed(GemmDesc &d)
+{
+    if (is_direct(d.small))
+        return;
+    d.ptile = packed_tile(d, d.small);
+    d.small = kClassLarge;
+    d.tiles_m = (int)((d.M + d.ptile - 1) / d.ptile);
+    d.tiles_n = (int)((d.N + d.ptile - 1) / d.ptile);
+    d.num_tiles = d.gram ? d.tiles_n * (d.tiles_n + 1) / 2 : d.tiles_m * d.tiles_n;
+}
+
 size_t gemm_max_tiles(int prec, int64_t M, int64_t N, int64_t K)
 {
     // of the class taken with dense operands, and of the small class, which

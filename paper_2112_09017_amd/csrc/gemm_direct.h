@@ -414,8 +414,8 @@ __global__ void __launch_bounds__(DirectCfg<CLS>::KW * 64, DirectCfg<CLS>::WPE)
     const int64_t row0 = (int64_t)tm * (32 * FM), col0 = (int64_t)tn * (32 * FN);
     DirectPacked<FM> oa;
     DirectPacked<FN> ob;
-    oa.init(d.A, (d.M + kPackRows - 1) / kPackRows * (kPackRows / 32), row0, lane);
-    ob.init(d.B, (d.N + kPackRows - 1) / kPackRows * (kPackRows / 32), col0, lane);
+    oa.init(d.A, packed_row_blocks(d.M), row0, lane);
+    ob.init(d.B, packed_row_blocks(d.N), col0, lane);
     f32x16 acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)

@@ -102,7 +102,19 @@ template <> struct Cfg<PREC_BF16X3 | kPacked> {
     static constexpr int BM = 256, BN = 256, BK = 16, WM = 2, WN = 2, OCC = 1, PIPE = 0;
     static constexpr int terms = 2, entry_bytes = 16;
 };
+// Smaller tiles of the same loop, for tile counts that would leave the last
+// round of 256 x 256 tiles half empty: 192 x 192 (96 x 96 per wave), and 128 x
+// 128 with two workgroups per CU.  Every element is the same sum in all three.
+constexpr int kTile192 = 64, kTile128 = 128;
+template <> struct Cfg<PREC_BF16X3 | kPacked | kTile192> : Cfg<PREC_BF16X3 | kPacked> {
+    static constexpr int BM = 192, BN = 192;
+};
+template <> struct Cfg<PREC_BF16X3 | kPacked | kTile128> : Cfg<PREC_BF16X3 | kPacked> {
+    static constexpr int BM = 128, BN = 128, OCC = 2;
+};
 template <> struct Cfg<PREC_F16X3 | kPacked> : Cfg<PREC_BF16X3 | kPacked> {};
+template <> struct Cfg<PREC_F16X3 | kPacked | kTile192> : Cfg<PREC_BF16X3 | kPacked | kTile192> {};
+template <> struct Cfg<PREC_F16X3 | kPacked | kTile128> : Cfg<PREC_BF16X3 | kPacked | kTile128> {};
 
 // Workgroups per CU a kernel is compiled for: the tile class's OCC, except
 // that the small 6xBF16 tile with both operands k-major (its loader keeps a
@@ -1201,6 +1213,11 @@ constexpr int kPackSlabK = 128;   // k covered by one workgroup of the pack kern
 // 16384 x 32768 x 16384: 151 GiB fetched per launch unpadded, 72 GiB with
 // 17 KiB, which fetched the least among the paddings tried).
 constexpr int kPackPadKiB = 17;
+// row blocks of a packed operand of R rows
+__host__ __device__ inline int64_t packed_row_blocks(int64_t R)
+{
+    return (R + kPackRows - 1) / kPackRows * (kPackRows / 32);
+}
 __host__ __device__ inline int64_t packed_kstride(int64_t rbt)
 {
     return (2 * rbt + kPackPadKiB) << 10;
@@ -1302,9 +1319,9 @@ __device__ __forceinline__ uint32_t lds_offset(const void *p)
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
 
-// Direct global -> LDS loads of one packed stage (k block kb): 16 chunks of
-// A (2 terms x 8 row blocks) and 16 of B.  Wave w moves operand (w >= 2 ? B
-// : A), term (w & 1), row blocks 0..7: eight 1 KiB chunks, each one
+// Direct global -> LDS loads of one packed stage (k block kb): 2 terms x BM / 32
+// row blocks of A and as many chunks of B.  Wave w moves operand (w >= 2 ? B
+// : A), term (w & 1), all row blocks: BM / 32 1 KiB chunks, each one
 // global_load_lds_dwordx4.  stage_lds: LDS byte offset of the stage buffer.
 // rbta / rbtb: row blocks of the packed A / B (the RB of the layout).
 template <int P>
@@ -1313,6 +1330,7 @@ __device__ __forceinline__ void packed_issue(const char *pa, const char *pb, int
                                              uint32_t stage_lds, int w, int lane)
 {
     using G = Geo<P>;
+    constexpr int NCH = Cfg<P>::BM / 32;
     const bool isb = w >= 2;
     const char *base = isb ? pb : pa;
     const int64_t rb0 = isb ? rbb : rba, rbt = isb ? rbtb : rbta;
@@ -1323,8 +1341,8 @@ __device__ __forceinline__ void packed_issue(const char *pa, const char *pb, int
         ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(wb >> 32)) << 32) |
         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)wb));
 #pragma unroll
-    for (int frow = 0; frow < 8; ++frow)   // consecutive row blocks are 2 KiB apart
-        dma16(wbase + (frow << 11), lane * 16, dst0 + ((tt * 8 + frow) << 10));
+    for (int frow = 0; frow < NCH; ++frow)   // consecutive row blocks are 2 KiB apart
+        dma16(wbase + (frow << 11), lane * 16, dst0 + ((tt * NCH + frow) << 10));
 }
 
 // Fragments of one packed stage for this wave, in two halves: the operands
@@ -1362,15 +1380,16 @@ __device__ __forceinline__ void packed_read_rest(const char *st, bf16x8 (&ahi)[G
 }
 
 // Wait until this wave's chunks of the next stage have landed, given how
-// many later stages (0..3, eight chunks each) may stay in flight.
+// many later stages (0..3, NCH chunks each) may stay in flight.
+template <int NCH>
 __device__ __forceinline__ void packed_wait(int later)
 {
     if (later >= 3)
-        wait_vmcnt<24>();
+        wait_vmcnt<3 * NCH>();
     else if (later == 2)
-        wait_vmcnt<16>();
+        wait_vmcnt<2 * NCH>();
     else if (later == 1)
-        wait_vmcnt<8>();
+        wait_vmcnt<NCH>();
     else
         wait_vmcnt<0>();
 }
@@ -1410,7 +1429,7 @@ __device__ __forceinline__ void packed_stage(int ss, int nst, f32x16 (&acc)[Geo<
     const bool more = ss + 1 < nst;
     const char *nst_ = smem + ((ss + 1) & (NS - 1)) * G::stage_bytes;
     if (more) {
-        packed_wait(min(nst - 2 - ss, NS - 2));
+        packed_wait<C::BM / 32>(min(nst - 2 - ss, NS - 2));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
@@ -1440,15 +1459,20 @@ __device__ __forceinline__ void packed_stage(int ss, int nst, f32x16 (&acc)[Geo<
 // min(K, (y + 1) slice_k)) (slice_k a multiple of 16) and writes C + y
 // slice_stride, as the split-K launch of the unpacked kernels does.
 template <int P>
-__global__ void __launch_bounds__(256, 1) gemm_packed_kernel(GemmDesc d)
+__global__ void __launch_bounds__(256, Cfg<P>::OCC) gemm_packed_kernel(GemmDesc d)
 {
+    using C = Cfg<P>;
     using G = Geo<P>;
+    static_assert(C::BM == C::BN, "square tiles: each wave moves BM / 32 chunks per stage");
     static_assert(G::KF == 1 && G::NT == 256, "one 16-k block per stage, four waves");
     constexpr int FM = G::FM, FN = G::FN, NS = kPackStages;
     __shared__ __attribute__((aligned(1024))) char smem[NS * G::stage_bytes];
     __shared__ double red[4];
     int tm, tn;
-    round_tile_coords(d, tm, tn);
+    if (C::OCC == 1)
+        round_tile_coords(d, tm, tn);
+    else
+        tile_coords(d, xcd_remap(blockIdx.x, d.num_tiles), tm, tn);
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int wm = w / 2, wn = w % 2;
     f32x16 acc[FM][FN];
@@ -1459,8 +1483,10 @@ __global__ void __launch_bounds__(256, 1) gemm_packed_kernel(GemmDesc d)
             acc[i][j] = f32x16{};
     const char *pa = reinterpret_cast<const char *>(d.A);
     const char *pb = reinterpret_cast<const char *>(d.B);
-    const int64_t rba = (int64_t)tm * 8, rbb = (int64_t)tn * 8;
-    const int64_t rbta = (int64_t)d.tiles_m * 8, rbtb = (int64_t)d.tiles_n * 8;
+    // a last 192-row tile reaches at most four row blocks past the padded rows:
+    // the padding between k blocks, whose products land in rows not stored
+    const int64_t rba = (int64_t)tm * (C::BM / 32), rbb = (int64_t)tn * (C::BN / 32);
+    const int64_t rbta = packed_row_blocks(d.M), rbtb = packed_row_blocks(d.N);
     if (d.slices > 1) {
         const int64_t k0 = (int64_t)blockIdx.y * d.slice_k;
         const int64_t kl = d.K - k0 < d.slice_k ? d.K - k0 : d.slice_k;
@@ -1480,7 +1506,7 @@ __global__ void __launch_bounds__(256, 1) gemm_packed_kernel(GemmDesc d)
             if (s < nst)
                 packed_issue<P>(pa, pb, rbta, rbtb, rba, rbb, s, smem_lds + s * G::stage_bytes, w,
                                 lane);
-        packed_wait(min(nst - 1, NS - 1));
+        packed_wait<C::BM / 32>(min(nst - 1, NS - 1));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         packed_read_first<P>(smem, alo, bhi, wm, wn, lane);
@@ -1621,7 +1647,7 @@ hipError_t launch_grouped_t(int akc, int bkc, int small, const GemmDesc *probs,
 // Packed operand bytes for R rows and inner dimension K.
 inline size_t packed_bytes(int64_t R, int64_t K)
 {
-    const int64_t rbt = (R + kPackRows - 1) / kPackRows * (kPackRows / 32);
+    const int64_t rbt = packed_row_blocks(R);
     const int64_t kbt = (K + 15) / 16;
     return rbt == 0 ? 0 : (size_t)kbt * (size_t)packed_kstride(rbt);
 }
@@ -1630,7 +1656,7 @@ template <int PREC>
 hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t R, int64_t K, float sc,
                           char *out, hipStream_t s)
 {
-    const int64_t rbt = (R + kPackRows - 1) / kPackRows * (kPackRows / 32);
+    const int64_t rbt = packed_row_blocks(R);
     const int64_t kbt = (K + 15) / 16;
     if (rbt == 0 || kbt == 0)
         return hipSuccess;
@@ -1655,8 +1681,19 @@ hipError_t launch_packed_x3(const GemmDesc &d, hipStream_t s)
     const int sl = d.slices > 1 ? d.slices : 1;
     if (sl > 1 && (d.slice_k <= 0 || d.slice_k % 16 != 0 || sl > 65535))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL((gemm_packed_kernel<PREC | kPacked>), dim3(d.num_tiles, sl),
-                       dim3(256), 0, s, d);
+    const dim3 grid(d.num_tiles, sl), block(256);
+    switch (d.ptile) {
+    case 256:
+        hipLaunchKernelGGL((gemm_packed_kernel<PREC | kPacked>), grid, block, 0, s, d);
+        break;
+    case 192:
+        hipLaunchKernelGGL((gemm_packed_kernel<PREC | kPacked | kTile192>), grid, block, 0, s, d);
+        break;
+    case 128:
+        hipLaunchKernelGGL((gemm_packed_kernel<PREC | kPacked | kTile128>), grid, block, 0, s, d);
+        break;
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -166,17 +166,27 @@ struct PolarWs {
     size_t parts_floats;
 };
 
-// Whether an M x N x K product takes the packed-operand kernel inside an
-// iteration: 3xBF16 or F16X3 on 256 x 256 tiles (at least 128 of them) with
-// K >= 256, as in la_gemm_ws.  The packed kernel computes every product exactly
-// as the unpacked one, so the choice never changes a result.
+static bool two_term(int prec) { return prec == PREC_BF16X3 || prec == PREC_F16X3; }
+
+// Whether an M x N x K product on large tiles (at least 128 of 256 x 256) takes
+// the packed-operand kernel: two 16-bit terms and K >= 256, as in la_gemm_ws.
+// The packed kernel computes every product exactly as the unpacked one, so the
+// choice never changes a result.
 static bool packs(int prec, int64_t M, int64_t N, int64_t K)
 {
-    return (prec == PREC_BF16X3 || prec == PREC_F16X3) && K >= 256 &&
-           ((M + 255) / 256) * ((N + 255) / 256) >= 128;
+    return two_term(prec) && K >= 256 && ((M + 255) / 256) * ((N + 255) / 256) >= 128;
 }
 
-// Bytes of the packed op(A) and op(B)^T of such a product (0 if it does not pack).
+// Whether a product of the small class takes it too where there is room for its
+// packs: the 128 x 128 packed tiles run at 28 to 44 ns per unit of K against 43
+// to 57 unpacked, the packs cost about 8 us each (2048^3: 59 + 16 us against
+// 86).
+static bool packs_small(int prec, const GemmDesc &d)
+{
+    return two_term(prec) && d.small == kClassSmall && std::min(d.M, d.N) >= 256 && d.K >= 1024;
+}
+
+// Bytes of the packed op(A) and op(B)^T of a product that packs (0 otherwise).
 static size_t pack_bytes(int prec, int64_t M, int64_t N, int64_t K)
 {
     if (!packs(prec, M, N, K))
@@ -184,14 +194,33 @@ static size_t pack_bytes(int prec, int64_t M, int64_t N, int64_t K)
     return align_up256(packed_x3_bytes(M, K)) + align_up256(packed_x3_bytes(N, K));
 }
 
+// The same for a product of the small class (dense operands).
+static size_t pack_small_bytes(int prec, int64_t M, int64_t N, int64_t K)
+{
+    GemmDesc d;
+    memset(&d, 0, sizeof d);
+    d.M = M;
+    d.N = N;
+    d.K = K;
+    d.a_kcontig = 1;
+    d.lda = K;
+    d.ldb = N;
+    gemm_finalize(d, prec);
+    if (!packs_small(prec, d))
+        return 0;
+    return align_up256(packed_x3_bytes(M, K)) + align_up256(packed_x3_bytes(N, K));
+}
+
 // Launch d, through the packed-operand kernel when it qualifies and pk (of at
 // least pack_bytes) is given: op(A) and op(B)^T are packed into pk first,
 // unless an operand packed earlier is passed (pre_a / pre_b).  K-slices of d
-// (d.slices > 1) run on whichever kernel is chosen.
-static hipError_t gemm_packed_or_plain(int prec, GemmDesc d, char *pk, hipStream_t s,
+// (d.slices > 1) run on whichever kernel is chosen; d's tile counts are those of
+// the launch.
+static hipError_t gemm_packed_or_plain(int prec, GemmDesc &d, char *pk, hipStream_t s,
                                        const char *pre_a = nullptr, const char *pre_b = nullptr)
 {
-    if (pk && !d.gram && !d.small && packs(prec, d.M, d.N, d.K)) {
+    if (pk && !d.gram &&
+        ((!d.small && packs(prec, d.M, d.N, d.K)) || packs_small(prec, d))) {
         char *pa = pk, *pb = pk + align_up256(packed_x3_bytes(d.M, d.K));
         hipError_t e = hipSuccess;
         if (!pre_a)
@@ -202,18 +231,19 @@ static hipError_t gemm_packed_or_plain(int prec, GemmDesc d, char *pk, hipStream
             return e;
         d.A = (const float *)(pre_a ? pre_a : pa);
         d.B = (const float *)(pre_b ? pre_b : pb);
+        gemm_set_packed(d);
         return launch_gemm_packed(prec, d, s);
     }
     return launch_gemm(prec, d, s);
 }
 
 // Whether a Gram X^T X (n x n, K = m) at prec runs on the packed-operand
-// kernel: 3xBF16 or F16X3 with at least 128 upper 256 x 256 tiles and K >= 256.  X^T is
-// packed once and serves as both operands.
+// kernel: two 16-bit terms with at least 128 upper 256 x 256 tiles and K >= 256.
+// X^T is packed once and serves as both operands.
 static bool gram_packs(int prec, int64_t m, int64_t n)
 {
     const int64_t nb = (n + 255) / 256;
-    return (prec == PREC_BF16X3 || prec == PREC_F16X3) && m >= 256 && nb * (nb + 1) / 2 >= 128;
+    return two_term(prec) && m >= 256 && nb * (nb + 1) / 2 >= 128;
 }
 
 // Packed copies the iteration keeps: X and P for a packed update, or X^T for
@@ -229,6 +259,22 @@ static size_t packed_update_bytes(const PolarPlan &p)
         b = std::max(b, pack_bytes(pr, p.m, p.n, p.n));
         if (gram_packs(pr, p.m, p.n))
             b = std::max(b, align_up256(packed_x3_bytes(p.n, p.m)));
+    }
+    return b;
+}
+
+// The same region for iterates of the small class.  It is part of what
+// la_polar_workspace_size asks for, but a workspace without it is taken, and
+// gives the same result on unpacked operands.
+static size_t packed_small_bytes(const PolarPlan &p)
+{
+    if (packed_update_bytes(p))
+        return 0;
+    size_t b = 0;
+    for (int pr : {p.prec_pre, p.prec_ns}) {
+        const size_t u = pack_small_bytes(pr, p.m, p.n, p.n);
+        if (u)
+            b = std::max(b, std::max(u, align_up256(packed_x3_bytes(p.n, p.m))));
     }
     return b;
 }
@@ -285,7 +331,7 @@ size_t polar_workspace_bytes(const PolarPlan &p)
     return b;
 }
 
-static PolarWs carve(const PolarPlan &p, void *ws)
+static PolarWs carve(const PolarPlan &p, void *ws, bool room)
 {
     PolarWs w;
     char *b = (char *)ws;
@@ -302,8 +348,26 @@ static PolarWs carve(const PolarPlan &p, void *ws)
     b += align256((size_t)sumsq_num_partials() * sizeof(double));
     w.scal = (double *)b;
     b += align256(8 * sizeof(double));
-    w.pk = packed_update_bytes(p) ? b : nullptr;
+    w.pk = packed_update_bytes(p) || (room && packed_small_bytes(p)) ? b : nullptr;
     return w;
+}
+
+// Launch the Gram-mode product d (k-major operands).  Where both operands are
+// one matrix and it qualifies, X^T is packed once into pk (if given) and read as
+// both; the packed kernel computes every product exactly as the unpacked one.
+static hipError_t gram_packed_or_plain(int prec, GemmDesc &d, char *pk, hipStream_t s)
+{
+    if (pk && d.A == d.B && d.lda == d.ldb &&
+        ((!d.small && gram_packs(prec, d.K, d.N)) || packs_small(prec, d))) {
+        hipError_t e = launch_pack(prec, d.A, d.lda, 0, d.N, d.K, d.scale_a, pk, s);
+        if (e != hipSuccess)
+            return e;
+        d.A = (const float *)pk;
+        d.B = (const float *)pk;
+        gemm_set_packed(d);
+        return launch_gemm_packed(prec, d, s);
+    }
+    return launch_gemm(prec, d, s);
 }
 
 // X1^T X2 for K x n operands X1, X2 (row-major, leading dimensions ld1, ld2)
@@ -337,17 +401,7 @@ static hipError_t gram_slices(int prec, const float *X1, int64_t ld1, float sc1,
     d.slices = slice_plan(K, want, &d.slice_k);
     d.slice_stride = n * n;
     *count = d.slices;
-    if (pk && X1 == X2 && ld1 == ld2 && gram_packs(prec, K, n) && !d.small) {
-        // X^T (n rows, K) packed once and read as both operands; the packed
-        // kernel computes every product exactly as the unpacked one
-        hipError_t e = launch_pack(prec, X1, ld1, 0, n, K, d.scale_a, pk, s);
-        if (e != hipSuccess)
-            return e;
-        d.A = (const float *)pk;
-        d.B = (const float *)pk;
-        return launch_gemm_packed(prec, d, s);
-    }
-    return launch_gemm(prec, d, s);
+    return gram_packed_or_plain(prec, d, pk, s);
 }
 
 // P <- alpha X^T X + gamma I (exactly symmetric), X m x n with leading dim ldx.
@@ -376,7 +430,7 @@ static hipError_t gram_step(const PolarPlan &p, int prec, const float *X, int64_
         d.gamma = (float)gamma;
         gemm_f16_scales(d, prec, kIterScale, kIterScale);
         gemm_finalize(d, prec);
-        return launch_gemm(prec, d, s);
+        return gram_packed_or_plain(prec, d, w.pk, s);
     }
     // the slices run in one launch; slice y sums k in [y ks, (y + 1) ks) into
     // the upper triangle of its own n x n part, and the parts are added in
@@ -438,9 +492,10 @@ static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int6
     d.stop = stop;
     gemm_f16_scales(d, prec, kIterScale, kIterScale);
     gemm_finalize(d, prec);
+    const hipError_t e = gemm_packed_or_plain(prec, d, w.pk, s);
     if (ntiles)
         *ntiles = d.tiles_m * d.tiles_n;
-    return gemm_packed_or_plain(prec, d, w.pk, s);
+    return e;
 }
 
 // Newton-Schulz (inversion) steps queued before the first look at the stop test, and
@@ -587,6 +642,29 @@ static size_t inverse_pack_bytes(const InvPlan &p)
     return inverse_step_pack_bytes(p) + inverse_a_pack_bytes(p);
 }
 
+// The same regions for products of the small class (used where the workspace
+// has room, as la_polar's).
+static size_t inverse_small_step_bytes(const InvPlan &p)
+{
+    if (inverse_pack_bytes(p))
+        return 0;
+    const int64_t k1 = p.wide ? p.m : p.n, k2 = p.wide ? p.n : p.m;
+    return std::max(pack_small_bytes(p.prec, p.r, p.r, k1), pack_small_bytes(p.prec, p.m, p.n, k2));
+}
+
+static size_t inverse_small_a_bytes(const InvPlan &p)
+{
+    const int64_t k1 = p.wide ? p.m : p.n;
+    return inverse_small_step_bytes(p) && pack_small_bytes(p.prec, p.r, p.r, k1)
+               ? align_up256(packed_x3_bytes(p.r, k1))
+               : 0;
+}
+
+static size_t inverse_small_pack_bytes(const InvPlan &p)
+{
+    return inverse_small_step_bytes(p) + inverse_small_a_bytes(p);
+}
+
 static size_t inverse_workspace_bytes(const InvPlan &p)
 {
     size_t b = 0;
@@ -599,7 +677,7 @@ static size_t inverse_workspace_bytes(const InvPlan &p)
     return b;
 }
 
-static InvWs inverse_carve(const InvPlan &p, void *ws)
+static InvWs inverse_carve(const InvPlan &p, void *ws, bool room)
 {
     InvWs w;
     char *b = (char *)ws;
@@ -616,6 +694,10 @@ static InvWs inverse_carve(const InvPlan &p, void *ws)
     w.pk = inverse_step_pack_bytes(p) ? b : nullptr;
     b += inverse_step_pack_bytes(p);
     w.pka = inverse_a_pack_bytes(p) ? b : nullptr;
+    if (room && inverse_small_step_bytes(p)) {
+        w.pk = b;
+        w.pka = inverse_small_a_bytes(p) ? b + inverse_small_step_bytes(p) : nullptr;
+    }
     return w;
 }
 
@@ -709,8 +791,9 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
     }
     u.stop = stop;
     gemm_finalize(u, prec);
+    e = gemm_packed_or_plain(prec, u, w.pk, s);
     *ntiles = u.tiles_m * u.tiles_n;
-    return gemm_packed_or_plain(prec, u, w.pk, s);
+    return e;
 }
 
 // Tile class of a product of packed operands: the direct class la_gemm would
@@ -722,7 +805,8 @@ static void gemm_packed_class(GemmDesc &d)
     t.ldb = std::max<int64_t>(d.K, 1);
     t.a_kcontig = t.b_kcontig = 1;
     gemm_finalize(t, PREC_BF16X3);
-    gemm_set_class(d, PREC_BF16X3, is_direct(t.small) ? t.small : kClassLarge);
+    gemm_set_class(d, PREC_BF16X3, t.small);
+    gemm_set_packed(d);
 }
 
 // Validation and descriptor of a la_gemm-style call.  *empty: nothing to do
@@ -1007,7 +1091,7 @@ la_status la_gemm_ws(la_context *ctx, int trans_a, int trans_b, int64_t m, int64
     if (st != LA_OK || empty)
         return st;
     hipStream_t s = (hipStream_t)hip_stream;
-    // packed path: 3xBF16 on 256 x 256 tiles with enough K to repay the pack pass
+    // packed path: 3xBF16 on large tiles with enough K to repay the pack pass
     if (p != PREC_BF16X3 || d.small || k < 256) {
         LA_HIP(launch_gemm(p, d, s), "la_gemm_ws: launch");
         return LA_OK;
@@ -1035,6 +1119,7 @@ la_status la_gemm_ws(la_context *ctx, int trans_a, int trans_b, int64_t m, int64
     LA_HIP(launch_pack(PREC_BF16X3, B, ldb, trans_b ? 1 : 0, n, k, 1.0f, wb, s), "la_gemm_ws: pack B");
     d.A = (const float *)wa;
     d.B = (const float *)wb;
+    gemm_set_packed(d);
     LA_HIP(launch_gemm_packed(PREC_BF16X3, d, s), "la_gemm_ws: launch");
     return LA_OK;
 }
@@ -1044,7 +1129,7 @@ size_t la_polar_workspace_size(int64_t m, int64_t n, const la_polar_opts *opts)
     PolarPlan p;
     if (polar_plan(m, n, opts, &p) != LA_OK)
         return 0;
-    return polar_workspace_bytes(p);
+    return polar_workspace_bytes(p) + packed_small_bytes(p);
 }
 
 }  // extern "C"
@@ -1131,7 +1216,11 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
     }
     LA_HIP(hipSetDevice(ctx->device), "la_polar: hipSetDevice");
     hipStream_t s = (hipStream_t)hip_stream;
-    PolarWs w = carve(p, workspace);
+    // the optional region after the required one is used only where it is free
+    const size_t full = need + packed_small_bytes(p);
+    const bool room = ws_bytes >= full && !overlaps(workspace, full, A, ab) &&
+                      !overlaps(workspace, full, U, ub) && !overlaps(workspace, full, H, hb);
+    PolarWs w = carve(p, workspace, room);
 
     la_polar_info inf;
     memset(&inf, 0, sizeof inf);
@@ -1296,7 +1385,7 @@ size_t la_inverse_workspace_size(int64_t n, int64_t m, const la_inverse_opts *op
     InvPlan p;
     if (inverse_plan(n, m, opts, &p) != LA_OK)
         return 0;
-    return inverse_workspace_bytes(p);
+    return inverse_workspace_bytes(p) + inverse_small_pack_bytes(p);
 }
 
 la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int64_t lda,
@@ -1333,7 +1422,10 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
     }
     LA_HIP(hipSetDevice(ctx->device), "la_inverse: hipSetDevice");
     hipStream_t s = (hipStream_t)hip_stream;
-    InvWs w = inverse_carve(p, workspace);
+    const size_t full = need + inverse_small_pack_bytes(p);
+    const bool room = ws_bytes >= full && !overlaps(workspace, full, A, ab) &&
+                      !overlaps(workspace, full, X, xb);
+    InvWs w = inverse_carve(p, workspace, room);
 
     la_inverse_info inf;
     memset(&inf, 0, sizeof inf);

@@ -46,6 +46,7 @@ struct GemmDesc {
     int tiles_m, tiles_n;
     int num_tiles;     // tiles launched (upper triangle only for gram)
     int small;         // tile class (chosen from the problem's own shape)
+    int ptile;         // packed operands: tile side, 256, 192 or 128 (gemm_set_packed)
     int quarters;      // small tiles covering large Gram tiles tail_first.. (4 per tile)
     int tail_first;
     // split-K slices in one launch: slice y takes k in [y slice_k, min(K,
@@ -77,6 +78,9 @@ void gemm_finalize(GemmDesc &d, int prec);
 bool direct_fits(const GemmDesc &d);
 // Sets d's tile class and the tile counts that follow from it.
 void gemm_set_class(GemmDesc &d, int prec, int cls);
+// Sets d up for packed operands (launch_gemm_packed): a direct class as it is,
+// else the tile side and the counts that follow from it.
+void gemm_set_packed(GemmDesc &d);
 // Most output tiles an M x N x K product (not a Gram) can take: the partials
 // its step norm needs.
 size_t gemm_max_tiles(int prec, int64_t M, int64_t N, int64_t K);
@@ -119,7 +123,7 @@ size_t packed_x3_bytes(int64_t rows, int64_t k);
 hipError_t launch_pack(int prec, const float *X, int64_t ld, int kc, int64_t rows, int64_t k,
                        float sc, void *out, hipStream_t s);
 // GEMM on packed operands: d.A and d.B point at packed op(A) (M x K) and
-// packed op(B)^T (N x K), on 256 x 256 tiles or a direct class (d.small).
+// packed op(B)^T (N x K), set up by gemm_set_packed.
 // Computes the same products in the same order as launch_gemm's kernel of that precision.
 hipError_t launch_gemm_packed(int prec, const GemmDesc &d, hipStream_t s);
 
