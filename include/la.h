@@ -279,9 +279,11 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
  * MatFuncEig-EigenvaluePolynomial).  coef is a HOST array of ncoef >= 1
  * finite doubles (rounded to FP32 where they enter a product's epilogue).
  * workspace: device memory of at least la_matfunc_workspace_size() bytes,
- * 256-byte aligned (three n x n FP32 buffers).  prec: AUTO = BF16X6 (the
- * recurrences accumulate the products' errors, so every product is kept at
- * FP32-level accuracy).  Both run on hip_stream and return after the last
+ * 256-byte aligned (three n x n FP32 buffers and, at the sizes that use them,
+ * packed operands; a workspace of the three buffers alone is taken too).
+ * prec: AUTO = BF16X6 (the recurrences accumulate the products' errors, so every
+ * product is kept at FP32-level accuracy), or, on the larger sizes and with the
+ * full workspace, its equivalent of two scaled fp16 terms per operand.  Both run on hip_stream and return after the last
  * kernel has completed.  F must not overlap A or the workspace.
  * ---------------------------------------------------------------------- */
 size_t la_matfunc_workspace_size(int64_t m, int64_t n);

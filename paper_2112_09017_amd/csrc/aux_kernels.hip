@@ -18,8 +18,8 @@ hipError_t launch_gemm_f16(const GemmDesc &d, hipStream_t s);
 hipError_t launch_grouped_f16(int, int, int, const GemmDesc *, const GroupItem *, int,
                               hipStream_t);
 hipError_t launch_pack_x3(const float *, int64_t, int, int64_t, int64_t, void *, hipStream_t);
-hipError_t launch_pack_f16(const float *, int64_t, int, int64_t, int64_t, float, void *,
-                           hipStream_t);
+hipError_t launch_pack_f16(const float *, int64_t, int, int64_t, int64_t, float, const uint32_t *,
+                           void *, hipStream_t);
 hipError_t launch_gemm_packed_x3(const GemmDesc &d, hipStream_t s);
 hipError_t launch_gemm_packed_f16(const GemmDesc &d, hipStream_t s);
 hipError_t launch_grouped_fp32(int, int, int, const GemmDesc *, const GroupItem *, int,
@@ -55,9 +55,9 @@ bool direct_fits(const GemmDesc &d)
 // 10, small 17; 640 11, 14, 31; 768 19, 17, 36; 1000 26, 20, 65; 1536 84, 63, 69;
 // 2048 166, 97, 90; 3000: small 274, large 277.
 // So: 32 x 32 tiles while one round of workgroups holds them, 64 x 64 tiles up
-// to 2.5 rounds of one per CU and, for the precisions whose small tiles do not
-// gain from a second workgroup per CU, from 4 to 6 rounds; large tiles once
-// they give half the CUs one; small tiles between.  A matrix with a side below
+// to 2.5 rounds of one per CU and, for FP32, whose small tiles do not gain from
+// a second workgroup per CU, from 4 to 6 rounds; large tiles once they give
+// half the CUs one; small tiles between.  A matrix with a side below
 // 128 is all edge to the staged classes and always direct, and large tiles
 // need both sides to hold one.
 static int gemm_class(const GemmDesc &d, int prec)
@@ -75,7 +75,7 @@ static int gemm_class(const GemmDesc &d, int prec)
     if (tiles(32) <= kCus || side < 2)
         return kClassDirect32;
     const int64_t t64 = tiles(64);
-    const bool one_deep = prec == PREC_BF16X6 || prec == PREC_FP32;
+    const bool one_deep = prec == PREC_FP32;
     if (side < 128 || 2 * t64 <= 5 * kCus || (one_deep && t64 > 4 * kCus && t64 <= 6 * kCus))
         return kClassDirect64;
     return kClassSmall;
@@ -193,11 +193,11 @@ hipError_t launch_gemm_grouped(int prec, int akc, int bkc, int cls, const GemmDe
 }
 
 hipError_t launch_pack(int prec, const float *X, int64_t ld, int kc, int64_t rows, int64_t k,
-                       float sc, void *out, hipStream_t s)
+                       float sc, void *out, hipStream_t s, const uint32_t *rmax)
 {
     switch (prec) {
     case PREC_BF16X3: return launch_pack_x3(X, ld, kc, rows, k, out, s);
-    case PREC_F16X3: return launch_pack_f16(X, ld, kc, rows, k, sc, out, s);
+    case PREC_F16X3: return launch_pack_f16(X, ld, kc, rows, k, sc, rmax, out, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -389,6 +389,51 @@ __global__ void transpose_scale_kernel(const float *__restrict__ A, int64_t lda,
                 X[row * ldx + col] = (float)((double)t[threadIdx.x][r] / a);
         }
         __syncthreads();
+    }
+}
+
+__global__ void zero_kernel(uint32_t *out, int64_t count)
+{
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count;
+         i += (int64_t)gridDim.x * blockDim.x)
+        out[i] = 0;
+}
+
+// One wave per row: the maximum of the magnitudes' bits over its columns.
+__global__ void __launch_bounds__(kThreads) row_absmax_kernel(const float *__restrict__ X,
+                                                              int64_t ldx, int64_t m, int64_t n,
+                                                              uint32_t *__restrict__ out)
+{
+    const int lane = threadIdx.x & 63;
+    for (int64_t r = blockIdx.x * (int64_t)(kThreads / 64) + (threadIdx.x >> 6); r < m;
+         r += (int64_t)gridDim.x * (kThreads / 64)) {
+        uint32_t v = 0;
+        for (int64_t c = lane; c < n; c += 64)
+            v = max(v, __float_as_uint(X[r * ldx + c]) & 0x7fffffffu);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1)
+            v = max(v, (uint32_t)__shfl_xor((int)v, off, 64));
+        if (lane == 0)
+            out[r] = v;
+    }
+}
+
+// One thread per column of a strip of rows; the strips meet by atomic maximum.
+constexpr int kMaxStrip = 64;
+__global__ void __launch_bounds__(kThreads) col_absmax_kernel(const float *__restrict__ X,
+                                                              int64_t ldx, int64_t m, int64_t n,
+                                                              uint32_t *__restrict__ out)
+{
+    const int64_t c = blockIdx.x * (int64_t)kThreads + threadIdx.x;
+    if (c >= n)
+        return;
+    for (int64_t r0 = blockIdx.y * (int64_t)kMaxStrip; r0 < m;
+         r0 += (int64_t)gridDim.y * kMaxStrip) {
+        const int64_t r1 = r0 + kMaxStrip < m ? r0 + kMaxStrip : m;
+        uint32_t v = 0;
+        for (int64_t r = r0; r < r1; ++r)
+            v = max(v, __float_as_uint(X[r * ldx + c]) & 0x7fffffffu);
+        atomicMax(out + c, v);
     }
 }
 
@@ -673,6 +718,38 @@ hipError_t launch_transpose_scale(const float *A, int64_t lda, float *X, int64_t
     const unsigned gy = (unsigned)std::min<int64_t>(tm, 65535);
     hipLaunchKernelGGL(transpose_scale_kernel, dim3((unsigned)tn, gy), dim3(32, 8), 0, s, A, lda,
                        X, ldx, n, m, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_zero(uint32_t *out, int64_t count, hipStream_t s)
+{
+    if (count <= 0)
+        return hipSuccess;
+    const int64_t g = std::min<int64_t>((count + kThreads - 1) / kThreads, 1024);
+    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)g), dim3(kThreads), 0, s, out, count);
+    return hipGetLastError();
+}
+
+hipError_t launch_absmax(const float *X, int64_t ldx, int64_t m, int64_t n, int by_row,
+                         uint32_t *out, hipStream_t s)
+{
+    if (m == 0 || n == 0)
+        return launch_zero(out, by_row ? m : n, s);
+    if (by_row) {
+        const int64_t g = std::min<int64_t>((m + 3) / 4, 65535);
+        hipLaunchKernelGGL(row_absmax_kernel, dim3((unsigned)g), dim3(kThreads), 0, s, X, ldx, m,
+                           n, out);
+        return hipGetLastError();
+    }
+    const hipError_t e = launch_zero(out, n, s);
+    if (e != hipSuccess)
+        return e;
+    const int64_t gx = (n + kThreads - 1) / kThreads;
+    if (gx > 0x7fffffff)
+        return hipErrorInvalidValue;
+    const int64_t gy = std::min<int64_t>((m + kMaxStrip - 1) / kMaxStrip, 65535);
+    hipLaunchKernelGGL(col_absmax_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(kThreads), 0, s,
+                       X, ldx, m, n, out);
     return hipGetLastError();
 }
 

@@ -210,6 +210,14 @@ template <> struct Split<PREC_BF16X6> {
     }
 };
 
+// Scaling of an operand row (or output row or column) by its own largest
+// magnitude, kept as the bits of |x|: the exponent s that takes it to [2^14, 2^15)
+// (0 for a row of zeros, or one that is not finite).
+__device__ __forceinline__ int row_exp(uint32_t mx)
+{
+    return mx == 0 || mx >= 0x7f800000u ? 0 : 141 - (int)(mx >> 23);
+}
+
 // ---------------------------------------------------------------- LDS layout
 
 // Slot of lane entry `lane` inside a 64-entry fragment block.  Measured on
@@ -797,11 +805,25 @@ __device__ __forceinline__ void epilogue(const GemmDesc &d,
     const int64_t rlo = (int64_t)tm * Cfg<PREC>::BM, clo = (int64_t)tn * Cfg<PREC>::BN;
     double ss = 0.0;
     const bool want_ss = d.partials != nullptr;
+    // operands scaled row by row: their exponents come out of each element here,
+    // and the largest magnitude of each output column is kept for the next product
+    constexpr bool ROWS = base_prec(PREC) == PREC_F16X3 && (PREC & kPacked) != 0;
+    const bool rowed = ROWS && d.row_max != nullptr;
+    uint32_t cmax[G::FN] = {};
 #pragma clang loop unroll(full)
     for (int i = 0; i < G::FM; ++i)
 #pragma clang loop unroll(full)
         for (int j = 0; j < G::FN; ++j) {
             const int64_t col = cb + j * 32;
+            if (rowed) {
+                const int ec = col < d.N ? row_exp(gmem(d.col_max)[col]) : 0;
+#pragma clang loop unroll(full)
+                for (int e = 0; e < 16; ++e) {
+                    int64_t row = rb + i * 32 + (e >> 2) * 8 + (e & 3);
+                    row = row < d.M ? row : d.M - 1;
+                    acc[i][j][e] = ldexpf(acc[i][j][e], -(row_exp(gmem(d.row_max)[row]) + ec));
+                }
+            }
             float ev[16];
             if (d.E) {
                 // past the edge a clamped in-range element is read and not used
@@ -834,8 +856,18 @@ __device__ __forceinline__ void epilogue(const GemmDesc &d,
                     const double df = (double)val - (double)evv;
                     ss += df * df;
                 }
+                if (ROWS)
+                    cmax[j] = max(cmax[j], __float_as_uint(val) & 0x7fffffffu);
             }
         }
+    if (ROWS && d.out_max) {
+#pragma clang loop unroll(full)
+        for (int j = 0; j < G::FN; ++j) {
+            const uint32_t m = max(cmax[j], (uint32_t)__shfl_xor((int)cmax[j], 32, 64));
+            if (lane < 32 && cb + j * 32 < d.N && m)
+                atomicMax(d.out_max + cb + j * 32, m);
+        }
+    }
     if (want_ss) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1)
@@ -1223,10 +1255,13 @@ __host__ __device__ inline int64_t packed_kstride(int64_t rbt)
     return (2 * rbt + kPackPadKiB) << 10;
 }
 
+// rmax: optional (PREC_F16X3), largest magnitude bits of each row of op(X), whose
+// entries are multiplied by 2^row_exp; else every entry is multiplied by sc.
 template <int PREC, bool KC>
 __global__ void __launch_bounds__(256) pack_x3_kernel(const float *__restrict__ X, int64_t ld,
                                                       int64_t R, int64_t K, int64_t kbt,
                                                       int64_t rbt, float sc,
+                                                      const uint32_t *__restrict__ rmax,
                                                       char *__restrict__ out)
 {
     __shared__ float tile[32][kPackSlabK + 1];
@@ -1284,6 +1319,12 @@ __global__ void __launch_bounds__(256) pack_x3_kernel(const float *__restrict__ 
 #pragma unroll
             for (int j = 0; j < 8; ++j)
                 v[j] = tile[r][kk + j];
+            if (base_prec(PREC) == PREC_F16X3 && rmax) {
+                const int s = r0 + r < R ? row_exp(rmax[r0 + r]) : 0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    v[j] = ldexpf(v[j], s);
+            }
             u32x4 parts[2];
             Split<PREC>::run(v, parts, sc);
             char *chunk = out + kb * packed_kstride(rbt) + ((rb * 2) << 10);
@@ -1654,7 +1695,7 @@ inline size_t packed_bytes(int64_t R, int64_t K)
 
 template <int PREC>
 hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t R, int64_t K, float sc,
-                          char *out, hipStream_t s)
+                          const uint32_t *rmax, char *out, hipStream_t s)
 {
     const int64_t rbt = packed_row_blocks(R);
     const int64_t kbt = (K + 15) / 16;
@@ -1666,10 +1707,10 @@ hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t R, int64_t
     const unsigned gy = (unsigned)(rbt < 65535 ? rbt : 65535);
     if (kc)
         hipLaunchKernelGGL((pack_x3_kernel<PREC, true>), dim3((unsigned)gx, gy), dim3(256), 0, s, X,
-                           ld, R, K, kbt, rbt, sc, out);
+                           ld, R, K, kbt, rbt, sc, rmax, out);
     else
         hipLaunchKernelGGL((pack_x3_kernel<PREC, false>), dim3((unsigned)gx, gy), dim3(256), 0, s, X,
-                           ld, R, K, kbt, rbt, sc, out);
+                           ld, R, K, kbt, rbt, sc, rmax, out);
     return hipGetLastError();
 }
 

@@ -21,7 +21,8 @@ size_t packed_x3_bytes(int64_t rows, int64_t k) { return dev::packed_bytes(rows,
 hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t rows, int64_t k, void *out,
                           hipStream_t s)
 {
-    return dev::launch_pack_x3<PREC_BF16X3>(X, ld, kc, rows, k, 1.0f, static_cast<char *>(out), s);
+    return dev::launch_pack_x3<PREC_BF16X3>(X, ld, kc, rows, k, 1.0f, nullptr,
+                                            static_cast<char *>(out), s);
 }
 
 hipError_t launch_gemm_packed_x3(const GemmDesc &d, hipStream_t s)

@@ -39,6 +39,11 @@ struct GemmDesc {
     // PREC_F16X3: powers of two op(A) and op(B) are multiplied by before their
     // split (the caller divides alpha by their product: gemm_f16_scales)
     float scale_a, scale_b;
+    // PREC_F16X3 on operands packed row by row (launch_pack's rmax): the bits of
+    // the largest magnitude of each row of op(A) and each column of op(B), or
+    // null; out_max: optional, takes the maximum with each output column's
+    const uint32_t *row_max, *col_max;
+    uint32_t *out_max;
     int a_kcontig, b_kcontig;
     int gram;
     int gram_upper;    // gram: write only the upper triangle (no mirror)
@@ -116,12 +121,13 @@ hipError_t launch_gemm_grouped(int prec, int a_kcontig, int b_kcontig, int cls,
                                const GroupItem *items_dev, int num_items, hipStream_t s);
 
 // Packed operands of two 16-bit terms (gemm_x3.hip: 3xBF16, gemm_f16x3.hip:
-// F16X3, whose entries are multiplied by sc before the split): op(X) (rows x k; kc: k contiguous,
+// F16X3, whose entries are multiplied by sc before the split, or, with rmax, each
+// row by the power of two that brings its largest entry to [2^14, 2^15)): op(X) (rows x k; kc: k contiguous,
 // X[r * ld + k], else X[k * ld + r]) split into bf16 hi/lo terms and laid out
 // in the GEMM's LDS fragment order, zero-padded to 256 rows and 16 k.
 size_t packed_x3_bytes(int64_t rows, int64_t k);
 hipError_t launch_pack(int prec, const float *X, int64_t ld, int kc, int64_t rows, int64_t k,
-                       float sc, void *out, hipStream_t s);
+                       float sc, void *out, hipStream_t s, const uint32_t *rmax = nullptr);
 // GEMM on packed operands: d.A and d.B point at packed op(A) (M x K) and
 // packed op(B)^T (N x K), set up by gemm_set_packed.
 // Computes the same products in the same order as launch_gemm's kernel of that precision.
@@ -175,6 +181,11 @@ hipError_t launch_step_state(const double *parts, int64_t count, StepState *st,
 // X = A^T / a (FP64 division, rounded once); A is n x m, X is m x n.
 hipError_t launch_transpose_scale(const float *A, int64_t lda, float *X, int64_t ldx,
                                   int64_t n, int64_t m, double a, hipStream_t s);
+// out[i] = bits of the largest magnitude in row i (by_row) or column i of the m x n
+// X (the largest of any NaN's bits if there is one).  launch_zero: count words.
+hipError_t launch_absmax(const float *X, int64_t ldx, int64_t m, int64_t n, int by_row,
+                         uint32_t *out, hipStream_t s);
+hipError_t launch_zero(uint32_t *out, int64_t count, hipStream_t s);
 // Y = s A + t I for an n x n A (FP64 per element, rounded once).
 hipError_t launch_affine(const float *A, int64_t lda, float *Y, int64_t ldy, int64_t n,
                          double sc, double t, hipStream_t s);

@@ -17,12 +17,132 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "la_internal.h"
 
 namespace la {
 namespace {
 
 size_t matfunc_bytes(int64_t n) { return 3 * align_up256((size_t)n * n * sizeof(float)); }
+
+// AUTO's products as three products of two scaled fp16 terms (PREC_F16X3) on
+// packed operands, in place of 6xBF16: half the matrix-core work and half the
+// FP32 accumulation roundings (degree 16 at 4096^2: 9.6 -> 6.4 ms; 3000^2 6.4 ->
+// 3.1 ms).  Each row of op(A) and each column of op(B) is scaled by
+// the power of two of its own largest entry, so rows and columns of very
+// different size keep their accuracy; an element far below its row's largest
+// keeps an absolute error of 2^-39 of that.  The largest entries come from one
+// pass over a fixed operand and, for the recurrence's iterates, from the
+// epilogue that writes them.  The packs live after the three matrices, where the
+// workspace has room.
+struct F16 {
+    bool on = false;
+    char *pa = nullptr, *pb = nullptr;            // packed op(A), op(B)^T
+    uint32_t *ra = nullptr, *cb[2] = {};          // their rows' and columns' maxima
+};
+
+// Whether an M x N x K product of the recurrence runs as F16X3: on tiles that the
+// packed kernel has (the direct ones are bound by reading their operands, not by
+// multiplying them), with K deep enough to repay the packs, and for the
+// accumulation roundings to outweigh the one bit less per operand.  (4096^2
+// product: 640 us at 6xBF16, 355 and 24 for the pack; errors of whole calls,
+// F16X3 / 6xBF16: degree 16 at 1700 1.51e-7 / 1.68e-7, 4096 2.23e-7 / 2.40e-7, odd
+// series of 6 terms at 4096 7.7e-7 / 8.4e-7; with K = 300 2.59e-7 / 2.48e-7 and no
+// gain in time.)
+bool f16_class(int64_t M, int64_t N, int64_t K, int gram)
+{
+    GemmDesc d;
+    memset(&d, 0, sizeof d);
+    d.M = M;
+    d.N = N;
+    d.K = K;
+    d.lda = gram ? N : K;
+    d.ldb = N;
+    d.a_kcontig = gram ? 0 : 1;
+    d.gram = gram;
+    gemm_finalize(d, PREC_F16X3);
+    return !is_direct(d.small) && std::min(M, N) >= 256 && K >= 1024;
+}
+
+size_t f16_bytes(int64_t m, int64_t n)
+{
+    size_t pa = 0, pb = 0;
+    if (f16_class(n, n, m, 1))
+        pa = std::max(pa, packed_x3_bytes(n, m));
+    if (f16_class(n, n, n, 0))
+        pa = std::max(pa, packed_x3_bytes(n, n));
+    if (f16_class(m, n, n, 0))
+        pa = std::max(pa, packed_x3_bytes(m, n));
+    if (!pa)
+        return 0;
+    pb = packed_x3_bytes(n, n);
+    return align_up256(pa) + align_up256(pb) +
+           align_up256((size_t)std::max(m, n) * sizeof(uint32_t)) +
+           2 * align_up256((size_t)n * sizeof(uint32_t));
+}
+
+F16 f16_carve(int64_t m, int64_t n, void *workspace)
+{
+    F16 f;
+    f.on = true;
+    char *b = (char *)workspace + matfunc_bytes(n) + f16_bytes(m, n);
+    for (uint32_t *&c : f.cb) {
+        b -= align_up256((size_t)n * sizeof(uint32_t));
+        c = (uint32_t *)b;
+    }
+    b -= align_up256((size_t)std::max(m, n) * sizeof(uint32_t));
+    f.ra = (uint32_t *)b;
+    b -= align_up256(packed_x3_bytes(n, n));
+    f.pb = b;
+    f.pa = (char *)workspace + matfunc_bytes(n);
+    return f;
+}
+
+// Packs op(A) = X (M x K, kc) or X^T (M columns, K rows, !kc) into f.pa, rows scaled
+// by their own largest entries.
+hipError_t f16_pack_a(const F16 &f, const float *X, int64_t ldx, int kc, int64_t M, int64_t K,
+                      hipStream_t s)
+{
+    hipError_t e = launch_absmax(X, ldx, kc ? M : K, kc ? K : M, kc, f.ra, s);
+    if (e == hipSuccess)
+        e = launch_pack(PREC_F16X3, X, ldx, kc, M, K, 1.0f, f.pa, s, f.ra);
+    return e;
+}
+
+// out = alpha op(A) Y + beta E + gamma I with op(A) (M x K) in f.pa and Y (K x N,
+// columns' maxima in f.cb[c]); the columns' maxima of out go to f.cb[c ^ 1].
+hipError_t f16_product(const F16 &f, int c, const float *Y, int64_t ldy, float *out, int64_t ldo,
+                       int64_t M, int64_t N, int64_t K, float alpha, float beta, const float *E,
+                       int64_t lde, float gamma, hipStream_t s)
+{
+    GemmDesc d;
+    memset(&d, 0, sizeof d);
+    d.C = out;
+    d.ldc = ldo;
+    d.M = M;
+    d.N = N;
+    d.K = K;
+    d.alpha = alpha;
+    d.gamma = gamma;
+    if (E) {
+        d.E = E;
+        d.lde = lde;
+        d.beta = beta;
+    }
+    hipError_t e = launch_pack(PREC_F16X3, Y, ldy, 0, N, K, 1.0f, f.pb, s, f.cb[c]);
+    if (e == hipSuccess)
+        e = launch_zero(f.cb[c ^ 1], N, s);
+    if (e != hipSuccess)
+        return e;
+    d.A = (const float *)f.pa;
+    d.B = (const float *)f.pb;
+    d.row_max = f.ra;
+    d.col_max = f.cb[c];
+    d.out_max = f.cb[c ^ 1];
+    gemm_set_packed(d);
+    return launch_gemm_packed(PREC_F16X3, d, s);
+}
 
 la_status check_coef(const double *coef, int ncoef, const char *who)
 {
@@ -36,6 +156,19 @@ la_status check_coef(const double *coef, int ncoef, const char *who)
             return LA_ERR_INVALID_ARG;
         }
     return LA_OK;
+}
+
+// The F16X3 packs of a call, on where prec is AUTO, some product takes them and
+// the workspace has a free region for them after the three matrices (a smaller
+// workspace runs every product at 6xBF16).
+F16 use_f16(int prec, int64_t m, int64_t n, void *workspace, size_t ws_bytes, const float *A,
+            size_t ab, const float *F, size_t fb)
+{
+    const size_t full = matfunc_bytes(n) + f16_bytes(m, n);
+    if (prec != LA_PREC_AUTO || full == matfunc_bytes(n) || ws_bytes < full ||
+        overlaps(workspace, full, A, ab) || overlaps(workspace, full, F, fb))
+        return F16{};
+    return f16_carve(m, n, workspace);
 }
 
 // out = alpha X Y + beta E + gamma I, X (M x K) and Y (K x N) row-major.
@@ -78,7 +211,7 @@ size_t la_matfunc_workspace_size(int64_t m, int64_t n)
 {
     if (m < 1 || n < 1)
         return 0;
-    return matfunc_bytes(n);
+    return matfunc_bytes(n) + f16_bytes(m, n);
 }
 
 la_status la_matfunc_odd(la_context *ctx, int64_t m, int64_t n, const float *A, int64_t lda,
@@ -118,6 +251,7 @@ la_status la_matfunc_odd(la_context *ctx, int64_t m, int64_t n, const float *A, 
         return LA_ERR_INVALID_ARG;
     }
     const int pr = resolve_prec(prec, PREC_BF16X6);
+    const F16 f = use_f16(prec, m, n, workspace, ws_bytes, A, extent_bytes(m, n, lda), F, fb);
     LA_HIP(hipSetDevice(ctx->device), "la_matfunc_odd: hipSetDevice");
     hipStream_t s = (hipStream_t)hip_stream;
     const int d = ncoef - 1;
@@ -149,20 +283,49 @@ la_status la_matfunc_odd(la_context *ctx, int64_t m, int64_t n, const float *A, 
         g.alpha = 1.0f;
         g.gram = 1;
         gemm_finalize(g, pr);
-        LA_HIP(launch_gemm(pr, g, s), "la_matfunc_odd: gram");
+        if (f.on && f16_class(n, n, m, 1)) {
+            LA_HIP(f16_pack_a(f, A, lda, 0, n, m, s), "la_matfunc_odd: pack");
+            g.A = (const float *)f.pa;
+            g.B = (const float *)f.pa;
+            g.row_max = f.ra;
+            g.col_max = f.ra;
+            gemm_finalize(g, PREC_F16X3);
+            gemm_set_packed(g);
+            LA_HIP(launch_gemm_packed(PREC_F16X3, g, s), "la_matfunc_odd: gram");
+        } else {
+            LA_HIP(launch_gemm(pr, g, s), "la_matfunc_odd: gram");
+        }
     }
     // Horner in G: P = c_d G + c_{d-1} I, then P <- G P + c_j I for j = d-2 .. 0
     int cur = 0;
     LA_HIP(launch_affine(G, n, P[cur], n, n, coef[d], coef[d - 1], s), "la_matfunc_odd: affine");
+    const bool f_horner = f.on && f16_class(n, n, n, 0), f_final = f.on && f16_class(m, n, n, 0);
+    if (f_horner && d >= 2) {
+        LA_HIP(f16_pack_a(f, G, n, 1, n, n, s), "la_matfunc_odd: pack");
+        LA_HIP(launch_absmax(P[cur], n, n, n, 0, f.cb[cur], s), "la_matfunc_odd: pack");
+    }
     for (int j = d - 2; j >= 0; --j) {
-        LA_HIP(product(pr, G, n, P[cur], n, P[cur ^ 1], n, n, n, n, 1.0f, 0.0f, nullptr, 0,
-                       (float)coef[j], s),
-               "la_matfunc_odd: horner");
+        if (f_horner)
+            LA_HIP(f16_product(f, cur, P[cur], n, P[cur ^ 1], n, n, n, n, 1.0f, 0.0f, nullptr, 0,
+                               (float)coef[j], s),
+                   "la_matfunc_odd: horner");
+        else
+            LA_HIP(product(pr, G, n, P[cur], n, P[cur ^ 1], n, n, n, n, 1.0f, 0.0f, nullptr, 0,
+                           (float)coef[j], s),
+                   "la_matfunc_odd: horner");
         cur ^= 1;
     }
     // F = A P
-    LA_HIP(product(pr, A, lda, P[cur], n, F, ldf, m, n, n, 1.0f, 0.0f, nullptr, 0, 0.0f, s),
-           "la_matfunc_odd: final product");
+    if (f_final) {
+        if (!f_horner || d < 2)
+            LA_HIP(launch_absmax(P[cur], n, n, n, 0, f.cb[cur], s), "la_matfunc_odd: pack");
+        LA_HIP(f16_pack_a(f, A, lda, 1, m, n, s), "la_matfunc_odd: pack");
+        LA_HIP(f16_product(f, cur, P[cur], n, F, ldf, m, n, n, 1.0f, 0.0f, nullptr, 0, 0.0f, s),
+               "la_matfunc_odd: final product");
+    } else {
+        LA_HIP(product(pr, A, lda, P[cur], n, F, ldf, m, n, n, 1.0f, 0.0f, nullptr, 0, 0.0f, s),
+               "la_matfunc_odd: final product");
+    }
     LA_HIP(hipStreamSynchronize(s), "la_matfunc_odd: sync");
     return LA_OK;
 }
@@ -208,6 +371,8 @@ la_status la_matfunc_cheb(la_context *ctx, int64_t n, const float *A, int64_t ld
         return LA_ERR_INVALID_ARG;
     }
     const int pr = resolve_prec(prec, PREC_BF16X6);
+    F16 f = use_f16(prec, n, n, workspace, ws_bytes, A, extent_bytes(n, n, lda), F, fb);
+    f.on = f.on && f16_class(n, n, n, 0);
     LA_HIP(hipSetDevice(ctx->device), "la_matfunc_cheb: hipSetDevice");
     hipStream_t s = (hipStream_t)hip_stream;
     // B = sc A + t I maps [lo, hi] onto [-1, 1]
@@ -229,30 +394,36 @@ la_status la_matfunc_cheb(la_context *ctx, int64_t n, const float *A, int64_t ld
     // b_{d-1} = 2 c_d B + c_{d-1} I (b_d = c_d I, b_{d+1} = 0)
     LA_HIP(launch_affine(A, lda, P[0], n, n, 2.0 * c[d] * sc, 2.0 * c[d] * t + c[d - 1], s),
            "la_matfunc_cheb: b_{d-1}");
+    // op(A) is B throughout; the iterate in P[i] has its columns' maxima in cb[i]
+    if (f.on) {
+        LA_HIP(f16_pack_a(f, B, n, 1, n, n, s), "la_matfunc_cheb: pack");
+        LA_HIP(launch_absmax(P[0], n, n, n, 0, f.cb[0], s), "la_matfunc_cheb: pack");
+    }
+    auto times_b = [&](int c, float *out, int64_t ldo, float alpha, float beta, const float *E,
+                       float gamma) {
+        if (f.on)
+            return f16_product(f, c, P[c], n, out, ldo, n, n, n, alpha, beta, E, n, gamma, s);
+        return product(pr, B, n, P[c], n, out, ldo, n, n, n, alpha, beta, E, n, gamma, s);
+    };
     if (d == 2) {
         // F = B b_1 - b_2 + c_0 I with b_2 = c_2 I
-        LA_HIP(product(pr, B, n, P[0], n, F, ldf, n, n, n, 1.0f, 0.0f, nullptr, 0,
-                       (float)(c[0] - c[2]), s),
+        LA_HIP(times_b(0, F, ldf, 1.0f, 0.0f, nullptr, (float)(c[0] - c[2])),
                "la_matfunc_cheb: final product");
         LA_HIP(hipStreamSynchronize(s), "la_matfunc_cheb: sync");
         return LA_OK;
     }
     // b_{d-2} = 2 B b_{d-1} - c_d I + c_{d-2} I
-    LA_HIP(product(pr, B, n, P[0], n, P[1], n, n, n, n, 2.0f, 0.0f, nullptr, 0,
-                   (float)(c[d - 2] - c[d]), s),
+    LA_HIP(times_b(0, P[1], n, 2.0f, 0.0f, nullptr, (float)(c[d - 2] - c[d])),
            "la_matfunc_cheb: clenshaw");
     int cur = 1;   // P[cur] = b_{k+1}, P[cur ^ 1] = b_{k+2}
     for (int k = d - 3; k >= 1; --k) {
         // b_k = 2 B b_{k+1} - b_{k+2} + c_k I, written over b_{k+2}
         float *prev = P[cur ^ 1];
-        LA_HIP(product(pr, B, n, P[cur], n, prev, n, n, n, n, 2.0f, -1.0f, prev, n, (float)c[k],
-                       s),
-               "la_matfunc_cheb: clenshaw");
+        LA_HIP(times_b(cur, prev, n, 2.0f, -1.0f, prev, (float)c[k]), "la_matfunc_cheb: clenshaw");
         cur ^= 1;
     }
     // F = B b_1 - b_2 + c_0 I
-    LA_HIP(product(pr, B, n, P[cur], n, F, ldf, n, n, n, 1.0f, -1.0f, P[cur ^ 1], n, (float)c[0],
-                   s),
+    LA_HIP(times_b(cur, F, ldf, 1.0f, -1.0f, P[cur ^ 1], (float)c[0]),
            "la_matfunc_cheb: final product");
     LA_HIP(hipStreamSynchronize(s), "la_matfunc_cheb: sync");
     return LA_OK;
