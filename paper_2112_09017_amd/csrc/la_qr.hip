@@ -228,8 +228,8 @@ __device__ inline double wave_sum(double v)
 //   6. all eight waves form [I; 0] - U Z, 16 blocks of 32 x 32, on the matrix
 //      cores and write it to Q (rows of this block; ldq).
 // write_u(Us): stores this thread's entries of U (step 1), given the values it
-// read from LDS before the call (the space is reused); s_kap: kappa_j in LDS
-// (read before the reuse); lds: the kernel's 80 KiB buffer.
+// read before the call (the LDS space is reused); s_kap: kappa_j (read before the
+// reuse); lds: the kernel's 80 KiB buffer.
 template <class WriteU>
 __device__ __forceinline__ void form_q64(WriteU write_u, int nc, int lane, int w, int rows,
                                          const float *s_kap, float *lds, float *Qb, int64_t ldq)
@@ -641,10 +641,14 @@ __global__ __launch_bounds__(8 * B) void qr_block_kernel(const float *X, int64_t
 // hanging.  Column j keeps x below the diagonal and the pivot x_j on it.
 // R (row block blk of R, ld ldr) is then written from the registers, and
 // Q = H_0 ... H_{nc-1} [I; 0] is formed in compact WY form (form_q64) and
-// written to Q (ldq); X may equal Q.
+// written to Q (ldq); X may equal Q.  SPLIT: instead the reflectors U go to Q
+// and their kappa to kap (64 per block), for qr_form64_kernel: the next level of
+// the TSQR tree needs R only, so the forming of Q (22 of a block's 59 us) leaves
+// the chain of levels.
+template <bool SPLIT>
 __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t ldx, Part part,
                                                          int nc, float *Q, int64_t ldq, float *R,
-                                                         int64_t ldr)
+                                                         int64_t ldr, float *kap)
 {
     constexpr int CPW = 8;              // columns per wave
     constexpr int RPL = kRows / 64;     // rows per lane
@@ -800,6 +804,34 @@ __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t
 #pragma unroll
     for (int cc = 0; cc < CPW; ++cc)
         u0c[cc] = own + cc < nc ? s_u0[own + cc] : 0.0f;
+    if constexpr (SPLIT) {
+        if (t < nc)
+            kap[blk * 64 + t] = s_kap[t];
+        const bool vecq = own + CPW <= nc && (ldq & 3) == 0 && ((uintptr_t)Q & 15) == 0;
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            const int r = rlo + i;
+            if (r >= rows)
+                continue;
+            float v[CPW];
+#pragma unroll
+            for (int cc = 0; cc < CPW; ++cc) {
+                const int c = own + cc;
+                v[cc] = r < c ? 0.0f : (r == c ? u0c[cc] : f[cc][i]);
+            }
+            float *qr = Q + (r0 + r) * ldq + own;
+            if (vecq) {
+                *(float4 *)qr = make_float4(v[0], v[1], v[2], v[3]);
+                *(float4 *)(qr + 4) = make_float4(v[4], v[5], v[6], v[7]);
+            } else {
+#pragma unroll
+                for (int cc = 0; cc < CPW; ++cc)
+                    if (own + cc < nc)
+                        qr[cc] = v[cc];
+            }
+        }
+        return;
+    }
     form_q64(
         [&](float *Us) {
 #pragma unroll
@@ -814,6 +846,67 @@ __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t
             }
         },
         nc, lane, w, rows, s_kap, lds, Q + r0 * ldq, ldq);
+}
+
+// Q of the blocks of several levels of a TSQR tree, in place of the reflectors
+// that qr_block64_kernel<true> left: one workgroup per block, every level's in one
+// launch (the same products as the unsplit kernel's, bit for bit).
+constexpr int kFormLevels = 24;
+struct FormArgs {
+    int levels, nc;
+    int first[kFormLevels + 1];   // first workgroup of each level
+    float *Q[kFormLevels];
+    const float *kap[kFormLevels];
+    int64_t ldq[kFormLevels];
+    Part part[kFormLevels];
+};
+__global__ __launch_bounds__(512) void qr_form64_kernel(FormArgs a)
+{
+    constexpr int CPW = 8, RPL = kRows / 64;
+    __shared__ __attribute__((aligned(16))) float lds[kRows * 64 + 64 * 64];
+    int l = 0;
+    while (l + 1 < a.levels && (int)blockIdx.x >= a.first[l + 1])
+        ++l;
+    const int64_t blk = (int)blockIdx.x - a.first[l];
+    const int64_t ldq = a.ldq[l];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int rlo = lane * RPL;
+    const int64_t r0 = part_start(a.part[l], blk);
+    const int rows = (int)(part_start(a.part[l], blk + 1) - r0);
+    const int nc = a.nc;
+    const int own = __builtin_amdgcn_readfirstlane(w * CPW);
+    float *Qb = a.Q[l] + r0 * ldq;
+    float f[CPW][RPL];
+    const bool vec = own + CPW <= nc && (ldq & 3) == 0 && ((uintptr_t)a.Q[l] & 15) == 0;
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+        const int r = rlo + i;
+        const float *qr = Qb + (int64_t)r * ldq + own;
+        if (vec) {
+            float4 x = make_float4(0.0f, 0.0f, 0.0f, 0.0f), y = x;
+            if (r < rows) {
+                x = *(const float4 *)qr;
+                y = *(const float4 *)(qr + 4);
+            }
+            f[0][i] = x.x, f[1][i] = x.y, f[2][i] = x.z, f[3][i] = x.w;
+            f[4][i] = y.x, f[5][i] = y.y, f[6][i] = y.z, f[7][i] = y.w;
+        } else {
+#pragma unroll
+            for (int cc = 0; cc < CPW; ++cc)
+                f[cc][i] = (own + cc < nc && r < rows) ? qr[cc] : 0.0f;
+        }
+    }
+    form_q64(
+        [&](float *Us) {
+#pragma unroll
+            for (int cc = 0; cc < CPW; ++cc)
+#pragma unroll
+                for (int i = 0; i < RPL; ++i) {
+                    const int r = rlo + i;
+                    Us[r * 64 + ((own + cc) ^ (r & 31))] = f[cc][i];
+                }
+        },
+        nc, lane, w, rows, a.kap[l] + blk * 64, lds, Qb, ldq);
 }
 
 // out[r, :] = (in[r, :] - sub [r < nc] e_r^T) M_b for every row r < part.rows,
@@ -1022,6 +1115,10 @@ struct TsqrPlan {
     int nb[kMaxLevels];
     size_t off[kMaxLevels];     // byte offset of buffer l (l >= 1)
     size_t bytes;
+    // kappa of every level's blocks, after the buffers, for a tree of several
+    // levels of at most 64 columns; a workspace without them factors and forms Q
+    // block by block (the same result)
+    size_t kap[kMaxLevels], kap_bytes;
 };
 
 TsqrPlan tsqr_plan(int64_t m, int nc)
@@ -1041,15 +1138,28 @@ TsqrPlan tsqr_plan(int64_t m, int nc)
     }
     p.levels = l;
     p.bytes = b;
+    if (nc <= 64 && l >= 1 && l < kFormLevels) {
+        size_t k = 0;
+        for (int i = 0; i <= l; ++i) {
+            p.kap[i] = k;
+            k += al((size_t)p.nb[i] * 64 * sizeof(float));
+        }
+        p.kap_bytes = k;
+    }
     return p;
 }
 
 template <int B>
 hipError_t tsqr_run_b(const float *A, int64_t lda, int nc, float *Q, int64_t ldq, float *R,
-                      int64_t ldr, char *ws, const TsqrPlan &tp, hipStream_t s)
+                      int64_t ldr, char *ws, const TsqrPlan &tp, char *kap, hipStream_t s)
 {
     const int L = tp.levels;
     auto buf = [&](int l) { return (float *)(ws + tp.off[l]); };
+    FormArgs fa;
+    fa.levels = L + 1;
+    fa.nc = nc;
+    fa.first[0] = 0;
+    const bool split = B == 64 && kap && tp.kap_bytes;
     for (int l = 0; l <= L; ++l) {
         const Part pl = make_part(tp.rows[l], nc);
         const float *in = l == 0 ? A : buf(l);
@@ -1058,12 +1168,30 @@ hipError_t tsqr_run_b(const float *A, int64_t lda, int nc, float *Q, int64_t ldq
         const int64_t ldo = l == 0 ? ldq : nc;
         float *ro = l == L ? R : buf(l + 1);
         const int64_t ldro = l == L ? ldr : nc;
-        if constexpr (B == 64)
-            hipLaunchKernelGGL(qr_block64_kernel, dim3(pl.nb), dim3(512), 0, s, in, ldi, pl, nc,
-                               qo, ldo, ro, ldro);
-        else
+        if constexpr (B == 64) {
+            if (split) {
+                float *kl = (float *)(kap + tp.kap[l]);
+                hipLaunchKernelGGL(qr_block64_kernel<true>, dim3(pl.nb), dim3(512), 0, s, in, ldi,
+                                   pl, nc, qo, ldo, ro, ldro, kl);
+                fa.Q[l] = qo;
+                fa.ldq[l] = ldo;
+                fa.part[l] = pl;
+                fa.kap[l] = kl;
+                fa.first[l + 1] = fa.first[l] + pl.nb;
+            } else {
+                hipLaunchKernelGGL(qr_block64_kernel<false>, dim3(pl.nb), dim3(512), 0, s, in, ldi,
+                                   pl, nc, qo, ldo, ro, ldro, (float *)nullptr);
+            }
+        } else {
             hipLaunchKernelGGL(qr_block_kernel<B>, dim3(pl.nb), dim3(8 * B), 0, s, in, ldi, pl,
                                nc, qo, ldo, ro, ldro);
+        }
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    if (split) {
+        hipLaunchKernelGGL(qr_form64_kernel, dim3(fa.first[L + 1]), dim3(512), 0, s, fa);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
@@ -1083,11 +1211,11 @@ hipError_t tsqr_run_b(const float *A, int64_t lda, int nc, float *Q, int64_t ldq
 }
 
 hipError_t tsqr_run(const float *A, int64_t lda, int nc, float *Q, int64_t ldq, float *R,
-                    int64_t ldr, char *ws, const TsqrPlan &tp, hipStream_t s)
+                    int64_t ldr, char *ws, const TsqrPlan &tp, char *kap, hipStream_t s)
 {
     if (nc <= 64)
-        return tsqr_run_b<64>(A, lda, nc, Q, ldq, R, ldr, ws, tp, s);
-    return tsqr_run_b<128>(A, lda, nc, Q, ldq, R, ldr, ws, tp, s);
+        return tsqr_run_b<64>(A, lda, nc, Q, ldq, R, ldr, ws, tp, kap, s);
+    return tsqr_run_b<128>(A, lda, nc, Q, ldq, R, ldr, ws, tp, kap, s);
 }
 
 // W = Q - [I; 0], Y = W (I - Q_1)^-1 for an m x nc Q; Minv: nc x nc scratch.
@@ -1239,6 +1367,7 @@ hipError_t gemm_sub(int prec, const float *X, int64_t ldx, const float *Z, int64
 // parts, and the split-K descriptors.
 struct CaqrWs {
     size_t qr, rr, tree, wy, w, y, z0, parts0, z1, parts1, probs, items, bytes;
+    size_t kap_bytes;   // after them: the TSQR tree's kappa (optional, as la_tsqr's)
 };
 
 CaqrWs caqr_ws(int64_t m, int64_t n, int b, int want_q)
@@ -1281,6 +1410,7 @@ CaqrWs caqr_ws(int64_t m, int64_t n, int b, int want_q)
     w.items = o;
     o += al(((size_t)np * sp_next * 4 + nwide * split_items_bound(b, n)) * sizeof(GroupItem));
     w.bytes = o;
+    w.kap_bytes = tsqr_plan(m, b).kap_bytes;
     return w;
 }
 
@@ -1340,7 +1470,8 @@ size_t la_tsqr_workspace_size(int64_t m, int64_t n)
 {
     if (n < 1 || n > kMaxPanel || m < n)
         return 0;
-    return std::max<size_t>(256, tsqr_plan(m, (int)n).bytes);
+    const TsqrPlan tp = tsqr_plan(m, (int)n);
+    return std::max<size_t>(256, tp.bytes + tp.kap_bytes);
 }
 
 la_status la_tsqr(la_context *ctx, int64_t m, int64_t n, const float *A, int64_t lda, float *Q,
@@ -1373,7 +1504,13 @@ la_status la_tsqr(la_context *ctx, int64_t m, int64_t n, const float *A, int64_t
     }
     LA_HIP(hipSetDevice(ctx->device), "la_tsqr: hipSetDevice");
     hipStream_t s = (hipStream_t)hip_stream;
-    LA_HIP(tsqr_run(A, lda, (int)n, Q, ldq, R, ldr, (char *)workspace, tp, s), "la_tsqr: launch");
+    // the optional region after the required one is used only where it is free
+    const size_t full = tp.bytes + tp.kap_bytes;
+    const bool room = tp.kap_bytes && ws_bytes >= full && !overlaps(A, ab, workspace, full) &&
+                      !overlaps(Q, qb, workspace, full) && !overlaps(R, rb, workspace, full);
+    LA_HIP(tsqr_run(A, lda, (int)n, Q, ldq, R, ldr, (char *)workspace, tp,
+                    room ? (char *)workspace + tp.bytes : nullptr, s),
+           "la_tsqr: launch");
     LA_HIP(hipStreamSynchronize(s), "la_tsqr: sync");
     return LA_OK;
 }
@@ -1427,7 +1564,8 @@ size_t la_caqr_workspace_size(int64_t m, int64_t n, int panel, int want_q)
 {
     if (n < 1 || m < n || panel < 1 || panel > kMaxPanel)
         return 0;
-    return caqr_ws(m, n, (int)std::min<int64_t>(panel, n), want_q).bytes;
+    const CaqrWs cw = caqr_ws(m, n, (int)std::min<int64_t>(panel, n), want_q);
+    return cw.bytes + cw.kap_bytes;
 }
 
 la_status la_caqr(la_context *ctx, int64_t m, int64_t n, float *A, int64_t lda, float *Q,
@@ -1461,6 +1599,12 @@ la_status la_caqr(la_context *ctx, int64_t m, int64_t n, float *A, int64_t lda, 
         set_error("%s: A, Q and the workspace must not overlap", who);
         return LA_ERR_INVALID_ARG;
     }
+    const size_t full = cw.bytes + cw.kap_bytes;
+    const size_t kap_room =
+        ws_bytes >= full && !overlaps(A, ab, workspace, full) &&
+                !(Q && overlaps(Q, extent_bytes(m, n, ldq), workspace, full))
+            ? cw.kap_bytes
+            : 0;
     const int pr = resolve_prec(prec, PREC_BF16X6);
     LA_HIP(hipSetDevice(ctx->device), "la_caqr: hipSetDevice");
     hipStream_t s = (hipStream_t)hip_stream;
@@ -1540,7 +1684,10 @@ la_status la_caqr(la_context *ctx, int64_t m, int64_t n, float *A, int64_t lda, 
         float *Ap = A + c * lda + c;
         float *W = wpan(jp), *Y = ypan(jp);
         const TsqrPlan tp = tsqr_plan(ml, nc);
-        LA_HIP(tsqr_run(Ap, lda, nc, Qr, b, Rr, b, ws + cw.tree, tp, s), "la_caqr: tsqr");
+        // (a later panel's tree has no more blocks than the first's)
+        LA_HIP(tsqr_run(Ap, lda, nc, Qr, b, Rr, b, ws + cw.tree, tp,
+                        tp.kap_bytes <= kap_room ? ws + cw.bytes : nullptr, s),
+               "la_caqr: tsqr");
         LA_HIP(wy_run(ml, nc, Qr, b, W, ldwy, Y, ldwy, Minv, flag, s), "la_caqr: wy");
         hipLaunchKernelGGL(place_r_kernel, dim3(grid1d(ml * nc)), dim3(256), 0, s, Ap, lda, ml,
                            nc, (const float *)Rr, (int64_t)b);
