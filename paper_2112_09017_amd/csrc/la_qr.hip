@@ -39,6 +39,7 @@ namespace {
 
 constexpr int kRows = 256;        // rows of one local factorisation
 constexpr int kMaxPanel = 128;
+constexpr int kRowmulRows = 128;   // rows of a block per workgroup of rowmul_kernel
 constexpr int kMaxLevels = 40;
 constexpr int kMaxSplits = 16;
 // The next panel's product W^T A_next (b x b output, K = the panel's rows) is
@@ -912,10 +913,15 @@ __global__ __launch_bounds__(512) void qr_form64_kernel(FormArgs a)
 // out[r, :] = (in[r, :] - sub [r < nc] e_r^T) M_b for every row r < part.rows,
 // with M_b = Mb + b * nc * nc (nc x nc, ld nc) for the partition block b
 // holding row r, or M_0 for every row when single; wout (optional) receives
-// in[r, :] - sub e_r^T.  Workgroup (b, y) takes rows 32 y .. 32 y + 31 of
-// block b, staged in LDS with M_b; 8 threads per row, each forming B / 8 of
-// its outputs.  out may equal in: every row is read whole before any
-// thread of the workgroup writes.
+// in[r, :] - sub e_r^T.  Workgroup (b, y) takes rows 128 y .. 128 y + 127 of
+// block b, each wave 32 of them on the matrix cores (v_mfma_f32_32x32x2f32): lane
+// l holds half of row l & 31 (k from B / 2 (l >> 5) on; step q takes k = q and
+// B / 2 + q), M_b is in LDS.  Latency bound on the tree's upper levels and in
+// CAQR's panels, HBM bound on the leaves (64 columns, 131072 rows, tree of six
+// levels: 20 us a level on the vector units with an index division per element,
+// 8.7 us now; CAQR's panels of 6144 rows 12 -> 7.3 us).  out may equal in: a wave
+// reads its rows whole
+// before it writes any.
 template <int B>
 __global__ __launch_bounds__(256) void rowmul_kernel(const float *in, int64_t ldi, Part part,
                                                      int single, int nc,
@@ -923,64 +929,99 @@ __global__ __launch_bounds__(256) void rowmul_kernel(const float *in, int64_t ld
                                                      int64_t ldo, float *wout, int64_t ldw,
                                                      int sub)
 {
-    constexpr int CG = 8, CPT = B / CG, RPB = 256 / CG;
-    __shared__ float xs[RPB * (B + 1)];
+    typedef float f32x16_t __attribute__((ext_vector_type(16)));
+    constexpr int HK = B / 2, NJ = B / 32;
     __shared__ __attribute__((aligned(16))) float ms[B * B];
-    const int t = threadIdx.x, rr = t / CG, cg = t % CG;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, li = lane & 31, h = lane >> 5;
     const int64_t b = blockIdx.x;
-    const int64_t rbase = part_start(part, b) + (int64_t)blockIdx.y * RPB;
+    const int64_t rbase = part_start(part, b) + (int64_t)blockIdx.y * kRowmulRows + 32 * w;
     const int64_t rend = part_start(part, b + 1);
-    if (rbase >= rend)
-        return;
-    const float *M = Mb + (single ? 0 : b * nc * nc);
-    for (int idx = t; idx < nc * nc; idx += 256)
-        ms[(idx / nc) * B + idx % nc] = M[idx];
-    for (int idx = t; idx < RPB * B; idx += 256) {
-        const int i = idx / B, k = idx % B;
-        const int64_t r = rbase + i;
-        float v = 0.0f;
-        if (r < rend && k < nc) {
-            v = in[r * ldi + k];
-            if (sub && r == k)
-                v -= 1.0f;
-            if (wout)
-                wout[r * ldw + k] = v;
+    if (rbase - 32 * w >= rend)
+        return;   // the whole workgroup
+    const int64_t row = rbase + li;
+    float x[HK];
+    const bool vec = nc == B && (ldi & 3) == 0 && ((uintptr_t)in & 15) == 0;
+    const float *xr = in + row * ldi + h * HK;
+    if (vec && row < rend) {
+#pragma unroll
+        for (int q = 0; q < HK; q += 4) {
+            const float4 v = *(const float4 *)(xr + q);
+            x[q] = v.x, x[q + 1] = v.y, x[q + 2] = v.z, x[q + 3] = v.w;
         }
-        xs[i * (B + 1) + k] = v;
+    } else {
+#pragma unroll
+        for (int q = 0; q < HK; ++q)
+            x[q] = row < rend && h * HK + q < nc ? xr[q] : 0.0f;
+    }
+    const float *M = Mb + (single ? 0 : b * nc * nc);
+    if (nc == B && ((uintptr_t)M & 15) == 0) {
+        constexpr int NV = B * B / 1024;   // 16-byte pieces per thread
+#pragma unroll
+        for (int v0 = 0; v0 < NV; v0 += 4) {
+            float4 mv[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                mv[v] = ((const float4 *)M)[(v0 + v) * 256 + t];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                ((float4 *)ms)[(v0 + v) * 256 + t] = mv[v];
+        }
+    } else {
+        for (int r = w; r < B; r += 4)
+#pragma unroll
+            for (int c = lane; c < B; c += 64)
+                ms[r * B + c] = r < nc && c < nc ? M[r * nc + c] : 0.0f;
+    }
+    if (sub) {
+#pragma unroll
+        for (int q = 0; q < HK; ++q)
+            if (row == h * HK + q && row < nc)
+                x[q] -= 1.0f;
+    }
+    if (wout && row < rend) {
+        float *wr = wout + row * ldw + h * HK;
+        if (nc == B && (ldw & 3) == 0 && ((uintptr_t)wout & 15) == 0) {
+#pragma unroll
+            for (int q = 0; q < HK; q += 4)
+                *(float4 *)(wr + q) = make_float4(x[q], x[q + 1], x[q + 2], x[q + 3]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < HK; ++q)
+                if (h * HK + q < nc)
+                    wr[q] = x[q];
+        }
     }
     __syncthreads();
-    const int64_t r = rbase + rr;
-    if (r >= rend)
-        return;
-    float acc[CPT];
+    f32x16_t acc[NJ] = {};
 #pragma unroll
-    for (int e = 0; e < CPT; ++e)
-        acc[e] = 0.0f;
-    for (int k = 0; k < nc; ++k) {
-        const float xv = xs[rr * (B + 1) + k];
+    for (int q = 0; q < HK; ++q)
 #pragma unroll
-        for (int e = 0; e < CPT; e += 4) {
-            const float4 mv = *(const float4 *)&ms[k * B + cg * CPT + e];
-            acc[e] = fmaf(xv, mv.x, acc[e]);
-            acc[e + 1] = fmaf(xv, mv.y, acc[e + 1]);
-            acc[e + 2] = fmaf(xv, mv.z, acc[e + 2]);
-            acc[e + 3] = fmaf(xv, mv.w, acc[e + 3]);
+        for (int j = 0; j < NJ; ++j)
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                x[q], ms[(h * HK + q) * B + 32 * j + li], acc[j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int64_t r = rbase + 8 * (e >> 2) + 4 * h + (e & 3);
+            if (r < rend && 32 * j + li < nc)
+                out[r * ldo + 32 * j + li] = acc[j][e];
         }
-    }
-#pragma unroll
-    for (int e = 0; e < CPT; ++e)
-        if (cg * CPT + e < nc)
-            out[r * ldo + cg * CPT + e] = acc[e];
 }
 
 // Minv = (I - Q_1)^-1 for the top nc x nc block Q_1 of Q (ld ldq), by
 // Gauss-Jordan elimination with partial pivoting in FP64 in LDS (512
-// threads; thread (i0, c) owns column c of rows i0, i0 + 512 / B, ...).
+// threads; thread (i0, c) owns column c of rows i0, i0 + 512 / B, ...), eight
+// columns at a time: the elimination is a chain of nc pivots, and with two
+// barriers and a pass over the whole array per pivot it took 64 us at nc = 64; 36
+// now.
 // Rows are not moved: step k pivots on the unused row p_k with the largest
-// |M[p_k][k]| (compared in FP32, ties to the lower row; every wave finds it
-// itself), scales row p_k and eliminates column k from the other rows, with
-// one barrier between reading the operands and writing the results and one
-// after.  The array then holds (P M)^-1 in pivot order, and
+// |M[p_k][k]| (compared in FP32, ties to the lower row), scales row p_k and
+// eliminates column k from the other rows.  Wave 0 does this to the eight
+// columns in its registers (lane = row); what they then hold is the matrix G of
+// the eight eliminations together, and every other column becomes
+// x_i <- (i a pivot of these eight ? 0 : x_i) + sum_j G_ij x_{p_j} with the x before,
+// by all waves.  The array ends as (P M)^-1 in pivot order, and
 // Minv[k][p_c] = B[p_k][c].  Rounded to FP32 (nc x nc, ld nc).  flag[0] = 1
 // if a pivot is below kPivotFloor in magnitude or not finite.
 template <int B>
@@ -991,9 +1032,12 @@ __global__ __launch_bounds__(512) void wy_inverse_kernel(const float *__restrict
     constexpr int LD = B + 1;
     constexpr int RP = 512 / B;   // row phases: thread (i0, c) takes rows i0 + RP q
     constexpr int RO = B / RP;    // rows owned per thread
-    constexpr int RL = B / 64;    // rows per lane in the pivot search
+    constexpr int RL = B / 64;    // rows per lane in wave 0's columns
+    constexpr int NB = 8;         // columns per panel
     __shared__ double M[B * LD];
+    __shared__ __attribute__((aligned(16))) double G[B * NB];
     __shared__ int piv[B];
+    __shared__ int panel_of[B];   // panel in which a row was the pivot, or -1
     const int t = threadIdx.x, lane = t & 63;
     const int cc = t % B, i0 = t / B;
     nc = __builtin_amdgcn_readfirstlane(nc);
@@ -1001,57 +1045,98 @@ __global__ __launch_bounds__(512) void wy_inverse_kernel(const float *__restrict
     for (int i = i0; i < nc; i += RP)
         if (ccol)
             M[i * LD + cc] = (i == cc ? 1.0 : 0.0) - (double)Q[(int64_t)i * ldq + cc];
+    if (t < B)
+        panel_of[t] = -1;
     bool used[RL];
 #pragma unroll
     for (int q = 0; q < RL; ++q)
         used[q] = false;
     __syncthreads();
-    for (int kv = 0; kv < nc; ++kv) {
-        const int k = __builtin_amdgcn_readfirstlane(kv);
-        // pivot (every wave): key = FP32 magnitude bits (low 7 mantissa bits dropped) | (127 - row)
-        unsigned key = 0;
+    for (int k0 = 0, pn = 0; k0 < nc; k0 += NB, ++pn) {
+        if (t < 64) {
+            double a[RL][NB];
 #pragma unroll
-        for (int q = 0; q < RL; ++q) {
-            const int r = lane + 64 * q;
-            if (r < nc && !used[q]) {
-                const unsigned kk = ((unsigned)__float_as_int((float)fabs(M[r * LD + k])) & ~0x7Fu) |
-                                    (unsigned)(127 - r);
-                key = kk > key ? kk : key;
+            for (int q = 0; q < RL; ++q)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const int r = lane + 64 * q;
+                    a[q][j] = r < nc && k0 + j < nc ? M[r * LD + k0 + j] : 0.0;
+                }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                if (k0 + j >= nc)
+                    break;
+                // key = FP32 magnitude bits (low 7 mantissa bits dropped) | (127 - row)
+                unsigned key = 0;
+#pragma unroll
+                for (int q = 0; q < RL; ++q) {
+                    const int r = lane + 64 * q;
+                    if (r < nc && !used[q]) {
+                        const unsigned kk =
+                            ((unsigned)__float_as_int((float)fabs(a[q][j])) & ~0x7Fu) |
+                            (unsigned)(127 - r);
+                        key = kk > key ? kk : key;
+                    }
+                }
+                key = wave_max(key);
+                const int p = __builtin_amdgcn_readfirstlane(127 - (int)(key & 0x7Fu));
+                double pr[NB];   // the pivot row's eight entries, uniform
+#pragma unroll
+                for (int jj = 0; jj < NB; ++jj) {
+                    double v = a[0][jj];
+                    if (RL > 1 && p >= 64)
+                        v = a[RL - 1][jj];
+                    pr[jj] = __hiloint2double(
+                        __builtin_amdgcn_readlane(__double2hiint(v), p & 63),
+                        __builtin_amdgcn_readlane(__double2loint(v), p & 63));
+                }
+                const double pv = pr[j], inv = 1.0 / pv;
+#pragma unroll
+                for (int q = 0; q < RL; ++q) {
+                    const bool isp = lane + 64 * q == p;
+                    const double fi = -a[q][j] * inv;
+#pragma unroll
+                    for (int jj = 0; jj < NB; ++jj)
+                        if (jj != j)
+                            a[q][jj] = isp ? pr[jj] * inv : fma(fi, pr[jj], a[q][jj]);
+                    a[q][j] = isp ? inv : fi;
+                    if (isp)
+                        used[q] = true;
+                }
+                if (lane == 0) {
+                    piv[k0 + j] = p;
+                    panel_of[p] = pn;
+                    if (!(fabs(pv) >= kPivotFloor && isfinite(pv)))
+                        flag[0] = 1;
+                }
             }
-        }
-        key = wave_max(key);
-        const int p = __builtin_amdgcn_readfirstlane(127 - (int)(key & 0x7Fu));
 #pragma unroll
-        for (int q = 0; q < RL; ++q)
-            if (lane + 64 * q == p)
-                used[q] = true;
-        const double pv = M[p * LD + k];
-        const double inv = 1.0 / pv;
-        const double prc = ccol ? M[p * LD + cc] : 0.0;
-        double mic[RO], fic[RO];
+            for (int q = 0; q < RL; ++q)
 #pragma unroll
-        for (int q = 0; q < RO; ++q) {
-            const int i = i0 + RP * q;
-            mic[q] = (i < nc && ccol) ? M[i * LD + cc] : 0.0;
-            fic[q] = i < nc ? M[i * LD + k] : 0.0;
-        }
-        if (t == 0) {
-            piv[k] = p;
-            if (!(fabs(pv) >= kPivotFloor && isfinite(pv)))
-                flag[0] = 1;
+                for (int j = 0; j < NB; ++j)
+                    G[(lane + 64 * q) * NB + j] = a[q][j];
         }
         __syncthreads();
+        const int nb = nc - k0 < NB ? nc - k0 : NB;
+        double xp[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            xp[j] = j < nb && ccol ? M[piv[k0 + j] * LD + cc] : 0.0;
+        __syncthreads();
         if (ccol) {
+            const int own = cc - k0;   // 0 .. nb - 1: a column of the panel itself
 #pragma unroll
             for (int q = 0; q < RO; ++q) {
                 const int i = i0 + RP * q;
                 if (i >= nc)
                     continue;
-                double v;
-                if (i == p)
-                    v = cc == k ? inv : prc * inv;
-                else
-                    v = cc == k ? -fic[q] * inv : fma(-fic[q] * inv, prc, mic[q]);
+                const double *g = G + i * NB;
+                double v = panel_of[i] == pn ? 0.0 : M[i * LD + cc];
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+                    v = fma(g[j], xp[j], v);
+                if (own >= 0 && own < nb)
+                    v = g[own];
                 M[i * LD + cc] = v;
             }
         }
@@ -1200,7 +1285,7 @@ hipError_t tsqr_run_b(const float *A, int64_t lda, int nc, float *Q, int64_t ldq
         const Part pl = make_part(tp.rows[l], nc);
         float *io = l == 0 ? Q : buf(l);
         const int64_t ld = l == 0 ? ldq : nc;
-        hipLaunchKernelGGL(rowmul_kernel<B>, dim3(pl.nb, kRows / 32), dim3(256), 0, s,
+        hipLaunchKernelGGL(rowmul_kernel<B>, dim3(pl.nb, kRows / kRowmulRows), dim3(256), 0, s,
                            (const float *)io, ld, pl, 0, nc, (const float *)buf(l + 1), io, ld,
                            (float *)nullptr, (int64_t)0, 0);
         hipError_t e = hipGetLastError();
@@ -1228,7 +1313,7 @@ hipError_t wy_run_b(int64_t m, int nc, const float *Q, int64_t ldq, float *W, in
     if (e != hipSuccess)
         return e;
     const Part p = make_part(m, nc);
-    hipLaunchKernelGGL(rowmul_kernel<B>, dim3(p.nb, kRows / 32), dim3(256), 0, s, Q, ldq, p, 1,
+    hipLaunchKernelGGL(rowmul_kernel<B>, dim3(p.nb, kRows / kRowmulRows), dim3(256), 0, s, Q, ldq, p, 1,
                        nc, (const float *)Minv, Y, ldy, W, ldw, 1);
     return hipGetLastError();
 }
