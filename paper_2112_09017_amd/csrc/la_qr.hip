@@ -30,6 +30,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "la_internal.h"
@@ -156,44 +157,48 @@ __device__ inline unsigned wave_max(unsigned v)
     return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// wave_sum of v[first .. N - 1], the N - first sums step by step side by side
-// (each step a DPP add: the moves read zero outside their rows)
-template <int CTRL, int ROWS = 0xF>
-__device__ inline float dppz_f32(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xF, true));
-}
+// Sums over the 64 lanes of a wave of N values per lane, halving the number of
+// values held at each of the first steps: v_permlane32_swap_b32 and
+// v_permlane16_swap_b32 put the halves of two values that belong together side by
+// side, so one add serves both (a value without a partner is paired with itself).
+// N = 8 takes 21 instructions against the 48 adds of eight wave_sum.  On return
+// out[i] is the wave-uniform total of v[i] times scale.
 template <int N>
-__device__ inline void wave_sums(float (&v)[N], int first)
+__device__ __forceinline__ void wave_sums(const float (&v)[N], float scale, float (&out)[N])
 {
+    constexpr int N1 = (N + 1) / 2, N2 = (N1 + 1) / 2;
+    static_assert(N >= 1 && N2 <= 2, "at most eight values");
+    float a[N1], b[N2];
 #pragma unroll
-    for (int k = 0; k < N; ++k)
-        if (k >= first)
-            v[k] += dppz_f32<0xB1>(v[k]);
+    for (int i = 0; i < N1; ++i) {
+        const int lo = 2 * i, hi = 2 * i + 1 < N ? 2 * i + 1 : lo;
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[lo]),
+                                                        __float_as_uint(v[hi]), false, false);
+        a[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
 #pragma unroll
-    for (int k = 0; k < N; ++k)
-        if (k >= first)
-            v[k] += dppz_f32<0x4E>(v[k]);
+    for (int i = 0; i < N2; ++i) {
+        const int lo = 2 * i, hi = 2 * i + 1 < N1 ? 2 * i + 1 : lo;
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[lo]),
+                                                        __float_as_uint(a[hi]), false, false);
+        b[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    float c = b[0];
+    if constexpr (N2 == 1) {
+        c += dpp_f32<0x128>(c);          // row_ror:8
+    } else {
+        const bool up = threadIdx.x & 8;   // this half of the row takes b[1]
+        const float keep = up ? b[1] : b[0], send = up ? b[0] : b[1];
+        c = keep + dpp_f32<0x128>(send);
+    }
+    c += dpp_f32<0xB1>(c);
+    c += dpp_f32<0x4E>(c);
+    c += dpp_f32<0x141>(c);              // row_half_mirror
+    c *= scale;
 #pragma unroll
-    for (int k = 0; k < N; ++k)
-        if (k >= first)
-            v[k] += dppz_f32<0x141>(v[k]);
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-        if (k >= first)
-            v[k] += dppz_f32<0x140>(v[k]);
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-        if (k >= first)
-            v[k] += dppz_f32<0x142, 0xA>(v[k]);
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-        if (k >= first)
-            v[k] += dppz_f32<0x143, 0xC>(v[k]);
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-        if (k >= first)
-            v[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[k]), 63));
+    for (int i = 0; i < N; ++i)
+        out[i] = __int_as_float(__builtin_amdgcn_readlane(
+            __float_as_int(c), 32 * (i & 1) + 16 * ((i >> 1) & 1) + 8 * ((i >> 2) & 1)));
 }
 __device__ inline double wave_sum(double v)
 {
@@ -640,6 +645,9 @@ __global__ __launch_bounds__(8 * B) void qr_block_kernel(const float *X, int64_t
 // wave to its left publishes without waiting on this one; it is bounded all
 // the same, and a wait that runs out marks the block's R with NaN instead of
 // hanging.  Column j keeps x below the diagonal and the pivot x_j on it.
+// The chain of 64 reflections bounds it (256 x 64: 44 us with a wave_sum per
+// column, the library's sqrt and divide and one poll per reflection, 36 us now;
+// leaves of 131072 rows, two blocks per CU, 49 -> 40 us).
 // R (row block blk of R, ld ldr) is then written from the registers, and
 // Q = H_0 ... H_{nc-1} [I; 0] is formed in compact WY form (form_q64) and
 // written to Q (ldq); X may equal Q.  SPLIT: instead the reflectors U go to Q
@@ -693,28 +701,27 @@ __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t
         }
     }
 
-    // x_c -= kappa (u^T x_c) u for columns cc >= first (compile time) of the
-    // wave; the column sums go through wave_sum's steps side by side
-    auto apply = [&](const float (&u)[RPL], float kap, int first) {
-        float d[CPW];
+    // x_c -= kappa (u^T x_c) u for the wave's columns FIRST .. CPW - 1
+    auto apply = [&](auto first, const float (&u)[RPL], float kap, auto &&between) {
+        constexpr int F = decltype(first)::value;
+        if constexpr (F < CPW) {
+            float d[CPW - F], sc[CPW - F];
 #pragma unroll
-        for (int cc = 0; cc < CPW; ++cc) {
-            d[cc] = 0.0f;
-            if (cc < first)
-                continue;
+            for (int c = 0; c < CPW - F; ++c) {
+                d[c] = 0.0f;
 #pragma unroll
-            for (int i = 0; i < RPL; ++i)
-                d[cc] = fmaf(u[i], f[cc][i], d[cc]);
-        }
-        wave_sums<CPW>(d, first);
+                for (int i = 0; i < RPL; ++i)
+                    d[c] = fmaf(u[i], f[F + c][i], d[c]);
+            }
+            wave_sums(d, kap, sc);
+            between();
 #pragma unroll
-        for (int cc = 0; cc < CPW; ++cc) {
-            if (cc < first)
-                continue;
-            const float sc = kap * d[cc];
+            for (int c = 0; c < CPW - F; ++c)
 #pragma unroll
-            for (int i = 0; i < RPL; ++i)
-                f[cc][i] = fmaf(-sc, u[i], f[cc][i]);
+                for (int i = 0; i < RPL; ++i)
+                    f[F + c][i] = fmaf(-sc[c], u[i], f[F + c][i]);
+        } else {
+            between();
         }
     };
 
@@ -723,27 +730,48 @@ __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t
     __syncthreads();
     bool timed_out = false;
     if (own < nc) {
-        // the reflections of the waves to the left, as they are published
+        // the reflections of the waves to the left, as they are published; the
+        // next one is read ahead where it is already there.  The wave whose
+        // turn is next goes ahead of the others on its SIMD.
+        int have = 0;
+        float4 uv, un;
+        float kv, kn;
+        bool ahead = false;
         for (int jv = 0; jv < own; ++jv) {
             const int j = __builtin_amdgcn_readfirstlane(jv);
-            int spins = 0;
-            while (__hip_atomic_load(s_pub, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= j) {
-                __builtin_amdgcn_s_sleep(1);
-                if (++spins > (1 << 22)) {
-                    timed_out = true;
-                    break;
+            if (j == own - CPW)
+                __builtin_amdgcn_s_setprio(2);
+            if (!ahead) {
+                int spins = 0;
+                while ((have = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                            s_pub, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP))) <= j) {
+                    if (j < own - CPW)
+                        __builtin_amdgcn_s_sleep(1);
+                    if (++spins > (1 << 22)) {
+                        timed_out = true;
+                        break;
+                    }
                 }
+                uv = *(const float4 *)&ubuf[j][rlo];
+                kv = s_kap[j];
             }
-            const float4 uv = *(const float4 *)&ubuf[j][rlo];
+            ahead = j + 1 < own && j + 1 < have;
+            if (ahead) {
+                un = *(const float4 *)&ubuf[j + 1][rlo];
+                kn = s_kap[j + 1];
+            }
             const float u[RPL] = {uv.x, uv.y, uv.z, uv.w};
-            apply(u, s_kap[j], 0);
+            apply(std::integral_constant<int, 0>{}, u, kv, [] {});
+            uv = un;
+            kv = kn;
         }
+        __builtin_amdgcn_s_setprio(3);
         // this wave's reflections
-#pragma unroll
-        for (int cj = 0; cj < CPW; ++cj) {
+        auto reflection = [&](auto cjc) {
+            constexpr int cj = decltype(cjc)::value;
             const int j = own + cj;
             if (j >= nc)
-                break;
+                return;
             float o[RPL], s4 = 0.0f;
 #pragma unroll
             for (int i = 0; i < RPL; ++i) {
@@ -756,10 +784,15 @@ __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t
                                                                       j >> 2));
             float u0 = 0.0f, kap = 0.0f, beta = 0.0f;   // a zero column needs no reflection
             if (ss >= 0x1p-96f && ss <= 0x1p96f) {
-                const float nrm = sqrtf(ss);
+                // sqrt and 1 / x by one Newton step from the hardware's estimates
+                // (within one ulp): well inside the normal range here, and a
+                // third of the chain of the library's
+                const float y = __builtin_amdgcn_rsqf(ss), g = ss * y;
+                const float nrm = fmaf(0.5f * y, fmaf(-g, g, ss), g);
                 beta = x0 >= 0.0f ? -nrm : nrm;
                 u0 = x0 - beta;
-                kap = 1.0f / (beta * (beta - x0));
+                const float q = -beta * u0, r = __builtin_amdgcn_rcpf(q);
+                kap = fmaf(r, fmaf(-q, r, 1.0f), r);
             } else {
                 double sd = 0.0;
 #pragma unroll
@@ -781,9 +814,21 @@ __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t
                 s_kap[j] = kap;
                 s_beta[j] = beta;
             }
-            __hip_atomic_store(s_pub, j + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            apply(o, kap, cj + 1);
-        }
+            // published once the sums are under way: the stores have then landed
+            apply(std::integral_constant<int, cj + 1>{}, o, kap, [&] {
+                __hip_atomic_store(s_pub, j + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            });
+        };
+        static_assert(CPW == 8, "one call per column");
+        reflection(std::integral_constant<int, 0>{});
+        reflection(std::integral_constant<int, 1>{});
+        reflection(std::integral_constant<int, 2>{});
+        reflection(std::integral_constant<int, 3>{});
+        reflection(std::integral_constant<int, 4>{});
+        reflection(std::integral_constant<int, 5>{});
+        reflection(std::integral_constant<int, 6>{});
+        reflection(std::integral_constant<int, 7>{});
+        __builtin_amdgcn_s_setprio(0);
     }
     __syncthreads();
     if (timed_out)
