@@ -198,11 +198,51 @@ __device__ __forceinline__ void direct_step(const float (&va)[FM][8], const floa
     }
 }
 
+// A T x T tile of values (LDS, row stride T + 1) as part of a packed operand of
+// R rows and K k: rows r0 .. and k0 .. of it (trans: the tile's columns are the
+// rows).  A thread takes 8 k of one row, so both terms go out as 16-byte stores,
+// consecutive over the rows.  The last block of k is filled with zeros; rows past
+// R are left, since what they hold reaches only elements that are not stored.
+// pairs: DirectOperand<false, 2>'s order, where row 2 i + b of a block of 64 is
+// index i of block b, and a last row on its own the second of its pair.
+template <int T, int NT>
+__device__ __forceinline__ void direct_pack_out(const float *tile, char *out, int64_t R, int64_t K,
+                                                int64_t r0, int64_t k0, bool trans, bool pairs,
+                                                int prec, float sc)
+{
+    const int64_t kstride = packed_kstride(packed_row_blocks(R));
+    for (int e = threadIdx.x; e < T * T / 8; e += NT) {
+        const int r = e % T, g = e / T;
+        const int64_t row = r0 + r, k = k0 + 8 * g;
+        if (row >= R || k >= ((K + 15) & ~(int64_t)15))
+            continue;
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float x = trans ? tile[(8 * g + j) * (T + 1) + r] : tile[r * (T + 1) + 8 * g + j];
+            v[j] = k + j < K ? x : 0.0f;
+        }
+        u32x4 parts[2];
+        if (prec == PREC_F16X3)
+            Split<PREC_F16X3>::run(v, parts, sc);
+        else
+            Split<PREC_BF16X3>::run(v, parts);
+        const int64_t q = pairs ? (row & ~(int64_t)63) + 32 * ((row & 1) | (row == R - 1)) +
+                                      ((row & 63) >> 1)
+                                : row;
+        auto *o = (__attribute__((address_space(1))) char *)(out + (k >> 4) * kstride +
+                                                              ((q >> 5) << 11)) +
+                  ((int)(q & 31) + 32 * (int)((k >> 3) & 1)) * 16;
+        *(__attribute__((address_space(1))) u32x4 *)o = parts[0];
+        *(__attribute__((address_space(1))) u32x4 *)(o + 1024) = parts[1];
+    }
+}
+
 // Sum of the waves' partial tiles in LDS (a fixed order, so reproducible), then
 // this wave's share of the elements through the common epilogue: out = alpha
 // acc + beta E + gamma I, mirrored for a full Gram, with the FP64 sum of
-// (out - E)^2.
-template <class OA, class OB, int FM, int FN, int KW>
+// (out - E)^2, and the packed copies of out.
+template <int PREC, class OA, class OB, int FM, int FN, int KW>
 __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)[FM][FN],
                                                 int64_t row0, int64_t col0, int tm, int tn, int w,
                                                 int lane, int stop, float *red, double *red8)
@@ -249,6 +289,11 @@ __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)
     }
     if (d.E)
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    constexpr int T = 32 * FM;
+    static_assert(FM == FN && T * (T + 1) <= HW * NE * 64, "the tile fits the sums' space");
+    const bool pack = Cfg<PREC>::terms == 2 && (d.pack_row || d.pack_col);
+    if (pack)
+        __syncthreads();   // every wave has read its sums
 #pragma unroll
     for (int q = 0; q < EPW; ++q) {
         const int64_t row = rows[q], col = cols[q];
@@ -262,9 +307,17 @@ __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)
         }
         if (row == col)
             val = val + d.gamma;
-        gmem(d.C)[row * d.ldc + col] = val;
-        if (d.gram && !d.gram_upper && row != col)
-            gmem(d.C)[col * d.ldc + row] = val;
+        if (d.C) {
+            gmem(d.C)[row * d.ldc + col] = val;
+            if (d.gram && !d.gram_upper && row != col)
+                gmem(d.C)[col * d.ldc + row] = val;
+        }
+        if (pack) {
+            const int lr = (int)(row - row0), lc = (int)(col - col0);
+            red[lr * (T + 1) + lc] = val;
+            if (d.gram && tm == tn)
+                red[lc * (T + 1) + lr] = val;
+        }
         if (want_ss) {
             const double df = (double)val - (double)evv;
             ss += df * df;
@@ -283,6 +336,21 @@ __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)
                 s += red8[k];
             gmem(d.partials)[(int64_t)tm * d.tiles_n + tn] = s;
         }
+    }
+    if constexpr (Cfg<PREC>::terms == 2) {
+        if (!pack)
+            return;
+        __syncthreads();
+        const bool pairs = d.pack_pairs;
+        if (d.pack_row)
+            direct_pack_out<T, KW * 64>(red, d.pack_row, d.M, d.N, row0, col0, false, pairs,
+                                        d.pack_prec, d.pack_scale);
+        if (d.gram && tm != tn)
+            direct_pack_out<T, KW * 64>(red, d.pack_row, d.M, d.N, col0, row0, true, pairs,
+                                        d.pack_prec, d.pack_scale);
+        if (d.pack_col)
+            direct_pack_out<T, KW * 64>(red, d.pack_col, d.N, d.M, col0, row0, true, false,
+                                        d.pack_prec, d.pack_scale);
     }
 }
 
@@ -346,7 +414,7 @@ __device__ __forceinline__ void direct_tile(const GemmDesc &d, int tm, int tn, i
     for (int s = 0; s < D - 1; ++s)
         if (i + s < cnt)
             direct_step<PREC, FM, FN>(va[s], vb[s], d.scale_a, d.scale_b, acc);
-    direct_epilogue<DirectOperand<AKC, FM>, DirectOperand<BKC, FN>, FM, FN, KW>(
+    direct_epilogue<PREC, DirectOperand<AKC, FM>, DirectOperand<BKC, FN>, FM, FN, KW>(
         d, acc, row0, col0, tm, tn, w, lane, stop, red, red8);
 }
 
@@ -396,22 +464,26 @@ __global__ void __launch_bounds__(DirectCfg<CLS>::KW * 64, DirectCfg<CLS>::WPE)
     direct_tile<PREC, AKC, BKC, CLS>(d, tm, tn, 0, d.K, red, red8);
 }
 
-// Packed operands, for la_gemm_packed's small shapes: every element is the
-// same sums in the same order as gemm_direct_kernel's (a partial step first,
-// the waves' steps interleaved).
-template <int PREC, int CLS>
-__global__ void __launch_bounds__(DirectCfg<CLS>::KW * 64, DirectCfg<CLS>::WPE)
-    gemm_direct_packed_kernel(GemmDesc d)
+// Packed operands, for la_gemm_packed's small shapes and for iterations whose
+// products write their results packed for the next (pack_row, pack_col): every
+// element is the same sums in the same order as gemm_direct_kernel's (a partial
+// step first, the waves' steps interleaved), and with PAIRS its place in the wave
+// too.  The unpacked kernel spends most of a step splitting operand values that
+// every tile in their row or column splits again; here a step is its loads and
+// MFMAs (3xBF16, n^3 in one graph: 256 4.5 -> 3.5 us, 512 6.3 -> 4.3, 1000 19.4
+// -> 11.6, 1600 60 -> 35).  Inside an iteration the operands come from the other
+// XCDs' writes and the launch is bound by fetching them: two, three and four
+// steps in flight measured the same (polar 1000^2 856, 861, 858 us).
+template <int PREC, int CLS, bool PAIRS>
+__device__ __forceinline__ void direct_packed_tile(const GemmDesc &d, int tm, int tn, float *red,
+                                                   double *red8)
 {
     using G = DirectCfg<CLS>;
     constexpr int FM = G::FM, FN = G::FN, KW = G::KW, D = 2;
-    __shared__ float red[direct_red_floats<CLS>()];
-    __shared__ double red8[DirectCfg<CLS>::KW];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int tm, tn;
-    tile_coords(d, xcd_remap(blockIdx.x, d.num_tiles), tm, tn);
     const int64_t row0 = (int64_t)tm * (32 * FM), col0 = (int64_t)tn * (32 * FN);
+    const int stop = d.stop ? *gmem(d.stop) : 0;
     DirectPacked<FM> oa;
     DirectPacked<FN> ob;
     oa.init(d.A, packed_row_blocks(d.M), row0, lane);
@@ -448,10 +520,43 @@ __global__ void __launch_bounds__(DirectCfg<CLS>::KW * 64, DirectCfg<CLS>::WPE)
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    if (i < cnt)
-        direct_mfma<PREC, FM, FN>(a[0], b[0], acc);
-    direct_epilogue<DirectOperand<true, FM>, DirectOperand<true, FN>, FM, FN, KW>(
-        d, acc, row0, col0, tm, tn, w, lane, 0, red, red8);
+#pragma unroll
+    for (int s = 0; s < D - 1; ++s)
+        if (i + s < cnt)
+            direct_mfma<PREC, FM, FN>(a[s], b[s], acc);
+    direct_epilogue<PREC, DirectOperand<true, FM>, DirectOperand<!PAIRS, FN>, FM, FN, KW>(
+        d, acc, row0, col0, tm, tn, w, lane, stop, red, red8);
+}
+
+template <int PREC, int CLS, bool PAIRS>
+__global__ void __launch_bounds__(DirectCfg<CLS>::KW * 64, DirectCfg<CLS>::WPE)
+    gemm_direct_packed_kernel(GemmDesc d)
+{
+    __shared__ float red[direct_red_floats<CLS>()];
+    __shared__ double red8[DirectCfg<CLS>::KW];
+    int tm, tn;
+    tile_coords(d, xcd_remap(blockIdx.x, d.num_tiles), tm, tn);
+    direct_packed_tile<PREC, CLS, PAIRS>(d, tm, tn, red, red8);
+}
+
+// The same for the items of a grouped launch (one workgroup per item).
+template <int PREC, int CLS, bool PAIRS>
+__global__ void __launch_bounds__(DirectCfg<CLS>::KW * 64, DirectCfg<CLS>::WPE)
+    gemm_direct_packed_items_kernel(const GemmDesc *__restrict__ probs,
+                                    const GroupItem *__restrict__ items, int num_items)
+{
+    __shared__ float red[direct_red_floats<CLS>()];
+    __shared__ double red8[DirectCfg<CLS>::KW];
+    const int it = blockIdx.x;
+    if (it >= num_items)
+        return;
+    const GroupItem gi = items[it];
+    if (gi.prob < 0)
+        return;   // empty item
+    const GemmDesc d = probs[gi.prob];
+    int tm, tn;
+    tile_coords(d, gi.tile, tm, tn);
+    direct_packed_tile<PREC, CLS, PAIRS>(d, tm, tn, red, red8);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -523,22 +628,54 @@ hipError_t launch_grouped_any(int akc, int bkc, int small, const GemmDesc *probs
     return launch_grouped_t<PREC>(akc, bkc, small, probs, items, num_items, s);
 }
 
+template <int PREC, int CLS> hipError_t launch_direct_packed(const GemmDesc &d, hipStream_t s)
+{
+    const dim3 grid(d.num_tiles), block(DirectCfg<CLS>::KW * 64);
+    if (d.b_pairs)
+        hipLaunchKernelGGL((gemm_direct_packed_kernel<PREC, CLS, true>), grid, block, 0, s, d);
+    else
+        hipLaunchKernelGGL((gemm_direct_packed_kernel<PREC, CLS, false>), grid, block, 0, s, d);
+    return hipGetLastError();
+}
+
 // Packed operands on the tile class of d.
 template <int PREC>
 hipError_t launch_packed_any(const GemmDesc &d, hipStream_t s)
 {
     if (d.num_tiles <= 0)
         return hipSuccess;
-    const dim3 grid(d.num_tiles);
     if (d.small == kClassDirect64)
-        hipLaunchKernelGGL((gemm_direct_packed_kernel<PREC, kClassDirect64>), grid,
-                           dim3(DirectCfg<kClassDirect64>::KW * 64), 0, s, d);
-    else if (d.small == kClassDirect32)
-        hipLaunchKernelGGL((gemm_direct_packed_kernel<PREC, kClassDirect32>), grid,
-                           dim3(DirectCfg<kClassDirect32>::KW * 64), 0, s, d);
+        return launch_direct_packed<PREC, kClassDirect64>(d, s);
+    if (d.small == kClassDirect32)
+        return launch_direct_packed<PREC, kClassDirect32>(d, s);
+    return launch_packed_x3<PREC>(d, s);
+}
+
+template <int PREC, int CLS>
+hipError_t launch_direct_packed_items(int pairs, const GemmDesc *probs, const GroupItem *items,
+                                      int num_items, hipStream_t s)
+{
+    const dim3 grid(num_items), block(DirectCfg<CLS>::KW * 64);
+    if (pairs)
+        hipLaunchKernelGGL((gemm_direct_packed_items_kernel<PREC, CLS, true>), grid, block, 0, s,
+                           probs, items, num_items);
     else
-        return launch_packed_x3<PREC>(d, s);
+        hipLaunchKernelGGL((gemm_direct_packed_items_kernel<PREC, CLS, false>), grid, block, 0, s,
+                           probs, items, num_items);
     return hipGetLastError();
+}
+
+template <int PREC>
+hipError_t launch_grouped_packed(int pairs, int cls, const GemmDesc *probs, const GroupItem *items,
+                                 int num_items, hipStream_t s)
+{
+    if (num_items <= 0)
+        return hipSuccess;
+    if (cls == kClassDirect64)
+        return launch_direct_packed_items<PREC, kClassDirect64>(pairs, probs, items, num_items, s);
+    if (cls == kClassDirect32)
+        return launch_direct_packed_items<PREC, kClassDirect32>(pairs, probs, items, num_items, s);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace dev

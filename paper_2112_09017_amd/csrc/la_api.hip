@@ -163,6 +163,7 @@ struct PolarWs {
     double *sumsq;   // norm partials
     double *scal;    // [0] ||A||_F^2, [1] ||U' - U||_F^2
     char *pk;        // packed 3xBF16 copies of U and P for the update (may be null)
+    PolarChain chain;   // where col is not null
     size_t parts_floats;
 };
 
@@ -331,7 +332,68 @@ size_t polar_workspace_bytes(const PolarPlan &p)
     return b;
 }
 
-static PolarWs carve(const PolarPlan &p, void *ws, bool room)
+// Smallest n of a polar on packed copies: below, writing them costs what reading
+// them saves (polar of n^2 without / with them: 256 358 / 365 us, 384 430 / 396,
+// 700 756 / 648, 1000 1104 / 857, 1600 2620 / 1780).  (The server's launches hold
+// many requests and are bound by their operands at any n.)
+constexpr int64_t kChainMinN = 320;
+
+// The shape of the update X P, X with leading dimension ldx (the tile class of the
+// two-term arithmetics is the same).
+static GemmDesc chain_update_desc(const PolarPlan &p, int64_t ldx, int prec)
+{
+    GemmDesc d;
+    memset(&d, 0, sizeof d);
+    d.lda = ldx;
+    d.a_kcontig = 1;
+    d.ldb = p.n;
+    d.M = p.m;
+    d.N = p.n;
+    d.K = p.n;
+    gemm_finalize(d, prec);
+    return d;
+}
+
+size_t polar_chain_bytes(const PolarPlan &p, int64_t ldx, bool served)
+{
+    if (!two_term(p.prec_pre) || !two_term(p.prec_ns))
+        return 0;
+    if (!served && (p.n < kChainMinN || update_splits(p) > 1))
+        return 0;
+    for (int64_t ld : {p.n, ldx})
+        for (int pr : {p.prec_pre, p.prec_ns}) {
+            if (!served && gram_splits(p.m, p.n, pr, p.max_acc) > 1)
+                return 0;
+            GemmDesc d = chain_update_desc(p, ld, pr);
+            if (!is_direct(d.small))
+                return 0;
+            d.a_kcontig = 0;
+            d.ldb = ld;
+            d.M = p.n;
+            d.K = p.m;
+            d.gram = 1;
+            gemm_finalize(d, pr);
+            if (!is_direct(d.small))
+                return 0;
+        }
+    return 2 * align_up256(packed_x3_bytes(p.m, p.n)) + align_up256(packed_x3_bytes(p.n, p.m)) +
+           align_up256(packed_x3_bytes(p.n, p.n));
+}
+
+PolarChain polar_chain_carve(const PolarPlan &p, char *base)
+{
+    PolarChain c;
+    const size_t row = align_up256(packed_x3_bytes(p.m, p.n));
+    c.row[0] = base;
+    c.row[1] = base + row;
+    c.col = base + 2 * row;
+    c.P = c.col + align_up256(packed_x3_bytes(p.n, p.m));
+    const GemmDesc d = chain_update_desc(p, p.n, p.prec_ns);
+    c.pairs = d.small == kClassDirect64;
+    return c;
+}
+
+static PolarWs carve(const PolarPlan &p, void *ws, bool room, bool chain)
 {
     PolarWs w;
     char *b = (char *)ws;
@@ -349,6 +411,11 @@ static PolarWs carve(const PolarPlan &p, void *ws, bool room)
     w.scal = (double *)b;
     b += align256(8 * sizeof(double));
     w.pk = packed_update_bytes(p) || (room && packed_small_bytes(p)) ? b : nullptr;
+    memset(&w.chain, 0, sizeof w.chain);
+    if (chain) {
+        w.chain = polar_chain_carve(p, b);
+        w.pk = nullptr;
+    }
     return w;
 }
 
@@ -405,9 +472,10 @@ static hipError_t gram_slices(int prec, const float *X1, int64_t ld1, float sc1,
 }
 
 // P <- alpha X^T X + gamma I (exactly symmetric), X m x n with leading dim ldx.
+// chained: X's packed columns are there, and P is written packed too.
 static hipError_t gram_step(const PolarPlan &p, int prec, const float *X, int64_t ldx,
                             double alpha, double gamma, float *P, const PolarWs &w,
-                            hipStream_t s)
+                            hipStream_t s, bool chained = false)
 {
     const int64_t m = p.m, n = p.n;
     const int splits = gram_splits(m, n, prec, p.max_acc);
@@ -430,6 +498,15 @@ static hipError_t gram_step(const PolarPlan &p, int prec, const float *X, int64_
         d.gamma = (float)gamma;
         gemm_f16_scales(d, prec, kIterScale, kIterScale);
         gemm_finalize(d, prec);
+        if (chained) {
+            d.A = d.B = (const float *)w.chain.col;
+            d.C = nullptr;   // only the update reads P
+            d.pack_row = w.chain.P;
+            d.pack_prec = prec;
+            d.pack_scale = kIterScale;
+            d.pack_pairs = w.chain.pairs;
+            return launch_gemm_packed(prec, d, s);
+        }
         return gram_packed_or_plain(prec, d, w.pk, s);
     }
     // the slices run in one launch; slice y sums k in [y ks, (y + 1) ks) into
@@ -443,12 +520,20 @@ static hipError_t gram_step(const PolarPlan &p, int prec, const float *X, int64_
     return launch_splitk_sym_reduce(w.parts, n * n, count, n, alpha, gamma, P, n, s);
 }
 
+// A chained update: whether X and P are there packed (X in buffer cur), and the
+// arithmetic that the next step reads Xn in.
+struct ChainStep {
+    bool packed;
+    int cur, next_prec;
+    bool only;   // nothing but the next step's products reads Xn
+};
+
 // Xn <- alpha X P + beta X (partials of (Xn - X)^2 in tiles if tiles != null;
 // *ntiles receives their count).
 static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int64_t ldx,
                               const float *P, double alpha, double beta, float *Xn, int64_t ldxn,
                               double *tiles, int *ntiles, const PolarWs &w, hipStream_t s,
-                              const int *stop = nullptr)
+                              const int *stop = nullptr, const ChainStep *cs = nullptr)
 {
     const int64_t m = p.m, n = p.n;
     GemmDesc d;
@@ -492,7 +577,21 @@ static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int6
     d.stop = stop;
     gemm_f16_scales(d, prec, kIterScale, kIterScale);
     gemm_finalize(d, prec);
-    const hipError_t e = gemm_packed_or_plain(prec, d, w.pk, s);
+    if (cs) {
+        d.pack_row = w.chain.row[cs->cur ^ 1];
+        d.pack_col = w.chain.col;
+        d.pack_prec = cs->next_prec;
+        d.pack_scale = kIterScale;
+        if (cs->only)
+            d.C = nullptr;
+        if (cs->packed) {
+            d.A = (const float *)w.chain.row[cs->cur];
+            d.B = (const float *)w.chain.P;
+            d.b_pairs = 1;
+        }
+    }
+    const hipError_t e = cs && cs->packed ? launch_gemm_packed(prec, d, s)
+                                          : gemm_packed_or_plain(prec, d, w.pk, s);
     if (ntiles)
         *ntiles = d.tiles_m * d.tiles_n;
     return e;
@@ -1129,7 +1228,8 @@ size_t la_polar_workspace_size(int64_t m, int64_t n, const la_polar_opts *opts)
     PolarPlan p;
     if (polar_plan(m, n, opts, &p) != LA_OK)
         return 0;
-    return polar_workspace_bytes(p) + packed_small_bytes(p);
+    return polar_workspace_bytes(p) +
+           std::max(packed_small_bytes(p), polar_chain_bytes(p, p.n));
 }
 
 }  // extern "C"
@@ -1217,10 +1317,14 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
     LA_HIP(hipSetDevice(ctx->device), "la_polar: hipSetDevice");
     hipStream_t s = (hipStream_t)hip_stream;
     // the optional region after the required one is used only where it is free
-    const size_t full = need + packed_small_bytes(p);
-    const bool room = ws_bytes >= full && !overlaps(workspace, full, A, ab) &&
-                      !overlaps(workspace, full, U, ub) && !overlaps(workspace, full, H, hb);
-    PolarWs w = carve(p, workspace, room);
+    auto room = [&](size_t extra) {
+        const size_t full = need + extra;
+        return ws_bytes >= full && !overlaps(workspace, full, A, ab) &&
+               !overlaps(workspace, full, U, ub) && !overlaps(workspace, full, H, hb);
+    };
+    const size_t chain_bytes = polar_chain_bytes(p, ldu);
+    const bool chain = chain_bytes && room(chain_bytes);
+    PolarWs w = carve(p, workspace, room(packed_small_bytes(p)), chain);
 
     la_polar_info inf;
     memset(&inf, 0, sizeof inf);
@@ -1269,15 +1373,24 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
     }
 
     // preconditioning: U <- a U (I - c U^T U), c = (4/27) a^2
+    // (chained from the second step on: X0 is not there packed)
+    ChainStep cs{false, 0, 0, false};
+    const ChainStep *csp = chain ? &cs : nullptr;
     for (int i = 0; i < p.k_pre; ++i) {
-        LA_HIP(gram_step(p, p.prec_pre, buf[cur], ld[cur], -p.c, 1.0, w.P, w, s),
+        cs.cur = cur;
+        cs.only = i + 1 < p.k_pre;
+        cs.next_prec = cs.only ? p.prec_pre : p.prec_ns;
+        LA_HIP(gram_step(p, p.prec_pre, buf[cur], ld[cur], -p.c, 1.0, w.P, w, s, cs.packed),
                "la_polar: precondition gram");
         LA_HIP(update_step(p, p.prec_pre, buf[cur], ld[cur], w.P, p.a, 0.0, buf[cur ^ 1],
-                           ld[cur ^ 1], nullptr, nullptr, w, s, dev_stop),
+                           ld[cur ^ 1], nullptr, nullptr, w, s, dev_stop, csp),
                "la_polar: precondition update");
+        cs.packed = chain;
         cur ^= 1;
         inf.iters_precond++;
     }
+    cs.next_prec = p.prec_ns;
+    cs.only = false;
 
     // Newton-Schulz: U' = U + U (I - U^T U) / 2, delta = ||U' - U||_F, until the
     // stop test (polar_host.h); a polish step runs at BF16X6
@@ -1298,11 +1411,14 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
         do {
             for (const int to = std::min(queued + batch, p.max_iter); queued < to; ++queued) {
                 int ntiles = 0;
-                LA_HIP(gram_step(p, p.prec_ns, buf[cur], ld[cur], -1.0, 1.0, w.P, w, s),
+                cs.cur = cur;
+                LA_HIP(gram_step(p, p.prec_ns, buf[cur], ld[cur], -1.0, 1.0, w.P, w, s,
+                                 cs.packed),
                        "la_polar: NS gram");
                 LA_HIP(update_step(p, p.prec_ns, buf[cur], ld[cur], w.P, 0.5, 1.0, buf[cur ^ 1],
-                                   ld[cur ^ 1], w.tiles, &ntiles, w, s, dev_stop),
+                                   ld[cur ^ 1], w.tiles, &ntiles, w, s, dev_stop, csp),
                        "la_polar: NS update");
+                cs.packed = chain;
                 LA_HIP(launch_step_state(w.tiles, ntiles, st, t, s), "la_polar: delta");
                 cur ^= 1;
             }
@@ -1328,11 +1444,14 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
     while (!ahead) {
         const int prec = stop.stopped ? PREC_BF16X6 : p.prec_ns;
         int ntiles = 0;
-        LA_HIP(gram_step(p, prec, buf[cur], ld[cur], -1.0, 1.0, w.P, w, s),
+        const bool last = stop.stopped;   // the polish step, from FP32
+        cs.cur = cur;
+        LA_HIP(gram_step(p, prec, buf[cur], ld[cur], -1.0, 1.0, w.P, w, s, cs.packed && !last),
                "la_polar: NS gram");
         LA_HIP(update_step(p, prec, buf[cur], ld[cur], w.P, 0.5, 1.0, buf[cur ^ 1], ld[cur ^ 1],
-                           w.tiles, &ntiles, w, s),
+                           w.tiles, &ntiles, w, s, nullptr, last ? nullptr : csp),
                "la_polar: NS update");
+        cs.packed = chain;
         LA_HIP(launch_reduce_fixed(w.tiles, ntiles, w.scal + 1, s), "la_polar: delta");
         LA_HIP(hipMemcpyAsync(h2 + 1, w.scal + 1, sizeof(double), hipMemcpyDeviceToHost, s),
                "la_polar: readback");

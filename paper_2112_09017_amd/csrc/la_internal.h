@@ -60,8 +60,17 @@ struct GemmDesc {
     int slices;
     int64_t slice_k, slice_stride;
     // direct classes: optional device word; while it is not 0 the launch leaves
-    // its output as it is (a step queued past the iteration's stop)
+    // its outputs as they are (a step queued past the iteration's stop)
     const int *stop;
+    // direct classes, two-term precisions: the output is also (or, with C null, only)
+    // written as packed operands of arithmetic pack_prec (factor pack_scale): pack_row with the
+    // output's rows as rows and its columns as k, pack_col the other way round
+    // (either may be null; a Gram's are one matrix: pack_row only).  pack_pairs:
+    // rows in the order the 64 x 64 class gives a row-contiguous operand.
+    char *pack_row, *pack_col;
+    float pack_scale;
+    int pack_prec, pack_pairs;
+    int b_pairs;       // packed operands: op(B)'s rows are in that order
 };
 
 // Tile classes.  Large (256 x 256) and small (128 x 128) tiles (gemm_tile.h) use
@@ -119,6 +128,10 @@ struct GroupItem {
 hipError_t launch_gemm_grouped(int prec, int a_kcontig, int b_kcontig, int cls,
                                const GemmDesc *probs_dev,
                                const GroupItem *items_dev, int num_items, hipStream_t s);
+// The same on packed operands: two-term precisions, direct classes; b_pairs is
+// every problem's.
+hipError_t launch_gemm_grouped_packed(int prec, int b_pairs, int cls, const GemmDesc *probs_dev,
+                                      const GroupItem *items_dev, int num_items, hipStream_t s);
 
 // Packed operands of two 16-bit terms (gemm_x3.hip: 3xBF16, gemm_f16x3.hip:
 // F16X3, whose entries are multiplied by sc before the split, or, with rmax, each
@@ -228,6 +241,25 @@ hipError_t launch_reduce_grouped(const ReduceItem *items_dev, int n, hipStream_t
 int gram_splits(int64_t m, int64_t n, int prec, int64_t max_acc);
 int acc_splits(int64_t K, int64_t max_acc);
 size_t polar_workspace_bytes(const PolarPlan &p);
+
+// Packed copies that the products of a polar iteration on the direct classes
+// hand on: each writes its result both as FP32 and split into the terms that the
+// next product reads (X_i as rows for the update, as columns for the Gram, P_i for
+// the update), so no operand is split again by every tile that reads it.  Every
+// product is the same bits as on FP32 operands (and its partial sums too), so a
+// caller without room for them runs unpacked with the same result.
+struct PolarChain {
+    char *row[2];   // X (m x n) with its rows as rows, for X in either buffer
+    char *col;      // X with its columns as rows
+    char *P;        // P (n x n)
+    int pairs;      // P's rows in pair order: the update is of the 64 x 64 class
+};
+// Bytes of a chain for p, 0 where its products don't take one: a product that is
+// not two-term or not of a direct class (X with leading dimension ldx in the
+// first buffer and n in the other), or, for la_polar, a split update, a split Gram
+// or n < kChainMinN.  served: the server's rule.
+size_t polar_chain_bytes(const PolarPlan &p, int64_t ldx, bool served = false);
+PolarChain polar_chain_carve(const PolarPlan &p, char *base);
 
 
 // Argument helpers shared by the ABI entry points (la_api.hip).

@@ -66,13 +66,21 @@ constexpr int kMaxSlots = 4096;
 // from larger ones.
 constexpr int kMaxBands = 2;
 constexpr double kBandWork = 2048.0 * 2048.0 * 2048.0;
-// launch groups of one staging pass: 4 product arithmetics x 4 tile classes x 2
-// phases, each with its descriptors and its items padded to kAlign
-constexpr int kMaxGroups = 32;
+// launch groups of one staging pass: 2 phases x (4 product arithmetics x 4 tile
+// classes, and the 2 two-term ones x 2 direct classes on packed operands), each with
+// its descriptors and its items padded to kStageAlign
+constexpr int kMaxGroups = 40;
+constexpr size_t kStageAlign = 128, kStagePad = 8192;
+static_assert(kMaxGroups * kStageAlign <= kStagePad, "padding of one staging pass");
+// A request takes the packed copies of its products' results (PolarChain) if at
+// least this many such requests fit the arena: they double its footprint (twelve
+// requests of 128^2 to 1536^2: 7.1 ms of ticks with them, 8.6 ms without).
+constexpr size_t kChainFit = 16;
 static_assert(2 * kMaxSlots * sizeof(double) <= kRedBytes, "norms of one tick");
 static_assert(2 * sizeof(ReduceItem) <= sizeof(GemmDesc), "reduce items in a descriptor slot");
 
 size_t up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
+size_t up_stage(size_t x) { return (x + kStageAlign - 1) & ~(kStageAlign - 1); }
 
 // Pinned host buffers reused across requests (power-of-two size classes), so a
 // submit does not pay for a pinned allocation once the pool has warmed up.  A
@@ -134,6 +142,8 @@ struct DevReq {
     float *A = nullptr, *X[2] = {nullptr, nullptr}, *P = nullptr;
     double *tiles = nullptr, *sumsq = nullptr, *scal = nullptr;
     int cur = 0;
+    PolarChain chain = {};   // where col is not null
+    int packed = 0;          // the arithmetic X[cur] is there packed in, 0: it is not
     float *io = nullptr;    // pinned: A on submit, U on completion (m n floats)
     float *hh = nullptr;    // pinned: H (n n floats)
     size_t io_cls = 0, hh_cls = 0;
@@ -150,6 +160,7 @@ size_t max_tiles(int64_t m, int64_t n)
 
 struct Launch {
     int prec, akc, bkc, cls;
+    bool packed;   // op(B) is in pair order if akc
     std::vector<GemmDesc> probs;
     std::vector<GroupItem> items;
 };
@@ -166,14 +177,16 @@ struct Staged {
 // and a launch of a few large-tile problems fills only part of the device.
 constexpr int kSide = 3;
 
-void add_problem(std::vector<Launch> &ls, int prec, int akc, int bkc, const GemmDesc &d)
+void add_problem(std::vector<Launch> &ls, int prec, int akc, int bkc, const GemmDesc &d,
+                 bool packed = false)
 {
     Launch *L = nullptr;
     for (auto &x : ls)
-        if (x.prec == prec && x.akc == akc && x.bkc == bkc && x.cls == d.small)
+        if (x.prec == prec && x.akc == akc && x.bkc == bkc && x.cls == d.small &&
+            x.packed == packed)
             L = &x;
     if (!L) {
-        ls.push_back(Launch{prec, akc, bkc, d.small, {}, {}});
+        ls.push_back(Launch{prec, akc, bkc, d.small, packed, {}, {}});
         L = &ls.back();
     }
     const int pid = (int)L->probs.size();
@@ -259,12 +272,19 @@ struct HipExec {
     // ---- the executor interface of serve_core.h
     bool bind() { return hipSetDevice(device) == hipSuccess; }
     size_t capacity() { return req_bytes; }
-    size_t footprint(const serve::Req &r)
+    static size_t plain_footprint(const serve::Req &r)
     {
         const size_t mn = (size_t)r.m * r.n, nn = (size_t)r.n * r.n;
         return up(mn * 4) * 3 + up(nn * 4) + up(max_tiles(r.m, r.n) * 8) +
                up((size_t)sumsq_num_partials() * 8) + up(8 * 8);
     }
+    // bytes of the request's packed copies, 0 where it goes without
+    size_t chain_bytes(const serve::Req &r) const
+    {
+        const size_t c = polar_chain_bytes(r.plan, r.n, true);
+        return c && (plain_footprint(r) + c) * kChainFit <= req_bytes ? c : 0;
+    }
+    size_t footprint(const serve::Req &r) { return plain_footprint(r) + chain_bytes(r); }
     // descriptors and tile items one tick stages for r: a Gram and an update,
     // at the most demanding precision the request may step at (H, staged after
     // the tick's wait, needs no more: two descriptors and twice the Gram's
@@ -287,9 +307,9 @@ struct HipExec {
         *descs = 3;
         *items = std::max(it, 2 * (size_t)h.num_tiles) + 2 * (kXcds - 1);
     }
-    // each budget keeps room for the kAlign padding of kMaxGroups launches
-    size_t desc_capacity() { return (kDescBytes - kMaxGroups * kAlign) / sizeof(GemmDesc); }
-    size_t item_capacity() { return (kItemBytes - kMaxGroups * kAlign) / sizeof(GroupItem); }
+    // each budget keeps room for the padding of kMaxGroups launches
+    size_t desc_capacity() { return (kDescBytes - kStagePad) / sizeof(GemmDesc); }
+    size_t item_capacity() { return (kItemBytes - kStagePad) / sizeof(GroupItem); }
 
     la_status stage_input(serve::Req &r, const float *A, int64_t lda)
     {
@@ -341,7 +361,12 @@ struct HipExec {
         d->sumsq = (double *)b;
         b += up((size_t)sumsq_num_partials() * 8);
         d->scal = (double *)b;
+        b += up(8 * 8);
         d->cur = 0;
+        d->packed = 0;
+        d->chain = PolarChain{};
+        if (chain_bytes(r))
+            d->chain = polar_chain_carve(r.plan, b);
     }
     void retire(serve::Req &) {}
 
@@ -384,13 +409,14 @@ struct HipExec {
             xcd_order(L);
             const size_t db = L.probs.size() * sizeof(GemmDesc);
             const size_t ib = L.items.size() * sizeof(GroupItem);
-            if (pos + up(db) + ib > kUpBytes)
+            const size_t ip = pos + up_stage(db);
+            if (ip + ib > kUpBytes)
                 return hipErrorOutOfMemory;
             memcpy(h_stage + pos, L.probs.data(), db);
-            memcpy(h_stage + pos + up(db), L.items.data(), ib);
+            memcpy(h_stage + ip, L.items.data(), ib);
             out.push_back(Staged{&L, (const GemmDesc *)(stage_dev + pos),
-                                 (const GroupItem *)(stage_dev + pos + up(db))});
-            pos += up(db) + up(ib);
+                                 (const GroupItem *)(stage_dev + ip)});
+            pos = ip + up_stage(ib);
         }
         return hipSuccess;
     }
@@ -418,8 +444,10 @@ struct HipExec {
         for (size_t i = 0; i < st.size() && e == hipSuccess; ++i) {
             const Launch &L = *st[i].L;
             hipStream_t s = i == 0 ? stream : side[(i - 1) % kSide];
-            e = launch_gemm_grouped(L.prec, L.akc, L.bkc, L.cls, st[i].dd, st[i].di,
-                                    (int)L.items.size(), s);
+            e = L.packed ? launch_gemm_grouped_packed(L.prec, L.akc, L.cls, st[i].dd, st[i].di,
+                                                      (int)L.items.size(), s)
+                         : launch_gemm_grouped(L.prec, L.akc, L.bkc, L.cls, st[i].dd, st[i].di,
+                                               (int)L.items.size(), s);
         }
         for (int k = 0; k < used && e == hipSuccess; ++k) {
             e = hipEventRecord(ev_side[k], side[k]);
@@ -478,7 +506,32 @@ struct HipExec {
                 gemm_set_class(gd, prec, kClassLarge);
             if (all_large && !is_direct(ud.small))
                 gemm_set_class(ud, prec, kClassLarge);
-            add_problem(grams, prec, 0, 0, gd);
+            const bool packed = d->chain.col && d->packed == prec;
+            if (packed) {
+                gd.A = gd.B = (const float *)d->chain.col;
+                gd.C = nullptr;   // only the update reads P
+                gd.pack_row = d->chain.P;
+                gd.pack_prec = prec;
+                gd.pack_scale = kIterScale;
+                gd.pack_pairs = d->chain.pairs;
+                ud.A = (const float *)d->chain.row[d->cur];
+                ud.B = (const float *)d->chain.P;
+                ud.b_pairs = 1;
+            }
+            d->packed = 0;
+            if (d->chain.col && (prec == PREC_BF16X3 || prec == PREC_F16X3)) {
+                // the next step's arithmetic (a polish step reads FP32)
+                const bool more = r->info.iters_precond + 1 < p.k_pre;
+                const int next = more ? p.prec_pre : p.prec_ns;
+                if (more)
+                    ud.C = nullptr;   // only the next step's products read it
+                ud.pack_row = d->chain.row[d->cur ^ 1];
+                ud.pack_col = d->chain.col;
+                ud.pack_prec = next;
+                ud.pack_scale = kIterScale;
+                d->packed = next;
+            }
+            add_problem(grams, prec, 0, 0, gd, packed);
             if (!pre) {
                 ud.beta = 1.0f;
                 ud.E = d->X[d->cur];
@@ -487,7 +540,7 @@ struct HipExec {
                 red.push_back(ReduceItem{d->tiles, (int64_t)ud.tiles_m * ud.tiles_n,
                                          dev_d + red.size()});
             }
-            add_problem(updates, prec, 1, 0, ud);
+            add_problem(updates, prec, 1, 0, ud, packed);
         }
         size_t pos = 0;
         std::vector<Staged> sg, su;
