@@ -22,9 +22,6 @@ hipError_t launch_pack_f16(const float *, int64_t, int, int64_t, int64_t, float,
                            void *, hipStream_t);
 hipError_t launch_gemm_packed_x3(const GemmDesc &d, hipStream_t s);
 hipError_t launch_gemm_packed_f16(const GemmDesc &d, hipStream_t s);
-hipError_t launch_grouped_packed_x3(int, int, const GemmDesc *, const GroupItem *, int, hipStream_t);
-hipError_t launch_grouped_packed_f16(int, int, const GemmDesc *, const GroupItem *, int,
-                                     hipStream_t);
 hipError_t launch_grouped_fp32(int, int, int, const GemmDesc *, const GroupItem *, int,
                                hipStream_t);
 hipError_t launch_grouped_x3(int, int, int, const GemmDesc *, const GroupItem *, int,
@@ -191,16 +188,6 @@ hipError_t launch_gemm_grouped(int prec, int akc, int bkc, int cls, const GemmDe
         return launch_grouped_x6(akc, bkc, cls, probs, items, num_items, s);
     case PREC_F16X3:
         return launch_grouped_f16(akc, bkc, cls, probs, items, num_items, s);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_gemm_grouped_packed(int prec, int b_pairs, int cls, const GemmDesc *probs,
-                                      const GroupItem *items, int num_items, hipStream_t s)
-{
-    switch (prec) {
-    case PREC_BF16X3: return launch_grouped_packed_x3(b_pairs, cls, probs, items, num_items, s);
-    case PREC_F16X3: return launch_grouped_packed_f16(b_pairs, cls, probs, items, num_items, s);
     default: return hipErrorInvalidValue;
     }
 }

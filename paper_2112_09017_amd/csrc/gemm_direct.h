@@ -241,44 +241,55 @@ __device__ __forceinline__ void direct_pack_out(const float *tile, char *out, in
 // Sum of the waves' partial tiles in LDS (a fixed order, so reproducible), then
 // this wave's share of the elements through the common epilogue: out = alpha
 // acc + beta E + gamma I, mirrored for a full Gram, with the FP64 sum of
-// (out - E)^2, and the packed copies of out.
-template <int PREC, class OA, class OB, int FM, int FN, int KW>
-__device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)[FM][FN],
+// (out - E)^2, and the packed copies of out.  A workgroup has KW / V waves, each
+// in the place of V of the KW (w, w + KW / V, ...: acc[v] and the elements of each).
+template <int PREC, class OA, class OB, int FM, int FN, int KW, int V>
+__device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)[V][FM][FN],
                                                 int64_t row0, int64_t col0, int tm, int tn, int w,
                                                 int lane, int stop, float *red, double *red8)
 {
-    constexpr int NE = FM * FN * 16, EPW = NE / KW, HW = KW / 2;
+    constexpr int NE = FM * FN * 16, EPT = NE / KW, EPW = EPT * V, HW = KW / 2, PW = KW / V;
+    static_assert(V == 1 || PW == HW, "a wave is one of the KW or a pair of them");
     auto at = [&](int v, int el) -> float & { return red[(v * NE + el) * 64 + lane]; };
-    // wave w < HW takes in wave w + HW's sums, then those are added in order:
+    // element q of this thread, of the place w + PW (q / EPT)
+    auto element = [&](int q) { return (w + PW * (q / EPT)) * EPT + q % EPT; };
+    // place w < HW takes in place w + HW's sums, then those are added in order:
     // half the LDS of KW partial tiles
-    if (w >= HW)
+    if constexpr (V == 1) {
+        if (w >= HW)
+#pragma unroll
+            for (int el = 0; el < NE; ++el)
+                at(w - HW, el) = acc[0][el / (16 * FN)][el / 16 % FN][el % 16];
+        __syncthreads();
+        if (w < HW)
+#pragma unroll
+            for (int el = 0; el < NE; ++el)
+                at(w, el) = acc[0][el / (16 * FN)][el / 16 % FN][el % 16] + at(w, el);
+    } else {
 #pragma unroll
         for (int el = 0; el < NE; ++el)
-            at(w - HW, el) = acc[el / (16 * FN)][el / 16 % FN][el % 16];
-    __syncthreads();
-    if (w < HW)
-#pragma unroll
-        for (int el = 0; el < NE; ++el)
-            at(w, el) = acc[el / (16 * FN)][el / 16 % FN][el % 16] + at(w, el);
+            at(w, el) = acc[0][el / (16 * FN)][el / 16 % FN][el % 16] +
+                        acc[V - 1][el / (16 * FN)][el / 16 % FN][el % 16];
+    }
     __syncthreads();
     float out[EPW];
 #pragma unroll
     for (int q = 0; q < EPW; ++q) {
-        float s = at(0, w * EPW + q);
+        float s = at(0, element(q));
 #pragma unroll
         for (int v = 1; v < HW; ++v)
-            s += at(v, w * EPW + q);
+            s += at(v, element(q));
         out[q] = s;
     }
     if (stop)
         return;   // uniform over the launch
     const bool want_ss = d.partials != nullptr;
-    double ss = 0.0;
+    double ss[V] = {};
     float ev[EPW];
     int64_t rows[EPW], cols[EPW];
 #pragma unroll
     for (int q = 0; q < EPW; ++q) {
-        const int el = w * EPW + q, blk = el >> 4, e = el & 15;
+        const int el = element(q), blk = el >> 4, e = el & 15;
         rows[q] = OA::row(d.M, row0, blk / FN, 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3));
         cols[q] = OB::row(d.N, col0, blk % FN, lane & 31);
         if (d.E) {
@@ -320,15 +331,18 @@ __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)
         }
         if (want_ss) {
             const double df = (double)val - (double)evv;
-            ss += df * df;
+            ss[q / EPT] += df * df;
         }
     }
     if (want_ss) {
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-            ss += __shfl_xor(ss, off, 64);
-        if (lane == 0)
-            red8[w] = ss;
+        for (int v = 0; v < V; ++v) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1)
+                ss[v] += __shfl_xor(ss[v], off, 64);
+            if (lane == 0)
+                red8[w + PW * v] = ss[v];
+        }
         __syncthreads();
         if (threadIdx.x == 0) {
             double s = 0.0;
@@ -343,38 +357,33 @@ __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)
         __syncthreads();
         const bool pairs = d.pack_pairs;
         if (d.pack_row)
-            direct_pack_out<T, KW * 64>(red, d.pack_row, d.M, d.N, row0, col0, false, pairs,
+            direct_pack_out<T, PW * 64>(red, d.pack_row, d.M, d.N, row0, col0, false, pairs,
                                         d.pack_prec, d.pack_scale);
         if (d.gram && tm != tn)
-            direct_pack_out<T, KW * 64>(red, d.pack_row, d.M, d.N, col0, row0, true, pairs,
+            direct_pack_out<T, PW * 64>(red, d.pack_row, d.M, d.N, col0, row0, true, pairs,
                                         d.pack_prec, d.pack_scale);
         if (d.pack_col)
-            direct_pack_out<T, KW * 64>(red, d.pack_col, d.N, d.M, col0, row0, true, false,
+            direct_pack_out<T, PW * 64>(red, d.pack_col, d.N, d.M, col0, row0, true, false,
                                         d.pack_prec, d.pack_scale);
     }
 }
 
-// One tile, k in [kb, ke) of the operands.
+// The sums of place w of the KW that share a tile, k in [kb, ke) of the operands.
 template <int PREC, bool AKC, bool BKC, int CLS>
-__device__ __forceinline__ void direct_tile(const GemmDesc &d, int tm, int tn, int64_t kb,
-                                            int64_t ke, float *red, double *red8)
+__device__ __forceinline__ void
+direct_sums(const GemmDesc &d, int64_t row0, int64_t col0, int64_t kb, int64_t ke, int w, int lane,
+            f32x16 (&acc)[DirectCfg<CLS>::FM][DirectCfg<CLS>::FN])
 {
     using G = DirectCfg<CLS>;
     constexpr int FM = G::FM, FN = G::FN, KW = G::KW;
     // steps of loads in flight per wave: what the registers of WPE waves per
     // SIMD leave beside the accumulators and the split terms
     constexpr int D = CLS == kClassDirect32 ? 3 : (PREC == PREC_BF16X6 ? 2 : 3);
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t row0 = (int64_t)tm * (32 * FM), col0 = (int64_t)tn * (32 * FN);
-    // read here, used by the epilogue: its latency is not waited for
-    const int stop = d.stop ? *gmem(d.stop) : 0;
     DirectOperand<AKC, FM> oa;
     DirectOperand<BKC, FN> ob;
     oa.init(d.A, d.lda, d.M, row0, lane);
     ob.init(d.B, d.ldb, d.N, col0, lane);
 
-    f32x16 acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -414,7 +423,25 @@ __device__ __forceinline__ void direct_tile(const GemmDesc &d, int tm, int tn, i
     for (int s = 0; s < D - 1; ++s)
         if (i + s < cnt)
             direct_step<PREC, FM, FN>(va[s], vb[s], d.scale_a, d.scale_b, acc);
-    direct_epilogue<PREC, DirectOperand<AKC, FM>, DirectOperand<BKC, FN>, FM, FN, KW>(
+}
+
+// One tile by KW / V waves.
+template <int PREC, bool AKC, bool BKC, int CLS, int V = 1>
+__device__ __forceinline__ void direct_tile(const GemmDesc &d, int tm, int tn, int64_t kb,
+                                            int64_t ke, float *red, double *red8)
+{
+    using G = DirectCfg<CLS>;
+    constexpr int FM = G::FM, FN = G::FN, KW = G::KW;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row0 = (int64_t)tm * (32 * FM), col0 = (int64_t)tn * (32 * FN);
+    // read here, used by the epilogue: its latency is not waited for
+    const int stop = d.stop ? *gmem(d.stop) : 0;
+    f32x16 acc[V][FM][FN];
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+        direct_sums<PREC, AKC, BKC, CLS>(d, row0, col0, kb, ke, w + KW / V * v, lane, acc[v]);
+    direct_epilogue<PREC, DirectOperand<AKC, FM>, DirectOperand<BKC, FN>, FM, FN, KW, V>(
         d, acc, row0, col0, tm, tn, w, lane, stop, red, red8);
 }
 
@@ -474,58 +501,62 @@ __global__ void __launch_bounds__(DirectCfg<CLS>::KW * 64, DirectCfg<CLS>::WPE)
 // -> 11.6, 1600 60 -> 35).  Inside an iteration the operands come from the other
 // XCDs' writes and the launch is bound by fetching them: two, three and four
 // steps in flight measured the same (polar 1000^2 856, 861, 858 us).
-template <int PREC, int CLS, bool PAIRS>
+template <int PREC, int CLS, bool PAIRS, int V = 1>
 __device__ __forceinline__ void direct_packed_tile(const GemmDesc &d, int tm, int tn, float *red,
                                                    double *red8)
 {
     using G = DirectCfg<CLS>;
     constexpr int FM = G::FM, FN = G::FN, KW = G::KW, D = 2;
     const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t row0 = (int64_t)tm * (32 * FM), col0 = (int64_t)tn * (32 * FN);
     const int stop = d.stop ? *gmem(d.stop) : 0;
     DirectPacked<FM> oa;
     DirectPacked<FN> ob;
     oa.init(d.A, packed_row_blocks(d.M), row0, lane);
     ob.init(d.B, packed_row_blocks(d.N), col0, lane);
-    f32x16 acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-            acc[i][j] = f32x16{};
+    f32x16 acc[V][FM][FN];
     const int nfull = (int)(d.K >> 4), kn = (int)(d.K & 15);
-    const int cnt = w < nfull ? (nfull - w + KW - 1) / KW : 0;
-    bf16x8 a[D][FM][2], b[D][FN][2];
-    if (kn && w == nfull % KW) {
-        oa.load(a[0], nfull);
-        ob.load(b[0], nfull);
-        direct_mfma<PREC, FM, FN>(a[0], b[0], acc);
-    }
-    auto fetch = [&](int s, int i) {
-        oa.load(a[s], w + KW * (int64_t)i);
-        ob.load(b[s], w + KW * (int64_t)i);
-    };
-    if (cnt > 0) {
 #pragma unroll
-        for (int s = 0; s < D; ++s)
-            fetch(s, min(s, cnt - 1));
-    }
-    int i = 0;
-    for (; i + D <= cnt; i += D) {
+    for (int v = 0; v < V; ++v) {
+        const int w = w0 + KW / V * v;
 #pragma unroll
-        for (int s = 0; s < D; ++s) {
-            direct_mfma<PREC, FM, FN>(a[s], b[s], acc);
-            fetch(s, min(i + s + D, cnt - 1));
-            __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+                acc[v][i][j] = f32x16{};
+        const int cnt = w < nfull ? (nfull - w + KW - 1) / KW : 0;
+        bf16x8 a[D][FM][2], b[D][FN][2];
+        if (kn && w == nfull % KW) {
+            oa.load(a[0], nfull);
+            ob.load(b[0], nfull);
+            direct_mfma<PREC, FM, FN>(a[0], b[0], acc[v]);
         }
-    }
+        auto fetch = [&](int s, int i) {
+            oa.load(a[s], w + KW * (int64_t)i);
+            ob.load(b[s], w + KW * (int64_t)i);
+        };
+        if (cnt > 0) {
 #pragma unroll
-    for (int s = 0; s < D - 1; ++s)
-        if (i + s < cnt)
-            direct_mfma<PREC, FM, FN>(a[s], b[s], acc);
-    direct_epilogue<PREC, DirectOperand<true, FM>, DirectOperand<!PAIRS, FN>, FM, FN, KW>(
-        d, acc, row0, col0, tm, tn, w, lane, stop, red, red8);
+            for (int s = 0; s < D; ++s)
+                fetch(s, min(s, cnt - 1));
+        }
+        int i = 0;
+        for (; i + D <= cnt; i += D) {
+#pragma unroll
+            for (int s = 0; s < D; ++s) {
+                direct_mfma<PREC, FM, FN>(a[s], b[s], acc[v]);
+                fetch(s, min(i + s + D, cnt - 1));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < D - 1; ++s)
+            if (i + s < cnt)
+                direct_mfma<PREC, FM, FN>(a[s], b[s], acc[v]);
+    }
+    direct_epilogue<PREC, DirectOperand<true, FM>, DirectOperand<!PAIRS, FN>, FM, FN, KW, V>(
+        d, acc, row0, col0, tm, tn, w0, lane, stop, red, red8);
 }
 
 template <int PREC, int CLS, bool PAIRS>
@@ -536,26 +567,6 @@ __global__ void __launch_bounds__(DirectCfg<CLS>::KW * 64, DirectCfg<CLS>::WPE)
     __shared__ double red8[DirectCfg<CLS>::KW];
     int tm, tn;
     tile_coords(d, xcd_remap(blockIdx.x, d.num_tiles), tm, tn);
-    direct_packed_tile<PREC, CLS, PAIRS>(d, tm, tn, red, red8);
-}
-
-// The same for the items of a grouped launch (one workgroup per item).
-template <int PREC, int CLS, bool PAIRS>
-__global__ void __launch_bounds__(DirectCfg<CLS>::KW * 64, DirectCfg<CLS>::WPE)
-    gemm_direct_packed_items_kernel(const GemmDesc *__restrict__ probs,
-                                    const GroupItem *__restrict__ items, int num_items)
-{
-    __shared__ float red[direct_red_floats<CLS>()];
-    __shared__ double red8[DirectCfg<CLS>::KW];
-    const int it = blockIdx.x;
-    if (it >= num_items)
-        return;
-    const GroupItem gi = items[it];
-    if (gi.prob < 0)
-        return;   // empty item
-    const GemmDesc d = probs[gi.prob];
-    int tm, tn;
-    tile_coords(d, gi.tile, tm, tn);
     direct_packed_tile<PREC, CLS, PAIRS>(d, tm, tn, red, red8);
 }
 
@@ -649,33 +660,6 @@ hipError_t launch_packed_any(const GemmDesc &d, hipStream_t s)
     if (d.small == kClassDirect32)
         return launch_direct_packed<PREC, kClassDirect32>(d, s);
     return launch_packed_x3<PREC>(d, s);
-}
-
-template <int PREC, int CLS>
-hipError_t launch_direct_packed_items(int pairs, const GemmDesc *probs, const GroupItem *items,
-                                      int num_items, hipStream_t s)
-{
-    const dim3 grid(num_items), block(DirectCfg<CLS>::KW * 64);
-    if (pairs)
-        hipLaunchKernelGGL((gemm_direct_packed_items_kernel<PREC, CLS, true>), grid, block, 0, s,
-                           probs, items, num_items);
-    else
-        hipLaunchKernelGGL((gemm_direct_packed_items_kernel<PREC, CLS, false>), grid, block, 0, s,
-                           probs, items, num_items);
-    return hipGetLastError();
-}
-
-template <int PREC>
-hipError_t launch_grouped_packed(int pairs, int cls, const GemmDesc *probs, const GroupItem *items,
-                                 int num_items, hipStream_t s)
-{
-    if (num_items <= 0)
-        return hipSuccess;
-    if (cls == kClassDirect64)
-        return launch_direct_packed_items<PREC, kClassDirect64>(pairs, probs, items, num_items, s);
-    if (cls == kClassDirect32)
-        return launch_direct_packed_items<PREC, kClassDirect32>(pairs, probs, items, num_items, s);
-    return hipErrorInvalidValue;
 }
 
 }  // namespace dev

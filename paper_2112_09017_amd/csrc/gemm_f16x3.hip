@@ -23,12 +23,6 @@ hipError_t launch_pack_f16(const float *X, int64_t ld, int kc, int64_t rows, int
                                            s);
 }
 
-hipError_t launch_grouped_packed_f16(int pairs, int cls, const GemmDesc *probs,
-                                    const GroupItem *items, int num_items, hipStream_t s)
-{
-    return dev::launch_grouped_packed<PREC_F16X3>(pairs, cls, probs, items, num_items, s);
-}
-
 hipError_t launch_gemm_packed_f16(const GemmDesc &d, hipStream_t s)
 {
     return dev::launch_packed_any<PREC_F16X3>(d, s);

@@ -25,12 +25,6 @@ hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t rows, int6
                                             static_cast<char *>(out), s);
 }
 
-hipError_t launch_grouped_packed_x3(int pairs, int cls, const GemmDesc *probs,
-                                    const GroupItem *items, int num_items, hipStream_t s)
-{
-    return dev::launch_grouped_packed<PREC_BF16X3>(pairs, cls, probs, items, num_items, s);
-}
-
 hipError_t launch_gemm_packed_x3(const GemmDesc &d, hipStream_t s)
 {
     return dev::launch_packed_any<PREC_BF16X3>(d, s);

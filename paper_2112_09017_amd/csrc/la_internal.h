@@ -71,6 +71,7 @@ struct GemmDesc {
     float pack_scale;
     int pack_prec, pack_pairs;
     int b_pairs;       // packed operands: op(B)'s rows are in that order
+    int prec, packed;  // launch_gemm_mixed: arithmetic; packed operands
 };
 
 // Tile classes.  Large (256 x 256) and small (128 x 128) tiles (gemm_tile.h) use
@@ -128,10 +129,12 @@ struct GroupItem {
 hipError_t launch_gemm_grouped(int prec, int a_kcontig, int b_kcontig, int cls,
                                const GemmDesc *probs_dev,
                                const GroupItem *items_dev, int num_items, hipStream_t s);
-// The same on packed operands: two-term precisions, direct classes; b_pairs is
-// every problem's.
-hipError_t launch_gemm_grouped_packed(int prec, int b_pairs, int cls, const GemmDesc *probs_dev,
-                                      const GroupItem *items_dev, int num_items, hipStream_t s);
+// The same over problems of the direct classes of several arithmetics (not FP32)
+// and classes, each with its own (d.prec, d.small) and on FP32 or packed operands
+// (d.packed).  update: op(A) k contiguous, op(B) row-contiguous or packed in pair
+// order; else both row-contiguous or packed in order.
+hipError_t launch_gemm_mixed(int update, const GemmDesc *probs_dev, const GroupItem *items_dev,
+                             int num_items, hipStream_t s);
 
 // Packed operands of two 16-bit terms (gemm_x3.hip: 3xBF16, gemm_f16x3.hip:
 // F16X3, whose entries are multiplied by sc before the split, or, with rmax, each

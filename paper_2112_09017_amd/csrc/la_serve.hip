@@ -66,12 +66,9 @@ constexpr int kMaxSlots = 4096;
 // from larger ones.
 constexpr int kMaxBands = 2;
 constexpr double kBandWork = 2048.0 * 2048.0 * 2048.0;
-// launch groups of one staging pass: 2 phases x (4 product arithmetics x 4 tile
-// classes, and the 2 two-term ones x 2 direct classes on packed operands), each with
-// its descriptors and its items padded to kStageAlign
-constexpr int kMaxGroups = 40;
-constexpr size_t kStageAlign = 128, kStagePad = 8192;
-static_assert(kMaxGroups * kStageAlign <= kStagePad, "padding of one staging pass");
+// launch groups of one staging pass: at most 4 product arithmetics x 4 tile classes
+// x 2 phases, each with its descriptors and its items padded to kAlign
+constexpr int kMaxGroups = 32;
 // A request takes the packed copies of its products' results (PolarChain) if at
 // least this many such requests fit the arena: they double its footprint (twelve
 // requests of 128^2 to 1536^2: 7.1 ms of ticks with them, 8.6 ms without).
@@ -80,7 +77,6 @@ static_assert(2 * kMaxSlots * sizeof(double) <= kRedBytes, "norms of one tick");
 static_assert(2 * sizeof(ReduceItem) <= sizeof(GemmDesc), "reduce items in a descriptor slot");
 
 size_t up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
-size_t up_stage(size_t x) { return (x + kStageAlign - 1) & ~(kStageAlign - 1); }
 
 // Pinned host buffers reused across requests (power-of-two size classes), so a
 // submit does not pay for a pinned allocation once the pool has warmed up.  A
@@ -160,7 +156,7 @@ size_t max_tiles(int64_t m, int64_t n)
 
 struct Launch {
     int prec, akc, bkc, cls;
-    bool packed;   // op(B) is in pair order if akc
+    bool mixed;   // prec and cls are each problem's own (launch_gemm_mixed)
     std::vector<GemmDesc> probs;
     std::vector<GroupItem> items;
 };
@@ -177,16 +173,21 @@ struct Staged {
 // and a launch of a few large-tile problems fills only part of the device.
 constexpr int kSide = 3;
 
-void add_problem(std::vector<Launch> &ls, int prec, int akc, int bkc, const GemmDesc &d,
+// Problems of the direct classes share one launch, FP32 ones and those of the
+// staged classes one per arithmetic and class.
+void add_problem(std::vector<Launch> &ls, int prec, int akc, int bkc, GemmDesc d,
                  bool packed = false)
 {
+    const bool mixed = is_direct(d.small) && prec != PREC_FP32;
+    d.prec = prec;
+    d.packed = packed;
     Launch *L = nullptr;
     for (auto &x : ls)
-        if (x.prec == prec && x.akc == akc && x.bkc == bkc && x.cls == d.small &&
-            x.packed == packed)
+        if (x.akc == akc && x.bkc == bkc && x.mixed == mixed &&
+            (mixed || (x.prec == prec && x.cls == d.small)))
             L = &x;
     if (!L) {
-        ls.push_back(Launch{prec, akc, bkc, d.small, packed, {}, {}});
+        ls.push_back(Launch{prec, akc, bkc, d.small, mixed, {}, {}});
         L = &ls.back();
     }
     const int pid = (int)L->probs.size();
@@ -248,7 +249,11 @@ void xcd_order(Launch &L)
     std::vector<int64_t> tiles, cost;
     for (const GemmDesc &d : L.probs) {
         tiles.push_back(d.num_tiles);
-        cost.push_back(d.K);
+        // (one class otherwise) a 64 x 64 tile is four 32 x 32 ones; a step on FP32
+        // operands takes about twice one on packed ones, at 6xBF16 four times
+        cost.push_back(!L.mixed ? d.K
+                                : d.K * (d.small == kClassDirect64 ? 4 : 1) *
+                                      (d.packed ? 1 : d.prec == PREC_BF16X6 ? 4 : 2));
     }
     const std::vector<serve::Slot> lay = serve::xcd_layout(tiles, cost, kXcds);
     L.items.resize(lay.size());
@@ -307,9 +312,9 @@ struct HipExec {
         *descs = 3;
         *items = std::max(it, 2 * (size_t)h.num_tiles) + 2 * (kXcds - 1);
     }
-    // each budget keeps room for the padding of kMaxGroups launches
-    size_t desc_capacity() { return (kDescBytes - kStagePad) / sizeof(GemmDesc); }
-    size_t item_capacity() { return (kItemBytes - kStagePad) / sizeof(GroupItem); }
+    // each budget keeps room for the kAlign padding of kMaxGroups launches
+    size_t desc_capacity() { return (kDescBytes - kMaxGroups * kAlign) / sizeof(GemmDesc); }
+    size_t item_capacity() { return (kItemBytes - kMaxGroups * kAlign) / sizeof(GroupItem); }
 
     la_status stage_input(serve::Req &r, const float *A, int64_t lda)
     {
@@ -409,14 +414,14 @@ struct HipExec {
             xcd_order(L);
             const size_t db = L.probs.size() * sizeof(GemmDesc);
             const size_t ib = L.items.size() * sizeof(GroupItem);
-            const size_t ip = pos + up_stage(db);
+            const size_t ip = pos + up(db);
             if (ip + ib > kUpBytes)
                 return hipErrorOutOfMemory;
             memcpy(h_stage + pos, L.probs.data(), db);
             memcpy(h_stage + ip, L.items.data(), ib);
             out.push_back(Staged{&L, (const GemmDesc *)(stage_dev + pos),
                                  (const GroupItem *)(stage_dev + ip)});
-            pos = ip + up_stage(ib);
+            pos = ip + up(ib);
         }
         return hipSuccess;
     }
@@ -444,10 +449,9 @@ struct HipExec {
         for (size_t i = 0; i < st.size() && e == hipSuccess; ++i) {
             const Launch &L = *st[i].L;
             hipStream_t s = i == 0 ? stream : side[(i - 1) % kSide];
-            e = L.packed ? launch_gemm_grouped_packed(L.prec, L.akc, L.cls, st[i].dd, st[i].di,
-                                                      (int)L.items.size(), s)
-                         : launch_gemm_grouped(L.prec, L.akc, L.bkc, L.cls, st[i].dd, st[i].di,
-                                               (int)L.items.size(), s);
+            e = L.mixed ? launch_gemm_mixed(L.akc, st[i].dd, st[i].di, (int)L.items.size(), s)
+                        : launch_gemm_grouped(L.prec, L.akc, L.bkc, L.cls, st[i].dd, st[i].di,
+                                              (int)L.items.size(), s);
         }
         for (int k = 0; k < used && e == hipSuccess; ++k) {
             e = hipEventRecord(ev_side[k], side[k]);

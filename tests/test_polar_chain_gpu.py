@@ -85,3 +85,29 @@ def test_server_chained_equals_plain(la):
     for a, b in zip(*out):
         assert a[0] == b[0] == la.Status.OK
         assert np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2]) and a[3] == b[3]
+
+
+@pytest.mark.parametrize("opts", [{}, dict(polish=True), dict(prec_precond=3, prec_ns=3),
+                                  dict(prec_precond=1, prec_ns=1)],
+                         ids=["default", "polish", "x6", "fp32"])
+def test_server_equals_polar(la, opts):
+    """One launch per phase takes every request in flight, whatever its size and
+    arithmetic: each tile is the sums of la_polar's launch in their order (below
+    4096 rows neither splits K), so the factors agree bit for bit."""
+    cs = [la_inputs.polar_case(m, n, 1e-2, seeds=(91 + m, 92 + n, 93)).A32
+          for m, n in [(1, 1), (40, 31), (130, 97), (300, 257), (700, 641), (1001, 1001)]]
+    with la.Server(1 << 30, max_slots=8) as srv:
+        ids = [srv.submit(a, **opts) for a in cs]
+        got, t0 = {}, time.time()
+        while len(got) < len(ids) and time.time() - t0 < 60:
+            for i in ids:
+                r = None if i in got else srv.poll(i)
+                if r is not None:
+                    got[i] = r
+            time.sleep(0.001)
+    for a, i in zip(cs, ids):
+        U, H, info = la.polar(torch.from_numpy(a).cuda(), **opts)
+        st, U2, H2, info2 = got[i]
+        assert st == la.Status.OK
+        assert np.array_equal(U.cpu().numpy(), U2) and np.array_equal(H.cpu().numpy(), H2)
+        assert info["iters_ns"] == info2["iters_ns"]
