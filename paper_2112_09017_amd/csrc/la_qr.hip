@@ -417,211 +417,8 @@ __device__ __forceinline__ void form_q64(WriteU write_u, int nc, int lane, int w
     }
 }
 
-// Householder QR of one row block (rows x nc, rows <= 256, 64 < nc <= 128)
-// per workgroup of 1024 threads, the block in registers.  Wave w owns columns
-// 8 w .. 8 w + 7; within the wave a column is held by L = 8 consecutive
-// lanes, each with RPL = 32 consecutive rows, so the column dot products
-// reduce inside the wave (group_sum) without a barrier.  (Blocks of at most
-// 64 columns: qr_block64_kernel.)
-//
-// Reflection j uses u = x - beta e_j (x = column j from row j down,
-// beta = -sign(x_j) ||x||) unscaled, H_j = I - kappa u u^T,
-// kappa = 1 / (beta (beta - x_j)).  ||x||^2 is summed in FP32, four
-// independent partial sums per lane and then across the lane group, and
-// beta and kappa are formed in FP32: these sit on the one-wave chain between
-// two barriers that every step waits for.  A column whose squares could
-// leave the FP32 range (sum outside [2^-96, 2^96], zero or non-finite) takes
-// FP64 squares, which are exact for FP32 entries, and FP64 beta and kappa.
-// The owners of column j form u (zero above row j, u_j = x_j - beta on it,
-// x below it) and publish it to one of two LDS buffers with kappa; after one
-// barrier every column c > j forms u^T x_c and x_c -= kappa (u^T x_c) u, and
-// the owners of column j + 1 (already updated) prepare the next reflection
-// into the other buffer.  One barrier per step.  Column j keeps x below the
-// diagonal and the pivot x_j on it; u_j, kappa and beta go to LDS arrays.
-// R (row block blk of R, ld ldr) is then written from the registers, and
-// Q = H_0 ... H_{nc-1} [I; 0] is formed in place and written to Q (ldq; X
-// may equal Q): last reflection first (column j becomes H_j e_j once the
-// columns to its right hold H_{j+1} ... e_c), one barrier per reflection.
-template <int B>
-__global__ __launch_bounds__(8 * B) void qr_block_kernel(const float *X, int64_t ldx, Part part,
-                                                         int nc, float *Q, int64_t ldq, float *R,
-                                                         int64_t ldr)
-{
-    static_assert(B == 128, "blocks of at most 64 columns: qr_block64_kernel");
-    constexpr int CPW = 8;              // columns per wave
-    constexpr int L = 64 / CPW;         // lanes per column
-    constexpr int RPL = kRows / L;      // rows per lane
-    // LDS: the two u buffers (alternating reflections) and u_j, kappa, beta
-    constexpr int kLdsF = 2 * kRows + 3 * B;
-    __shared__ __attribute__((aligned(16))) float lds[kLdsF];
-    float(*ubuf)[kRows] = reinterpret_cast<float(*)[kRows]>(lds);
-    float *s_u0 = lds + 2 * kRows, *s_kap = s_u0 + B, *s_beta = s_kap + B;
-
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int c = w * CPW + lane / L;
-    const int rlo = (lane % L) * RPL;
-    const int64_t blk = blockIdx.x;
-    const int64_t r0 = part_start(part, blk);
-    const int rows = (int)(part_start(part, blk + 1) - r0);
-    nc = __builtin_amdgcn_readfirstlane(nc);
-    const bool col = c < nc;
-
-    float f[RPL], u[RPL];
-#pragma unroll
-    for (int i = 0; i < RPL; ++i)
-        f[i] = (col && rlo + i < rows) ? X[(r0 + rlo + i) * ldx + c] : 0.0f;
-
-    // owners of column jn (all L lanes): reflection jn from their column.
-    // The column from row jn down (zero above) goes to ubuf[jn & 1] while its
-    // squares accumulate; the pivot x_jn is read back from LDS (one wave's LDS
-    // accesses complete in order), and its lane overwrites it with u_jn once
-    // beta is known.
-    auto prepare = [&](int jn, float *ub) {
-        float s4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int i = 0; i < RPL; i += 4) {
-            float o[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                o[e] = rlo + i + e < jn ? 0.0f : f[i + e];
-                s4[e] = fmaf(o[e], o[e], s4[e]);
-            }
-            *(float4 *)&ub[rlo + i] = make_float4(o[0], o[1], o[2], o[3]);
-        }
-        // the pivot x_jn, read back below, was stored by one of the owner lanes
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        const float ss = group_sum<L>((s4[0] + s4[1]) + (s4[2] + s4[3]));
-        float u0 = 0.0f, kap = 0.0f, beta = 0.0f;   // a zero column needs no reflection
-        if (ss >= 0x1p-96f && ss <= 0x1p96f) {
-            const float nrm = sqrtf(ss), x0 = ub[jn];
-            beta = x0 >= 0.0f ? -nrm : nrm;
-            u0 = x0 - beta;
-            kap = 1.0f / (beta * (beta - x0));
-        } else {
-            double sd = 0.0;
-#pragma unroll
-            for (int i = 0; i < RPL; ++i) {
-                const double v = rlo + i < jn ? 0.0 : (double)f[i];
-                sd = fma(v, v, sd);
-            }
-            const double nrm = sqrt(group_sum<L>(sd));
-            const double x0 = ub[jn];
-            if (nrm > 0.0) {
-                const double bt = x0 >= 0.0 ? -nrm : nrm;
-                u0 = (float)(x0 - bt);
-                kap = (float)(1.0 / (bt * (bt - x0)));
-                beta = (float)bt;
-            }
-        }
-        if (rlo == 0) {
-            s_u0[jn] = u0;
-            s_kap[jn] = kap;
-            s_beta[jn] = beta;
-        }
-        if (rlo <= jn && jn < rlo + RPL)
-            ub[jn] = u0;
-    };
-    // owners of column jn: its stored reflector (x below the diagonal) to ubuf[jn & 1]
-    auto republish = [&](int jn) {
-        const float u0 = s_u0[jn];
-        float *ub = ubuf[jn & 1];
-#pragma unroll
-        for (int i = 0; i < RPL; i += 4) {
-            float o[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int r = rlo + i + e;
-                o[e] = r < jn ? 0.0f : (r == jn ? u0 : f[i + e]);
-            }
-            *(float4 *)&ub[rlo + i] = make_float4(o[0], o[1], o[2], o[3]);
-        }
-    };
-
-    // f -= sc u with the u of the current step
-    auto axpy_u = [&](float sc) {
-#pragma unroll
-        for (int i = 0; i < RPL; ++i)
-            f[i] = fmaf(-sc, u[i], f[i]);
-    };
-
-    // f -= kappa_j (u_j^T f) u_j for this lane's column, u_j read from ub
-    auto reflect = [&](const float *ub, float kap, bool apply) {
-        float d4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int i = 0; i < RPL; i += 4) {
-            const float4 uv = *(const float4 *)&ub[rlo + i];
-            const float ua[4] = {uv.x, uv.y, uv.z, uv.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                u[i + e] = ua[e];
-                d4[e] = fmaf(ua[e], f[i + e], d4[e]);
-            }
-        }
-        const float d = group_sum<L>((d4[0] + d4[1]) + (d4[2] + d4[3]));
-        axpy_u(apply ? kap * d : 0.0f);
-    };
-
-    if (c == 0)
-        prepare(0, ubuf[0]);
-    __syncthreads();
-    for (int jv = 0; jv < nc; ++jv) {
-        const int j = __builtin_amdgcn_readfirstlane(jv);
-        reflect(ubuf[j & 1], s_kap[j], col && c > j);
-        if (c == j + 1 && col)
-            prepare(j + 1, ubuf[(j + 1) & 1]);
-        __syncthreads();
-    }
-
-    float *Rb = R + blk * nc * ldr;
-#pragma unroll
-    for (int i = 0; i < RPL; ++i) {
-        const int rr = rlo + i;
-        if (col && rr < nc)
-            Rb[(int64_t)rr * ldr + c] = c > rr ? f[i] : (c == rr ? s_beta[rr] : 0.0f);
-    }
-
-    if (c == nc - 1)
-        republish(nc - 1);
-    __syncthreads();
-    for (int jv = nc - 1; jv >= 0; --jv) {
-        const int j = __builtin_amdgcn_readfirstlane(jv);
-        const float *ub = ubuf[j & 1];
-        const float kap = s_kap[j], u0 = s_u0[j];
-        float d4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int i = 0; i < RPL; i += 4) {
-            const float4 uv = *(const float4 *)&ub[rlo + i];
-            const float ua[4] = {uv.x, uv.y, uv.z, uv.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                u[i + e] = ua[e];
-                d4[e] = fmaf(ua[e], f[i + e], d4[e]);
-            }
-        }
-        const float d = group_sum<L>((d4[0] + d4[1]) + (d4[2] + d4[3]));
-        if (col && c > j) {
-            axpy_u(kap * d);
-        } else if (c == j) {
-            // column j = H_j e_j = e_j - kappa u_j u (u is zero above row j)
-            const float s2 = kap * u0;
-#pragma unroll
-            for (int i = 0; i < RPL; ++i)
-                f[i] = rlo + i == j ? 1.0f : 0.0f;
-            axpy_u(s2);
-        }
-        if (c == j - 1)
-            republish(j - 1);
-        __syncthreads();
-    }
-
-#pragma unroll
-    for (int i = 0; i < RPL; ++i)
-        if (col && rlo + i < rows)
-            Q[(r0 + rlo + i) * ldq + c] = f[i];
-}
-
-// Householder QR of one row block (rows x nc, rows <= 256, nc <= 64) per
-// workgroup of 8 waves, the block in registers with the rows across the
+// Householder QR of one row block (rows x nc, rows <= 256, nc <= NC) per
+// workgroup of NC / 8 waves, the block in registers with the rows across the
 // lanes: lane l holds rows 4 l .. 4 l + 3 of its wave's 8 columns (wave w:
 // columns 8 w .. 8 w + 7).  A column vector such as u_j is then spread over
 // the lanes of every wave alike, so the wave that forms a reflection keeps
@@ -653,9 +450,10 @@ __global__ __launch_bounds__(8 * B) void qr_block_kernel(const float *X, int64_t
 // written to Q (ldq); X may equal Q.  SPLIT: instead the reflectors U go to Q
 // and their kappa to kap (64 per block), for qr_form64_kernel: the next level of
 // the TSQR tree needs R only, so the forming of Q (22 of a block's 59 us) leaves
-// the chain of levels.
-template <bool SPLIT>
-__global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t ldx, Part part,
+// the chain of levels.  NC = 128 (64 < nc) is always split, for qr_form128_kernel,
+// and has its kappa in U's zero upper triangle: kappa_c at (0, c), kappa_0 at (1, 2).
+template <int NC, bool SPLIT>
+__global__ __launch_bounds__(NC * 8) void qr_block_kernel(const float *X, int64_t ldx, Part part,
                                                          int nc, float *Q, int64_t ldq, float *R,
                                                          int64_t ldr, float *kap)
 {
@@ -665,12 +463,13 @@ __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t
     // it), u_j's pivot entry, kappa, beta and the count of published
     // reflections; the same space then holds U and S / Z of the compact WY
     // form (80 KiB in all, so two workgroups share a CU)
-    constexpr int kLdsF = kRows * 64 + 64 * 64;
-    static_assert(64 * kRows + 3 * 64 + 1 <= kLdsF, "reflection buffers fit the WY space");
+    constexpr int kLdsF = SPLIT ? NC * kRows + 3 * NC + 4 : kRows * 64 + 64 * 64;
+    static_assert(NC == 64 || SPLIT, "more than 64 columns: qr_form128_kernel forms Q");
+    static_assert(NC * kRows + 3 * NC + 1 <= kLdsF, "reflection buffers fit the WY space");
     __shared__ __attribute__((aligned(16))) float lds[kLdsF];
     float(*ubuf)[kRows] = reinterpret_cast<float(*)[kRows]>(lds);
-    float *s_u0 = lds + 64 * kRows, *s_kap = s_u0 + 64, *s_beta = s_kap + 64;
-    int *s_pub = reinterpret_cast<int *>(s_beta + 64);
+    float *s_u0 = lds + NC * kRows, *s_kap = s_u0 + NC, *s_beta = s_kap + NC;
+    int *s_pub = reinterpret_cast<int *>(s_beta + NC);
 
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int rlo = lane * RPL;
@@ -851,7 +650,7 @@ __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t
     for (int cc = 0; cc < CPW; ++cc)
         u0c[cc] = own + cc < nc ? s_u0[own + cc] : 0.0f;
     if constexpr (SPLIT) {
-        if (t < nc)
+        if (NC == 64 && t < nc)
             kap[blk * 64 + t] = s_kap[t];
         const bool vecq = own + CPW <= nc && (ldq & 3) == 0 && ((uintptr_t)Q & 15) == 0;
 #pragma unroll
@@ -864,6 +663,12 @@ __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t
             for (int cc = 0; cc < CPW; ++cc) {
                 const int c = own + cc;
                 v[cc] = r < c ? 0.0f : (r == c ? u0c[cc] : f[cc][i]);
+                if (NC == 128 && c < nc) {
+                    if (r == 0 && c > 0)
+                        v[cc] = s_kap[c];
+                    if (r == 1 && c == 2)
+                        v[cc] = s_kap[0];
+                }
             }
             float *qr = Q + (r0 + r) * ldq + own;
             if (vecq) {
@@ -876,26 +681,26 @@ __global__ __launch_bounds__(512) void qr_block64_kernel(const float *X, int64_t
                         qr[cc] = v[cc];
             }
         }
-        return;
-    }
-    form_q64(
-        [&](float *Us) {
+    } else {
+        form_q64(
+            [&](float *Us) {
 #pragma unroll
-            for (int cc = 0; cc < CPW; ++cc) {
-                const int c = own + cc;
+                for (int cc = 0; cc < CPW; ++cc) {
+                    const int c = own + cc;
 #pragma unroll
-                for (int i = 0; i < RPL; ++i) {
-                    const int r = rlo + i;
-                    const float v = (c >= nc || r < c) ? 0.0f : (r == c ? u0c[cc] : f[cc][i]);
-                    Us[r * 64 + (c ^ (r & 31))] = v;
+                    for (int i = 0; i < RPL; ++i) {
+                        const int r = rlo + i;
+                        const float v = (c >= nc || r < c) ? 0.0f : (r == c ? u0c[cc] : f[cc][i]);
+                        Us[r * 64 + (c ^ (r & 31))] = v;
+                    }
                 }
-            }
-        },
-        nc, lane, w, rows, s_kap, lds, Q + r0 * ldq, ldq);
+            },
+            nc, lane, w, rows, s_kap, lds, Q + r0 * ldq, ldq);
+    }
 }
 
 // Q of the blocks of several levels of a TSQR tree, in place of the reflectors
-// that qr_block64_kernel<true> left: one workgroup per block, every level's in one
+// that qr_block_kernel<64, true> left: one workgroup per block, every level's in one
 // launch (the same products as the unsplit kernel's, bit for bit).
 constexpr int kFormLevels = 24;
 struct FormArgs {
@@ -955,13 +760,108 @@ __global__ __launch_bounds__(512) void qr_form64_kernel(FormArgs a)
         nc, lane, w, rows, a.kap[l] + blk * 64, lds, Qb, ldq);
 }
 
+// The same for 64 < nc <= 128, in place of the U and kappa that
+// qr_block_kernel<128, true> left: Q = H_0 ... H_{nc-1} [I; 0], last reflection
+// first (column j becomes H_j e_j once the columns to its right hold
+// H_{j+1} ... e_c), one barrier per reflection.  1024 threads; wave w owns columns
+// 8 w .. 8 w + 7, a column is held by L = 8 consecutive lanes with RPL = 32
+// consecutive rows each, and its dot products reduce inside the wave.  Off the
+// chain of levels it costs its throughput only, one workgroup per CU (131072 x 128:
+// 5.0 -> 1.8 ms, 236482 x 76 3.0 -> 1.4, against one kernel that factored and
+// formed a block in 300 us a level).
+__global__ __launch_bounds__(1024) void qr_form128_kernel(FormArgs a)
+{
+    constexpr int B = 128;
+    constexpr int CPW = 8;              // columns per wave
+    constexpr int L = 64 / CPW;         // lanes per column
+    constexpr int RPL = kRows / L;      // rows per lane
+    // the two u buffers (alternating reflections) and kappa
+    __shared__ __attribute__((aligned(16))) float ubuf[2][kRows];
+    __shared__ float s_kap[B];
+    int l = 0;
+    while (l + 1 < a.levels && (int)blockIdx.x >= a.first[l + 1])
+        ++l;
+    const int64_t blk = (int)blockIdx.x - a.first[l];
+    const int64_t ldq = a.ldq[l];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int c = w * CPW + lane / L;
+    const int rlo = (lane % L) * RPL;
+    const int64_t r0 = part_start(a.part[l], blk);
+    const int rows = (int)(part_start(a.part[l], blk + 1) - r0);
+    const int nc = __builtin_amdgcn_readfirstlane(a.nc);
+    const bool col = c < nc;
+    float *Qb = a.Q[l] + r0 * ldq;
+
+    // column c of U, zero above its diagonal (where the kappa are)
+    float f[RPL], u[RPL];
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+        const int r = rlo + i;
+        f[i] = (col && r < rows && r >= c) ? Qb[(int64_t)r * ldq + c] : 0.0f;
+    }
+    if (t < nc)
+        s_kap[t] = t ? Qb[t] : Qb[ldq + 2];
+
+    // owners of column jn: its reflector to ubuf[jn & 1]
+    auto publish = [&](int jn) {
+        float *ub = ubuf[jn & 1];
+#pragma unroll
+        for (int i = 0; i < RPL; i += 4)
+            *(float4 *)&ub[rlo + i] = make_float4(f[i], f[i + 1], f[i + 2], f[i + 3]);
+    };
+    auto axpy_u = [&](float sc) {
+#pragma unroll
+        for (int i = 0; i < RPL; ++i)
+            f[i] = fmaf(-sc, u[i], f[i]);
+    };
+    if (c == nc - 1)
+        publish(nc - 1);
+    __syncthreads();
+    for (int jv = nc - 1; jv >= 0; --jv) {
+        const int j = __builtin_amdgcn_readfirstlane(jv);
+        const float *ub = ubuf[j & 1];
+        const float kap = s_kap[j], u0 = ub[j];
+        float d4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int i = 0; i < RPL; i += 4) {
+            const float4 uv = *(const float4 *)&ub[rlo + i];
+            const float ua[4] = {uv.x, uv.y, uv.z, uv.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                u[i + e] = ua[e];
+                d4[e] = fmaf(ua[e], f[i + e], d4[e]);
+            }
+        }
+        const float d = group_sum<L>((d4[0] + d4[1]) + (d4[2] + d4[3]));
+        if (col && c > j) {
+            axpy_u(kap * d);
+        } else if (c == j) {
+            // column j = H_j e_j = e_j - kappa u_j u (u is zero above row j)
+            const float s2 = kap * u0;
+#pragma unroll
+            for (int i = 0; i < RPL; ++i)
+                f[i] = rlo + i == j ? 1.0f : 0.0f;
+            axpy_u(s2);
+        }
+        if (c == j - 1)
+            publish(j - 1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < RPL; ++i)
+        if (col && rlo + i < rows)
+            Qb[(int64_t)(rlo + i) * ldq + c] = f[i];
+}
+
 // out[r, :] = (in[r, :] - sub [r < nc] e_r^T) M_b for every row r < part.rows,
 // with M_b = Mb + b * nc * nc (nc x nc, ld nc) for the partition block b
 // holding row r, or M_0 for every row when single; wout (optional) receives
 // in[r, :] - sub e_r^T.  Workgroup (b, y) takes rows 128 y .. 128 y + 127 of
 // block b, each wave 32 of them on the matrix cores (v_mfma_f32_32x32x2f32): lane
 // l holds half of row l & 31 (k from B / 2 (l >> 5) on; step q takes k = q and
-// B / 2 + q), M_b is in LDS.  Latency bound on the tree's upper levels and in
+// B / 2 + q, in four sums, at B = 128 two, that shorten the chain of
+// roundings: with one, A - Q R came out 1.5% larger than from the vector units); M_b
+// is in LDS.  Latency bound on the tree's upper levels and in
 // CAQR's panels, HBM bound on the leaves (64 columns, 131072 rows, tree of six
 // levels: 20 us a level on the vector units with an index division per element,
 // 8.7 us now; CAQR's panels of 6144 rows 12 -> 7.3 us).  out may equal in: a wave
@@ -1037,20 +937,33 @@ __global__ __launch_bounds__(256) void rowmul_kernel(const float *in, int64_t ld
         }
     }
     __syncthreads();
-    f32x16_t acc[NJ] = {};
+    constexpr int NS = B == 64 ? 4 : 2;
+    f32x16_t acc[NS][NJ] = {};
 #pragma unroll
-    for (int q = 0; q < HK; ++q)
+    for (int q = 0; q < HK / NS; ++q)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-            acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                x[q], ms[(h * HK + q) * B + 32 * j + li], acc[j], 0, 0, 0);
+#pragma unroll
+            for (int p = 0; p < NS; ++p) {
+                const int k = q + HK / NS * p;
+                acc[p][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                    x[k], ms[(h * HK + k) * B + 32 * j + li], acc[p][j], 0, 0, 0);
+            }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        if constexpr (NS == 4) {
+            acc[0][j] += acc[2][j];
+            acc[1][j] += acc[3][j];
+        }
+        acc[0][j] += acc[1][j];
+    }
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const int64_t r = rbase + 8 * (e >> 2) + 4 * h + (e & 3);
             if (r < rend && 32 * j + li < nc)
-                out[r * ldo + 32 * j + li] = acc[j][e];
+                out[r * ldo + 32 * j + li] = acc[0][j][e];
         }
 }
 
@@ -1301,7 +1214,7 @@ hipError_t tsqr_run_b(const float *A, int64_t lda, int nc, float *Q, int64_t ldq
         if constexpr (B == 64) {
             if (split) {
                 float *kl = (float *)(kap + tp.kap[l]);
-                hipLaunchKernelGGL(qr_block64_kernel<true>, dim3(pl.nb), dim3(512), 0, s, in, ldi,
+                hipLaunchKernelGGL((qr_block_kernel<64, true>), dim3(pl.nb), dim3(512), 0, s, in, ldi,
                                    pl, nc, qo, ldo, ro, ldro, kl);
                 fa.Q[l] = qo;
                 fa.ldq[l] = ldo;
@@ -1309,16 +1222,33 @@ hipError_t tsqr_run_b(const float *A, int64_t lda, int nc, float *Q, int64_t ldq
                 fa.kap[l] = kl;
                 fa.first[l + 1] = fa.first[l] + pl.nb;
             } else {
-                hipLaunchKernelGGL(qr_block64_kernel<false>, dim3(pl.nb), dim3(512), 0, s, in, ldi,
+                hipLaunchKernelGGL((qr_block_kernel<64, false>), dim3(pl.nb), dim3(512), 0, s, in, ldi,
                                    pl, nc, qo, ldo, ro, ldro, (float *)nullptr);
             }
         } else {
-            hipLaunchKernelGGL(qr_block_kernel<B>, dim3(pl.nb), dim3(8 * B), 0, s, in, ldi, pl,
-                               nc, qo, ldo, ro, ldro);
+            hipLaunchKernelGGL((qr_block_kernel<B, true>), dim3(pl.nb), dim3(8 * B), 0, s, in, ldi,
+                               pl, nc, qo, ldo, ro, ldro, (float *)nullptr);
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
+    }
+    if constexpr (B == 128) {
+        // every level's Q, kFormLevels levels at a time
+        for (int l0 = 0; l0 <= L; l0 += kFormLevels) {
+            fa.levels = std::min(kFormLevels, L + 1 - l0);
+            for (int i = 0; i < fa.levels; ++i) {
+                const int l = l0 + i;
+                fa.part[i] = make_part(tp.rows[l], nc);
+                fa.Q[i] = l == 0 ? Q : buf(l);
+                fa.ldq[i] = l == 0 ? ldq : nc;
+                fa.first[i + 1] = fa.first[i] + fa.part[i].nb;
+            }
+            hipLaunchKernelGGL(qr_form128_kernel, dim3(fa.first[fa.levels]), dim3(1024), 0, s, fa);
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess)
+                return e;
+        }
     }
     if (split) {
         hipLaunchKernelGGL(qr_form64_kernel, dim3(fa.first[L + 1]), dim3(512), 0, s, fa);
