@@ -185,16 +185,20 @@ typedef struct {
  * arguments).  opts may be NULL.  It holds the second iterate (m n floats),
  * P (n^2), split-K Gram parts for tall inputs (up to 16 n^2), FP64 partials,
  * and, when a step runs at 3xBF16 on staged tiles, packed copies of the
- * iterate and of P for the update (about m n + n^2 floats). */
+ * iterate and of P for the update (about m n + n^2 floats).  On mid-size and
+ * small inputs its last part (packed operands, about 3 m n + n^2 floats on the
+ * small ones) is optional: la_polar takes a workspace without it and computes
+ * the same bits from FP32 operands. */
 size_t la_polar_workspace_size(int64_t m, int64_t n, const la_polar_opts *opts);
 
 /* A (m x n, lda >= n, m >= n >= 1) is read only.  U (m x n, ldu >= n)
  * receives the polar factor; H (n x n, ldh >= n) receives
  * (U^T A + A^T U) / 2 (the paper's H = U^T A, symmetrised) unless H is NULL.
  * U and H must not overlap A, each other or the workspace.
- * workspace: device memory of at least la_polar_workspace_size() bytes,
- * 256-byte aligned.  Runs on hip_stream and returns after the last kernel
- * has completed (it reads one FP64 norm back per iteration).
+ * workspace: device memory of la_polar_workspace_size() bytes (less its
+ * optional part), 256-byte aligned.  Runs on hip_stream and returns after the
+ * last kernel has completed (it reads one FP64 norm back per iteration, on
+ * small inputs once per batch of queued steps).
  * LA_ERR_NONFINITE if ||A||_F is 0, Inf or NaN, or a step norm is not
  * finite; LA_ERR_NOT_CONVERGED if the cap was hit (U then holds the last
  * iterate).  info may be NULL. */
@@ -210,7 +214,8 @@ la_status la_polar(la_context *ctx, int64_t m, int64_t n, const float *A,
  * library holds statically on every GPU it runs on (from the first la_create
  * on that device until the process ends).  Allocates nothing: no device or
  * host allocation is made by the call.  LA_ERR_TOO_LARGE if
- * la_polar_workspace_size(m, n, opts) exceeds LA_POLAR_NOALLOC_BYTES (square
+ * la_polar_workspace_size(m, n, opts), less its optional part, exceeds
+ * LA_POLAR_NOALLOC_BYTES (square
  * inputs up to about n = 2000 fit at the default options).  The buffer keeps
  * the last call's contents (nothing in it needs to start at zero), and all
  * calls on one GPU share it: calls that overlap in time on one GPU (from

@@ -14,9 +14,10 @@
 //      NS_Polar, first step);
 //   2. advances every active request of the band, the new ones included, by
 //      one iteration of Algorithm NS_Polar (a preconditioning step, eqs.
-//      a_def-RogueMatrix, or a Newton-Schulz step, eq. NewtonSchulz): one
-//      grouped Gram launch and one grouped update launch per precision and
-//      tile class cover all of them, whatever their sizes; the tick's
+//      a_def-RogueMatrix, or a Newton-Schulz step, eq. NewtonSchulz): a Gram
+//      phase and an update phase cover all of them, each one grouped launch for
+//      the direct tile classes, whatever the requests' sizes and arithmetics,
+//      and one per precision and class for the staged ones; the tick's
 //      descriptors, tile items and reduce items go up in one copy, and the
 //      launches of a phase run side by side on up to four streams (a launch
 //      of a few large-tile problems fills only part of the device);
