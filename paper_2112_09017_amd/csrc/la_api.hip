@@ -155,6 +155,13 @@ int gram_splits(int64_t m, int64_t n, int prec, int64_t max_acc)
 size_t align_up256(size_t x) { return (x + 255) & ~(size_t)255; }
 static size_t align256(size_t x) { return align_up256(x); }
 
+// A region for packed operands; a product whose packs don't fit it runs unpacked,
+// with the same result.
+struct PackBuf {
+    char *p;        // null: none
+    size_t bytes;
+};
+
 struct PolarWs {
     float *X;        // m x n, ld n: the iterate's second buffer
     float *P;        // n x n: I - c U^T U or I - U^T U
@@ -162,7 +169,7 @@ struct PolarWs {
     double *tiles;   // per-tile (or per-block) step-norm partials
     double *sumsq;   // norm partials
     double *scal;    // [0] ||A||_F^2, [1] ||U' - U||_F^2
-    char *pk;        // packed 3xBF16 copies of U and P for the update (may be null)
+    PackBuf pk;      // packed copies of U and P for the update, or of U^T for the Gram
     PolarChain chain;   // where col is not null
     size_t parts_floats;
 };
@@ -212,17 +219,18 @@ static size_t pack_small_bytes(int prec, int64_t M, int64_t N, int64_t K)
     return align_up256(packed_x3_bytes(M, K)) + align_up256(packed_x3_bytes(N, K));
 }
 
-// Launch d, through the packed-operand kernel when it qualifies and pk (of at
-// least pack_bytes) is given: op(A) and op(B)^T are packed into pk first,
+// Launch d, through the packed-operand kernel when it qualifies and its packs fit
+// pk: op(A) and op(B)^T are packed into pk first,
 // unless an operand packed earlier is passed (pre_a / pre_b).  K-slices of d
 // (d.slices > 1) run on whichever kernel is chosen; d's tile counts are those of
 // the launch.
-static hipError_t gemm_packed_or_plain(int prec, GemmDesc &d, char *pk, hipStream_t s,
+static hipError_t gemm_packed_or_plain(int prec, GemmDesc &d, PackBuf pk, hipStream_t s,
                                        const char *pre_a = nullptr, const char *pre_b = nullptr)
 {
-    if (pk && !d.gram &&
+    const size_t ab = align_up256(packed_x3_bytes(d.M, d.K));
+    if (pk.p && !d.gram && ab + align_up256(packed_x3_bytes(d.N, d.K)) <= pk.bytes &&
         ((!d.small && packs(prec, d.M, d.N, d.K)) || packs_small(prec, d))) {
-        char *pa = pk, *pb = pk + align_up256(packed_x3_bytes(d.M, d.K));
+        char *pa = pk.p, *pb = pk.p + ab;
         hipError_t e = hipSuccess;
         if (!pre_a)
             e = launch_pack(prec, d.A, d.lda, d.a_kcontig, d.M, d.K, d.scale_a, pa, s);
@@ -264,20 +272,30 @@ static size_t packed_update_bytes(const PolarPlan &p)
     return b;
 }
 
-// The same region for iterates of the small class.  It is part of what
-// la_polar_workspace_size asks for, but a workspace without it is taken, and
-// gives the same result on unpacked operands.
+// Bytes by which that region has to grow for the products of the small class that
+// pack.  It is part of what la_polar_workspace_size asks for, but a
+// workspace without it is taken, and gives the same result on unpacked operands.
 static size_t packed_small_bytes(const PolarPlan &p)
 {
-    if (packed_update_bytes(p))
-        return 0;
     size_t b = 0;
     for (int pr : {p.prec_pre, p.prec_ns}) {
-        const size_t u = pack_small_bytes(pr, p.m, p.n, p.n);
-        if (u)
-            b = std::max(b, std::max(u, align_up256(packed_x3_bytes(p.n, p.m))));
+        if (!two_term(pr))
+            continue;
+        b = std::max(b, pack_small_bytes(pr, p.m, p.n, p.n));
+        GemmDesc g;
+        memset(&g, 0, sizeof g);
+        g.M = p.n;
+        g.N = p.n;
+        g.K = p.m;
+        g.lda = p.n;
+        g.ldb = p.n;
+        g.gram = 1;
+        gemm_finalize(g, pr);
+        if (packs_small(pr, g))
+            b = std::max(b, align_up256(packed_x3_bytes(p.n, p.m)));
     }
-    return b;
+    const size_t have = packed_update_bytes(p);
+    return b > have ? b - have : 0;
 }
 
 // Slices of the update X P (K = n) and of each half of H (K = m).
@@ -410,27 +428,28 @@ static PolarWs carve(const PolarPlan &p, void *ws, bool room, bool chain)
     b += align256((size_t)sumsq_num_partials() * sizeof(double));
     w.scal = (double *)b;
     b += align256(8 * sizeof(double));
-    w.pk = packed_update_bytes(p) || (room && packed_small_bytes(p)) ? b : nullptr;
+    w.pk.bytes = packed_update_bytes(p) + (room ? packed_small_bytes(p) : 0);
+    w.pk.p = w.pk.bytes ? b : nullptr;
     memset(&w.chain, 0, sizeof w.chain);
     if (chain) {
         w.chain = polar_chain_carve(p, b);
-        w.pk = nullptr;
+        w.pk = PackBuf{};
     }
     return w;
 }
 
 // Launch the Gram-mode product d (k-major operands).  Where both operands are
-// one matrix and it qualifies, X^T is packed once into pk (if given) and read as
+// one matrix, it qualifies and X^T fits pk, X^T is packed once into pk and read as
 // both; the packed kernel computes every product exactly as the unpacked one.
-static hipError_t gram_packed_or_plain(int prec, GemmDesc &d, char *pk, hipStream_t s)
+static hipError_t gram_packed_or_plain(int prec, GemmDesc &d, PackBuf pk, hipStream_t s)
 {
-    if (pk && d.A == d.B && d.lda == d.ldb &&
+    if (pk.p && d.A == d.B && d.lda == d.ldb && packed_x3_bytes(d.N, d.K) <= pk.bytes &&
         ((!d.small && gram_packs(prec, d.K, d.N)) || packs_small(prec, d))) {
-        hipError_t e = launch_pack(prec, d.A, d.lda, 0, d.N, d.K, d.scale_a, pk, s);
+        hipError_t e = launch_pack(prec, d.A, d.lda, 0, d.N, d.K, d.scale_a, pk.p, s);
         if (e != hipSuccess)
             return e;
-        d.A = (const float *)pk;
-        d.B = (const float *)pk;
+        d.A = (const float *)pk.p;
+        d.B = (const float *)pk.p;
         gemm_set_packed(d);
         return launch_gemm_packed(prec, d, s);
     }
@@ -445,7 +464,7 @@ static hipError_t gram_packed_or_plain(int prec, GemmDesc &d, char *pk, hipStrea
 static hipError_t gram_slices(int prec, const float *X1, int64_t ld1, float sc1,
                               const float *X2, int64_t ld2, float sc2, int64_t K, int64_t n,
                               int want, float *parts, int *count, hipStream_t s,
-                              char *pk = nullptr)
+                              PackBuf pk = PackBuf{})
 {
     GemmDesc d;
     memset(&d, 0, sizeof d);
@@ -716,7 +735,7 @@ struct InvWs {
     double *tiles;   // per-tile step-norm partials
     double *sumsq;   // norm partials
     double *scal;    // [0] ||A A^T||_F^2, [1] ||X' - X||_F^2
-    char *pk;        // packed 3xBF16 operands of the step's products (may be null)
+    PackBuf pk;      // packed operands of the step's products
     char *pka;       // A packed once for the first product (may be null)
 };
 
@@ -741,22 +760,21 @@ static size_t inverse_pack_bytes(const InvPlan &p)
     return inverse_step_pack_bytes(p) + inverse_a_pack_bytes(p);
 }
 
-// The same regions for products of the small class (used where the workspace
-// has room, as la_polar's).
+// The same regions with products of the small class too, where those need more (used
+// where the workspace has room, as la_polar's).
 static size_t inverse_small_step_bytes(const InvPlan &p)
 {
-    if (inverse_pack_bytes(p))
-        return 0;
     const int64_t k1 = p.wide ? p.m : p.n, k2 = p.wide ? p.n : p.m;
-    return std::max(pack_small_bytes(p.prec, p.r, p.r, k1), pack_small_bytes(p.prec, p.m, p.n, k2));
+    const size_t have = inverse_step_pack_bytes(p);
+    const size_t b = std::max(have, std::max(pack_small_bytes(p.prec, p.r, p.r, k1),
+                                             pack_small_bytes(p.prec, p.m, p.n, k2)));
+    return b > have ? b : 0;
 }
 
 static size_t inverse_small_a_bytes(const InvPlan &p)
 {
     const int64_t k1 = p.wide ? p.m : p.n;
-    return inverse_small_step_bytes(p) && pack_small_bytes(p.prec, p.r, p.r, k1)
-               ? align_up256(packed_x3_bytes(p.r, k1))
-               : 0;
+    return pack_small_bytes(p.prec, p.r, p.r, k1) ? align_up256(packed_x3_bytes(p.r, k1)) : 0;
 }
 
 static size_t inverse_small_pack_bytes(const InvPlan &p)
@@ -790,13 +808,17 @@ static InvWs inverse_carve(const InvPlan &p, void *ws, bool room)
     b += align256((size_t)sumsq_num_partials() * sizeof(double));
     w.scal = (double *)b;
     b += align256(8 * sizeof(double));
-    w.pk = inverse_step_pack_bytes(p) ? b : nullptr;
-    b += inverse_step_pack_bytes(p);
+    w.pk.bytes = inverse_step_pack_bytes(p);
+    w.pk.p = w.pk.bytes ? b : nullptr;
+    b += w.pk.bytes;
     w.pka = inverse_a_pack_bytes(p) ? b : nullptr;
+    b += inverse_a_pack_bytes(p);
     if (room && inverse_small_step_bytes(p)) {
-        w.pk = b;
-        w.pka = inverse_small_a_bytes(p) ? b + inverse_small_step_bytes(p) : nullptr;
+        w.pk.p = b;
+        w.pk.bytes = inverse_small_step_bytes(p);
     }
+    if (room && inverse_small_a_bytes(p))
+        w.pka = b + inverse_small_step_bytes(p);
     return w;
 }
 
