@@ -73,7 +73,8 @@ typedef enum {
  *            it: each operand, times a power of two, as two fp16 terms of 23
  *            bits together, products lh + hl + hh, whose measured error is no
  *            larger; reported as BF16X6), Newton-Schulz at BF16X3;
- *            la_inverse -> BF16X3 steps and one BF16X6 step; la_matfunc_* ->
+ *            la_inverse -> BF16X3 steps and one BF16X6 step (on the larger
+ *            sizes an equivalent of two scaled fp16 terms); la_matfunc_* ->
  *            BF16X6.
  * The paper's TPU "fp32" matmul is itself a bf16-based emulation at about
  * six times the bf16 cost (section II); BF16X6 is the analogue here. */

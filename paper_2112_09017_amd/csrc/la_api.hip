@@ -679,7 +679,7 @@ struct InvPlan {
     int64_t r;       // side of the formed product
     int wide;        // 1: n <= m (forms A X); 0: n > m (forms X A)
     double eps;
-    int max_iter, polish, literal;
+    int max_iter, polish, literal, f16_polish;
     int prec;
 };
 
@@ -709,12 +709,13 @@ static la_status inverse_plan(int64_t n, int64_t m, const la_inverse_opts *opts,
     p.r = p.wide ? n : m;
     p.eps = o.eps > 0.0 ? o.eps : ldexp(1.0, -24);
     p.max_iter = o.max_iter > 0 ? o.max_iter : 100;
-    // AUTO: 3xBF16 steps, then one 6xBF16 step.  Forming I - A X near the
-    // fixed point cancels to O(1) from terms of size ~cond(A), so the dropped
-    // lo*lo products of 3xBF16 (2^-18 relative) limit its accuracy; the
-    // iteration converges quadratically, so one 6xBF16 step restores FP32-level
-    // accuracy.
+    // AUTO: 3xBF16 steps, then one at FP32 level (6xBF16, or F16X3 on the larger
+    // sizes: polish_f16).  Forming I - A X near the fixed point cancels to O(1) from
+    // terms of size ~cond(A), so the dropped lo*lo products of 3xBF16 (2^-18
+    // relative) limit its accuracy; the iteration converges quadratically, so one
+    // such step restores FP32-level accuracy.
     p.polish = o.polish != 0 || o.prec == LA_PREC_AUTO;
+    p.f16_polish = o.prec == LA_PREC_AUTO;
     p.literal = o.literal_delta != 0;
     p.prec = resolve_prec(o.prec, PREC_BF16X3);
     *out = p;
@@ -737,6 +738,7 @@ struct InvWs {
     double *scal;    // [0] ||A A^T||_F^2, [1] ||X' - X||_F^2
     PackBuf pk;      // packed operands of the step's products
     char *pka;       // A packed once for the first product (may be null)
+    uint32_t *mx;    // maxima of an F16X3 polish product's rows and columns (may be null)
 };
 
 // Packed operands of the larger of the two products of a step: R = A X
@@ -782,6 +784,28 @@ static size_t inverse_small_pack_bytes(const InvPlan &p)
     return inverse_small_step_bytes(p) + inverse_small_a_bytes(p);
 }
 
+// Whether an M x N x K product of AUTO's polish step runs as F16X3, each row of
+// op(A) and column of op(B) scaled by its own largest entry, instead of 6xBF16:
+// where the step's products pack (pk) and K is deep enough, as for the matrix
+// functions, that its fewer accumulation roundings outweigh one bit less per
+// operand.  (3000^2: a product 438 us at 6xBF16, 160 and 70 for the maxima and packs,
+// the inverse 7.72 -> 7.21 ms; its error at cond 10 1.17e-6 -> 8.9e-7, cond 30 2.27e-6
+// -> 1.66e-6.)
+static bool polish_f16(const InvPlan &p, const GemmDesc &d)
+{
+    return p.f16_polish && d.K >= 1024 &&
+           ((!d.small && packs(PREC_F16X3, d.M, d.N, d.K)) || packs_small(PREC_F16X3, d));
+}
+
+// Bytes of the maxima those products need (part of the size asked for; a workspace
+// without them polishes at 6xBF16).
+static size_t inverse_max_bytes(const InvPlan &p)
+{
+    return p.f16_polish && (inverse_step_pack_bytes(p) || inverse_small_step_bytes(p))
+               ? 2 * align_up256((size_t)std::max(p.m, p.n) * sizeof(uint32_t))
+               : 0;
+}
+
 static size_t inverse_workspace_bytes(const InvPlan &p)
 {
     size_t b = 0;
@@ -794,10 +818,12 @@ static size_t inverse_workspace_bytes(const InvPlan &p)
     return b;
 }
 
-static InvWs inverse_carve(const InvPlan &p, void *ws, bool room)
+static InvWs inverse_carve(const InvPlan &p, void *ws, bool room, bool max_room)
 {
     InvWs w;
     char *b = (char *)ws;
+    w.mx = max_room ? (uint32_t *)(b + inverse_workspace_bytes(p) + inverse_small_pack_bytes(p))
+                    : nullptr;
     w.X = (float *)b;
     b += align256((size_t)p.m * p.n * sizeof(float));
     w.R = (float *)b;
@@ -842,6 +868,29 @@ static bool queues_ahead(const InvPlan &p, int64_t ldx)
     return true;
 }
 
+// A product of the polish step (op(A) k contiguous, op(B) row-contiguous) as F16X3,
+// packed into w.pk.
+static hipError_t polish_product(const InvPlan &p, GemmDesc &d, const InvWs &w, hipStream_t s)
+{
+    uint32_t *ra = w.mx, *cb = w.mx + align_up256((size_t)std::max(p.m, p.n) * 4) / 4;
+    char *pa = w.pk.p, *pb = w.pk.p + align_up256(packed_x3_bytes(d.M, d.K));
+    hipError_t e = launch_absmax(d.A, d.lda, d.M, d.K, 1, ra, s);
+    if (e == hipSuccess)
+        e = launch_absmax(d.B, d.ldb, d.K, d.N, 0, cb, s);
+    if (e == hipSuccess)
+        e = launch_pack(PREC_F16X3, d.A, d.lda, 1, d.M, d.K, 1.0f, pa, s, ra);
+    if (e == hipSuccess)
+        e = launch_pack(PREC_F16X3, d.B, d.ldb, 0, d.N, d.K, 1.0f, pb, s, cb);
+    if (e != hipSuccess)
+        return e;
+    d.A = (const float *)pa;
+    d.B = (const float *)pb;
+    d.row_max = ra;
+    d.col_max = cb;
+    gemm_set_packed(d);
+    return launch_gemm_packed(PREC_F16X3, d, s);
+}
+
 // One step X' = X + X (I - A X)  (wide / square)  or  X + (I - X A) X  (tall),
 // with FP64 per-tile partials of (X' - X)^2 in w.tiles.
 static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64_t lda,
@@ -875,10 +924,23 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
         d.K = p.n;
     }
     gemm_finalize(d, prec);
-    // A was packed once for the step precision (the polish step does not pack)
+    // A was packed once for the step precision (the polish step packs its own)
     const char *pre = prec == p.prec ? w.pka : nullptr;
-    hipError_t e = gemm_packed_or_plain(prec, d, w.pk, s, p.wide ? pre : nullptr,
-                                        p.wide ? nullptr : pre);
+    auto f16 = [&](GemmDesc &g) {
+        if (prec != PREC_BF16X6 || !w.mx ||
+            align_up256(packed_x3_bytes(g.M, g.K)) + align_up256(packed_x3_bytes(g.N, g.K)) >
+                w.pk.bytes)
+            return false;
+        GemmDesc t = g;
+        gemm_finalize(t, PREC_F16X3);
+        if (!polish_f16(p, t))
+            return false;
+        g = t;
+        return true;
+    };
+    hipError_t e = f16(d) ? polish_product(p, d, w, s)
+                          : gemm_packed_or_plain(prec, d, w.pk, s, p.wide ? pre : nullptr,
+                                                 p.wide ? nullptr : pre);
     if (e != hipSuccess)
         return e;
 
@@ -912,7 +974,7 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
     }
     u.stop = stop;
     gemm_finalize(u, prec);
-    e = gemm_packed_or_plain(prec, u, w.pk, s);
+    e = f16(u) ? polish_product(p, u, w, s) : gemm_packed_or_plain(prec, u, w.pk, s);
     *ntiles = u.tiles_m * u.tiles_n;
     return e;
 }
@@ -1526,7 +1588,7 @@ size_t la_inverse_workspace_size(int64_t n, int64_t m, const la_inverse_opts *op
     InvPlan p;
     if (inverse_plan(n, m, opts, &p) != LA_OK)
         return 0;
-    return inverse_workspace_bytes(p) + inverse_small_pack_bytes(p);
+    return inverse_workspace_bytes(p) + inverse_small_pack_bytes(p) + inverse_max_bytes(p);
 }
 
 la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int64_t lda,
@@ -1563,10 +1625,12 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
     }
     LA_HIP(hipSetDevice(ctx->device), "la_inverse: hipSetDevice");
     hipStream_t s = (hipStream_t)hip_stream;
-    const size_t full = need + inverse_small_pack_bytes(p);
-    const bool room = ws_bytes >= full && !overlaps(workspace, full, A, ab) &&
-                      !overlaps(workspace, full, X, xb);
-    InvWs w = inverse_carve(p, workspace, room);
+    auto room = [&](size_t extra) {
+        return ws_bytes >= need + extra && !overlaps(workspace, need + extra, A, ab) &&
+               !overlaps(workspace, need + extra, X, xb);
+    };
+    const size_t packs_b = inverse_small_pack_bytes(p), max_b = inverse_max_bytes(p);
+    InvWs w = inverse_carve(p, workspace, room(packs_b), max_b && room(packs_b + max_b));
 
     la_inverse_info inf;
     memset(&inf, 0, sizeof inf);
