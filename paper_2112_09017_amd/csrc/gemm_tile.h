@@ -801,8 +801,15 @@ __device__ __forceinline__ void epilogue(const GemmDesc &d,
     const int64_t rb = row0 + wm * G::TM + (lane >> 5) * 4;
     const int64_t cb = col0 + wn * G::TN + (lane & 31);
     // rows and columns before the tile's own belong to its neighbours (row0 /
-    // col0 moved back inside the matrix)
+    // col0 moved back inside the matrix).  The tile's own are tested as 32-bit
+    // offsets, one unsigned compare each for both ends (four 64-bit compares an
+    // element cost short products 3 to 8%: 3392 x 4672 x 91 at 3xBF16 81 -> 88 us)
     const int64_t rlo = (int64_t)tm * Cfg<PREC>::BM, clo = (int64_t)tn * Cfg<PREC>::BN;
+    const uint32_t lr = (uint32_t)(rb - rlo), lc = (uint32_t)(cb - clo);
+    const int64_t rend = row0 + Cfg<PREC>::BM, cend = col0 + Cfg<PREC>::BN;
+    const uint32_t rspan = (uint32_t)((rend < d.M ? rend : d.M) - rlo);
+    const uint32_t cspan = (uint32_t)((cend < d.N ? cend : d.N) - clo);
+    const bool diag = d.gram && tm == tn;   // the other Gram tiles lie above the diagonal
     double ss = 0.0;
     const bool want_ss = d.partials != nullptr;
     // operands scaled row by row: their exponents come out of each element here,
@@ -839,7 +846,8 @@ __device__ __forceinline__ void epilogue(const GemmDesc &d,
 #pragma clang loop unroll(full)
             for (int e = 0; e < 16; ++e) {
                 const int64_t row = rb + i * 32 + (e >> 2) * 8 + (e & 3);
-                if (row < rlo || row >= d.M || col < clo || col >= d.N || (d.gram && row > col))
+                const uint32_t er = lr + i * 32 + (e >> 2) * 8 + (e & 3), ec = lc + j * 32;
+                if (er >= rspan || ec >= cspan || (diag && er > ec))
                     continue;
                 float val = d.alpha * acc[i][j][e];
                 float evv = 0.0f;
