@@ -992,6 +992,30 @@ static void gemm_packed_class(GemmDesc &d)
     gemm_set_packed(d);
 }
 
+// Tile class of an unpacked product that qualifies for 256 x 256 tiles: 128 x 128 ones
+// (the same sums) where their rounds, two workgroups per CU, come out cheaper.  A
+// round of the large ones starts and ends with nothing beside it on its CU, 35 us
+// that a short K does not repay.  Microseconds a round, measured from K = 64 to 1600
+// on five shapes (3392 x 4672 x 91 at 3xBF16 90 -> 36 us, 8000^2 x 400 286 -> 244,
+// 2900 x 12000 x 800 296 -> 225; 8000^2 x 1600 672 large against 706).
+static void gemm_pick_tiles(GemmDesc &d, int prec)
+{
+    if (d.small != kClassLarge || d.gram)
+        return;
+    double l0 = 34.5, lk = 0.0835, s0 = 9.4, sk = 0.049;   // 3xBF16
+    if (prec == PREC_FP32) {
+        l0 = 40.0, lk = 0.2535, s0 = 9.5, sk = 0.146;
+    } else if (prec == PREC_BF16X6) {
+        l0 = 36.0, lk = 0.14, s0 = 7.5, sk = 0.0853;
+        if (!d.a_kcontig && !d.b_kcontig)
+            s0 = 19.0, sk = 0.094;
+    }
+    auto tiles = [&](int64_t t) { return ((d.M + t - 1) / t) * ((d.N + t - 1) / t); };
+    const int64_t rl = (tiles(256) + 255) / 256, rs = (tiles(128) + 511) / 512;
+    if (rs * (s0 + sk * d.K) < 0.97 * rl * (l0 + lk * d.K))
+        gemm_set_class(d, prec, kClassSmall);
+}
+
 // Validation and descriptor of a la_gemm-style call.  *empty: nothing to do
 // (m or n is 0) after successful validation.
 static la_status gemm_prepare(const char *who, la_context *ctx, int trans_a, int trans_b,
@@ -1163,6 +1187,7 @@ la_status la_gemm(la_context *ctx, int trans_a, int trans_b, int64_t m, int64_t 
                                 beta, C, ldc, prec, &d, &p, &empty);
     if (st != LA_OK || empty)
         return st;
+    gemm_pick_tiles(d, p);
     LA_HIP(launch_gemm(p, d, (hipStream_t)hip_stream), "la_gemm: launch");
     return LA_OK;
 }
@@ -1276,6 +1301,7 @@ la_status la_gemm_ws(la_context *ctx, int trans_a, int trans_b, int64_t m, int64
     hipStream_t s = (hipStream_t)hip_stream;
     // packed path: 3xBF16 on large tiles with enough K to repay the pack pass
     if (p != PREC_BF16X3 || d.small || k < 256) {
+        gemm_pick_tiles(d, p);
         LA_HIP(launch_gemm(p, d, s), "la_gemm_ws: launch");
         return LA_OK;
     }
