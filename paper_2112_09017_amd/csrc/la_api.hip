@@ -1011,7 +1011,8 @@ static void gemm_pick_tiles(GemmDesc &d, int prec)
             s0 = 19.0, sk = 0.094;
     }
     auto tiles = [&](int64_t t) { return ((d.M + t - 1) / t) * ((d.N + t - 1) / t); };
-    const int64_t rl = (tiles(256) + 255) / 256, rs = (tiles(128) + 511) / 512;
+    // (the small ones start as others end, so a last partial round counts in part)
+    const double rl = (double)((tiles(256) + 255) / 256), rs = std::max(1.0, tiles(128) / 512.0);
     if (rs * (s0 + sk * d.K) < 0.97 * rl * (l0 + lk * d.K))
         gemm_set_class(d, prec, kClassSmall);
 }
