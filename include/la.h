@@ -69,10 +69,12 @@ typedef enum {
  *   BF16X6 : x = hi + mid + lo (three bf16 terms, 24 significant bits);
  *            products hh + hm + mh + mm + hl + lh.
  *   AUTO   : la_gemm -> BF16X3; la_polar -> per phase (see la_polar_opts):
- *            preconditioning and H at BF16X6 (from n = 192 as an equivalent of
- *            it: each operand, times a power of two, as two fp16 terms of 23
- *            bits together, products lh + hl + hh, whose measured error is no
- *            larger; reported as BF16X6), Newton-Schulz at BF16X3;
+ *            preconditioning and H at the FP32 level, Newton-Schulz at BF16X3.
+ *            The FP32 level is BF16X6, or, from n = 320 and if three quarters of
+ *            the entries in each row and column of A are at least 2^-18 ||A||_F,
+ *            two fp16 terms per operand (times a power of two, 23 bits together;
+ *            products lh + hl + hh), whose measured error on such inputs is no
+ *            larger; both are reported as BF16X6;
  *            la_inverse -> BF16X3 steps and one BF16X6 step (on the larger
  *            sizes an equivalent of two scaled fp16 terms); la_matfunc_* ->
  *            BF16X6.
@@ -157,9 +159,10 @@ typedef struct {
                          A / ||A||_F; fixes the preconditioning count     [2^-23] */
     double eps;       /* tolerance: stop once ||U' - U||_F <= max(M,N) eps [2^-23] */
     int max_iter;     /* cap on Newton-Schulz steps                     [100]   */
-    int prec_precond; /* la_precision of the preconditioning GEMMs [AUTO=BF16X6] */
+    int prec_precond; /* la_precision of the preconditioning GEMMs
+                         [AUTO = BF16X6 or its equivalent, see LA_PREC_AUTO]  */
     int prec_ns;      /* la_precision of the Newton-Schulz GEMMs   [AUTO=BF16X3] */
-    int prec_h;       /* la_precision of H = sym(U^T A)            [AUTO=BF16X6] */
+    int prec_h;       /* la_precision of H = sym(U^T A)  [AUTO as prec_precond] */
     int polish;       /* 1: one extra Newton-Schulz step at BF16X6 after the
                          stop test                                          [0] */
     int no_stagnation;/* 1: disable the stagnation stop                     [0] */
@@ -177,7 +180,8 @@ typedef struct {
     double fro_norm_a;   /* ||A||_F, accumulated in FP64 on the GPU            */
     double last_delta;   /* ||U' - U||_F of the last step (FP64)               */
     int stop_reason;     /* 0 tolerance, 1 stagnation, 2 iteration cap        */
-    int prec_precond;    /* resolved precisions actually used                 */
+    int prec_precond;    /* resolved precisions: BF16X6 for AUTO's FP32 level,
+                            whichever of its two forms ran                    */
     int prec_ns;
     int prec_h;
 } la_polar_info;

@@ -1395,10 +1395,11 @@ la_status la_polar_noalloc(la_context *ctx, int64_t m, int64_t n, const float *A
 
 namespace la {
 
-static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A, int64_t lda,
+static la_status polar_impl(la_context *ctx, const PolarPlan &plan, const float *A, int64_t lda,
                             float *U, int64_t ldu, float *H, int64_t ldh, void *workspace,
                             size_t ws_bytes, la_polar_info *info, void *hip_stream)
 {
+    PolarPlan p = plan;
     const int64_t m = p.m, n = p.n;
     if (lda < n || ldu < n || (H && ldh < n)) {
         set_error("la_polar: leading dimension smaller than n");
@@ -1434,7 +1435,7 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
                !overlaps(workspace, full, U, ub) && !overlaps(workspace, full, H, hb);
     };
     const size_t chain_bytes = polar_chain_bytes(p, ldu);
-    const bool chain = chain_bytes && room(chain_bytes);
+    bool chain = chain_bytes && room(chain_bytes);
     PolarWs w = carve(p, workspace, room(packed_small_bytes(p)), chain);
 
     la_polar_info inf;
@@ -1449,13 +1450,26 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
     float *buf[2] = {U, w.X};
     int64_t ld[2] = {ldu, n};
     int cur = 0;
-    double h2[2];
+    double h2[8];
     double fro = 0.0;
     StopState stop;
     bool converged = false, finite = true;
 
     LA_HIP(launch_sumsq(A, m, n, lda, w.sumsq, s), "la_polar: norm");
     const bool ahead = queues_ahead(p, ldu);
+    // an A too uneven for F16X3 runs those phases at 6xBF16 (the second iterate's
+    // buffer holds the counts, the state's spare words the answer)
+    const bool check = uses_f16(p, H != nullptr);
+    static_assert(sizeof(StepState) <= kUnevenWord * sizeof(double), "the state leaves the word");
+    uint32_t *uneven = (uint32_t *)(w.scal + kUnevenWord);
+    auto fall_back = [&]() {
+        uint32_t u = 0;
+        memcpy(&u, h2 + kUnevenWord, sizeof u);
+        if (!u)
+            return;
+        without_f16(p);
+        chain = chain && two_term(p.prec_pre);
+    };
     StepState *st = (StepState *)w.scal;
     const int *dev_stop = nullptr;
     auto bad_norm = [&]() {
@@ -1470,12 +1484,25 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &p, const float *A,
         dev_stop = &st->stop;
         LA_HIP(launch_scale_by_norm(A, lda, buf[cur], ld[cur], m, n, &st->norm2, s, dev_stop),
                "la_polar: scale");
+        if (check) {
+            LA_HIP(launch_uneven(A, lda, m, n, &st->norm2, nullptr, 0, (uint32_t *)w.X, uneven, s),
+                   "la_polar: unevenness");
+            LA_HIP(hipMemcpyAsync(h2, w.scal, sizeof h2, hipMemcpyDeviceToHost, s),
+                   "la_polar: readback");
+            LA_HIP(hipStreamSynchronize(s), "la_polar: sync");
+            fall_back();
+        }
     } else {
         // ||A||_F in FP64
         LA_HIP(launch_reduce_fixed(w.sumsq, sumsq_num_partials(), w.scal, s), "la_polar: norm");
-        LA_HIP(hipMemcpyAsync(h2, w.scal, sizeof(double), hipMemcpyDeviceToHost, s),
+        if (check)
+            LA_HIP(launch_uneven(A, lda, m, n, w.scal, nullptr, 0, (uint32_t *)w.X, uneven, s),
+                   "la_polar: unevenness");
+        LA_HIP(hipMemcpyAsync(h2, w.scal, sizeof h2, hipMemcpyDeviceToHost, s),
                "la_polar: readback");
         LA_HIP(hipStreamSynchronize(s), "la_polar: sync");
+        if (check)
+            fall_back();
         fro = sqrt(h2[0]);
         inf.fro_norm_a = fro;
         if (!(fro > 0.0) || !isfinite(fro))

@@ -190,6 +190,8 @@ struct StepTest {
     double scale, tol, stag_below;
     int tol_doubles, max_steps;
 };
+// word (of 8 bytes) of the 64-byte state regions that holds launch_uneven's answer
+constexpr int kUnevenWord = 6;
 hipError_t launch_norm_state(const double *parts, int64_t count, StepState *st, hipStream_t s);
 hipError_t launch_clear_state(StepState *st, hipStream_t s);
 hipError_t launch_step_state(const double *parts, int64_t count, StepState *st,
@@ -202,6 +204,17 @@ hipError_t launch_transpose_scale(const float *A, int64_t lda, float *X, int64_t
 hipError_t launch_absmax(const float *X, int64_t ldx, int64_t m, int64_t n, int by_row,
                          uint32_t *out, hipStream_t s);
 hipError_t launch_zero(uint32_t *out, int64_t count, hipStream_t s);
+// *flag = 1 if the m x n X (m, n >= 1) is too uneven for PREC_F16X3, else 0: more than
+// a quarter of the entries of some row or column fall below the magnitude from which
+// two scaled fp16 terms hold 23 bits.  Zeros count.  With nrm2 that is 2^-18 sqrt(*nrm2)
+// (operands scaled by sqrt(*nrm2) and kIterScale); else 2^-17 of the largest magnitude of
+// the entry's row (by_row) or column, given in mx.  A product with one operand that
+// is even in this sense has an error floor below the rounding of its accumulation,
+// whatever the other holds: every column of the other meets entries of the size of the
+// first one's largest.  counts: m + n words of scratch.
+hipError_t launch_uneven(const float *X, int64_t ldx, int64_t m, int64_t n, const double *nrm2,
+                         const uint32_t *mx, int by_row, uint32_t *counts, uint32_t *flag,
+                         hipStream_t s);
 // Y = s A + t I for an n x n A (FP64 per element, rounded once).
 hipError_t launch_affine(const float *A, int64_t lda, float *Y, int64_t ldy, int64_t n,
                          double sc, double t, hipStream_t s);

@@ -300,7 +300,9 @@ struct HipExec {
     void stage_need(const serve::Req &r, size_t *descs, size_t *items)
     {
         size_t it = 0;
-        int precs[3] = {r.plan.prec_pre, r.plan.prec_ns, r.plan.polish ? (int)PREC_BF16X6 : 0};
+        // (an input too uneven for F16X3 steps at BF16X6 instead)
+        int precs[4] = {r.plan.prec_pre, r.plan.prec_ns, r.plan.polish ? (int)PREC_BF16X6 : 0,
+                        uses_f16(r.plan, true) ? (int)PREC_BF16X6 : 0};
         for (int pr : precs) {
             if (!pr)
                 continue;
@@ -466,7 +468,12 @@ struct HipExec {
                    std::vector<double> &fro2, std::vector<double> &delta2)
     {
         hipError_t e = hipSuccess;
-        // 1. new requests: input, ||A||_F^2 in FP64, X0 = A / ||A||_F on the device
+        double *dev_d = (double *)(stage_dev + kUpBytes);
+        // 1. new requests: input, ||A||_F^2 in FP64, X0 = A / ||A||_F on the device,
+        // and for those with phases on F16X3 whether A is too uneven for it (the other
+        // iterate's buffer holds the counts), read back before their first step
+        uint32_t *uneven = (uint32_t *)dev_d;   // free until the tick's norms are written
+        std::vector<serve::Req *> checked;
         for (serve::Req *r : fresh) {
             DevReq *d = (DevReq *)r->x;
             if (e == hipSuccess)
@@ -478,7 +485,21 @@ struct HipExec {
                 e = launch_reduce_fixed(d->sumsq, sumsq_num_partials(), d->scal, stream);
             if (e == hipSuccess)
                 e = launch_scale_by_norm(d->A, r->n, d->X[0], r->n, r->m, r->n, d->scal, stream);
+            if (e == hipSuccess && uses_f16(r->plan, true)) {
+                e = launch_uneven(d->A, r->n, r->m, r->n, d->scal, nullptr, 0, (uint32_t *)d->X[1],
+                                  uneven + checked.size(), stream);
+                checked.push_back(r);
+            }
             d->cur = 0;
+        }
+        if (e == hipSuccess && !checked.empty()) {
+            e = hipMemcpyAsync(h_red, uneven, checked.size() * sizeof(uint32_t),
+                               hipMemcpyDeviceToHost, stream);
+            if (e == hipSuccess)
+                e = hipStreamSynchronize(stream);
+            for (size_t i = 0; i < checked.size() && e == hipSuccess; ++i)
+                if (((const uint32_t *)h_red)[i])
+                    without_f16(checked[i]->plan);
         }
         // 2. one step for every running request.  A tick whose requests would
         // fill the device twice over with large tiles runs all of them on large
@@ -494,7 +515,6 @@ struct HipExec {
         const bool all_large = large_load >= 2 * (int64_t)ctx->num_cus;
         std::vector<Launch> grams, updates;
         std::vector<ReduceItem> red;
-        double *dev_d = (double *)(stage_dev + kUpBytes);
         for (serve::Req *r : fresh)
             red.push_back(ReduceItem{((DevReq *)r->x)->scal, 1, dev_d + red.size()});
         for (serve::Req *r : run) {

@@ -48,8 +48,10 @@ constexpr double kMinSminus = 1e-3;
 // (smaller ones an absolute error of 2^-40).
 constexpr float kIterScale = 32768.0f;
 
-// Smallest n whose AUTO preconditioning and H run as F16X3 (see polar_plan).
-constexpr int64_t kF16MinN = 192;
+// Smallest n whose AUTO preconditioning and H run as F16X3 on even inputs (see
+// polar_plan): below it, where no packed copies are handed on, 6xBF16 costs as much
+// (whole polars, F16X3 / 6xBF16: 256^2 358 / 365 us, 300^2 392 / 400, 500^2 450 / 505).
+constexpr int64_t kF16MinN = 320;
 
 // Arithmetic of H = sym(U^T A) for ||A||_F = fro: *sc receives the F16X3 factor
 // of A, the power of two that takes fro, and so every |A_ij|, below 2^15.  An A
@@ -123,13 +125,15 @@ inline la_status polar_plan(int64_t m, int64_t n, const la_polar_opts *opts, Pol
         set_error("la_polar_opts: need %g <= s_minus < 1 and finite s0, eps", kMinSminus);
         return LA_ERR_INVALID_ARG;
     }
-    // AUTO's FP32-level phases run as F16X3 from n = kF16MinN: half the matrix
+    // AUTO's FP32-level phases run as F16X3 from n = kF16MinN where A is even enough
+    // (launch_uneven; otherwise the caller takes without_f16): half the matrix
     // core work of BF16X6, and half the FP32 accumulation roundings, which
     // outweigh its one bit less per operand.  Measured error of U against FP64
-    // (square A, cond 10 and 1e3, F16X3 / BF16X6): n = 64 2.98e-6 / 2.95e-6,
-    // 192 3.06e-6 / 3.11e-6, 1000 3.30e-6 / 3.63e-6, 4096 4.57e-6 / 5.75e-6;
-    // of H: 128 2.57e-6 / 2.54e-6, 192 2.57e-6 / 2.60e-6, 4096 2.86e-6 /
-    // 3.16e-6; below n = 192 the two cross, so the smaller sizes keep BF16X6.
+    // (square A, cond 10 and 1e3, F16X3 / BF16X6): n = 192 3.06e-6 / 3.11e-6, 1000
+    // 3.30e-6 / 3.63e-6, 4096 4.57e-6 / 5.75e-6; of H: 192 2.57e-6 / 2.60e-6, 4096
+    // 2.86e-6 / 3.16e-6.  The one factor for all of X leaves small entries an
+    // absolute error only: orthonormal columns times 1 .. 2^-20, 800 x 384, worst
+    // column of U 4.8e-5 against 3.0e-6, which is why uneven inputs keep BF16X6.
     // 16384^2: precond Gram 21.0 -> 10.7 ms, update 39.5 -> 20 ms, the whole
     // polar 1.288 -> 0.866 s; 131072 x 4096 0.653 -> 0.454 s.
     const int fp32_level = n >= kF16MinN ? (int)PREC_F16X3 : (int)PREC_BF16X6;
@@ -150,6 +154,20 @@ inline la_status polar_plan(int64_t m, int64_t n, const la_polar_opts *opts, Pol
     p.k_pre = k;
     *out = p;
     return LA_OK;
+}
+
+// Whether a polar at p (with H or not) has a phase on F16X3, and the plan of an input
+// too uneven for it (launch_uneven): those phases at BF16X6.
+inline bool uses_f16(const PolarPlan &p, bool want_h)
+{
+    return (p.prec_pre == PREC_F16X3 && p.k_pre > 0) || (p.prec_h == PREC_F16X3 && want_h);
+}
+inline void without_f16(PolarPlan &p)
+{
+    if (p.prec_pre == PREC_F16X3)
+        p.prec_pre = PREC_BF16X6;
+    if (p.prec_h == PREC_F16X3)
+        p.prec_h = PREC_BF16X6;
 }
 
 // Stop test of the Newton-Schulz loop: the algorithm's ||U' - U||_F <=
