@@ -864,9 +864,10 @@ __global__ __launch_bounds__(1024) void qr_form128_kernel(FormArgs a)
 // is in LDS.  Latency bound on the tree's upper levels and in
 // CAQR's panels, HBM bound on the leaves (64 columns, 131072 rows, tree of six
 // levels: 20 us a level on the vector units with an index division per element,
-// 8.7 us now; CAQR's panels of 6144 rows 12 -> 7.3 us).  out may equal in: a wave
-// reads its rows whole
-// before it writes any.
+// 8.7 us now; CAQR's panels of 6144 rows 12 -> 7.3 us); at most 32 columns take
+// B = 32, whose rows are not padded to 64 (la_wy of 1000000 x 32:
+// 334 -> 133 us).  out may equal in: a
+// wave reads its rows whole before it writes any.
 template <int B>
 __global__ __launch_bounds__(256) void rowmul_kernel(const float *in, int64_t ldi, Part part,
                                                      int single, int nc,
@@ -885,12 +886,20 @@ __global__ __launch_bounds__(256) void rowmul_kernel(const float *in, int64_t ld
         return;   // the whole workgroup
     const int64_t row = rbase + li;
     float x[HK];
-    const bool vec = nc == B && (ldi & 3) == 0 && ((uintptr_t)in & 15) == 0;
+    const bool vec = (nc & 3) == 0 && (ldi & 3) == 0 && ((uintptr_t)in & 15) == 0;
     const float *xr = in + row * ldi + h * HK;
-    if (vec && row < rend) {
+    if (vec && nc == B && row < rend) {
 #pragma unroll
         for (int q = 0; q < HK; q += 4) {
             const float4 v = *(const float4 *)(xr + q);
+            x[q] = v.x, x[q + 1] = v.y, x[q + 2] = v.z, x[q + 3] = v.w;
+        }
+    } else if (B == 32 && vec && row < rend) {
+#pragma unroll
+        for (int q = 0; q < HK; q += 4) {
+            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (h * HK + q < nc)
+                v = *(const float4 *)(xr + q);
             x[q] = v.x, x[q + 1] = v.y, x[q + 2] = v.z, x[q + 3] = v.w;
         }
     } else {
@@ -901,20 +910,21 @@ __global__ __launch_bounds__(256) void rowmul_kernel(const float *in, int64_t ld
     const float *M = Mb + (single ? 0 : b * nc * nc);
     if (nc == B && ((uintptr_t)M & 15) == 0) {
         constexpr int NV = B * B / 1024;   // 16-byte pieces per thread
+        constexpr int VS = NV < 4 ? NV : 4;
 #pragma unroll
-        for (int v0 = 0; v0 < NV; v0 += 4) {
-            float4 mv[4];
+        for (int v0 = 0; v0 < NV; v0 += VS) {
+            float4 mv[VS];
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
+            for (int v = 0; v < VS; ++v)
                 mv[v] = ((const float4 *)M)[(v0 + v) * 256 + t];
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
+            for (int v = 0; v < VS; ++v)
                 ((float4 *)ms)[(v0 + v) * 256 + t] = mv[v];
         }
     } else {
         for (int r = w; r < B; r += 4)
 #pragma unroll
-            for (int c = lane; c < B; c += 64)
+            for (int c = lane; c < B; c += 64)   // (B = 32: half of the wave)
                 ms[r * B + c] = r < nc && c < nc ? M[r * nc + c] : 0.0f;
     }
     if (sub) {
@@ -925,10 +935,16 @@ __global__ __launch_bounds__(256) void rowmul_kernel(const float *in, int64_t ld
     }
     if (wout && row < rend) {
         float *wr = wout + row * ldw + h * HK;
-        if (nc == B && (ldw & 3) == 0 && ((uintptr_t)wout & 15) == 0) {
+        const bool vecw = (nc & 3) == 0 && (ldw & 3) == 0 && ((uintptr_t)wout & 15) == 0;
+        if (vecw && nc == B) {
 #pragma unroll
             for (int q = 0; q < HK; q += 4)
                 *(float4 *)(wr + q) = make_float4(x[q], x[q + 1], x[q + 2], x[q + 3]);
+        } else if (B == 32 && vecw) {
+#pragma unroll
+            for (int q = 0; q < HK; q += 4)
+                if (h * HK + q < nc)
+                    *(float4 *)(wr + q) = make_float4(x[q], x[q + 1], x[q + 2], x[q + 3]);
         } else {
 #pragma unroll
             for (int q = 0; q < HK; ++q)
@@ -937,7 +953,7 @@ __global__ __launch_bounds__(256) void rowmul_kernel(const float *in, int64_t ld
         }
     }
     __syncthreads();
-    constexpr int NS = B == 64 ? 4 : 2;
+    constexpr int NS = B == 128 ? 2 : 4;
     f32x16_t acc[NS][NJ] = {};
 #pragma unroll
     for (int q = 0; q < HK / NS; ++q)
@@ -1192,6 +1208,17 @@ TsqrPlan tsqr_plan(int64_t m, int nc)
     return p;
 }
 
+hipError_t launch_rowmul(const float *in, int64_t ldi, const Part &part, int single, int nc,
+                         const float *Mb, float *out, int64_t ldo, float *wout, int64_t ldw,
+                         int sub, hipStream_t s)
+{
+    const dim3 grid(part.nb, kRows / kRowmulRows), block(256);
+    auto *k = nc <= 32 ? rowmul_kernel<32> : nc <= 64 ? rowmul_kernel<64> : rowmul_kernel<128>;
+    hipLaunchKernelGGL(k, grid, block, 0, s, in, ldi, part, single, nc, Mb, out, ldo, wout, ldw,
+                       sub);
+    return hipGetLastError();
+}
+
 template <int B>
 hipError_t tsqr_run_b(const float *A, int64_t lda, int nc, float *Q, int64_t ldq, float *R,
                       int64_t ldr, char *ws, const TsqrPlan &tp, char *kap, hipStream_t s)
@@ -1260,10 +1287,7 @@ hipError_t tsqr_run_b(const float *A, int64_t lda, int nc, float *Q, int64_t ldq
         const Part pl = make_part(tp.rows[l], nc);
         float *io = l == 0 ? Q : buf(l);
         const int64_t ld = l == 0 ? ldq : nc;
-        hipLaunchKernelGGL(rowmul_kernel<B>, dim3(pl.nb, kRows / kRowmulRows), dim3(256), 0, s,
-                           (const float *)io, ld, pl, 0, nc, (const float *)buf(l + 1), io, ld,
-                           (float *)nullptr, (int64_t)0, 0);
-        hipError_t e = hipGetLastError();
+        hipError_t e = launch_rowmul(io, ld, pl, 0, nc, buf(l + 1), io, ld, nullptr, 0, 0, s);
         if (e != hipSuccess)
             return e;
     }
@@ -1288,9 +1312,7 @@ hipError_t wy_run_b(int64_t m, int nc, const float *Q, int64_t ldq, float *W, in
     if (e != hipSuccess)
         return e;
     const Part p = make_part(m, nc);
-    hipLaunchKernelGGL(rowmul_kernel<B>, dim3(p.nb, kRows / kRowmulRows), dim3(256), 0, s, Q, ldq, p, 1,
-                       nc, (const float *)Minv, Y, ldy, W, ldw, 1);
-    return hipGetLastError();
+    return launch_rowmul(Q, ldq, p, 1, nc, Minv, Y, ldy, W, ldw, 1, s);
 }
 
 hipError_t wy_run(int64_t m, int nc, const float *Q, int64_t ldq, float *W, int64_t ldw, float *Y,
