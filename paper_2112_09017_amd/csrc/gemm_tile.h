@@ -116,15 +116,6 @@ template <> struct Cfg<PREC_F16X3 | kPacked> : Cfg<PREC_BF16X3 | kPacked> {};
 template <> struct Cfg<PREC_F16X3 | kPacked | kTile192> : Cfg<PREC_BF16X3 | kPacked | kTile192> {};
 template <> struct Cfg<PREC_F16X3 | kPacked | kTile128> : Cfg<PREC_BF16X3 | kPacked | kTile128> {};
 
-// Workgroups per CU a kernel is compiled for: the tile class's OCC, except
-// that the small 6xBF16 tile with both operands k-major (its loader keeps a
-// 64-bit address per row it loads) would spill at two and keeps one.
-template <int PREC, bool AKC, bool BKC>
-constexpr int kernel_occ()
-{
-    return (PREC == (PREC_BF16X6 | kSmall) && !AKC && !BKC) ? 1 : Cfg<PREC>::OCC;
-}
-
 template <int PREC> struct Geo {
     using C = Cfg<PREC>;
     static constexpr int NT = C::WM * C::WN * 64;
@@ -283,7 +274,10 @@ struct Loader {
     static_assert(UNITS % NT == 0, "every thread must own whole units");
     float v[UPT][R][8];
     float sc = 1.0f;  // the operand's factor before the split (PREC_F16X3)
-    int off[UPT];  // element offset of the unit's first element from the stage base
+    // offsets from the stage base: of the unit's first element in elements (KC), or of
+    // each of its 8 k in bytes
+    int off[UPT];
+    uint32_t koff[KC ? 1 : UPT][8];
 
     // (row, k8) of entry q of unit uid.  KC: within each 16 consecutive units
     // the row advances and k8 is fixed; k8 changes every 16 units, so a load
@@ -309,7 +303,13 @@ struct Loader {
         for (int u = 0; u < UPT; ++u) {
             const int uid = threadIdx.x + u * NT;
             const int row = row_of(uid, 0), k8 = k8_of(uid);
-            off[u] = KC ? (int)(row * ld + 8 * k8) : (int)(8 * k8 * ld + row);
+            if constexpr (KC) {
+                off[u] = (int)(row * ld + 8 * k8);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    koff[u][j] = 4u * ((uint32_t)(8 * k8 + j) * (uint32_t)ld + (uint32_t)row);
+            }
         }
     }
 
@@ -331,9 +331,21 @@ struct Loader {
                     }
                 }
             } else {
+                // One uniform address per stage and a 32-bit byte offset per k (at most
+                // 31 rows of less than 2^23 floats: below 2^32).  The base is opaque to
+                // the compiler, which would otherwise keep a 64-bit address per k and
+                // thread across the stages, 32 registers that the 6xBF16 kernels with
+                // both operands row-contiguous do not have: the large tile spilled
+                // right behind its loads, the small one ran one workgroup per CU
+                // (130 x 60000 x 300 96 -> 75 us)
+                uint64_t b0 = reinterpret_cast<uint64_t>(base);
+                asm("" : "+s"(b0));
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const auto p = gmem(base) + off[u] + (int64_t)j * ld;
+                    const auto p = reinterpret_cast<
+                        const __attribute__((address_space(1))) float *>(
+                        reinterpret_cast<const __attribute__((address_space(1))) char *>(b0) +
+                        koff[u][j]);
                     if constexpr (R == 4) {
                         const f32x4 a = *reinterpret_cast<gf32x4u *>(p);
 #pragma unroll
@@ -1161,7 +1173,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc &d, int tm, int tn, cha
 // ---------------------------------------------------------------- kernels
 
 template <int PREC, bool AKC, bool BKC>
-__global__ void __launch_bounds__(Geo<PREC>::NT, (kernel_occ<PREC, AKC, BKC>())) gemm_kernel(GemmDesc d)
+__global__ void __launch_bounds__(Geo<PREC>::NT, Cfg<PREC>::OCC) gemm_kernel(GemmDesc d)
 {
     __shared__ __attribute__((aligned(16))) char smem[2 * Geo<PREC>::stage_bytes];
     __shared__ double red[Cfg<PREC>::WM * Cfg<PREC>::WN];
@@ -1189,7 +1201,7 @@ __global__ void __launch_bounds__(Geo<PREC>::NT, (kernel_occ<PREC, AKC, BKC>()))
 // slice but the last is made of whole stages and keeps the operands' 16-byte
 // alignment.
 template <int PREC, bool AKC, bool BKC>
-__global__ void __launch_bounds__(Geo<PREC>::NT, (kernel_occ<PREC, AKC, BKC>()))
+__global__ void __launch_bounds__(Geo<PREC>::NT, Cfg<PREC>::OCC)
     gemm_sliced_kernel(GemmDesc d)
 {
     __shared__ __attribute__((aligned(16))) char smem[2 * Geo<PREC>::stage_bytes];
@@ -1212,7 +1224,7 @@ __global__ void __launch_bounds__(Geo<PREC>::NT, (kernel_occ<PREC, AKC, BKC>()))
 // as gemm_kernel would; it runs on XCD b % kXcds, so the caller places the
 // items on the XCDs by their position in the list.
 template <int PREC, bool AKC, bool BKC>
-__global__ void __launch_bounds__(Geo<PREC>::NT, (kernel_occ<PREC, AKC, BKC>()))
+__global__ void __launch_bounds__(Geo<PREC>::NT, Cfg<PREC>::OCC)
     gemm_items_kernel(const GemmDesc *__restrict__ probs, const GroupItem *__restrict__ items,
                       int num_items)
 {

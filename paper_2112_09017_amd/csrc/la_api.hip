@@ -1007,8 +1007,6 @@ static void gemm_pick_tiles(GemmDesc &d, int prec)
         l0 = 40.0, lk = 0.2535, s0 = 9.5, sk = 0.146;
     } else if (prec == PREC_BF16X6) {
         l0 = 36.0, lk = 0.14, s0 = 7.5, sk = 0.0853;
-        if (!d.a_kcontig && !d.b_kcontig)
-            s0 = 19.0, sk = 0.094;
     }
     auto tiles = [&](int64_t t) { return ((d.M + t - 1) / t) * ((d.N + t - 1) / t); };
     // (the small ones start as others end, so a last partial round counts in part)
