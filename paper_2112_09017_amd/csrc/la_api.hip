@@ -994,20 +994,19 @@ static void gemm_packed_class(GemmDesc &d)
 
 // Tile class of an unpacked product that qualifies for 256 x 256 tiles: 128 x 128 ones
 // (the same sums) where their rounds, two workgroups per CU, come out cheaper.  A
-// round of the large ones starts and ends with nothing beside it on its CU, 35 us
+// round of the large ones starts and ends with nothing beside it on its CU, 33 us
 // that a short K does not repay.  Microseconds a round, measured from K = 64 to 1600
-// on five shapes (3392 x 4672 x 91 at 3xBF16 90 -> 36 us, 8000^2 x 400 286 -> 244,
-// 2900 x 12000 x 800 296 -> 225; 8000^2 x 1600 672 large against 706).
+// on five shapes (3xBF16, large / small: 3392 x 4672 x 91 53 / 32 us, 8000^2 x 400 246 / 219,
+// 2900 x 12000 x 800 280 / 219, 8000^2 x 800 370 / 383, x 1600 642 / 712).
 static void gemm_pick_tiles(GemmDesc &d, int prec)
 {
     if (d.small != kClassLarge || d.gram)
         return;
-    double l0 = 34.5, lk = 0.0835, s0 = 9.4, sk = 0.049;   // 3xBF16
-    if (prec == PREC_FP32) {
+    double l0 = 33.5, lk = 0.0788, s0 = 8.3, sk = 0.0575;   // 3xBF16
+    if (prec == PREC_FP32)
         l0 = 40.0, lk = 0.2535, s0 = 9.5, sk = 0.146;
-    } else if (prec == PREC_BF16X6) {
-        l0 = 36.0, lk = 0.14, s0 = 7.5, sk = 0.0853;
-    }
+    else if (prec == PREC_BF16X6)
+        l0 = 32.5, lk = 0.1207, s0 = 6.0, sk = 0.0826;
     auto tiles = [&](int64_t t) { return ((d.M + t - 1) / t) * ((d.N + t - 1) / t); };
     // (the small ones start as others end, so a last partial round counts in part)
     const double rl = (double)((tiles(256) + 255) / 256), rs = std::max(1.0, tiles(128) / 512.0);

@@ -36,6 +36,22 @@ struct GemmDesc {
     int64_t lda, ldb, ldc, lde;
     int64_t M, N, K;
     float alpha, beta, gamma;
+    int a_kcontig, b_kcontig;
+    int gram;
+    int gram_upper;    // gram: write only the upper triangle (no mirror)
+    int vec_a, vec_b;  // the operand's leading dimension suits the loader's 32-bit offsets
+    int tiles_m, tiles_n;
+    int num_tiles;     // tiles launched (upper triangle only for gram)
+    int small;         // tile class (chosen from the problem's own shape)
+    int quarters;      // small tiles covering large Gram tiles tail_first.. (4 per tile)
+    int tail_first;
+    // split-K slices in one launch: slice y takes k in [y slice_k, min(K,
+    // (y + 1) slice_k)) and writes C + y slice_stride (slice_k a multiple of
+    // 32, so every slice but the last is whole K stages)
+    int slices;
+    int64_t slice_k, slice_stride;
+    // (what every launch reads ends here, in three lines of kernel arguments: each
+    // further line a kernel touches late is a read it waits for)
     // PREC_F16X3: powers of two op(A) and op(B) are multiplied by before their
     // split (the caller divides alpha by their product: gemm_f16_scales)
     float scale_a, scale_b;
@@ -44,21 +60,7 @@ struct GemmDesc {
     // null; out_max: optional, takes the maximum with each output column's
     const uint32_t *row_max, *col_max;
     uint32_t *out_max;
-    int a_kcontig, b_kcontig;
-    int gram;
-    int gram_upper;    // gram: write only the upper triangle (no mirror)
-    int vec_a, vec_b;  // the operand's leading dimension suits the loader's 32-bit offsets
-    int tiles_m, tiles_n;
-    int num_tiles;     // tiles launched (upper triangle only for gram)
-    int small;         // tile class (chosen from the problem's own shape)
     int ptile;         // packed operands: tile side, 256, 192 or 128 (gemm_set_packed)
-    int quarters;      // small tiles covering large Gram tiles tail_first.. (4 per tile)
-    int tail_first;
-    // split-K slices in one launch: slice y takes k in [y slice_k, min(K,
-    // (y + 1) slice_k)) and writes C + y slice_stride (slice_k a multiple of
-    // 32, so every slice but the last is whole K stages)
-    int slices;
-    int64_t slice_k, slice_stride;
     // direct classes: optional device word; while it is not 0 the launch leaves
     // its outputs as they are (a step queued past the iteration's stop)
     const int *stop;
