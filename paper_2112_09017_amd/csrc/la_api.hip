@@ -979,6 +979,33 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
     return e;
 }
 
+// Tile class of a caller's product whose 64 x 64 tiles take a third (FP32: also a fifth
+// or sixth) round of workgroups, one per CU each: 128 x 128 tiles instead unless K is
+// long enough to repay that round.  (us, direct / small, NN where not named: 1500^2 x 64
+// 3xBF16 17.0 / 12.8, x 256 22.9 / 18.9, x 640 31.5 / 31.2, x 2000 67 / 82, NT 76 / 82;
+// 6xBF16 x 256 24.1 / 22.3, x 600 36 / 39, x 2000 84 / 99, 1536^2 x 2048 NT 98 / 84; FP32
+// 529 tiles x 256 30.0 / 29.2, x 600 55 / 58, 576 tiles x 600 71 / 58, x 2000 163 / 168,
+// 1521 tiles x 256 58 / 52, x 1200 195 / 200.)  3xBF16 has one line for all layouts,
+// since la_gemm_packed gives the same bits for each.  The steps of the iterations keep
+// the direct class there, which lets them be queued ahead of their stop test.
+static void gemm_last_round(GemmDesc &d, int prec)
+{
+    constexpr int64_t kCus = 256;
+    const int64_t tiles = (int64_t)d.tiles_m * d.tiles_n;
+    if (d.small != kClassDirect64 || std::min(d.M, d.N) < 128 || tiles <= 2 * kCus)
+        return;
+    const bool nt = d.a_kcontig && d.b_kcontig, tn = !d.a_kcontig && !d.b_kcontig;
+    int64_t min_k;
+    if (prec != PREC_FP32)
+        min_k = prec != PREC_BF16X6 ? 640 : nt ? INT64_MAX : 320;
+    else if (2 * tiles <= 5 * kCus)
+        min_k = 256 + (nt ? 8 : tn ? 10 : 16) * std::max<int64_t>(0, tiles - 520);
+    else
+        min_k = 256 + 2 * std::max<int64_t>(0, tiles - 1089);
+    if (d.K < min_k)
+        gemm_set_class(d, prec, kClassSmall);
+}
+
 // Tile class of a product of packed operands: the direct class la_gemm would
 // take for the shape with dense operands (the same sums), else 256 x 256 tiles.
 static void gemm_packed_class(GemmDesc &d)
@@ -988,6 +1015,7 @@ static void gemm_packed_class(GemmDesc &d)
     t.ldb = std::max<int64_t>(d.K, 1);
     t.a_kcontig = t.b_kcontig = 1;
     gemm_finalize(t, PREC_BF16X3);
+    gemm_last_round(t, PREC_BF16X3);
     gemm_set_class(d, PREC_BF16X3, t.small);
     gemm_set_packed(d);
 }
@@ -1077,6 +1105,7 @@ static la_status gemm_prepare(const char *who, la_context *ctx, int trans_a, int
         d.beta = beta;
     }
     gemm_finalize(d, p);
+    gemm_last_round(d, p);
     *out = d;
     *prec_out = p;
     return LA_OK;
