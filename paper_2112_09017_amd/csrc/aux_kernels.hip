@@ -19,7 +19,7 @@ hipError_t launch_grouped_f16(int, int, int, const GemmDesc *, const GroupItem *
                               hipStream_t);
 hipError_t launch_pack_x3(const float *, int64_t, int, int64_t, int64_t, void *, hipStream_t);
 hipError_t launch_pack_f16(const float *, int64_t, int, int64_t, int64_t, float, const uint32_t *,
-                           void *, hipStream_t);
+                           void *, const int *, const PackCheck &, hipStream_t);
 hipError_t launch_gemm_packed_x3(const GemmDesc &d, hipStream_t s);
 hipError_t launch_gemm_packed_f16(const GemmDesc &d, hipStream_t s);
 hipError_t launch_grouped_fp32(int, int, int, const GemmDesc *, const GroupItem *, int,
@@ -193,11 +193,12 @@ hipError_t launch_gemm_grouped(int prec, int akc, int bkc, int cls, const GemmDe
 }
 
 hipError_t launch_pack(int prec, const float *X, int64_t ld, int kc, int64_t rows, int64_t k,
-                       float sc, void *out, hipStream_t s, const uint32_t *rmax)
+                       float sc, void *out, hipStream_t s, const uint32_t *rmax, const int *skip,
+                       const PackCheck &check)
 {
     switch (prec) {
     case PREC_BF16X3: return launch_pack_x3(X, ld, kc, rows, k, out, s);
-    case PREC_F16X3: return launch_pack_f16(X, ld, kc, rows, k, sc, rmax, out, s);
+    case PREC_F16X3: return launch_pack_f16(X, ld, kc, rows, k, sc, rmax, out, skip, check, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -437,73 +438,68 @@ __global__ void __launch_bounds__(kThreads) col_absmax_kernel(const float *__res
     }
 }
 
-// Entries too small for all bits of two scaled fp16 terms (launch_uneven), counted
-// per row and per column in one pass.  MODE 0: below 2^-18 sqrt(*nrm2); 1, 2: below
-// 2^-17 of the power of two under the largest magnitude of their row or column (mx;
-// a row or column of zeros has none).  A wave takes 16 rows of 256 columns: a
-// lane counts its four columns in registers, and lane i the ballots of row i, so
-// an even operand takes no atomics to speak of.  Bound by reading X on large inputs,
-// by its launches and the read of the answer on small ones (polar 320^2 388 -> 415 us,
-// 1000^2 907 -> 930, 16384^2 0.872 s either way).
-constexpr int kEvenRows = 16, kEvenGroups = 4;
-__device__ __forceinline__ float even_floor(uint32_t mx)
-{
-    return __uint_as_float(mx & 0x7f800000u) * 0x1p-17f;
-}
-template <int MODE>
+// Entries too small for all bits of two scaled fp16 terms, below 2^-18 sqrt(*nrm2),
+// counted per row and per column in one pass; whoever takes a count past its quarter
+// decides.  A wave takes 16 rows of 128 columns: a lane counts its two columns in
+// registers, and lane i the ballots of row i, so an even operand takes no atomics to
+// speak of.  Bound by reading X.  (Polars with this pass / without: 320^2 389 / 385 us,
+// 400^2 413 / 407, 1000^2 856 / 861, 16384^2 0.874 / 0.876 s.)
+constexpr int kEvenRows = 16, kEvenGroups = 2;
 __global__ void __launch_bounds__(kThreads)
     small_count_kernel(const float *__restrict__ X, int64_t ldx, int64_t m, int64_t n,
-                       const double *__restrict__ nrm2, const uint32_t *__restrict__ mx,
-                       uint32_t *__restrict__ rows, uint32_t *__restrict__ cols)
+                       const double *__restrict__ nrm2, uint32_t *counts, int *flag, StepState *st)
 {
     const int lane = threadIdx.x & 63;
+    bool bad = false;
     const int64_t c0 =
         (blockIdx.x * (int64_t)(kThreads / 64) + (threadIdx.x >> 6)) * (64 * kEvenGroups) + lane;
-    const float t = MODE == 0 ? (float)(sqrt(*nrm2) * 0x1p-18) : 0.0f;
-    float ct[kEvenGroups];
+    const float t = (float)(sqrt(*nrm2) * 0x1p-18);
     uint32_t cc[kEvenGroups] = {};
-#pragma unroll
-    for (int g = 0; g < kEvenGroups; ++g)
-        ct[g] = MODE == 2 && c0 + 64 * g < n ? even_floor(mx[c0 + 64 * g]) : t;
     for (int64_t r0 = blockIdx.y * (int64_t)kEvenRows; r0 < m;
          r0 += gridDim.y * (int64_t)kEvenRows) {
         uint32_t rc = 0;
 #pragma unroll
         for (int i = 0; i < kEvenRows; ++i) {
             const int64_t r = r0 + i < m ? r0 + i : m - 1;
-            const float rt = MODE == 1 ? even_floor(mx[r]) : 0.0f;
             uint32_t count = 0;
 #pragma unroll
             for (int g = 0; g < kEvenGroups; ++g) {
                 const int64_t c = c0 + 64 * g;
                 const float v = X[r * ldx + (c < n ? c : n - 1)];
-                const bool small =
-                    fabsf(v) < (MODE == 1 ? rt : ct[g]) && c < n && r0 + i < m;
+                const bool small = fabsf(v) < t && c < n && r0 + i < m;
                 cc[g] += small;
                 count += (uint32_t)__popcll(__ballot(small));
             }
             rc = lane == i ? count : rc;
         }
         if (lane < kEvenRows && rc)
-            atomicAdd(rows + r0 + lane, rc);
+            bad |= 4 * (int64_t)(atomicAdd(counts + r0 + lane, rc) + rc) > n;
     }
 #pragma unroll
     for (int g = 0; g < kEvenGroups; ++g)
         if (cc[g])
-            atomicAdd(cols + c0 + 64 * g, cc[g]);
+            bad |= 4 * (int64_t)(atomicAdd(counts + m + c0 + 64 * g, cc[g]) + cc[g]) > m;
+    if (!bad)
+        return;
+    if (flag)
+        *flag = 1;
+    if (st && atomicCAS(&st->stop, 0, 1) == 0)
+        st->reason = kReasonUneven;
 }
 
-// flag = 1 if more than a quarter of some row's or column's entries were counted
-// (counts: m rows, then n columns), else 0.
-__global__ void __launch_bounds__(1024) uneven_kernel(const uint32_t *__restrict__ counts,
-                                                      int64_t m, int64_t n, uint32_t *flag)
+// Y = X with row r times 2^s (unscale: 2^-s), s taking mx[r] (bits) to [2^14, 2^15), 0 for a
+// row of zeros or one that is not finite.
+__global__ void __launch_bounds__(kThreads)
+    scale_rows_kernel(const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t m, int64_t n,
+                      const uint32_t *__restrict__ mx, int unscale)
 {
-    bool bad = false;
-    for (int64_t i = threadIdx.x; i < m + n; i += 1024)
-        bad |= 4 * (int64_t)counts[i] > (i < m ? n : m);
-    const int any = __syncthreads_or(bad);
-    if (threadIdx.x == 0)
-        *flag = any ? 1 : 0;
+    for (int64_t r = blockIdx.y; r < m; r += gridDim.y) {
+        const uint32_t b = mx[r];
+        const int s = b == 0 || b >= 0x7f800000u ? 0 : 141 - (int)(b >> 23);
+        for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n;
+             c += (int64_t)gridDim.x * blockDim.x)
+            Y[r * ldy + c] = ldexpf(X[r * ldx + c], unscale ? -s : s);
+    }
 }
 
 // Y = s A + t I for an n x n A, in FP64 per element, rounded once (A is not
@@ -822,32 +818,26 @@ hipError_t launch_absmax(const float *X, int64_t ldx, int64_t m, int64_t n, int 
     return hipGetLastError();
 }
 
-hipError_t launch_uneven(const float *X, int64_t ldx, int64_t m, int64_t n, const double *nrm2,
-                         const uint32_t *mx, int by_row, uint32_t *counts, uint32_t *flag,
-                         hipStream_t s)
+hipError_t launch_scale_rows(const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t m,
+                             int64_t n, const uint32_t *mx, int unscale, hipStream_t s)
 {
-    hipError_t e = launch_zero(counts, m + n, s);
-    if (e != hipSuccess)
-        return e;
+    if (m == 0 || n == 0)
+        return hipSuccess;
+    hipLaunchKernelGGL(scale_rows_kernel, grid2d(m, n), dim3(kThreads), 0, s, X, ldx, Y, ldy, m, n,
+                       mx, unscale);
+    return hipGetLastError();
+}
+
+hipError_t launch_uneven(const float *X, int64_t ldx, int64_t m, int64_t n, const double *nrm2,
+                         uint32_t *counts, int *flag, StepState *st, hipStream_t s)
+{
     const int64_t gx = (n + kThreads * kEvenGroups - 1) / (kThreads * kEvenGroups);
     if (gx > 0x7fffffff)
         return hipErrorInvalidValue;
     const int64_t strips = (m + kEvenRows - 1) / kEvenRows;
     const int64_t gy = std::min<int64_t>(strips, std::max<int64_t>(1, 2048 / gx));
-    const dim3 grid((unsigned)gx, (unsigned)gy), block(kThreads);
-    if (nrm2)
-        hipLaunchKernelGGL(small_count_kernel<0>, grid, block, 0, s, X, ldx, m, n, nrm2, mx, counts,
-                           counts + m);
-    else if (by_row)
-        hipLaunchKernelGGL(small_count_kernel<1>, grid, block, 0, s, X, ldx, m, n, nrm2, mx, counts,
-                           counts + m);
-    else
-        hipLaunchKernelGGL(small_count_kernel<2>, grid, block, 0, s, X, ldx, m, n, nrm2, mx, counts,
-                           counts + m);
-    e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(uneven_kernel, dim3(1), dim3(1024), 0, s, counts, m, n, flag);
+    hipLaunchKernelGGL(small_count_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(kThreads), 0, s, X,
+                       ldx, m, n, nrm2, counts, flag, st);
     return hipGetLastError();
 }
 

@@ -246,7 +246,7 @@ __device__ __forceinline__ void direct_pack_out(const float *tile, char *out, in
 template <int PREC, class OA, class OB, int FM, int FN, int KW, int V>
 __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)[V][FM][FN],
                                                 int64_t row0, int64_t col0, int tm, int tn, int w,
-                                                int lane, int stop, float *red, double *red8)
+                                                int lane, float *red, double *red8)
 {
     constexpr int NE = FM * FN * 16, EPT = NE / KW, EPW = EPT * V, HW = KW / 2, PW = KW / V;
     static_assert(V == 1 || PW == HW, "a wave is one of the KW or a pair of them");
@@ -281,8 +281,6 @@ __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)
             s += at(v, element(q));
         out[q] = s;
     }
-    if (stop)
-        return;   // uniform over the launch
     const bool want_ss = d.partials != nullptr;
     double ss[V] = {};
     float ev[EPW];
@@ -368,11 +366,12 @@ __device__ __forceinline__ void direct_epilogue(const GemmDesc &d, f32x16 (&acc)
     }
 }
 
-// The sums of place w of the KW that share a tile, k in [kb, ke) of the operands.
+// The sums of place w of the KW that share a tile, k in [kb, ke) of the operands (left
+// undone with stop, looked at once the first loads are on their way).
 template <int PREC, bool AKC, bool BKC, int CLS>
 __device__ __forceinline__ void
 direct_sums(const GemmDesc &d, int64_t row0, int64_t col0, int64_t kb, int64_t ke, int w, int lane,
-            f32x16 (&acc)[DirectCfg<CLS>::FM][DirectCfg<CLS>::FN])
+            int stop, f32x16 (&acc)[DirectCfg<CLS>::FM][DirectCfg<CLS>::FN])
 {
     using G = DirectCfg<CLS>;
     constexpr int FM = G::FM, FN = G::FN, KW = G::KW;
@@ -404,6 +403,8 @@ direct_sums(const GemmDesc &d, int64_t row0, int64_t col0, int64_t kb, int64_t k
         for (int s = 0; s < D; ++s)
             fetch(s, min(s, cnt - 1));
     }
+    if (stop)
+        return;
     if (kn && w == nfull % KW) {
         float ta[FM][8], tb[FN][8];
         oa.load_tail(ta, kb + 16 * (int64_t)nfull, kn, lane);
@@ -435,14 +436,15 @@ __device__ __forceinline__ void direct_tile(const GemmDesc &d, int tm, int tn, i
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t row0 = (int64_t)tm * (32 * FM), col0 = (int64_t)tn * (32 * FN);
-    // read here, used by the epilogue: its latency is not waited for
     const int stop = d.stop ? *gmem(d.stop) : 0;
     f32x16 acc[V][FM][FN];
 #pragma unroll
     for (int v = 0; v < V; ++v)
-        direct_sums<PREC, AKC, BKC, CLS>(d, row0, col0, kb, ke, w + KW / V * v, lane, acc[v]);
+        direct_sums<PREC, AKC, BKC, CLS>(d, row0, col0, kb, ke, w + KW / V * v, lane, stop, acc[v]);
+    if (stop)
+        return;   // uniform over the launch
     direct_epilogue<PREC, DirectOperand<AKC, FM>, DirectOperand<BKC, FN>, FM, FN, KW, V>(
-        d, acc, row0, col0, tm, tn, w, lane, stop, red, red8);
+        d, acc, row0, col0, tm, tn, w, lane, red, red8);
 }
 
 template <int CLS> constexpr int direct_red_floats()
@@ -541,6 +543,8 @@ __device__ __forceinline__ void direct_packed_tile(const GemmDesc &d, int tm, in
             for (int s = 0; s < D; ++s)
                 fetch(s, min(s, cnt - 1));
         }
+        if (stop)
+            return;   // uniform over the launch
         int i = 0;
         for (; i + D <= cnt; i += D) {
 #pragma unroll
@@ -556,7 +560,7 @@ __device__ __forceinline__ void direct_packed_tile(const GemmDesc &d, int tm, in
                 direct_mfma<PREC, FM, FN>(a[s], b[s], acc[v]);
     }
     direct_epilogue<PREC, DirectOperand<true, FM>, DirectOperand<!PAIRS, FN>, FM, FN, KW, V>(
-        d, acc, row0, col0, tm, tn, w0, lane, stop, red, red8);
+        d, acc, row0, col0, tm, tn, w0, lane, red, red8);
 }
 
 template <int PREC, int CLS, bool PAIRS>

@@ -17,10 +17,11 @@ hipError_t launch_grouped_f16(int akc, int bkc, int cls, const GemmDesc *probs,
 }
 
 hipError_t launch_pack_f16(const float *X, int64_t ld, int kc, int64_t rows, int64_t k, float sc,
-                           const uint32_t *rmax, void *out, hipStream_t s)
+                           const uint32_t *rmax, void *out, const int *skip,
+                           const PackCheck &check, hipStream_t s)
 {
     return dev::launch_pack_x3<PREC_F16X3>(X, ld, kc, rows, k, sc, rmax, static_cast<char *>(out),
-                                           s);
+                                           skip, check, s);
 }
 
 hipError_t launch_gemm_packed_f16(const GemmDesc &d, hipStream_t s)

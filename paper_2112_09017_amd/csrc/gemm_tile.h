@@ -1301,9 +1301,12 @@ __global__ void __launch_bounds__(256) pack_x3_kernel(const float *__restrict__ 
                                                       int64_t R, int64_t K, int64_t kbt,
                                                       int64_t rbt, float sc,
                                                       const uint32_t *__restrict__ rmax,
-                                                      char *__restrict__ out)
+                                                      char *__restrict__ out, const int *skip,
+                                                      PackCheck check)
 {
     __shared__ float tile[32][kPackSlabK + 1];
+    if (base_prec(PREC) == PREC_F16X3 && skip && *skip)
+        return;
     const int t = threadIdx.x;
     for (int64_t rb = blockIdx.y; rb < rbt; rb += gridDim.y) {
         const int64_t r0 = rb * 32, k0 = (int64_t)blockIdx.x * kPackSlabK;
@@ -1363,6 +1366,30 @@ __global__ void __launch_bounds__(256) pack_x3_kernel(const float *__restrict__ 
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
                     v[j] = ldexpf(v[j], s);
+                if (check.counts) {
+                    // counted per row and per k (the wave holds 32 rows of 16); an even
+                    // operand takes no atomics to speak of
+                    const uint32_t mx = r0 + r < R ? rmax[r0 + r] : 0;
+                    uint32_t cr = 0;
+                    bool bad = false;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const bool few = mx && k0 + kk + j < K &&
+                                         (mx >= 0x7f800000u || fabsf(v[j]) < 0x1p-3f);
+                        const uint64_t b = __ballot(few);
+                        if (!b)
+                            continue;
+                        cr += few;
+                        const uint32_t ck =
+                            (uint32_t)__popc(lane < 32 ? (uint32_t)b : (uint32_t)(b >> 32));
+                        if ((lane & 31) == 0 && ck)
+                            bad |= 4 * (int64_t)(atomicAdd(check.counts + R + k0 + kk + j, ck) + ck) > R;
+                    }
+                    if (cr)
+                        bad |= 4 * (int64_t)(atomicAdd(check.counts + r0 + r, cr) + cr) > K;
+                    if (bad)
+                        atomicOr(check.flag, check.bit);
+                }
             }
             u32x4 parts[2];
             Split<PREC>::run(v, parts, sc);
@@ -1548,6 +1575,8 @@ __global__ void __launch_bounds__(256, Cfg<P>::OCC) gemm_packed_kernel(GemmDesc 
     constexpr int FM = G::FM, FN = G::FN, NS = kPackStages;
     __shared__ __attribute__((aligned(1024))) char smem[NS * G::stage_bytes];
     __shared__ double red[4];
+    if (base_prec(P) == PREC_F16X3 && d.stop && *gmem(d.stop))
+        return;
     int tm, tn;
     if (C::OCC == 1)
         round_tile_coords(d, tm, tn);
@@ -1734,7 +1763,8 @@ inline size_t packed_bytes(int64_t R, int64_t K)
 
 template <int PREC>
 hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t R, int64_t K, float sc,
-                          const uint32_t *rmax, char *out, hipStream_t s)
+                          const uint32_t *rmax, char *out, const int *skip,
+                          const PackCheck &check, hipStream_t s)
 {
     const int64_t rbt = packed_row_blocks(R);
     const int64_t kbt = (K + 15) / 16;
@@ -1746,10 +1776,10 @@ hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t R, int64_t
     const unsigned gy = (unsigned)(rbt < 65535 ? rbt : 65535);
     if (kc)
         hipLaunchKernelGGL((pack_x3_kernel<PREC, true>), dim3((unsigned)gx, gy), dim3(256), 0, s, X,
-                           ld, R, K, kbt, rbt, sc, rmax, out);
+                           ld, R, K, kbt, rbt, sc, rmax, out, skip, check);
     else
         hipLaunchKernelGGL((pack_x3_kernel<PREC, false>), dim3((unsigned)gx, gy), dim3(256), 0, s, X,
-                           ld, R, K, kbt, rbt, sc, rmax, out);
+                           ld, R, K, kbt, rbt, sc, rmax, out, skip, check);
     return hipGetLastError();
 }
 

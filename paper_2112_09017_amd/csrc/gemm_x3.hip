@@ -22,7 +22,7 @@ hipError_t launch_pack_x3(const float *X, int64_t ld, int kc, int64_t rows, int6
                           hipStream_t s)
 {
     return dev::launch_pack_x3<PREC_BF16X3>(X, ld, kc, rows, k, 1.0f, nullptr,
-                                            static_cast<char *>(out), s);
+                                            static_cast<char *>(out), nullptr, PackCheck(), s);
 }
 
 hipError_t launch_gemm_packed_x3(const GemmDesc &d, hipStream_t s)

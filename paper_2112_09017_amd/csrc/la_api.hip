@@ -494,7 +494,7 @@ static hipError_t gram_slices(int prec, const float *X1, int64_t ld1, float sc1,
 // chained: X's packed columns are there, and P is written packed too.
 static hipError_t gram_step(const PolarPlan &p, int prec, const float *X, int64_t ldx,
                             double alpha, double gamma, float *P, const PolarWs &w,
-                            hipStream_t s, bool chained = false)
+                            hipStream_t s, bool chained = false, const int *stop = nullptr)
 {
     const int64_t m = p.m, n = p.n;
     const int splits = gram_splits(m, n, prec, p.max_acc);
@@ -515,6 +515,7 @@ static hipError_t gram_step(const PolarPlan &p, int prec, const float *X, int64_
         d.K = m;
         d.alpha = (float)alpha;
         d.gamma = (float)gamma;
+        d.stop = stop;
         gemm_f16_scales(d, prec, kIterScale, kIterScale);
         gemm_finalize(d, prec);
         if (chained) {
@@ -923,6 +924,7 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
         d.b_kcontig = 0;
         d.K = p.n;
     }
+    d.stop = stop;
     gemm_finalize(d, prec);
     // A was packed once for the step precision (the polish step packs its own)
     const char *pre = prec == p.prec ? w.pka : nullptr;
@@ -1476,134 +1478,146 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &plan, const float 
     float *buf[2] = {U, w.X};
     int64_t ld[2] = {ldu, n};
     int cur = 0;
-    double h2[8];
+    double h2[2];
     double fro = 0.0;
     StopState stop;
     bool converged = false, finite = true;
 
     LA_HIP(launch_sumsq(A, m, n, lda, w.sumsq, s), "la_polar: norm");
     const bool ahead = queues_ahead(p, ldu);
-    // an A too uneven for F16X3 runs those phases at 6xBF16 (the second iterate's
-    // buffer holds the counts, the state's spare words the answer)
-    const bool check = uses_f16(p, H != nullptr);
-    static_assert(sizeof(StepState) <= kUnevenWord * sizeof(double), "the state leaves the word");
-    uint32_t *uneven = (uint32_t *)(w.scal + kUnevenWord);
-    auto fall_back = [&]() {
-        uint32_t u = 0;
-        memcpy(&u, h2 + kUnevenWord, sizeof u);
-        if (!u)
-            return;
-        without_f16(p);
-        chain = chain && two_term(p.prec_pre);
-    };
     StepState *st = (StepState *)w.scal;
-    const int *dev_stop = nullptr;
+    StepState h;
+    const int *dev_stop = ahead ? &st->stop : nullptr;
     auto bad_norm = [&]() {
         if (info)
             *info = inf;
         set_error("la_polar: ||A||_F = %g (zero or not finite)", fro);
         return LA_ERR_NONFINITE;
     };
-    if (ahead) {
-        // the norm stays on the device; an A without one stops every later write
+    // The norm; an A without one, or one too uneven for the F16X3 phases (the counts are
+    // in the second iterate's buffer), stops every later write of queued steps.  Steps
+    // that wait for the host take what they need from the readback of the norm.
+    auto begin = [&]() {
         LA_HIP(launch_norm_state(w.sumsq, sumsq_num_partials(), st, s), "la_polar: norm");
-        dev_stop = &st->stop;
-        LA_HIP(launch_scale_by_norm(A, lda, buf[cur], ld[cur], m, n, &st->norm2, s, dev_stop),
-               "la_polar: scale");
-        if (check) {
-            LA_HIP(launch_uneven(A, lda, m, n, &st->norm2, nullptr, 0, (uint32_t *)w.X, uneven, s),
+        if (ahead)
+            LA_HIP(launch_scale_by_norm(A, lda, buf[0], ld[0], m, n, &st->norm2, s, dev_stop),
+                   "la_polar: scale");
+        if (uses_f16(p, H != nullptr)) {
+            LA_HIP(launch_zero((uint32_t *)w.X, m + n, s), "la_polar: unevenness");
+            LA_HIP(launch_uneven(A, lda, m, n, &st->norm2, (uint32_t *)w.X, nullptr, st, s),
                    "la_polar: unevenness");
-            LA_HIP(hipMemcpyAsync(h2, w.scal, sizeof h2, hipMemcpyDeviceToHost, s),
-                   "la_polar: readback");
-            LA_HIP(hipStreamSynchronize(s), "la_polar: sync");
-            fall_back();
         }
-    } else {
-        // ||A||_F in FP64
-        LA_HIP(launch_reduce_fixed(w.sumsq, sumsq_num_partials(), w.scal, s), "la_polar: norm");
-        if (check)
-            LA_HIP(launch_uneven(A, lda, m, n, w.scal, nullptr, 0, (uint32_t *)w.X, uneven, s),
-                   "la_polar: unevenness");
-        LA_HIP(hipMemcpyAsync(h2, w.scal, sizeof h2, hipMemcpyDeviceToHost, s),
-               "la_polar: readback");
+        return LA_OK;
+    };
+    auto read_state = [&]() {
+        LA_HIP(hipMemcpyAsync(&h, st, sizeof h, hipMemcpyDeviceToHost, s), "la_polar: readback");
         LA_HIP(hipStreamSynchronize(s), "la_polar: sync");
-        if (check)
-            fall_back();
-        fro = sqrt(h2[0]);
+        return LA_OK;
+    };
+    auto fall_back = [&]() {
+        without_f16(p);
+        chain = chain && two_term(p.prec_pre);
+    };
+    la_status rc = begin();
+    if (rc != LA_OK)
+        return rc;
+    if (!ahead) {
+        rc = read_state();
+        if (rc != LA_OK)
+            return rc;
+        fro = sqrt(h.norm2);
         inf.fro_norm_a = fro;
         if (!(fro > 0.0) || !isfinite(fro))
             return bad_norm();
+        if (h.reason == kReasonUneven)
+            fall_back();
         LA_HIP(launch_scale(A, lda, buf[cur], ld[cur], m, n, fro, s), "la_polar: scale");
     }
 
     // preconditioning: U <- a U (I - c U^T U), c = (4/27) a^2
     // (chained from the second step on: X0 is not there packed)
     ChainStep cs{false, 0, 0, false};
-    const ChainStep *csp = chain ? &cs : nullptr;
-    for (int i = 0; i < p.k_pre; ++i) {
-        cs.cur = cur;
-        cs.only = i + 1 < p.k_pre;
-        cs.next_prec = cs.only ? p.prec_pre : p.prec_ns;
-        LA_HIP(gram_step(p, p.prec_pre, buf[cur], ld[cur], -p.c, 1.0, w.P, w, s, cs.packed),
-               "la_polar: precondition gram");
-        LA_HIP(update_step(p, p.prec_pre, buf[cur], ld[cur], w.P, p.a, 0.0, buf[cur ^ 1],
-                           ld[cur ^ 1], nullptr, nullptr, w, s, dev_stop, csp),
-               "la_polar: precondition update");
-        cs.packed = chain;
-        cur ^= 1;
-        inf.iters_precond++;
-    }
-    cs.next_prec = p.prec_ns;
-    cs.only = false;
-
-    // Newton-Schulz: U' = U + U (I - U^T U) / 2, delta = ||U' - U||_F, until the
-    // stop test (polar_host.h); a polish step runs at BF16X6
-    if (ahead) {
-        // Steps are queued in batches; the device applies the stop test after
-        // each, and from the stop on leaves the iterates alone.  256^2: 20 us
-        // of readback and wait per step saved, 540 -> 360 us for the polar
-        // (9 steps), at 10 us per step queued in vain.
-        StepTest t;
-        t.scale = 1.0;
-        t.tol = (double)std::max(m, n) * p.eps;
-        t.tol_doubles = 0;
-        t.stag_below = p.stagnation ? 1e-2 * sqrt((double)n) : 0.0;
-        t.max_steps = p.max_iter;
-        const int start = cur;
-        StepState h;
-        int queued = 0, batch = kFirstBatch;
-        do {
-            for (const int to = std::min(queued + batch, p.max_iter); queued < to; ++queued) {
-                int ntiles = 0;
-                cs.cur = cur;
-                LA_HIP(gram_step(p, p.prec_ns, buf[cur], ld[cur], -1.0, 1.0, w.P, w, s,
-                                 cs.packed),
-                       "la_polar: NS gram");
-                LA_HIP(update_step(p, p.prec_ns, buf[cur], ld[cur], w.P, 0.5, 1.0, buf[cur ^ 1],
-                                   ld[cur ^ 1], w.tiles, &ntiles, w, s, dev_stop, csp),
-                       "la_polar: NS update");
-                cs.packed = chain;
-                LA_HIP(launch_step_state(w.tiles, ntiles, st, t, s), "la_polar: delta");
-                cur ^= 1;
-            }
-            batch = kNextBatch;
-            LA_HIP(hipMemcpyAsync(&h, st, sizeof h, hipMemcpyDeviceToHost, s),
-                   "la_polar: readback");
-            LA_HIP(hipStreamSynchronize(s), "la_polar: sync");
-        } while (!h.stop);
-        fro = sqrt(h.norm2);
-        inf.fro_norm_a = fro;
-        if (!(fro > 0.0) || !isfinite(fro)) {
-            inf.iters_precond = 0;
-            return bad_norm();
+    const ChainStep *csp = nullptr;
+    // (an uneven input of queued steps goes through a second time)
+    for (bool again = true; again;) {
+        cs.packed = false;
+        csp = chain ? &cs : nullptr;
+        inf.iters_precond = 0;
+        for (int i = 0; i < p.k_pre; ++i) {
+            cs.cur = cur;
+            cs.only = i + 1 < p.k_pre;
+            cs.next_prec = cs.only ? p.prec_pre : p.prec_ns;
+            LA_HIP(gram_step(p, p.prec_pre, buf[cur], ld[cur], -p.c, 1.0, w.P, w, s, cs.packed,
+                             dev_stop),
+                   "la_polar: precondition gram");
+            LA_HIP(update_step(p, p.prec_pre, buf[cur], ld[cur], w.P, p.a, 0.0, buf[cur ^ 1],
+                               ld[cur ^ 1], nullptr, nullptr, w, s, dev_stop, csp),
+                   "la_polar: precondition update");
+            cs.packed = chain;
+            cur ^= 1;
+            inf.iters_precond++;
         }
-        cur = (start + h.steps) & 1;
-        inf.iters_ns = h.steps;
-        inf.last_delta = h.delta;
-        finite = h.reason != 3;
-        converged = h.reason < 2;
-        if (finite)
-            inf.stop_reason = h.reason;
+        cs.next_prec = p.prec_ns;
+        cs.only = false;
+
+        // Newton-Schulz: U' = U + U (I - U^T U) / 2, delta = ||U' - U||_F, until the
+        // stop test (polar_host.h); a polish step runs at BF16X6
+        if (ahead) {
+            // Steps are queued in batches; the device applies the stop test after
+            // each, and from the stop on leaves the iterates alone.  256^2: 20 us
+            // of readback and wait per step saved, 540 -> 360 us for the polar
+            // (9 steps), at 10 us per step queued in vain.
+            StepTest t;
+            t.scale = 1.0;
+            t.tol = (double)std::max(m, n) * p.eps;
+            t.tol_doubles = 0;
+            t.stag_below = p.stagnation ? 1e-2 * sqrt((double)n) : 0.0;
+            t.max_steps = p.max_iter;
+            const int start = cur;
+            int queued = 0, batch = kFirstBatch;
+            do {
+                for (const int to = std::min(queued + batch, p.max_iter); queued < to; ++queued) {
+                    int ntiles = 0;
+                    cs.cur = cur;
+                    LA_HIP(gram_step(p, p.prec_ns, buf[cur], ld[cur], -1.0, 1.0, w.P, w, s,
+                                     cs.packed, dev_stop),
+                           "la_polar: NS gram");
+                    LA_HIP(update_step(p, p.prec_ns, buf[cur], ld[cur], w.P, 0.5, 1.0, buf[cur ^ 1],
+                                       ld[cur ^ 1], w.tiles, &ntiles, w, s, dev_stop, csp),
+                           "la_polar: NS update");
+                    cs.packed = chain;
+                    LA_HIP(launch_step_state(w.tiles, ntiles, st, t, s), "la_polar: delta");
+                    cur ^= 1;
+                }
+                batch = kNextBatch;
+                rc = read_state();
+                if (rc != LA_OK)
+                    return rc;
+            } while (!h.stop);
+            if (h.reason == kReasonUneven) {
+                // nothing after X0 was written: once more from there
+                fall_back();
+                cur = 0;
+                rc = begin();
+                if (rc != LA_OK)
+                    return rc;
+                continue;
+            }
+            fro = sqrt(h.norm2);
+            inf.fro_norm_a = fro;
+            if (!(fro > 0.0) || !isfinite(fro)) {
+                inf.iters_precond = 0;
+                return bad_norm();
+            }
+            cur = (start + h.steps) & 1;
+            inf.iters_ns = h.steps;
+            inf.last_delta = h.delta;
+            finite = h.reason != 3;
+            converged = h.reason < 2;
+            if (finite)
+                inf.stop_reason = h.reason;
+        }
+        again = false;
     }
     while (!ahead) {
         const int prec = stop.stopped ? PREC_BF16X6 : p.prec_ns;

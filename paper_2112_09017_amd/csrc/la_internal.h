@@ -61,8 +61,9 @@ struct GemmDesc {
     const uint32_t *row_max, *col_max;
     uint32_t *out_max;
     int ptile;         // packed operands: tile side, 256, 192 or 128 (gemm_set_packed)
-    // direct classes: optional device word; while it is not 0 the launch leaves
-    // its outputs as they are (a step queued past the iteration's stop)
+    // direct classes and packed operands: optional device word; while it is not 0 the
+    // launch leaves its outputs as they are (a step queued past the iteration's stop, a
+    // product of an input too uneven for its arithmetic)
     const int *stop;
     // direct classes, two-term precisions: the output is also (or, with C null, only)
     // written as packed operands of arithmetic pack_prec (factor pack_scale): pack_row with the
@@ -140,12 +141,26 @@ hipError_t launch_gemm_mixed(int update, const GemmDesc *probs_dev, const GroupI
 
 // Packed operands of two 16-bit terms (gemm_x3.hip: 3xBF16, gemm_f16x3.hip:
 // F16X3, whose entries are multiplied by sc before the split, or, with rmax, each
-// row by the power of two that brings its largest entry to [2^14, 2^15)): op(X) (rows x k; kc: k contiguous,
+// row by the power of two that brings its largest entry to [2^14, 2^15); with skip, nothing
+// is done while *skip is not 0): op(X) (rows x k; kc: k contiguous,
 // X[r * ld + k], else X[k * ld + r]) split into bf16 hi/lo terms and laid out
 // in the GEMM's LDS fragment order, zero-padded to 256 rows and 16 k.
 size_t packed_x3_bytes(int64_t rows, int64_t k);
+// A matrix is too uneven for PREC_F16X3 if more than a quarter of the entries of some row
+// or column are smaller than what two scaled fp16 terms hold with 23 bits (zeros too).  A
+// product with one operand that is even has an error floor below the rounding of its
+// accumulation, whatever the other holds: every column of the other meets entries of
+// the size of the first one's largest.  A pack with rmax and counts (rows + k words of
+// zeros) looks for entries below 2^-17 of their row's largest (a row of zeros has none)
+// and sets bit in *flag if op(X) is uneven.
+struct PackCheck {
+    uint32_t *counts = nullptr;
+    int *flag = nullptr;
+    int bit = 0;
+};
 hipError_t launch_pack(int prec, const float *X, int64_t ld, int kc, int64_t rows, int64_t k,
-                       float sc, void *out, hipStream_t s, const uint32_t *rmax = nullptr);
+                       float sc, void *out, hipStream_t s, const uint32_t *rmax = nullptr,
+                       const int *skip = nullptr, const PackCheck &check = PackCheck());
 // GEMM on packed operands: d.A and d.B point at packed op(A) (M x K) and
 // packed op(B)^T (N x K), set up by gemm_set_packed.
 // Computes the same products in the same order as launch_gemm's kernel of that precision.
@@ -192,8 +207,8 @@ struct StepTest {
     double scale, tol, stag_below;
     int tol_doubles, max_steps;
 };
-// word (of 8 bytes) of the 64-byte state regions that holds launch_uneven's answer
-constexpr int kUnevenWord = 6;
+// StepState::reason of an input too uneven for the arithmetic of the steps queued
+constexpr int kReasonUneven = 4;
 hipError_t launch_norm_state(const double *parts, int64_t count, StepState *st, hipStream_t s);
 hipError_t launch_clear_state(StepState *st, hipStream_t s);
 hipError_t launch_step_state(const double *parts, int64_t count, StepState *st,
@@ -206,17 +221,16 @@ hipError_t launch_transpose_scale(const float *A, int64_t lda, float *X, int64_t
 hipError_t launch_absmax(const float *X, int64_t ldx, int64_t m, int64_t n, int by_row,
                          uint32_t *out, hipStream_t s);
 hipError_t launch_zero(uint32_t *out, int64_t count, hipStream_t s);
-// *flag = 1 if the m x n X (m, n >= 1) is too uneven for PREC_F16X3, else 0: more than
-// a quarter of the entries of some row or column fall below the magnitude from which
-// two scaled fp16 terms hold 23 bits.  Zeros count.  With nrm2 that is 2^-18 sqrt(*nrm2)
-// (operands scaled by sqrt(*nrm2) and kIterScale); else 2^-17 of the largest magnitude of
-// the entry's row (by_row) or column, given in mx.  A product with one operand that
-// is even in this sense has an error floor below the rounding of its accumulation,
-// whatever the other holds: every column of the other meets entries of the size of the
-// first one's largest.  counts: m + n words of scratch.
+// Y (may be X) = X with each row times the power of two that takes its largest magnitude
+// (mx: launch_absmax by row) to [2^14, 2^15), or divided by it (unscale).
+hipError_t launch_scale_rows(const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t m,
+                             int64_t n, const uint32_t *mx, int unscale, hipStream_t s);
+// Whether the m x n X (m, n >= 1, ||X||_F^2 in *nrm2) is too uneven (see PackCheck) for
+// operands scaled by their norm: with entries below 2^-18 ||X||_F for the small ones.  If
+// so *flag (may be null) becomes 1, and *st (may be null; unless stopped) stops for
+// kReasonUneven; else both stay as they are.  counts: m + n words of zeros.
 hipError_t launch_uneven(const float *X, int64_t ldx, int64_t m, int64_t n, const double *nrm2,
-                         const uint32_t *mx, int by_row, uint32_t *counts, uint32_t *flag,
-                         hipStream_t s);
+                         uint32_t *counts, int *flag, StepState *st, hipStream_t s);
 // Y = s A + t I for an n x n A (FP64 per element, rounded once).
 hipError_t launch_affine(const float *A, int64_t lda, float *Y, int64_t ldy, int64_t n,
                          double sc, double t, hipStream_t s);

@@ -472,8 +472,13 @@ struct HipExec {
         // 1. new requests: input, ||A||_F^2 in FP64, X0 = A / ||A||_F on the device,
         // and for those with phases on F16X3 whether A is too uneven for it (the other
         // iterate's buffer holds the counts), read back before their first step
-        uint32_t *uneven = (uint32_t *)dev_d;   // free until the tick's norms are written
+        int *uneven = (int *)dev_d;   // free until the tick's norms are written
         std::vector<serve::Req *> checked;
+        for (serve::Req *r : fresh)
+            if (uses_f16(r->plan, true))
+                checked.push_back(r);
+        e = launch_zero((uint32_t *)uneven, (int64_t)checked.size(), stream);
+        int ncheck = 0;
         for (serve::Req *r : fresh) {
             DevReq *d = (DevReq *)r->x;
             if (e == hipSuccess)
@@ -485,20 +490,20 @@ struct HipExec {
                 e = launch_reduce_fixed(d->sumsq, sumsq_num_partials(), d->scal, stream);
             if (e == hipSuccess)
                 e = launch_scale_by_norm(d->A, r->n, d->X[0], r->n, r->m, r->n, d->scal, stream);
-            if (e == hipSuccess && uses_f16(r->plan, true)) {
-                e = launch_uneven(d->A, r->n, r->m, r->n, d->scal, nullptr, 0, (uint32_t *)d->X[1],
-                                  uneven + checked.size(), stream);
-                checked.push_back(r);
-            }
+            if (e == hipSuccess && uses_f16(r->plan, true))
+                e = launch_zero((uint32_t *)d->X[1], r->m + r->n, stream);
+            if (e == hipSuccess && uses_f16(r->plan, true))
+                e = launch_uneven(d->A, r->n, r->m, r->n, d->scal, (uint32_t *)d->X[1],
+                                  uneven + ncheck++, nullptr, stream);
             d->cur = 0;
         }
         if (e == hipSuccess && !checked.empty()) {
-            e = hipMemcpyAsync(h_red, uneven, checked.size() * sizeof(uint32_t),
+            e = hipMemcpyAsync(h_red, uneven, checked.size() * sizeof(int),
                                hipMemcpyDeviceToHost, stream);
             if (e == hipSuccess)
                 e = hipStreamSynchronize(stream);
             for (size_t i = 0; i < checked.size() && e == hipSuccess; ++i)
-                if (((const uint32_t *)h_red)[i])
+                if (((const int *)h_red)[i])
                     without_f16(checked[i]->plan);
         }
         // 2. one step for every running request.  A tick whose requests would
