@@ -292,9 +292,12 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
  * 256-byte aligned (three n x n FP32 buffers and, at the sizes that use them,
  * packed operands; a workspace of the three buffers alone is taken too).
  * prec: AUTO = BF16X6 (the recurrences accumulate the products' errors, so every
- * product is kept at FP32-level accuracy), or, on the larger sizes and with the
- * full workspace, its equivalent of two scaled fp16 terms per operand.  Both run on hip_stream and return after the last
- * kernel has completed.  F must not overlap A or the workspace.
+ * product is kept at FP32-level accuracy), or, on the larger sizes, with the full
+ * workspace, and where the product's fixed operand is even (three quarters of the
+ * entries in each of its rows and columns are at least 2^-17 of the largest beside them),
+ * its equivalent of two scaled fp16 terms per operand: the result then depends, within
+ * that accuracy, on whether the workspace holds more than the three buffers.  Both run
+ * on hip_stream and return after the last kernel has completed.  F must not overlap A or the workspace.
  * ---------------------------------------------------------------------- */
 size_t la_matfunc_workspace_size(int64_t m, int64_t n);
 

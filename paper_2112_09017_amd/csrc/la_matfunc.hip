@@ -27,20 +27,32 @@ namespace {
 size_t matfunc_bytes(int64_t n) { return 3 * align_up256((size_t)n * n * sizeof(float)); }
 
 // AUTO's products as three products of two scaled fp16 terms (PREC_F16X3) on
-// packed operands, in place of 6xBF16: half the matrix-core work and half the
-// FP32 accumulation roundings (degree 16 at 4096^2: 9.6 -> 6.4 ms; 3000^2 6.4 ->
-// 3.1 ms).  Each row of op(A) and each column of op(B) is scaled by
-// the power of two of its own largest entry, so rows and columns of very
-// different size keep their accuracy; an element far below its row's largest
-// keeps an absolute error of 2^-39 of that.  The largest entries come from one
-// pass over a fixed operand and, for the recurrence's iterates, from the
-// epilogue that writes them.  The packs live after the three matrices, where the
-// workspace has room.
+// packed operands, in place of 6xBF16, where the fixed operand is even: half the
+// matrix-core work and half the FP32 accumulation roundings (degree 16 at 4096^2:
+// 9.6 -> 6.4 ms; 3000^2 6.4 -> 3.1 ms).  Each row of op(A) and each column of op(B) is
+// scaled by the power of two of its own largest entry, so rows and columns of very
+// different size keep their accuracy.  An element far below its row's largest keeps
+// an absolute error of 2^-39 of that only, which a sum sees where the other operand is
+// large there (B = D S D^-1, D from 1 to 2^20, degree 8 at 2048^2: error 3.1e-7 against
+// 1.6e-7 with the similarity undone; odd series of columns from 1 to 2^-30: 5e-3 against
+// 4.3e-7 in the worst), so an uneven fixed operand (PackCheck) keeps 6xBF16.
+// The answer stays on the device, where it turns the packs and products
+// queued behind it into nothing; the host reads it after the last of them and queues
+// them again at 6xBF16.  The largest entries come from one pass over a fixed operand
+// and, for the recurrence's iterates, from the epilogue that writes them.  The packs
+// live after the three matrices, where the workspace has room.
 struct F16 {
     bool on = false;
     char *pa = nullptr, *pb = nullptr;            // packed op(A), op(B)^T
     uint32_t *ra = nullptr, *cb[2] = {};          // their rows' and columns' maxima
+    int *uneven = nullptr;   // answers: [0] for the recurrence (kUneven*), [1] for F = A P
+    uint32_t *counts[3] = {};   // of the Gram's A, of Horner's G or the series' B, of A's rows
 };
+constexpr int kUnevenA = 1, kUnevenG = 2;
+constexpr size_t kFlagWords = 64;
+
+// Words of the answers and the counts after them.
+size_t f16_count_words(int64_t m, int64_t n) { return kFlagWords + 2 * (size_t)(m + 2 * n); }
 
 // Whether an M x N x K product of the recurrence runs as F16X3: on tiles that the
 // packed kernel has (the direct ones are bound by reading their operands, not by
@@ -79,14 +91,20 @@ size_t f16_bytes(int64_t m, int64_t n)
     pb = packed_x3_bytes(n, n);
     return align_up256(pa) + align_up256(pb) +
            align_up256((size_t)std::max(m, n) * sizeof(uint32_t)) +
-           2 * align_up256((size_t)n * sizeof(uint32_t));
+           2 * align_up256((size_t)n * sizeof(uint32_t)) +
+           align_up256(f16_count_words(m, n) * sizeof(uint32_t));
 }
 
 F16 f16_carve(int64_t m, int64_t n, void *workspace)
 {
     F16 f;
     f.on = true;
-    char *b = (char *)workspace + matfunc_bytes(n) + f16_bytes(m, n);
+    char *b = (char *)workspace + matfunc_bytes(n) + f16_bytes(m, n) -
+              align_up256(f16_count_words(m, n) * sizeof(uint32_t));
+    f.uneven = (int *)b;
+    f.counts[0] = (uint32_t *)b + kFlagWords;
+    f.counts[1] = f.counts[0] + m + n;
+    f.counts[2] = f.counts[1] + 2 * n;
     for (uint32_t *&c : f.cb) {
         b -= align_up256((size_t)n * sizeof(uint32_t));
         c = (uint32_t *)b;
@@ -100,19 +118,21 @@ F16 f16_carve(int64_t m, int64_t n, void *workspace)
 }
 
 // Packs op(A) = X (M x K, kc) or X^T (M columns, K rows, !kc) into f.pa, rows scaled
-// by their own largest entries.
+// by their own largest entries; an uneven X sets bit in f.uneven[w].
 hipError_t f16_pack_a(const F16 &f, const float *X, int64_t ldx, int kc, int64_t M, int64_t K,
-                      hipStream_t s)
+                      int w, int bit, uint32_t *counts, hipStream_t s)
 {
     hipError_t e = launch_absmax(X, ldx, kc ? M : K, kc ? K : M, kc, f.ra, s);
     if (e == hipSuccess)
-        e = launch_pack(PREC_F16X3, X, ldx, kc, M, K, 1.0f, f.pa, s, f.ra);
+        e = launch_pack(PREC_F16X3, X, ldx, kc, M, K, 1.0f, f.pa, s, f.ra, nullptr,
+                        PackCheck{counts, f.uneven + w, bit});
     return e;
 }
 
 // out = alpha op(A) Y + beta E + gamma I with op(A) (M x K) in f.pa and Y (K x N,
-// columns' maxima in f.cb[c]); the columns' maxima of out go to f.cb[c ^ 1].
-hipError_t f16_product(const F16 &f, int c, const float *Y, int64_t ldy, float *out, int64_t ldo,
+// columns' maxima in f.cb[c]); the columns' maxima of out go to f.cb[c ^ 1].  Nothing is
+// done where f.uneven[w].
+hipError_t f16_product(const F16 &f, int w, int c, const float *Y, int64_t ldy, float *out, int64_t ldo,
                        int64_t M, int64_t N, int64_t K, float alpha, float beta, const float *E,
                        int64_t lde, float gamma, hipStream_t s)
 {
@@ -130,7 +150,8 @@ hipError_t f16_product(const F16 &f, int c, const float *Y, int64_t ldy, float *
         d.lde = lde;
         d.beta = beta;
     }
-    hipError_t e = launch_pack(PREC_F16X3, Y, ldy, 0, N, K, 1.0f, f.pb, s, f.cb[c]);
+    d.stop = f.uneven + w;
+    hipError_t e = launch_pack(PREC_F16X3, Y, ldy, 0, N, K, 1.0f, f.pb, s, f.cb[c], d.stop);
     if (e == hipSuccess)
         e = launch_zero(f.cb[c ^ 1], N, s);
     if (e != hipSuccess)
@@ -265,8 +286,12 @@ la_status la_matfunc_odd(la_context *ctx, int64_t m, int64_t n, const float *A, 
     float *G = (float *)workspace;
     float *P[2] = {(float *)((char *)workspace + nb), (float *)((char *)workspace + 2 * nb)};
 
+    // A is the fixed operand of the Gram and of F = A P, G of Horner's products
+    bool f_gram = f.on && f16_class(n, n, m, 1), f_final = f.on && f16_class(m, n, n, 0);
+    bool f_horner = f.on && d >= 2 && f16_class(n, n, n, 0);
+    const bool scaled = f_final;
     // G = A^T A (symmetric tiles only, mirror-written)
-    {
+    auto gram = [&]() {
         GemmDesc g;
         memset(&g, 0, sizeof g);
         g.A = A;
@@ -282,51 +307,96 @@ la_status la_matfunc_odd(la_context *ctx, int64_t m, int64_t n, const float *A, 
         g.K = m;
         g.alpha = 1.0f;
         g.gram = 1;
-        gemm_finalize(g, pr);
-        if (f.on && f16_class(n, n, m, 1)) {
-            LA_HIP(f16_pack_a(f, A, lda, 0, n, m, s), "la_matfunc_odd: pack");
-            g.A = (const float *)f.pa;
-            g.B = (const float *)f.pa;
-            g.row_max = f.ra;
-            g.col_max = f.ra;
-            gemm_finalize(g, PREC_F16X3);
-            gemm_set_packed(g);
-            LA_HIP(launch_gemm_packed(PREC_F16X3, g, s), "la_matfunc_odd: gram");
-        } else {
+        if (!f_gram) {
+            gemm_finalize(g, pr);
             LA_HIP(launch_gemm(pr, g, s), "la_matfunc_odd: gram");
+            return LA_OK;
         }
-    }
+        LA_HIP(f16_pack_a(f, A, lda, 0, n, m, 0, kUnevenA, f.counts[0], s), "la_matfunc_odd: pack");
+        g.A = (const float *)f.pa;
+        g.B = (const float *)f.pa;
+        g.row_max = f.ra;
+        g.col_max = f.ra;
+        g.stop = f.uneven;
+        gemm_finalize(g, PREC_F16X3);
+        gemm_set_packed(g);
+        LA_HIP(launch_gemm_packed(PREC_F16X3, g, s), "la_matfunc_odd: gram");
+        return LA_OK;
+    };
     // Horner in G: P = c_d G + c_{d-1} I, then P <- G P + c_j I for j = d-2 .. 0
     int cur = 0;
-    LA_HIP(launch_affine(G, n, P[cur], n, n, coef[d], coef[d - 1], s), "la_matfunc_odd: affine");
-    const bool f_horner = f.on && f16_class(n, n, n, 0), f_final = f.on && f16_class(m, n, n, 0);
-    if (f_horner && d >= 2) {
-        LA_HIP(f16_pack_a(f, G, n, 1, n, n, s), "la_matfunc_odd: pack");
-        LA_HIP(launch_absmax(P[cur], n, n, n, 0, f.cb[cur], s), "la_matfunc_odd: pack");
-    }
-    for (int j = d - 2; j >= 0; --j) {
-        if (f_horner)
-            LA_HIP(f16_product(f, cur, P[cur], n, P[cur ^ 1], n, n, n, n, 1.0f, 0.0f, nullptr, 0,
+    auto horner = [&]() {
+        cur = 0;
+        LA_HIP(launch_affine(G, n, P[0], n, n, coef[d], coef[d - 1], s), "la_matfunc_odd: affine");
+        if (f_horner) {
+            LA_HIP(f16_pack_a(f, G, n, 1, n, n, 0, kUnevenG, f.counts[1], s), "la_matfunc_odd: pack");
+            LA_HIP(launch_absmax(P[0], n, n, n, 0, f.cb[0], s), "la_matfunc_odd: pack");
+        }
+        for (int j = d - 2; j >= 0; --j) {
+            if (f_horner)
+                LA_HIP(f16_product(f, 0, cur, P[cur], n, P[cur ^ 1], n, n, n, n, 1.0f, 0.0f, nullptr,
+                                   0, (float)coef[j], s),
+                       "la_matfunc_odd: horner");
+            else
+                LA_HIP(product(pr, G, n, P[cur], n, P[cur ^ 1], n, n, n, n, 1.0f, 0.0f, nullptr, 0,
                                (float)coef[j], s),
-                   "la_matfunc_odd: horner");
-        else
-            LA_HIP(product(pr, G, n, P[cur], n, P[cur ^ 1], n, n, n, n, 1.0f, 0.0f, nullptr, 0,
-                           (float)coef[j], s),
-                   "la_matfunc_odd: horner");
-        cur ^= 1;
-    }
+                       "la_matfunc_odd: horner");
+            cur ^= 1;
+        }
+        return LA_OK;
+    };
     // F = A P
-    if (f_final) {
-        if (!f_horner || d < 2)
-            LA_HIP(launch_absmax(P[cur], n, n, n, 0, f.cb[cur], s), "la_matfunc_odd: pack");
-        LA_HIP(f16_pack_a(f, A, lda, 1, m, n, s), "la_matfunc_odd: pack");
-        LA_HIP(f16_product(f, cur, P[cur], n, F, ldf, m, n, n, 1.0f, 0.0f, nullptr, 0, 0.0f, s),
-               "la_matfunc_odd: final product");
-    } else {
-        LA_HIP(product(pr, A, lda, P[cur], n, F, ldf, m, n, n, 1.0f, 0.0f, nullptr, 0, 0.0f, s),
-               "la_matfunc_odd: final product");
+    auto last = [&]() {
+        if (f_final) {
+            if (!f_horner)
+                LA_HIP(launch_absmax(P[cur], n, n, n, 0, f.cb[cur], s), "la_matfunc_odd: pack");
+            LA_HIP(f16_pack_a(f, A, lda, 1, m, n, 1, 1, f.counts[2], s), "la_matfunc_odd: pack");
+            LA_HIP(f16_product(f, 1, cur, P[cur], n, F, ldf, m, n, n, 1.0f, 0.0f, nullptr, 0, 0.0f,
+                               s),
+                   "la_matfunc_odd: final product");
+        } else if (scaled) {
+            // an uneven A, at 6xBF16: its rows scaled all the same, so that the third
+            // term of a small row's entries stays in range
+            float *As = (float *)f.pa;
+            LA_HIP(launch_absmax(A, lda, m, n, 1, f.ra, s), "la_matfunc_odd: rows");
+            LA_HIP(launch_scale_rows(A, lda, As, n, m, n, f.ra, 0, s), "la_matfunc_odd: rows");
+            LA_HIP(product(pr, As, n, P[cur], n, F, ldf, m, n, n, 1.0f, 0.0f, nullptr, 0, 0.0f, s),
+                   "la_matfunc_odd: final product");
+            LA_HIP(launch_scale_rows(F, ldf, F, ldf, m, n, f.ra, 1, s), "la_matfunc_odd: rows");
+        } else {
+            LA_HIP(product(pr, A, lda, P[cur], n, F, ldf, m, n, n, 1.0f, 0.0f, nullptr, 0, 0.0f, s),
+                   "la_matfunc_odd: final product");
+        }
+        return LA_OK;
+    };
+    // from the first phase on; what an uneven operand turned into nothing is queued again
+    for (int phase = 0; phase < 3;) {
+        if (f.on)
+            LA_HIP(launch_zero((uint32_t *)f.uneven, f16_count_words(m, n), s),
+                   "la_matfunc_odd: unevenness");
+        if (phase == 0 && (st = gram()) != LA_OK)
+            return st;
+        if (phase <= 1 && (st = horner()) != LA_OK)
+            return st;
+        if ((st = last()) != LA_OK)
+            return st;
+        int uneven[2] = {0, 0};
+        if (f.on)
+            LA_HIP(hipMemcpyAsync(uneven, f.uneven, sizeof uneven, hipMemcpyDeviceToHost, s),
+                   "la_matfunc_odd: readback");
+        LA_HIP(hipStreamSynchronize(s), "la_matfunc_odd: sync");
+        if (uneven[1])
+            f_final = false;
+        if (uneven[0] & kUnevenA) {
+            f_gram = false;
+            phase = 0;
+        } else if (uneven[0]) {
+            f_horner = false;
+            phase = 1;
+        } else {
+            phase = uneven[1] ? 2 : 3;
+        }
     }
-    LA_HIP(hipStreamSynchronize(s), "la_matfunc_odd: sync");
     return LA_OK;
 }
 
@@ -395,37 +465,47 @@ la_status la_matfunc_cheb(la_context *ctx, int64_t n, const float *A, int64_t ld
     LA_HIP(launch_affine(A, lda, P[0], n, n, 2.0 * c[d] * sc, 2.0 * c[d] * t + c[d - 1], s),
            "la_matfunc_cheb: b_{d-1}");
     // op(A) is B throughout; the iterate in P[i] has its columns' maxima in cb[i]
-    if (f.on) {
-        LA_HIP(f16_pack_a(f, B, n, 1, n, n, s), "la_matfunc_cheb: pack");
-        LA_HIP(launch_absmax(P[0], n, n, n, 0, f.cb[0], s), "la_matfunc_cheb: pack");
-    }
     auto times_b = [&](int c, float *out, int64_t ldo, float alpha, float beta, const float *E,
                        float gamma) {
         if (f.on)
-            return f16_product(f, c, P[c], n, out, ldo, n, n, n, alpha, beta, E, n, gamma, s);
+            return f16_product(f, 0, c, P[c], n, out, ldo, n, n, n, alpha, beta, E, n, gamma, s);
         return product(pr, B, n, P[c], n, out, ldo, n, n, n, alpha, beta, E, n, gamma, s);
     };
-    if (d == 2) {
-        // F = B b_1 - b_2 + c_0 I with b_2 = c_2 I
-        LA_HIP(times_b(0, F, ldf, 1.0f, 0.0f, nullptr, (float)(c[0] - c[2])),
-               "la_matfunc_cheb: final product");
+    // from b_{d-1} on; where B is uneven, nothing has been written and the loop runs again
+    for (int uneven = 1; uneven;) {
+        uneven = 0;
+        if (f.on) {
+            LA_HIP(launch_zero((uint32_t *)f.uneven, f16_count_words(n, n), s),
+                   "la_matfunc_cheb: unevenness");
+            LA_HIP(f16_pack_a(f, B, n, 1, n, n, 0, 1, f.counts[1], s), "la_matfunc_cheb: pack");
+            LA_HIP(launch_absmax(P[0], n, n, n, 0, f.cb[0], s), "la_matfunc_cheb: pack");
+        }
+        if (d == 2) {
+            // F = B b_1 - b_2 + c_0 I with b_2 = c_2 I
+            LA_HIP(times_b(0, F, ldf, 1.0f, 0.0f, nullptr, (float)(c[0] - c[2])),
+                   "la_matfunc_cheb: final product");
+        } else {
+            // b_{d-2} = 2 B b_{d-1} - c_d I + c_{d-2} I
+            LA_HIP(times_b(0, P[1], n, 2.0f, 0.0f, nullptr, (float)(c[d - 2] - c[d])),
+                   "la_matfunc_cheb: clenshaw");
+            int cur = 1;   // P[cur] = b_{k+1}, P[cur ^ 1] = b_{k+2}
+            for (int k = d - 3; k >= 1; --k) {
+                // b_k = 2 B b_{k+1} - b_{k+2} + c_k I, written over b_{k+2}
+                float *prev = P[cur ^ 1];
+                LA_HIP(times_b(cur, prev, n, 2.0f, -1.0f, prev, (float)c[k]),
+                       "la_matfunc_cheb: clenshaw");
+                cur ^= 1;
+            }
+            // F = B b_1 - b_2 + c_0 I
+            LA_HIP(times_b(cur, F, ldf, 1.0f, -1.0f, P[cur ^ 1], (float)c[0]),
+                   "la_matfunc_cheb: final product");
+        }
+        if (f.on)
+            LA_HIP(hipMemcpyAsync(&uneven, f.uneven, sizeof uneven, hipMemcpyDeviceToHost, s),
+                   "la_matfunc_cheb: readback");
         LA_HIP(hipStreamSynchronize(s), "la_matfunc_cheb: sync");
-        return LA_OK;
+        f.on = f.on && !uneven;
     }
-    // b_{d-2} = 2 B b_{d-1} - c_d I + c_{d-2} I
-    LA_HIP(times_b(0, P[1], n, 2.0f, 0.0f, nullptr, (float)(c[d - 2] - c[d])),
-           "la_matfunc_cheb: clenshaw");
-    int cur = 1;   // P[cur] = b_{k+1}, P[cur ^ 1] = b_{k+2}
-    for (int k = d - 3; k >= 1; --k) {
-        // b_k = 2 B b_{k+1} - b_{k+2} + c_k I, written over b_{k+2}
-        float *prev = P[cur ^ 1];
-        LA_HIP(times_b(cur, prev, n, 2.0f, -1.0f, prev, (float)c[k]), "la_matfunc_cheb: clenshaw");
-        cur ^= 1;
-    }
-    // F = B b_1 - b_2 + c_0 I
-    LA_HIP(times_b(cur, F, ldf, 1.0f, -1.0f, P[cur ^ 1], (float)c[0]),
-           "la_matfunc_cheb: final product");
-    LA_HIP(hipStreamSynchronize(s), "la_matfunc_cheb: sync");
     return LA_OK;
 }
 
