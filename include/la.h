@@ -75,9 +75,10 @@ typedef enum {
  *            two fp16 terms per operand (times a power of two, 23 bits together;
  *            products lh + hl + hh), whose measured error on such inputs is no
  *            larger; both are reported as BF16X6;
- *            la_inverse -> BF16X3 steps and one BF16X6 step (on the larger
- *            sizes an equivalent of two scaled fp16 terms); la_matfunc_* ->
- *            BF16X6.
+ *            la_inverse -> BF16X3 steps and one BF16X6 step (on the larger sizes,
+ *            with the full workspace and even A and X as for la_matfunc_*, an
+ *            equivalent of two scaled fp16 terms); la_matfunc_* -> BF16X6 or its
+ *            equivalent.
  * The paper's TPU "fp32" matmul is itself a bf16-based emulation at about
  * six times the bf16 cost (section II); BF16X6 is the analogue here. */
 typedef enum {

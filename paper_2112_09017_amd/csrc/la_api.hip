@@ -739,8 +739,12 @@ struct InvWs {
     double *scal;    // [0] ||A A^T||_F^2, [1] ||X' - X||_F^2
     PackBuf pk;      // packed operands of the step's products
     char *pka;       // A packed once for the first product (may be null)
-    uint32_t *mx;    // maxima of an F16X3 polish product's rows and columns (may be null)
+    // F16X3 polish: maxima of a product's rows and columns (may be null: 6xBF16); answer
+    // and counts of unevenness (A's, then X's)
+    uint32_t *mx, *counts;
+    int *uneven;
 };
+constexpr size_t kFlagWords = 64;
 
 // Packed operands of the larger of the two products of a step: R = A X
 // (r x r, K = m) or X A (K = n), then X R (m x n, K = n) or R X (K = m);
@@ -791,7 +795,8 @@ static size_t inverse_small_pack_bytes(const InvPlan &p)
 // functions, that its fewer accumulation roundings outweigh one bit less per
 // operand.  (3000^2: a product 438 us at 6xBF16, 160 and 70 for the maxima and packs,
 // the inverse 7.72 -> 7.21 ms; its error at cond 10 1.17e-6 -> 8.9e-7, cond 30 2.27e-6
-// -> 1.66e-6.)
+// -> 1.66e-6.)  A and X, one of which is in each product, have to be even for it
+// (PackCheck); an input where they are not is polished once more, at 6xBF16.
 static bool polish_f16(const InvPlan &p, const GemmDesc &d)
 {
     return p.f16_polish && d.K >= 1024 &&
@@ -803,7 +808,8 @@ static bool polish_f16(const InvPlan &p, const GemmDesc &d)
 static size_t inverse_max_bytes(const InvPlan &p)
 {
     return p.f16_polish && (inverse_step_pack_bytes(p) || inverse_small_step_bytes(p))
-               ? 2 * align_up256((size_t)std::max(p.m, p.n) * sizeof(uint32_t))
+               ? 2 * align_up256((size_t)std::max(p.m, p.n) * sizeof(uint32_t)) +
+                     align_up256((kFlagWords + 2 * (size_t)(p.m + p.n)) * sizeof(uint32_t))
                : 0;
 }
 
@@ -823,8 +829,11 @@ static InvWs inverse_carve(const InvPlan &p, void *ws, bool room, bool max_room)
 {
     InvWs w;
     char *b = (char *)ws;
-    w.mx = max_room ? (uint32_t *)(b + inverse_workspace_bytes(p) + inverse_small_pack_bytes(p))
-                    : nullptr;
+    char *mb = b + inverse_workspace_bytes(p) + inverse_small_pack_bytes(p);
+    w.mx = max_room ? (uint32_t *)mb : nullptr;
+    mb += 2 * align_up256((size_t)std::max(p.m, p.n) * sizeof(uint32_t));
+    w.uneven = (int *)mb;
+    w.counts = (uint32_t *)mb + kFlagWords;
     w.X = (float *)b;
     b += align256((size_t)p.m * p.n * sizeof(float));
     w.R = (float *)b;
@@ -870,20 +879,25 @@ static bool queues_ahead(const InvPlan &p, int64_t ldx)
 }
 
 // A product of the polish step (op(A) k contiguous, op(B) row-contiguous) as F16X3,
-// packed into w.pk.
-static hipError_t polish_product(const InvPlan &p, GemmDesc &d, const InvWs &w, hipStream_t s)
+// packed into w.pk, unless *w.uneven; A or X is op(A) (p.wide) or op(B).
+static hipError_t polish_product(const InvPlan &p, GemmDesc &d, const InvWs &w, uint32_t *counts,
+                                 hipStream_t s)
 {
     uint32_t *ra = w.mx, *cb = w.mx + align_up256((size_t)std::max(p.m, p.n) * 4) / 4;
     char *pa = w.pk.p, *pb = w.pk.p + align_up256(packed_x3_bytes(d.M, d.K));
     hipError_t e = launch_absmax(d.A, d.lda, d.M, d.K, 1, ra, s);
     if (e == hipSuccess)
         e = launch_absmax(d.B, d.ldb, d.K, d.N, 0, cb, s);
+    const PackCheck check{counts, w.uneven, 1};
     if (e == hipSuccess)
-        e = launch_pack(PREC_F16X3, d.A, d.lda, 1, d.M, d.K, 1.0f, pa, s, ra);
+        e = launch_pack(PREC_F16X3, d.A, d.lda, 1, d.M, d.K, 1.0f, pa, s, ra, nullptr,
+                        p.wide ? check : PackCheck());
     if (e == hipSuccess)
-        e = launch_pack(PREC_F16X3, d.B, d.ldb, 0, d.N, d.K, 1.0f, pb, s, cb);
+        e = launch_pack(PREC_F16X3, d.B, d.ldb, 0, d.N, d.K, 1.0f, pb, s, cb, nullptr,
+                        p.wide ? PackCheck() : check);
     if (e != hipSuccess)
         return e;
+    d.stop = w.uneven;
     d.A = (const float *)pa;
     d.B = (const float *)pb;
     d.row_max = ra;
@@ -940,7 +954,7 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
         g = t;
         return true;
     };
-    hipError_t e = f16(d) ? polish_product(p, d, w, s)
+    hipError_t e = f16(d) ? polish_product(p, d, w, w.counts, s)
                           : gemm_packed_or_plain(prec, d, w.pk, s, p.wide ? pre : nullptr,
                                                  p.wide ? nullptr : pre);
     if (e != hipSuccess)
@@ -976,7 +990,8 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
     }
     u.stop = stop;
     gemm_finalize(u, prec);
-    e = f16(u) ? polish_product(p, u, w, s) : gemm_packed_or_plain(prec, u, w.pk, s);
+    e = f16(u) ? polish_product(p, u, w, w.counts + p.m + p.n, s)
+               : gemm_packed_or_plain(prec, u, w.pk, s);
     *ntiles = u.tiles_m * u.tiles_n;
     return e;
 }
@@ -1828,14 +1843,25 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
     for (; it < total && finite; ++it) {
         const bool polishing = stopped;
         const int prec = polishing ? PREC_BF16X6 : p.prec;
-        int ntiles = 0;
+        int ntiles = 0, uneven = 0;
+        if (polishing && w.mx)
+            LA_HIP(launch_zero((uint32_t *)w.uneven, kFlagWords + 2 * (p.m + p.n), s),
+                   "la_inverse: unevenness");
         LA_HIP(inverse_step(p, prec, A, lda, buf[cur], ld[cur], buf[cur ^ 1], ld[cur ^ 1], w,
                             &ntiles, s),
                "la_inverse: step");
+        if (polishing && w.mx)
+            LA_HIP(hipMemcpyAsync(&uneven, w.uneven, sizeof uneven, hipMemcpyDeviceToHost, s),
+                   "la_inverse: readback");
         LA_HIP(launch_reduce_fixed(w.tiles, ntiles, w.scal + 1, s), "la_inverse: delta");
         LA_HIP(hipMemcpyAsync(h2 + 1, w.scal + 1, sizeof(double), hipMemcpyDeviceToHost, s),
                "la_inverse: readback");
         LA_HIP(hipStreamSynchronize(s), "la_inverse: sync");
+        if (uneven) {
+            w.mx = nullptr;
+            --it;
+            continue;
+        }
         cur ^= 1;
         inf.iters++;
         const double delta = scale * sqrt(h2[1]);
