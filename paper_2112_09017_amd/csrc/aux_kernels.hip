@@ -37,14 +37,6 @@ int tile_n(int prec, int cls) { return tile_m(prec, cls); }
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-bool direct_fits(const GemmDesc &d)
-{
-    constexpr int64_t kMaxElems = (int64_t)1 << 29;
-    const int64_t ea = d.a_kcontig ? d.M * d.lda : d.M + 8 * d.lda;
-    const int64_t eb = d.b_kcontig ? d.N * d.ldb : d.N + 8 * d.ldb;
-    return ea < kMaxElems && eb < kMaxElems;
-}
-
 // Tile class of a product, by its shape alone.  Measured (ns per unit of K,
 // 3xBF16 / 6xBF16 / FP32; the last round of workgroups counts as a whole one):
 //   direct64, up to 512 tiles 28 / 35 / 59, 1024 47 / 56 / 107, 1536 62 / 71 /
@@ -70,8 +62,6 @@ static int gemm_class(const GemmDesc &d, int prec)
     const int64_t side = std::min(d.M, d.N);
     if (side >= 256 && tiles(256) >= kCus / 2)
         return kClassLarge;
-    if (!direct_fits(d))
-        return kClassSmall;
     if (tiles(32) <= kCus || side < 2)
         return kClassDirect32;
     const int64_t t64 = tiles(64);
@@ -150,19 +140,15 @@ void gemm_set_packed(GemmDesc &d)
 
 size_t gemm_max_tiles(int prec, int64_t M, int64_t N, int64_t K)
 {
-    // of the class taken with dense operands, and of the small class, which
-    // stands in for a direct one where a leading dimension is too long for it
+    // of its own class, and of 128 x 128 tiles, which stand in for large ones
     GemmDesc d{};
     d.M = M;
     d.N = N;
     d.K = K;
-    d.lda = K;
-    d.ldb = N;
-    d.a_kcontig = 1;
     gemm_finalize(d, prec);
-    const size_t dense = (size_t)d.tiles_m * d.tiles_n;
+    const size_t own = (size_t)d.tiles_m * d.tiles_n;
     gemm_set_class(d, prec, kClassSmall);
-    return std::max(dense, (size_t)d.tiles_m * d.tiles_n);
+    return std::max(own, (size_t)d.tiles_m * d.tiles_n);
 }
 
 hipError_t launch_gemm(int prec, const GemmDesc &d, hipStream_t s)

@@ -48,10 +48,12 @@ typedef const __attribute__((address_space(1))) char gchar;
 // consecutive bytes per k over the lanes for F = 2); a start past R - F is
 // moved back to it, so the last lane of an odd R repeats a row instead of
 // reading past the matrix.  row() gives the op(X) row of block b, index i, or
-// -1 where it is past the edge or such a repeat.
+// -1 where it is past the edge or such a repeat.  (Offsets are 64-bit a lane: any
+// leading dimension; the loop's addresses were 64-bit sums already, so 32-bit ones
+// saved three registers and no instruction of it.)
 template <bool KC, int F> struct DirectOperand {
     gchar *base;
-    uint32_t off[KC ? F : 1];
+    uint64_t off[KC ? F : 1];
     int64_t ld;
 
     __device__ __forceinline__ void init(const float *X, int64_t ld_, int64_t R, int64_t r0,
@@ -64,11 +66,11 @@ template <bool KC, int F> struct DirectOperand {
 #pragma unroll
             for (int b = 0; b < F; ++b) {
                 const int64_t r = r0 + 32 * b + i;
-                off[b] = (uint32_t)(((r < R ? r : R - 1) * ld + 8 * h) * 4);
+                off[b] = (uint64_t)(((r < R ? r : R - 1) * ld + 8 * h) * 4);
             }
         } else {
             const int64_t r = r0 + F * i;
-            off[0] = (uint32_t)(((r < R - F ? r : R - F) + 8 * h * ld) * 4);
+            off[0] = (uint64_t)(((r < R - F ? r : R - F) + 8 * h * ld) * 4);
         }
     }
     // the step's values; k0 (uniform) + 16 <= K

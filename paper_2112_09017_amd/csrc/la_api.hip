@@ -202,7 +202,7 @@ static size_t pack_bytes(int prec, int64_t M, int64_t N, int64_t K)
     return align_up256(packed_x3_bytes(M, K)) + align_up256(packed_x3_bytes(N, K));
 }
 
-// The same for a product of the small class (dense operands).
+// The same for a product of the small class.
 static size_t pack_small_bytes(int prec, int64_t M, int64_t N, int64_t K)
 {
     GemmDesc d;
@@ -210,9 +210,6 @@ static size_t pack_small_bytes(int prec, int64_t M, int64_t N, int64_t K)
     d.M = M;
     d.N = N;
     d.K = K;
-    d.a_kcontig = 1;
-    d.lda = K;
-    d.ldb = N;
     gemm_finalize(d, prec);
     if (!packs_small(prec, d))
         return 0;
@@ -356,15 +353,11 @@ size_t polar_workspace_bytes(const PolarPlan &p)
 // many requests and are bound by their operands at any n.)
 constexpr int64_t kChainMinN = 320;
 
-// The shape of the update X P, X with leading dimension ldx (the tile class of the
-// two-term arithmetics is the same).
-static GemmDesc chain_update_desc(const PolarPlan &p, int64_t ldx, int prec)
+// The shape of the update X P (its tile class at the two-term arithmetics is the same).
+static GemmDesc update_shape(const PolarPlan &p, int prec)
 {
     GemmDesc d;
     memset(&d, 0, sizeof d);
-    d.lda = ldx;
-    d.a_kcontig = 1;
-    d.ldb = p.n;
     d.M = p.m;
     d.N = p.n;
     d.K = p.n;
@@ -372,28 +365,25 @@ static GemmDesc chain_update_desc(const PolarPlan &p, int64_t ldx, int prec)
     return d;
 }
 
-size_t polar_chain_bytes(const PolarPlan &p, int64_t ldx, bool served)
+size_t polar_chain_bytes(const PolarPlan &p, bool served)
 {
     if (!two_term(p.prec_pre) || !two_term(p.prec_ns))
         return 0;
     if (!served && (p.n < kChainMinN || update_splits(p) > 1))
         return 0;
-    for (int64_t ld : {p.n, ldx})
-        for (int pr : {p.prec_pre, p.prec_ns}) {
-            if (!served && gram_splits(p.m, p.n, pr, p.max_acc) > 1)
-                return 0;
-            GemmDesc d = chain_update_desc(p, ld, pr);
-            if (!is_direct(d.small))
-                return 0;
-            d.a_kcontig = 0;
-            d.ldb = ld;
-            d.M = p.n;
-            d.K = p.m;
-            d.gram = 1;
-            gemm_finalize(d, pr);
-            if (!is_direct(d.small))
-                return 0;
-        }
+    for (int pr : {p.prec_pre, p.prec_ns}) {
+        if (!served && gram_splits(p.m, p.n, pr, p.max_acc) > 1)
+            return 0;
+        GemmDesc d = update_shape(p, pr);
+        if (!is_direct(d.small))
+            return 0;
+        d.M = p.n;
+        d.K = p.m;
+        d.gram = 1;
+        gemm_finalize(d, pr);
+        if (!is_direct(d.small))
+            return 0;
+    }
     return 2 * align_up256(packed_x3_bytes(p.m, p.n)) + align_up256(packed_x3_bytes(p.n, p.m)) +
            align_up256(packed_x3_bytes(p.n, p.n));
 }
@@ -406,8 +396,7 @@ PolarChain polar_chain_carve(const PolarPlan &p, char *base)
     c.row[1] = base + row;
     c.col = base + 2 * row;
     c.P = c.col + align_up256(packed_x3_bytes(p.n, p.m));
-    const GemmDesc d = chain_update_desc(p, p.n, p.prec_ns);
-    c.pairs = d.small == kClassDirect64;
+    c.pairs = update_shape(p, p.prec_ns).small == kClassDirect64;
     return c;
 }
 
@@ -622,29 +611,13 @@ static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int6
 constexpr int kFirstBatch = 10, kNextBatch = 4;
 constexpr int kFirstInvBatch = 16;
 
-// Whether every step of p runs on the direct kernels (X in either buffer):
-// launches short enough that the host's turn between steps would take longer,
-// so the steps are queued ahead of their stop test.  (With polish the step
-// after the stop differs, so those wait.)
-static bool queues_ahead(const PolarPlan &p, int64_t ldu)
+// Whether every step of p runs on the direct kernels: launches short enough that
+// the host's turn between steps would take longer, so the steps are queued ahead of
+// their stop test.  (With polish the step after the stop differs, so those wait.)
+static bool queues_ahead(const PolarPlan &p)
 {
-    if (p.polish || update_splits(p) > 1)
-        return false;
-    for (int64_t ld : {p.n, ldu})
-        for (int pr : {p.prec_pre, p.prec_ns}) {
-            GemmDesc d;
-            memset(&d, 0, sizeof d);
-            d.lda = ld;
-            d.a_kcontig = 1;
-            d.ldb = p.n;
-            d.M = p.m;
-            d.N = p.n;
-            d.K = p.n;
-            gemm_finalize(d, pr);
-            if (!is_direct(d.small))
-                return false;
-        }
-    return true;
+    return !p.polish && update_splits(p) <= 1 && is_direct(update_shape(p, p.prec_pre).small) &&
+           is_direct(update_shape(p, p.prec_ns).small);
 }
 
 // H = (U^T A + A^T U) / 2 in one symmetric pass: the upper triangle of U^T A
@@ -858,24 +831,17 @@ static InvWs inverse_carve(const InvPlan &p, void *ws, bool room, bool max_room)
     return w;
 }
 
-// Whether the steps' updates run on the direct kernels (X in either buffer), so
-// that they are queued ahead of their stop test as la_polar's are.
-static bool queues_ahead(const InvPlan &p, int64_t ldx)
+// Whether the steps' updates run on the direct kernels, so that they are queued
+// ahead of their stop test as la_polar's are.
+static bool queues_ahead(const InvPlan &p)
 {
-    for (int64_t ld : {p.n, ldx}) {
-        GemmDesc u;
-        memset(&u, 0, sizeof u);
-        u.M = p.m;
-        u.N = p.n;
-        u.K = p.wide ? p.n : p.m;
-        u.lda = p.wide ? ld : p.r;
-        u.ldb = p.wide ? p.r : ld;
-        u.a_kcontig = 1;
-        gemm_finalize(u, p.prec);
-        if (!is_direct(u.small))
-            return false;
-    }
-    return true;
+    GemmDesc u;
+    memset(&u, 0, sizeof u);
+    u.M = p.m;
+    u.N = p.n;
+    u.K = p.wide ? p.n : p.m;
+    gemm_finalize(u, p.prec);
+    return is_direct(u.small);
 }
 
 // A product of the polish step (op(A) k contiguous, op(B) row-contiguous) as F16X3,
@@ -1023,17 +989,12 @@ static void gemm_last_round(GemmDesc &d, int prec)
         gemm_set_class(d, prec, kClassSmall);
 }
 
-// Tile class of a product of packed operands: the direct class la_gemm would
-// take for the shape with dense operands (the same sums), else 256 x 256 tiles.
+// Tile class of a product of packed operands: the direct class that la_gemm takes
+// for the shape (the same sums), else the tile side of gemm_set_packed.
 static void gemm_packed_class(GemmDesc &d)
 {
-    GemmDesc t = d;
-    t.lda = std::max<int64_t>(d.K, 1);
-    t.ldb = std::max<int64_t>(d.K, 1);
-    t.a_kcontig = t.b_kcontig = 1;
-    gemm_finalize(t, PREC_BF16X3);
-    gemm_last_round(t, PREC_BF16X3);
-    gemm_set_class(d, PREC_BF16X3, t.small);
+    gemm_finalize(d, PREC_BF16X3);
+    gemm_last_round(d, PREC_BF16X3);
     gemm_set_packed(d);
 }
 
@@ -1315,8 +1276,8 @@ la_status la_gemm_packed(la_context *ctx, int64_t m, int64_t n, int64_t k, float
         d.lde = ldc;
         d.beta = beta;
     }
-    // the class la_gemm takes for this shape (dense operands), so that the sums
-    // are the same; the 128 x 128 class adds as the large tiles do
+    // the class la_gemm takes for this shape, so that the sums are the same; the
+    // 128 x 128 class adds as the large tiles do
     gemm_packed_class(d);
     LA_HIP(launch_gemm_packed(PREC_BF16X3, d, (hipStream_t)hip_stream), "la_gemm_packed: launch");
     return LA_OK;
@@ -1383,7 +1344,7 @@ size_t la_polar_workspace_size(int64_t m, int64_t n, const la_polar_opts *opts)
     if (polar_plan(m, n, opts, &p) != LA_OK)
         return 0;
     return polar_workspace_bytes(p) +
-           std::max(packed_small_bytes(p), polar_chain_bytes(p, p.n));
+           std::max(packed_small_bytes(p), polar_chain_bytes(p));
 }
 
 }  // extern "C"
@@ -1477,7 +1438,7 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &plan, const float 
         return ws_bytes >= full && !overlaps(workspace, full, A, ab) &&
                !overlaps(workspace, full, U, ub) && !overlaps(workspace, full, H, hb);
     };
-    const size_t chain_bytes = polar_chain_bytes(p, ldu);
+    const size_t chain_bytes = polar_chain_bytes(p);
     bool chain = chain_bytes && room(chain_bytes);
     PolarWs w = carve(p, workspace, room(packed_small_bytes(p)), chain);
 
@@ -1499,7 +1460,7 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &plan, const float 
     bool converged = false, finite = true;
 
     LA_HIP(launch_sumsq(A, m, n, lda, w.sumsq, s), "la_polar: norm");
-    const bool ahead = queues_ahead(p, ldu);
+    const bool ahead = queues_ahead(p);
     StepState *st = (StepState *)w.scal;
     StepState h;
     const int *dev_stop = ahead ? &st->stop : nullptr;
@@ -1803,7 +1764,7 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
     const int total = p.max_iter + (p.polish ? 1 : 0);
     bool stopped = false, finite = true;
     int it = 0;
-    if (queues_ahead(p, ldx)) {
+    if (queues_ahead(p)) {
         // steps queued in batches, the stop test on the device (as in la_polar)
         StepTest t;
         t.scale = scale;

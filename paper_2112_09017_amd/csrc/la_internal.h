@@ -81,8 +81,9 @@ struct GemmDesc {
 // the same K stages and product order, so the choice between these two never
 // changes a result.  The direct classes (gemm_direct.h: 64 x 64 and 32 x 32
 // tiles whose waves split K) each add in an order of their own, the same on
-// packed operands.  The class follows from the problem's own shape, so a
-// problem's result does not depend on what it is launched with.
+// packed operands.  The class follows from the problem's own shape, whatever the
+// leading dimensions, so a problem's result does not depend on what it is launched
+// with or where its operands lie.
 constexpr int kClassLarge = 0, kClassSmall = 1, kClassDirect64 = 2, kClassDirect32 = 3;
 inline bool is_direct(int cls) { return cls >= kClassDirect64; }
 
@@ -92,8 +93,6 @@ int tile_n(int prec, int cls = 0);
 
 // Fills the derived fields (tile class, vec flags, tile counts) of d.
 void gemm_finalize(GemmDesc &d, int prec);
-// Whether d's operands suit the direct kernels' 32-bit byte offsets.
-bool direct_fits(const GemmDesc &d);
 // Sets d's tile class and the tile counts that follow from it.
 void gemm_set_class(GemmDesc &d, int prec, int cls);
 // Sets d up for packed operands (launch_gemm_packed): a direct class as it is,
@@ -287,10 +286,9 @@ struct PolarChain {
     int pairs;      // P's rows in pair order: the update is of the 64 x 64 class
 };
 // Bytes of a chain for p, 0 where its products don't take one: a product that is
-// not two-term or not of a direct class (X with leading dimension ldx in the
-// first buffer and n in the other), or, for la_polar, a split update, a split Gram
-// or n < kChainMinN.  served: the server's rule.
-size_t polar_chain_bytes(const PolarPlan &p, int64_t ldx, bool served = false);
+// not two-term or not of a direct class, or, for la_polar, a split update, a split
+// Gram or n < kChainMinN.  served: the server's rule.
+size_t polar_chain_bytes(const PolarPlan &p, bool served = false);
 PolarChain polar_chain_carve(const PolarPlan &p, char *base);
 
 

@@ -1329,12 +1329,9 @@ size_t wy_bytes(int nc) { return al((size_t)nc * nc * sizeof(float)) + 256; }
 // that a panel of 64 columns has no idle half tile and each workgroup's share
 // of K is a few steps per wave.  32 x 32 tiles while they cover the output in
 // four (the next panel's product: the slices give the chip enough workgroups
-// and the launch is on the critical path), 64 x 64 tiles else.  An operand too
-// long for the direct kernels' offsets keeps the staged small tiles.
+// and the launch is on the critical path), 64 x 64 tiles else.
 int split_class(const GemmDesc &d)
 {
-    if (!direct_fits(d))
-        return kClassSmall;
     return (d.M <= 64 && d.N <= 64) || d.M < 2 || d.N < 2 ? kClassDirect32 : kClassDirect64;
 }
 

@@ -287,7 +287,7 @@ struct HipExec {
     // bytes of the request's packed copies, 0 where it goes without
     size_t chain_bytes(const serve::Req &r) const
     {
-        const size_t c = polar_chain_bytes(r.plan, r.n, true);
+        const size_t c = polar_chain_bytes(r.plan, true);
         return c && (plain_footprint(r) + c) * kChainFit <= req_bytes ? c : 0;
     }
     size_t footprint(const serve::Req &r) { return plain_footprint(r) + chain_bytes(r); }
