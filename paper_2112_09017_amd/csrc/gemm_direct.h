@@ -582,7 +582,7 @@ template <int PREC, int CLS>
 hipError_t launch_direct(const GemmDesc &d, hipStream_t s)
 {
     const int sl = d.slices > 1 ? d.slices : 1;
-    if (sl > 1 && (d.slice_k <= 0 || d.slice_k % 16 != 0 || sl > 65535))
+    if (sl > 1 && (d.slice_k <= 0 || sl > 65535))
         return hipErrorInvalidValue;
     // a row-contiguous operand is read FM (FN) rows at a time
     if (d.M < DirectCfg<CLS>::FM || d.N < DirectCfg<CLS>::FN)

@@ -47,7 +47,7 @@ struct GemmDesc {
     int tail_first;
     // split-K slices in one launch: slice y takes k in [y slice_k, min(K,
     // (y + 1) slice_k)) and writes C + y slice_stride (slice_k a multiple of
-    // 32, so every slice but the last is whole K stages)
+    // 32, so every slice but the last is whole K stages; any on the direct classes)
     int slices;
     int64_t slice_k, slice_stride;
     // (what every launch reads ends here, in three lines of kernel arguments: each

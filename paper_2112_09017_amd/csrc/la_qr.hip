@@ -31,7 +31,6 @@
 
 #include <algorithm>
 #include <type_traits>
-#include <vector>
 
 #include "la_internal.h"
 
@@ -1346,87 +1345,36 @@ int splits_for(int64_t tiles, int64_t K, int num_cus, int max_splits, int64_t mi
     return (int)std::max<int64_t>(1, std::min<int64_t>(sp, max_splits));
 }
 
-// Split-K GEMMs Z (rows x cols, ld cols) = X^T V with X (K x rows, ldx) and
-// V (K x cols, ldv): the slices are independent problems of one grouped
-// launch (so they run side by side), each writing its own slice
-// of parts (max_splits x rows x cols scratch), summed in slice order.  The
-// descriptors of every such product of a factorisation are built on the host
-// first and uploaded once.
-struct SplitGemm {
-    int first_prob, first_item, num_items, splits, cls;
-    float *Z, *parts;
-    int64_t rows, cols;
-};
-
-struct SplitBatch {
-    std::vector<GemmDesc> probs;
-    std::vector<GroupItem> items;
-    std::vector<SplitGemm> gemms;
-};
-
-void add_split(SplitBatch &sb, int prec, const float *X, int64_t ldx, const float *V, int64_t ldv,
-               int64_t rows, int64_t cols, int64_t K, float *Z, float *parts, int num_cus,
-               int max_splits, int64_t min_slice)
+// Split-K GEMM Z (rows x cols, ld cols) = X^T V with X (K x rows, ldx) and V
+// (K x cols, ldv) in one launch: each slice of K writes its own part (max_splits x
+// rows x cols scratch), and the parts are summed in slice order.
+hipError_t run_split(int prec, const float *X, int64_t ldx, const float *V, int64_t ldv,
+                     int64_t rows, int64_t cols, int64_t K, float *Z, float *parts, int num_cus,
+                     int max_splits, int64_t min_slice, hipStream_t s)
 {
     GemmDesc d;
     memset(&d, 0, sizeof d);
+    d.A = X;
     d.lda = ldx;
     d.a_kcontig = 0;
+    d.B = V;
     d.ldb = ldv;
     d.b_kcontig = 0;
     d.ldc = cols;
     d.M = rows;
     d.N = cols;
+    d.K = K;
     d.alpha = 1.0f;
-    gemm_finalize(d, prec);
     gemm_set_class(d, prec, split_class(d));
-    const int splits = splits_for(d.num_tiles, K, num_cus, max_splits, min_slice);
-    const int64_t ks = (K + splits - 1) / splits;
-    SplitGemm g;
-    g.first_prob = (int)sb.probs.size();
-    g.first_item = (int)sb.items.size();
-    g.splits = splits;
-    g.Z = Z;
-    g.parts = parts;
-    g.rows = rows;
-    g.cols = cols;
-    g.cls = d.small;
-    for (int sp = 0; sp < splits; ++sp) {
-        const int64_t k0 = sp * ks;
-        const int64_t kl = std::min<int64_t>(ks, K - k0);
-        d.A = X + k0 * ldx;
-        d.B = V + k0 * ldv;
-        d.C = splits == 1 ? Z : parts + (size_t)sp * rows * cols;
-        d.K = kl > 0 ? kl : 0;
-        const int pid = (int)sb.probs.size() - g.first_prob;
-        sb.probs.push_back(d);
-        for (int tt = 0; tt < d.num_tiles; ++tt)
-            sb.items.push_back(GroupItem{pid, tt});
-    }
-    g.num_items = (int)sb.items.size() - g.first_item;
-    sb.gemms.push_back(g);
-}
-
-// Upper bound of the items one split product of b x cols adds, in the class
-// with the most tiles: splits * tiles <= 2 num_cus + tiles, and at most
-// kMaxSplits * tiles; num_cus is taken as at most 1024.
-size_t split_items_bound(int b, int64_t cols)
-{
-    const size_t tiles = (size_t)((b + 63) / 64) * (size_t)((cols + 63) / 64);
-    return std::max<size_t>(std::min<size_t>(kMaxSplits * tiles, 2048 + tiles),
-                            kMaxSplits * 4);   // one of at most four 32 x 32 tiles
-}
-
-hipError_t run_split(int prec, const SplitBatch &sb, int which, const GemmDesc *probs_dev,
-                     const GroupItem *items_dev, hipStream_t s)
-{
-    const SplitGemm &g = sb.gemms[which];
-    hipError_t e = launch_gemm_grouped(prec, 0, 0, g.cls, probs_dev + g.first_prob,
-                                       items_dev + g.first_item, g.num_items, s);
-    if (e != hipSuccess || g.splits == 1)
+    d.slices = splits_for(d.num_tiles, K, num_cus, max_splits, min_slice);
+    d.slice_k = (K + d.slices - 1) / d.slices;
+    d.slice_stride = rows * cols;
+    d.C = d.slices == 1 ? Z : parts;
+    const hipError_t e = launch_gemm(prec, d, s);
+    if (e != hipSuccess || d.slices == 1)
         return e;
-    hipLaunchKernelGGL(sum_slices_kernel, dim3(grid1d(g.rows * g.cols)), dim3(256), 0, s,
-                       (const float *)g.parts, g.splits, g.rows, g.cols, g.Z, g.cols);
+    hipLaunchKernelGGL(sum_slices_kernel, dim3(grid1d(rows * cols)), dim3(256), 0, s,
+                       (const float *)parts, d.slices, rows, cols, Z, cols);
     return hipGetLastError();
 }
 
@@ -1442,10 +1390,10 @@ hipError_t gemm_sub(int prec, const float *X, int64_t ldx, const float *Z, int64
 // Workspace of la_caqr, in order: Qr (m x b), Rr (b x b), the TSQR tree of an
 // m x b panel, Minv + flag, W and Y (m x n each with Q; without Q two m x b
 // buffers each, alternating between panels), then for the critical stream Z0
-// (b x b) and its split-K parts, for the trailing stream Z1 (b x n) and its
-// parts, and the split-K descriptors.
+// (b x b) and its split-K parts, and for the trailing stream Z1 (b x n) and its
+// parts.
 struct CaqrWs {
-    size_t qr, rr, tree, wy, w, y, z0, parts0, z1, parts1, probs, items, bytes;
+    size_t qr, rr, tree, wy, w, y, z0, parts0, z1, parts1, bytes;
     size_t kap_bytes;   // after them: the TSQR tree's kappa (optional, as la_tsqr's)
 };
 
@@ -1479,15 +1427,6 @@ CaqrWs caqr_ws(int64_t m, int64_t n, int b, int want_q)
     o += al((size_t)b * n * sizeof(float));
     w.parts1 = o;
     o += al(sp_wide * b * n * sizeof(float));
-    // split-K descriptors: next-panel and trailing products of every panel,
-    // and the Q pass
-    const int64_t np = (n + b - 1) / b;
-    // (a next-panel product has at most four tiles, b <= 128)
-    const size_t nwide = (size_t)np * (want_q ? 2 : 1);
-    w.probs = o;
-    o += al(((size_t)np * sp_next + nwide * sp_wide) * sizeof(GemmDesc));
-    w.items = o;
-    o += al(((size_t)np * sp_next * 4 + nwide * split_items_bound(b, n)) * sizeof(GroupItem));
     w.bytes = o;
     w.kap_bytes = tsqr_plan(m, b).kap_bytes;
     return w;
@@ -1705,46 +1644,6 @@ la_status la_caqr(la_context *ctx, int64_t m, int64_t n, float *A, int64_t lda, 
     // where it overlaps the next panels' factorisations.  The next-panel
     // update of panel j waits for the trailing update of panel j - 1 (which
     // covers those columns); a trailing update waits for its panel's W and Y.
-    SplitBatch sb;
-    std::vector<int> zn(np, -1), zt(np, -1), zq(np, -1);
-    for (int64_t jp = 0; jp < np; ++jp) {
-        const int64_t c = jp * b, ml = m - c;
-        const int nc = (int)std::min<int64_t>(b, n - c);
-        const int64_t nx = c + nc, nc2 = std::min<int64_t>(b, n - nx), rest = nx + nc2;
-        if (nc2 > 0) {
-            zn[jp] = (int)sb.gemms.size();
-            add_split(sb, pr, wpan(jp), ldwy, A + c * lda + nx, lda, nc, nc2, ml, Z0, P0,
-                      ctx->num_cus, kMaxSplitsNext, kMinSliceNext);
-        }
-        if (rest < n) {
-            zt[jp] = (int)sb.gemms.size();
-            add_split(sb, pr, wpan(jp), ldwy, A + c * lda + rest, lda, nc, n - rest, ml, Z1, P1,
-                      ctx->num_cus, kMaxSplits, kMinSlice);
-        }
-    }
-    if (Q)
-        for (int64_t jp = np - 1; jp >= 0; --jp) {
-            const int64_t c = jp * b, ml = m - c;
-            const int nc = (int)std::min<int64_t>(b, n - c);
-            zq[jp] = (int)sb.gemms.size();
-            add_split(sb, pr, ypan(jp), n, Q + c * ldq + c, ldq, nc, n - c, ml, Z1, P1,
-                      ctx->num_cus, kMaxSplits, kMinSlice);
-        }
-    if (sb.probs.size() * sizeof(GemmDesc) > cw.items - cw.probs ||
-        sb.items.size() * sizeof(GroupItem) > cw.bytes - cw.items) {
-        set_error("%s: split-K descriptors exceed their workspace region", who);
-        return LA_ERR_OUT_OF_MEMORY;
-    }
-    GemmDesc *probs_dev = (GemmDesc *)(ws + cw.probs);
-    GroupItem *items_dev = (GroupItem *)(ws + cw.items);
-    if (!sb.probs.empty()) {
-        LA_HIP(hipMemcpyAsync(probs_dev, sb.probs.data(), sb.probs.size() * sizeof(GemmDesc),
-                              hipMemcpyHostToDevice, s),
-               "la_caqr: descriptors");
-        LA_HIP(hipMemcpyAsync(items_dev, sb.items.data(), sb.items.size() * sizeof(GroupItem),
-                              hipMemcpyHostToDevice, s),
-               "la_caqr: items");
-    }
     LookAhead la;
     LA_HIP(hipStreamCreateWithFlags(&la.s1, hipStreamNonBlocking), "la_caqr: stream");
     LA_HIP(hipEventCreateWithFlags(&la.wy_ready, hipEventDisableTiming), "la_caqr: event");
@@ -1779,14 +1678,16 @@ la_status la_caqr(la_context *ctx, int64_t m, int64_t n, float *A, int64_t lda, 
                 trail_pending = false;
             }
             // next panel's columns <- Q_f^T (...) = (...) - Y (W^T (...))
-            LA_HIP(run_split(pr, sb, zn[jp], probs_dev, items_dev, s),
+            LA_HIP(run_split(pr, W, ldwy, A + c * lda + nx, lda, nc, nc2, ml, Z0, P0, ctx->num_cus,
+                             kMaxSplitsNext, kMinSliceNext, s),
                    "la_caqr: W^T A_next");
             LA_HIP(gemm_sub(pr, Y, ldwy, Z0, ml, nc2, nc, A + c * lda + nx, lda, s),
                    "la_caqr: next-panel update");
         }
         if (rest < n) {
             LA_HIP(hipStreamWaitEvent(la.s1, la.wy_ready, 0), "la_caqr: wait");
-            LA_HIP(run_split(pr, sb, zt[jp], probs_dev, items_dev, la.s1),
+            LA_HIP(run_split(pr, W, ldwy, A + c * lda + rest, lda, nc, n - rest, ml, Z1, P1,
+                             ctx->num_cus, kMaxSplits, kMinSlice, la.s1),
                    "la_caqr: W^T A_rest");
             LA_HIP(gemm_sub(pr, Y, ldwy, Z1, ml, n - rest, nc, A + c * lda + rest, lda, la.s1),
                    "la_caqr: trailing update");
@@ -1805,7 +1706,8 @@ la_status la_caqr(la_context *ctx, int64_t m, int64_t n, float *A, int64_t lda, 
             const int nc = (int)std::min<int64_t>(b, n - c);
             float *Qc = Q + c * ldq + c;
             // Q[c:, c:] <- Q_f Q[c:, c:] = Q[c:, c:] - W (Y^T Q[c:, c:])
-            LA_HIP(run_split(pr, sb, zq[jp], probs_dev, items_dev, s),
+            LA_HIP(run_split(pr, ypan(jp), n, Qc, ldq, nc, n - c, ml, Z1, P1, ctx->num_cus,
+                             kMaxSplits, kMinSlice, s),
                    "la_caqr: Y^T Q");
             LA_HIP(gemm_sub(pr, wpan(jp), n, Z1, ml, n - c, nc, Qc, ldq, s), "la_caqr: Q");
         }
