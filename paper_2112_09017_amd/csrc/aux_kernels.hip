@@ -138,17 +138,9 @@ void gemm_set_packed(GemmDesc &d)
     d.num_tiles = d.gram ? d.tiles_n * (d.tiles_n + 1) / 2 : d.tiles_m * d.tiles_n;
 }
 
-size_t gemm_max_tiles(int prec, int64_t M, int64_t N, int64_t K)
+size_t step_partials(int64_t M, int64_t N)
 {
-    // of its own class, and of 128 x 128 tiles, which stand in for large ones
-    GemmDesc d{};
-    d.M = M;
-    d.N = N;
-    d.K = K;
-    gemm_finalize(d, prec);
-    const size_t own = (size_t)d.tiles_m * d.tiles_n;
-    gemm_set_class(d, prec, kClassSmall);
-    return std::max(own, (size_t)d.tiles_m * d.tiles_n);
+    return (size_t)((M + 127) / 128) * (size_t)((N + 127) / 128);
 }
 
 hipError_t launch_gemm(int prec, const GemmDesc &d, hipStream_t s)
@@ -235,6 +227,35 @@ __global__ void __launch_bounds__(kThreads) sumsq_kernel(const float *__restrict
         for (int64_t c = threadIdx.x; c < n; c += kThreads) {
             const double x = (double)row[c];
             acc += x * x;
+        }
+    }
+    const double s = block_sum(acc, sh);
+    if (threadIdx.x == 0)
+        parts[blockIdx.x] = s;
+}
+
+// The same of the differences to E: a step norm whose partials per tile have no room.
+// Bound by reading both (1000000 x 64, 512 MB: 150 us).
+__global__ void __launch_bounds__(kThreads) diff_sumsq_kernel(const float *__restrict__ X,
+                                                              int64_t ldx,
+                                                              const float *__restrict__ E,
+                                                              int64_t lde, int64_t m, int64_t n,
+                                                              double *__restrict__ parts)
+{
+    __shared__ double sh[kThreads / 64];
+    double acc = 0.0;
+    const int64_t total = m * n, step = (int64_t)gridDim.x * kThreads;
+    int64_t r = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / n;
+    int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x - r * n;
+    const int64_t dr = step / n, dc = step - dr * n;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += step) {
+        const double df = (double)X[r * ldx + c] - (double)E[r * lde + c];
+        acc += df * df;
+        r += dr;
+        c += dc;
+        if (c >= n) {
+            c -= n;
+            ++r;
         }
     }
     const double s = block_sum(acc, sh);
@@ -702,6 +723,14 @@ hipError_t launch_sumsq(const float *X, int64_t m, int64_t n, int64_t ld, double
 {
     hipLaunchKernelGGL(sumsq_kernel, dim3(kSumsqBlocks), dim3(kThreads), 0, s, X, m, n, ld,
                        partials);
+    return hipGetLastError();
+}
+
+hipError_t launch_diff_sumsq(const float *X, int64_t ldx, const float *E, int64_t lde, int64_t m,
+                             int64_t n, double *partials, hipStream_t s)
+{
+    hipLaunchKernelGGL(diff_sumsq_kernel, dim3(kSumsqBlocks), dim3(kThreads), 0, s, X, ldx, E, lde,
+                       m, n, partials);
     return hipGetLastError();
 }
 

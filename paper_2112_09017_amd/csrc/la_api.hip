@@ -167,7 +167,7 @@ struct PolarWs {
     float *P;        // n x n: I - c U^T U or I - U^T U
     float *parts;    // split-K slices of a Gram, an update or H (may be null)
     double *tiles;   // per-tile (or per-block) step-norm partials
-    double *sumsq;   // norm partials
+    double *sumsq;   // norm partials, then the rest of the step-norm partials
     double *scal;    // [0] ||A||_F^2, [1] ||U' - U||_F^2
     PackBuf pk;      // packed copies of U and P for the update, or of U^T for the Gram
     PolarChain chain;   // where col is not null
@@ -328,10 +328,7 @@ static size_t parts_floats(const PolarPlan &p)
 
 static size_t max_update_tiles(const PolarPlan &p)
 {
-    size_t t = (size_t)splitk_update_num_partials();
-    for (int pr : {PREC_FP32, PREC_BF16X3, PREC_BF16X6, PREC_F16X3})
-        t = std::max(t, gemm_max_tiles(pr, p.m, p.n, p.n));
-    return t;
+    return std::max((size_t)splitk_update_num_partials(), step_partials(p.m, p.n));
 }
 
 size_t polar_workspace_bytes(const PolarPlan &p)
@@ -537,11 +534,48 @@ struct ChainStep {
     bool only;   // nothing but the next step's products reads Xn
 };
 
-// Xn <- alpha X P + beta X (partials of (Xn - X)^2 in tiles if tiles != null;
-// *ntiles receives their count).
+// Partials of a step norm (Xn - X)^2, where they ended up.
+struct StepNorm {
+    const double *parts;
+    int64_t count;
+};
+
+// The Gram's slices have been added before the update, so their region is free for its
+// partials (polar of 1000000 x 64 20.2 ms with the pass behind the update, 19.0 without).
+static double *spare_region(const PolarWs &w, int64_t count)
+{
+    return 2 * (size_t)count <= w.parts_floats ? (double *)w.parts : nullptr;
+}
+
+// Where the partials of a launch of tiles_m x tiles_n tiles go; without room for them
+// the launch has none and step_norm_after writes others behind it.
+template <class Ws>
+static double *step_norm_room(const GemmDesc &d, const Ws &w, StepNorm *norm)
+{
+    norm->count = (int64_t)d.tiles_m * d.tiles_n;
+    double *to = step_room(norm->count, w.tiles, w.sumsq, sumsq_num_partials())
+                     ? w.tiles
+                     : spare_region(w, norm->count);
+    norm->parts = to;
+    return to;
+}
+
+template <class Ws>
+static hipError_t step_norm_after(const GemmDesc &d, const Ws &w, StepNorm *norm, hipStream_t s)
+{
+    if (norm->parts) {
+        norm->count = (int64_t)d.tiles_m * d.tiles_n;   // (packed operands: other tiles)
+        return hipSuccess;
+    }
+    norm->parts = w.sumsq;
+    norm->count = sumsq_num_partials();
+    return launch_diff_sumsq(d.C, d.ldc, d.E, d.lde, d.M, d.N, w.sumsq, s);
+}
+
+// Xn <- alpha X P + beta X, with the partials of (Xn - X)^2 if norm is not null.
 static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int64_t ldx,
                               const float *P, double alpha, double beta, float *Xn, int64_t ldxn,
-                              double *tiles, int *ntiles, const PolarWs &w, hipStream_t s,
+                              StepNorm *norm, const PolarWs &w, hipStream_t s,
                               const int *stop = nullptr, const ChainStep *cs = nullptr)
 {
     const int64_t m = p.m, n = p.n;
@@ -569,10 +603,11 @@ static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int6
         hipError_t e = gemm_packed_or_plain(prec, d, w.pk, s);
         if (e != hipSuccess)
             return e;
-        if (ntiles)
-            *ntiles = splitk_update_num_partials();
+        if (norm)
+            *norm = StepNorm{w.tiles, splitk_update_num_partials()};
         return launch_splitk_update_reduce(w.parts, d.slices, m, n, alpha, beta,
-                                           beta != 0.0 ? X : nullptr, ldx, Xn, ldxn, tiles, s);
+                                           beta != 0.0 ? X : nullptr, ldx, Xn, ldxn,
+                                           norm ? w.tiles : nullptr, s);
     }
     d.C = Xn;
     d.ldc = ldxn;
@@ -582,10 +617,11 @@ static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int6
         d.lde = ldx;
         d.beta = (float)beta;
     }
-    d.partials = tiles;
     d.stop = stop;
     gemm_f16_scales(d, prec, kIterScale, kIterScale);
     gemm_finalize(d, prec);
+    if (norm)
+        d.partials = step_norm_room(d, w, norm);
     if (cs) {
         d.pack_row = w.chain.row[cs->cur ^ 1];
         d.pack_col = w.chain.col;
@@ -601,9 +637,7 @@ static hipError_t update_step(const PolarPlan &p, int prec, const float *X, int6
     }
     const hipError_t e = cs && cs->packed ? launch_gemm_packed(prec, d, s)
                                           : gemm_packed_or_plain(prec, d, w.pk, s);
-    if (ntiles)
-        *ntiles = d.tiles_m * d.tiles_n;
-    return e;
+    return e == hipSuccess && norm ? step_norm_after(d, w, norm, s) : e;
 }
 
 // Newton-Schulz (inversion) steps queued before the first look at the stop test, and
@@ -696,19 +730,11 @@ static la_status inverse_plan(int64_t n, int64_t m, const la_inverse_opts *opts,
     return LA_OK;
 }
 
-static size_t inverse_max_tiles(const InvPlan &p)
-{
-    size_t t = 0;
-    for (int pr : {PREC_FP32, PREC_BF16X3, PREC_BF16X6})
-        t = std::max(t, gemm_max_tiles(pr, p.m, p.n, p.wide ? p.n : p.m));
-    return t;
-}
-
 struct InvWs {
     float *X;        // m x n, ld n: the iterate's second buffer
     float *R;        // r x r: the Gram A A^T (or A^T A), then I - A X (or I - X A)
     double *tiles;   // per-tile step-norm partials
-    double *sumsq;   // norm partials
+    double *sumsq;   // norm partials, then the rest of the step-norm partials
     double *scal;    // [0] ||A A^T||_F^2, [1] ||X' - X||_F^2
     PackBuf pk;      // packed operands of the step's products
     char *pka;       // A packed once for the first product (may be null)
@@ -718,6 +744,7 @@ struct InvWs {
     int *uneven;
 };
 constexpr size_t kFlagWords = 64;
+static double *spare_region(const InvWs &, int64_t) { return nullptr; }
 
 // Packed operands of the larger of the two products of a step: R = A X
 // (r x r, K = m) or X A (K = n), then X R (m x n, K = n) or R X (K = m);
@@ -791,7 +818,7 @@ static size_t inverse_workspace_bytes(const InvPlan &p)
     size_t b = 0;
     b += align256((size_t)p.m * p.n * sizeof(float));
     b += align256((size_t)p.r * p.r * sizeof(float));
-    b += align256(inverse_max_tiles(p) * sizeof(double));
+    b += align256(step_partials(p.m, p.n) * sizeof(double));
     b += align256((size_t)sumsq_num_partials() * sizeof(double));
     b += align256(8 * sizeof(double));
     b += inverse_pack_bytes(p);
@@ -812,7 +839,7 @@ static InvWs inverse_carve(const InvPlan &p, void *ws, bool room, bool max_room)
     w.R = (float *)b;
     b += align256((size_t)p.r * p.r * sizeof(float));
     w.tiles = (double *)b;
-    b += align256(inverse_max_tiles(p) * sizeof(double));
+    b += align256(step_partials(p.m, p.n) * sizeof(double));
     w.sumsq = (double *)b;
     b += align256((size_t)sumsq_num_partials() * sizeof(double));
     w.scal = (double *)b;
@@ -873,10 +900,10 @@ static hipError_t polish_product(const InvPlan &p, GemmDesc &d, const InvWs &w, 
 }
 
 // One step X' = X + X (I - A X)  (wide / square)  or  X + (I - X A) X  (tall),
-// with FP64 per-tile partials of (X' - X)^2 in w.tiles.
+// with FP64 partials of (X' - X)^2.
 static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64_t lda,
                                const float *X, int64_t ldx, float *Xn, int64_t ldxn,
-                               const InvWs &w, int *ntiles, hipStream_t s,
+                               const InvWs &w, StepNorm *norm, hipStream_t s,
                                const int *stop = nullptr)
 {
     GemmDesc d;
@@ -936,7 +963,6 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
     u.beta = 1.0f;
     u.E = X;
     u.lde = ldx;
-    u.partials = w.tiles;
     if (p.wide) {               // X' = X + X R: X (m x n) . R (n x n)
         u.A = X;
         u.lda = ldx;
@@ -956,10 +982,11 @@ static hipError_t inverse_step(const InvPlan &p, int prec, const float *A, int64
     }
     u.stop = stop;
     gemm_finalize(u, prec);
-    e = f16(u) ? polish_product(p, u, w, w.counts + p.m + p.n, s)
-               : gemm_packed_or_plain(prec, u, w.pk, s);
-    *ntiles = u.tiles_m * u.tiles_n;
-    return e;
+    const bool fp16 = f16(u);
+    u.partials = step_norm_room(u, w, norm);
+    e = fp16 ? polish_product(p, u, w, w.counts + p.m + p.n, s)
+             : gemm_packed_or_plain(prec, u, w.pk, s);
+    return e == hipSuccess ? step_norm_after(u, w, norm, s) : e;
 }
 
 // Tile class of a caller's product whose 64 x 64 tiles take a third (FP32: also a fifth
@@ -1459,7 +1486,6 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &plan, const float 
     StopState stop;
     bool converged = false, finite = true;
 
-    LA_HIP(launch_sumsq(A, m, n, lda, w.sumsq, s), "la_polar: norm");
     const bool ahead = queues_ahead(p);
     StepState *st = (StepState *)w.scal;
     StepState h;
@@ -1474,6 +1500,7 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &plan, const float 
     // in the second iterate's buffer), stops every later write of queued steps.  Steps
     // that wait for the host take what they need from the readback of the norm.
     auto begin = [&]() {
+        LA_HIP(launch_sumsq(A, m, n, lda, w.sumsq, s), "la_polar: norm");
         LA_HIP(launch_norm_state(w.sumsq, sumsq_num_partials(), st, s), "la_polar: norm");
         if (ahead)
             LA_HIP(launch_scale_by_norm(A, lda, buf[0], ld[0], m, n, &st->norm2, s, dev_stop),
@@ -1527,7 +1554,7 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &plan, const float 
                              dev_stop),
                    "la_polar: precondition gram");
             LA_HIP(update_step(p, p.prec_pre, buf[cur], ld[cur], w.P, p.a, 0.0, buf[cur ^ 1],
-                               ld[cur ^ 1], nullptr, nullptr, w, s, dev_stop, csp),
+                               ld[cur ^ 1], nullptr, w, s, dev_stop, csp),
                    "la_polar: precondition update");
             cs.packed = chain;
             cur ^= 1;
@@ -1553,16 +1580,17 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &plan, const float 
             int queued = 0, batch = kFirstBatch;
             do {
                 for (const int to = std::min(queued + batch, p.max_iter); queued < to; ++queued) {
-                    int ntiles = 0;
+                    StepNorm norm;
                     cs.cur = cur;
                     LA_HIP(gram_step(p, p.prec_ns, buf[cur], ld[cur], -1.0, 1.0, w.P, w, s,
                                      cs.packed, dev_stop),
                            "la_polar: NS gram");
                     LA_HIP(update_step(p, p.prec_ns, buf[cur], ld[cur], w.P, 0.5, 1.0, buf[cur ^ 1],
-                                       ld[cur ^ 1], w.tiles, &ntiles, w, s, dev_stop, csp),
+                                       ld[cur ^ 1], &norm, w, s, dev_stop, csp),
                            "la_polar: NS update");
                     cs.packed = chain;
-                    LA_HIP(launch_step_state(w.tiles, ntiles, st, t, s), "la_polar: delta");
+                    LA_HIP(launch_step_state(norm.parts, norm.count, st, t, s),
+                           "la_polar: delta");
                     cur ^= 1;
                 }
                 batch = kNextBatch;
@@ -1597,16 +1625,16 @@ static la_status polar_impl(la_context *ctx, const PolarPlan &plan, const float 
     }
     while (!ahead) {
         const int prec = stop.stopped ? PREC_BF16X6 : p.prec_ns;
-        int ntiles = 0;
+        StepNorm norm;
         const bool last = stop.stopped;   // the polish step, from FP32
         cs.cur = cur;
         LA_HIP(gram_step(p, prec, buf[cur], ld[cur], -1.0, 1.0, w.P, w, s, cs.packed && !last),
                "la_polar: NS gram");
         LA_HIP(update_step(p, prec, buf[cur], ld[cur], w.P, 0.5, 1.0, buf[cur ^ 1], ld[cur ^ 1],
-                           w.tiles, &ntiles, w, s, nullptr, last ? nullptr : csp),
+                           &norm, w, s, nullptr, last ? nullptr : csp),
                "la_polar: NS update");
         cs.packed = chain;
-        LA_HIP(launch_reduce_fixed(w.tiles, ntiles, w.scal + 1, s), "la_polar: delta");
+        LA_HIP(launch_reduce_fixed(norm.parts, norm.count, w.scal + 1, s), "la_polar: delta");
         LA_HIP(hipMemcpyAsync(h2 + 1, w.scal + 1, sizeof(double), hipMemcpyDeviceToHost, s),
                "la_polar: readback");
         LA_HIP(hipStreamSynchronize(s), "la_polar: sync");
@@ -1778,12 +1806,12 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
         int queued = 0, batch = kFirstInvBatch;
         do {
             for (const int to = std::min(queued + batch, p.max_iter); queued < to; ++queued) {
-                int ntiles = 0;
+                StepNorm norm;
                 const int from = queued & 1;
                 LA_HIP(inverse_step(p, p.prec, A, lda, buf[from], ld[from], buf[from ^ 1],
-                                    ld[from ^ 1], w, &ntiles, s, &st->stop),
+                                    ld[from ^ 1], w, &norm, s, &st->stop),
                        "la_inverse: step");
-                LA_HIP(launch_step_state(w.tiles, ntiles, st, t, s), "la_inverse: delta");
+                LA_HIP(launch_step_state(norm.parts, norm.count, st, t, s), "la_inverse: delta");
             }
             batch = kNextBatch;
             LA_HIP(hipMemcpyAsync(&h, st, sizeof h, hipMemcpyDeviceToHost, s),
@@ -1804,17 +1832,18 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
     for (; it < total && finite; ++it) {
         const bool polishing = stopped;
         const int prec = polishing ? PREC_BF16X6 : p.prec;
-        int ntiles = 0, uneven = 0;
+        int uneven = 0;
+        StepNorm norm;
         if (polishing && w.mx)
             LA_HIP(launch_zero((uint32_t *)w.uneven, kFlagWords + 2 * (p.m + p.n), s),
                    "la_inverse: unevenness");
         LA_HIP(inverse_step(p, prec, A, lda, buf[cur], ld[cur], buf[cur ^ 1], ld[cur ^ 1], w,
-                            &ntiles, s),
+                            &norm, s),
                "la_inverse: step");
         if (polishing && w.mx)
             LA_HIP(hipMemcpyAsync(&uneven, w.uneven, sizeof uneven, hipMemcpyDeviceToHost, s),
                    "la_inverse: readback");
-        LA_HIP(launch_reduce_fixed(w.tiles, ntiles, w.scal + 1, s), "la_inverse: delta");
+        LA_HIP(launch_reduce_fixed(norm.parts, norm.count, w.scal + 1, s), "la_inverse: delta");
         LA_HIP(hipMemcpyAsync(h2 + 1, w.scal + 1, sizeof(double), hipMemcpyDeviceToHost, s),
                "la_inverse: readback");
         LA_HIP(hipStreamSynchronize(s), "la_inverse: sync");

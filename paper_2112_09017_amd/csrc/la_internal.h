@@ -98,9 +98,16 @@ void gemm_set_class(GemmDesc &d, int prec, int cls);
 // Sets d up for packed operands (launch_gemm_packed): a direct class as it is,
 // else the tile side and the counts that follow from it.
 void gemm_set_packed(GemmDesc &d);
-// Most output tiles an M x N x K product (not a Gram) can take: the partials
-// its step norm needs.
-size_t gemm_max_tiles(int prec, int64_t M, int64_t N, int64_t K);
+// Partials of a step norm that a workspace has room for, of an M x N iterate: one per
+// 128 x 128 tile.  The region of the norm partials (sumsq_num_partials) follows it and
+// is free during the steps, so a launch of smaller tiles may write its partials over both
+// (step_room); a launch with more of them (a long side beside one below 128, and a few
+// sizes at FP32) leaves its partials out, and launch_diff_sumsq writes others.
+size_t step_partials(int64_t M, int64_t N);
+inline bool step_room(int64_t count, const double *tiles, const double *sumsq, int sumsq_count)
+{
+    return count <= (sumsq - tiles) + sumsq_count;
+}
 
 // Sets the factors of a PREC_F16X3 product (powers of two sa, sb with |sa a| and
 // |sb b| below the fp16 range for every entry of its operands) and takes them
@@ -178,6 +185,9 @@ hipError_t launch_short_update(int prec, const float *Y, int64_t ldy, const floa
 int sumsq_num_partials();
 hipError_t launch_sumsq(const float *X, int64_t m, int64_t n, int64_t ld,
                         double *partials, hipStream_t s);
+// The same of X - E.
+hipError_t launch_diff_sumsq(const float *X, int64_t ldx, const float *E, int64_t lde, int64_t m,
+                             int64_t n, double *partials, hipStream_t s);
 // out[0] = sum of parts[0..count) in a fixed order (deterministic).
 hipError_t launch_reduce_fixed(const double *parts, int64_t count, double *out,
                                hipStream_t s);

@@ -137,7 +137,7 @@ class PinnedPool {
 // Device and host state of one request.
 struct DevReq {
     float *A = nullptr, *X[2] = {nullptr, nullptr}, *P = nullptr;
-    double *tiles = nullptr, *sumsq = nullptr, *scal = nullptr;
+    double *tiles = nullptr, *sumsq = nullptr, *scal = nullptr;   // (tiles: over sumsq too)
     int cur = 0;
     PolarChain chain = {};   // where col is not null
     int packed = 0;          // the arithmetic X[cur] is there packed in, 0: it is not
@@ -145,15 +145,6 @@ struct DevReq {
     float *hh = nullptr;    // pinned: H (n n floats)
     size_t io_cls = 0, hh_cls = 0;
 };
-
-// Most update tiles any precision uses for an m x n iterate.
-size_t max_tiles(int64_t m, int64_t n)
-{
-    size_t t = 0;
-    for (int pr : {PREC_FP32, PREC_BF16X3, PREC_BF16X6, PREC_F16X3})
-        t = std::max(t, gemm_max_tiles(pr, m, n, n));
-    return t;
-}
 
 struct Launch {
     int prec, akc, bkc, cls;
@@ -281,7 +272,7 @@ struct HipExec {
     static size_t plain_footprint(const serve::Req &r)
     {
         const size_t mn = (size_t)r.m * r.n, nn = (size_t)r.n * r.n;
-        return up(mn * 4) * 3 + up(nn * 4) + up(max_tiles(r.m, r.n) * 8) +
+        return up(mn * 4) * 3 + up(nn * 4) + up(step_partials(r.m, r.n) * 8) +
                up((size_t)sumsq_num_partials() * 8) + up(8 * 8);
     }
     // bytes of the request's packed copies, 0 where it goes without
@@ -365,7 +356,7 @@ struct HipExec {
         d->P = (float *)b;
         b += up(nn * 4);
         d->tiles = (double *)b;
-        b += up(max_tiles(r.m, r.n) * 8);
+        b += up(step_partials(r.m, r.n) * 8);
         d->sumsq = (double *)b;
         b += up((size_t)sumsq_num_partials() * 8);
         d->scal = (double *)b;
@@ -520,6 +511,7 @@ struct HipExec {
         const bool all_large = large_load >= 2 * (int64_t)ctx->num_cus;
         std::vector<Launch> grams, updates;
         std::vector<ReduceItem> red;
+        std::vector<GemmDesc> no_room;   // updates whose step norms are taken behind them
         for (serve::Req *r : fresh)
             red.push_back(ReduceItem{((DevReq *)r->x)->scal, 1, dev_d + red.size()});
         for (serve::Req *r : run) {
@@ -566,9 +558,15 @@ struct HipExec {
                 ud.beta = 1.0f;
                 ud.E = d->X[d->cur];
                 ud.lde = r->n;
-                ud.partials = d->tiles;
-                red.push_back(ReduceItem{d->tiles, (int64_t)ud.tiles_m * ud.tiles_n,
-                                         dev_d + red.size()});
+                const int64_t nt = (int64_t)ud.tiles_m * ud.tiles_n;
+                if (step_room(nt, d->tiles, d->sumsq, sumsq_num_partials())) {
+                    ud.partials = d->tiles;
+                    red.push_back(ReduceItem{d->tiles, nt, dev_d + red.size()});
+                } else {
+                    no_room.push_back(ud);
+                    no_room.back().partials = d->sumsq;
+                    red.push_back(ReduceItem{d->sumsq, sumsq_num_partials(), dev_d + red.size()});
+                }
             }
             add_problem(updates, prec, 1, 0, ud, packed);
         }
@@ -592,6 +590,9 @@ struct HipExec {
             e = run_phase(sg);
         if (e == hipSuccess)
             e = run_phase(su);
+        for (const GemmDesc &u : no_room)
+            if (e == hipSuccess)
+                e = launch_diff_sumsq(u.C, u.ldc, u.E, u.lde, u.M, u.N, u.partials, stream);
         // 3. the norms of the new requests and the step norms, one readback
         if (e == hipSuccess && !red.empty()) {
             e = launch_reduce_grouped(dev_ri, (int)red.size(), stream);

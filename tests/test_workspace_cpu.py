@@ -35,3 +35,18 @@ A, X, H = 1 << 44, 2 << 44, 3 << 44
     (5, 5, 128, 1, 3840)])
 def test_caqr(m, n, panel, q, size):
     assert required("la_caqr", m, n, A, n, X if q else None, n, panel, WS, 0, None) <= size
+
+
+@pytest.mark.parametrize("m,n,size", [
+    (256, 256, 1065216), (1000, 1000, 16016640), (100000, 1, 417280), (100000, 64, 26452224),
+    (100000, 100, 42056960), (1000000, 3, 12089088), (10000000, 1, 40653568)])
+def test_polar(m, n, size):
+    assert required("la_polar", m, n, A, n, X, n, None, n, WS, None, None, None) <= size
+
+
+@pytest.mark.parametrize("n,m,size", [
+    (256, 256, 532992), (1000, 1000, 8008960), (1600, 1600, 20489984), (1, 100000, 415232),
+    (64, 100000, 25631232), (100000, 100, 40055040), (3, 1000000, 12071424),
+    (10000000, 1, 40633856)])
+def test_inverse(n, m, size):
+    assert required("la_inverse", n, m, A, m, X, n, WS, None, None, None) <= size
