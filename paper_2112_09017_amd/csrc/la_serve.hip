@@ -70,6 +70,10 @@ constexpr double kBandWork = 2048.0 * 2048.0 * 2048.0;
 // launch groups of one staging pass: at most 4 product arithmetics x 4 tile classes
 // x 2 phases, each with its descriptors and its items padded to kAlign
 constexpr int kMaxGroups = 32;
+// Most tiles of a direct class a request's update may have, beside the few of its Gram, in
+// a tick's items: longer ones (12.5M rows) take 128 x 128 tiles.
+constexpr int64_t kMaxDirectTiles =
+    (int64_t)((kItemBytes - kMaxGroups * kAlign) / sizeof(GroupItem)) - 1024;
 // A request takes the packed copies of its products' results (PolarChain) if at
 // least this many such requests fit the arena: they double its footprint (twelve
 // requests of 128^2 to 1536^2: 7.1 ms of ticks with them, 8.6 ms without).
@@ -231,6 +235,9 @@ GemmDesc update_desc(const float *X, const float *P, float *Xn, int64_t m, int64
     d.alpha = alpha;
     gemm_f16_scales(d, prec, kIterScale, kIterScale);
     gemm_finalize(d, prec);
+    // (the smaller tiles of a long thin update would pass the tick's items)
+    if (is_direct(d.small) && d.num_tiles > kMaxDirectTiles)
+        gemm_set_class(d, prec, kClassSmall);
     return d;
 }
 
@@ -278,7 +285,8 @@ struct HipExec {
     // bytes of the request's packed copies, 0 where it goes without
     size_t chain_bytes(const serve::Req &r) const
     {
-        const size_t c = polar_chain_bytes(r.plan, true);
+        const GemmDesc u = update_desc(nullptr, nullptr, nullptr, r.m, r.n, 1.0f, r.plan.prec_ns);
+        const size_t c = is_direct(u.small) ? polar_chain_bytes(r.plan, true) : 0;
         return c && (plain_footprint(r) + c) * kChainFit <= req_bytes ? c : 0;
     }
     size_t footprint(const serve::Req &r) { return plain_footprint(r) + chain_bytes(r); }
