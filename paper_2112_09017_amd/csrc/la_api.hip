@@ -1331,8 +1331,10 @@ la_status la_gemm_ws(la_context *ctx, int trans_a, int trans_b, int64_t m, int64
     if (st != LA_OK || empty)
         return st;
     hipStream_t s = (hipStream_t)hip_stream;
-    // packed path: 3xBF16 on large tiles with enough K to repay the pack pass
-    if (p != PREC_BF16X3 || d.small || k < 256) {
+    // packed path: 3xBF16 on large tiles with enough K to repay the pack pass (the
+    // workspace is asked for whatever the smaller side, though one below 256 packs nothing)
+    const bool plain = p != PREC_BF16X3 || d.small || k < 256;
+    if (plain && !packs(p, m, n, k)) {
         gemm_pick_tiles(d, p);
         LA_HIP(launch_gemm(p, d, s), "la_gemm_ws: launch");
         return LA_OK;
@@ -1353,6 +1355,10 @@ la_status la_gemm_ws(la_context *ctx, int trans_a, int trans_b, int64_t m, int64
         overlaps(workspace, need, C, extent_bytes(m, n, ldc))) {
         set_error("la_gemm_ws: workspace overlaps A, B or C");
         return LA_ERR_INVALID_ARG;
+    }
+    if (plain) {
+        LA_HIP(launch_gemm(p, d, s), "la_gemm_ws: launch");
+        return LA_OK;
     }
     char *wa = (char *)workspace, *wb = wa + pa;
     // op(A) rows are the output rows; op(B)^T rows are the output columns

@@ -64,3 +64,15 @@ def test_third_round(la, prec, m, n, ks, ta, tb):
         if prec == 2:
             D = la.gemm_packed(la.pack_bf16x3(a), la.pack_bf16x3(b.T), m, n, k)
             assert torch.equal(C, D)
+
+
+@pytest.mark.parametrize("m,n,k", [(4096, 2048, 256), (100, 33000, 300), (32513, 7, 256)])
+def test_workspace_is_asked_for(la, m, n, k):
+    # 3xBF16 with at least 128 tiles of 256 x 256, also where a side is below 256
+    a, b = operands(m, n, k, 0, 0)
+    short = torch.empty(la.gemm_workspace_size(m, n, k) - 1, dtype=torch.uint8, device="cuda")
+    assert short.data_ptr() % 256 == 0
+    with pytest.raises(la.LAError) as e:
+        la.gemm_ws(a, b, workspace=short)
+    assert e.value.status == la.Status.OUT_OF_MEMORY
+    assert torch.equal(la.gemm_ws(a, b), la.gemm(a, b))
