@@ -612,19 +612,14 @@ hipError_t launch_any(const GemmDesc &d, hipStream_t s)
     return launch_t<PREC>(d, s);
 }
 
+// (op(B) is row-contiguous: launch_grouped_any)
 template <int PREC, int CLS>
-hipError_t launch_direct_items(int akc, int bkc, const GemmDesc *probs, const GroupItem *items,
+hipError_t launch_direct_items(int akc, const GemmDesc *probs, const GroupItem *items,
                                int num_items, hipStream_t s)
 {
     const dim3 grid(num_items), block(DirectCfg<CLS>::KW * 64);
-    if (akc && bkc)
-        hipLaunchKernelGGL((gemm_direct_items_kernel<PREC, true, true, CLS>), grid, block, 0, s,
-                           probs, items, num_items);
-    else if (akc)
+    if (akc)
         hipLaunchKernelGGL((gemm_direct_items_kernel<PREC, true, false, CLS>), grid, block, 0, s,
-                           probs, items, num_items);
-    else if (bkc)
-        hipLaunchKernelGGL((gemm_direct_items_kernel<PREC, false, true, CLS>), grid, block, 0, s,
                            probs, items, num_items);
     else
         hipLaunchKernelGGL((gemm_direct_items_kernel<PREC, false, false, CLS>), grid, block, 0, s,
@@ -632,17 +627,24 @@ hipError_t launch_direct_items(int akc, int bkc, const GemmDesc *probs, const Gr
     return hipGetLastError();
 }
 
+// A grouped launch of one class.  Every caller's op(B) is row-contiguous, and the direct
+// classes come here at FP32 only (launch_gemm_mixed takes the others): nothing else is
+// built.
 template <int PREC>
 hipError_t launch_grouped_any(int akc, int bkc, int small, const GemmDesc *probs,
                               const GroupItem *items, int num_items, hipStream_t s)
 {
     if (num_items <= 0)
         return hipSuccess;
-    if (small == kClassDirect64)
-        return launch_direct_items<PREC, kClassDirect64>(akc, bkc, probs, items, num_items, s);
-    if (small == kClassDirect32)
-        return launch_direct_items<PREC, kClassDirect32>(akc, bkc, probs, items, num_items, s);
-    return launch_grouped_t<PREC>(akc, bkc, small, probs, items, num_items, s);
+    if (bkc)
+        return hipErrorInvalidValue;
+    if (!is_direct(small))
+        return launch_grouped_t<PREC>(akc, small, probs, items, num_items, s);
+    if constexpr (PREC == PREC_FP32)
+        return small == kClassDirect64
+                   ? launch_direct_items<PREC, kClassDirect64>(akc, probs, items, num_items, s)
+                   : launch_direct_items<PREC, kClassDirect32>(akc, probs, items, num_items, s);
+    return hipErrorInvalidValue;
 }
 
 template <int PREC, int CLS> hipError_t launch_direct_packed(const GemmDesc &d, hipStream_t s)

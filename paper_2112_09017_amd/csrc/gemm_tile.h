@@ -1724,18 +1724,12 @@ hipError_t launch_t(const GemmDesc &d, hipStream_t s)
 }
 
 template <int PREC>
-hipError_t launch_grouped_one(int akc, int bkc, const GemmDesc *probs, const GroupItem *items,
+hipError_t launch_grouped_one(int akc, const GemmDesc *probs, const GroupItem *items,
                               int num_items, hipStream_t s)
 {
     const dim3 grid(num_items), block(Geo<PREC>::NT);
-    if (akc && bkc)
-        hipLaunchKernelGGL((gemm_items_kernel<PREC, true, true>), grid, block, 0, s, probs, items,
-                           num_items);
-    else if (akc)
+    if (akc)
         hipLaunchKernelGGL((gemm_items_kernel<PREC, true, false>), grid, block, 0, s, probs, items,
-                           num_items);
-    else if (bkc)
-        hipLaunchKernelGGL((gemm_items_kernel<PREC, false, true>), grid, block, 0, s, probs, items,
                            num_items);
     else
         hipLaunchKernelGGL((gemm_items_kernel<PREC, false, false>), grid, block, 0, s, probs,
@@ -1744,13 +1738,11 @@ hipError_t launch_grouped_one(int akc, int bkc, const GemmDesc *probs, const Gro
 }
 
 template <int PREC>
-hipError_t launch_grouped_t(int akc, int bkc, int small, const GemmDesc *probs,
-                            const GroupItem *items, int num_items, hipStream_t s)
+hipError_t launch_grouped_t(int akc, int small, const GemmDesc *probs, const GroupItem *items,
+                            int num_items, hipStream_t s)
 {
-    if (num_items <= 0)
-        return hipSuccess;
-    return small ? launch_grouped_one<PREC | kSmall>(akc, bkc, probs, items, num_items, s)
-                 : launch_grouped_one<PREC>(akc, bkc, probs, items, num_items, s);
+    return small ? launch_grouped_one<PREC | kSmall>(akc, probs, items, num_items, s)
+                 : launch_grouped_one<PREC>(akc, probs, items, num_items, s);
 }
 
 // Packed operand bytes for R rows and inner dimension K.

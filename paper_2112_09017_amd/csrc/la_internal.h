@@ -130,7 +130,8 @@ constexpr int kXcds = 8;
 // share precision, operand layouts and tile class.  probs / items live in
 // device memory.  One workgroup per item, item b on workgroup b, hence on XCD
 // b % kXcds.  An item with prob < 0 is empty (padding of a list laid out for
-// the XCDs).
+// the XCDs).  hipErrorInvalidValue for an op(B) with k contiguous, and for the direct
+// classes at another arithmetic than FP32.
 struct GroupItem {
     int prob;
     int tile;   // linear tile index within the problem
