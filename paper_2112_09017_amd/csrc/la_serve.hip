@@ -60,7 +60,7 @@ constexpr size_t kAlign = 256;
 constexpr size_t kDescBytes = 512u << 10;    // descriptor (and reduce item) budget
 constexpr size_t kItemBytes = 3u << 20;      // GroupItem budget
 constexpr size_t kUpBytes = kDescBytes + kItemBytes;
-constexpr size_t kRedBytes = 512u << 10;     // norms read back
+constexpr size_t kRedBytes = 512u << 10;     // norms and answers read back
 constexpr size_t kBandReserve = kUpBytes + kRedBytes;
 constexpr int kMaxSlots = 4096;
 // Size bands: square requests up to n = 2048 (m n^2 <= 2048^3) tick apart
@@ -78,7 +78,8 @@ constexpr int64_t kMaxDirectTiles =
 // least this many such requests fit the arena: they double its footprint (twelve
 // requests of 128^2 to 1536^2: 7.1 ms of ticks with them, 8.6 ms without).
 constexpr size_t kChainFit = 16;
-static_assert(2 * kMaxSlots * sizeof(double) <= kRedBytes, "norms of one tick");
+static_assert(2 * kMaxSlots * sizeof(double) + kMaxSlots * sizeof(int) <= kRedBytes,
+              "norms and answers of one tick");
 static_assert(2 * sizeof(ReduceItem) <= sizeof(GemmDesc), "reduce items in a descriptor slot");
 
 size_t up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
@@ -270,7 +271,7 @@ struct HipExec {
     hipStream_t side[kSide] = {};
     hipEvent_t ev_go = nullptr, ev_side[kSide] = {};
     char *h_stage = nullptr;     // pinned mirror of the staging area
-    double *h_red = nullptr;     // pinned: norms read back
+    double *h_red = nullptr;     // pinned: norms and answers read back
     PinnedPool *pool = nullptr;  // shared by the bands
 
     // ---- the executor interface of serve_core.h
@@ -470,13 +471,15 @@ struct HipExec {
         double *dev_d = (double *)(stage_dev + kUpBytes);
         // 1. new requests: input, ||A||_F^2 in FP64, X0 = A / ||A||_F on the device,
         // and for those with phases on F16X3 whether A is too uneven for it (the other
-        // iterate's buffer holds the counts), read back before their first step
-        int *uneven = (int *)dev_d;   // free until the tick's norms are written
+        // iterate's buffer holds the counts), read back with the norms
+        int *uneven = (int *)(dev_d + 2 * kMaxSlots);
+        const int *h_uneven = (const int *)(h_red + 2 * kMaxSlots);
         std::vector<serve::Req *> checked;
         for (serve::Req *r : fresh)
             if (uses_f16(r->plan, true))
                 checked.push_back(r);
-        e = launch_zero((uint32_t *)uneven, (int64_t)checked.size(), stream);
+        if (!checked.empty())
+            e = launch_zero((uint32_t *)uneven, (int64_t)checked.size(), stream);
         int ncheck = 0;
         for (serve::Req *r : fresh) {
             DevReq *d = (DevReq *)r->x;
@@ -495,15 +498,6 @@ struct HipExec {
                 e = launch_uneven(d->A, r->n, r->m, r->n, d->scal, (uint32_t *)d->X[1],
                                   uneven + ncheck++, nullptr, stream);
             d->cur = 0;
-        }
-        if (e == hipSuccess && !checked.empty()) {
-            e = hipMemcpyAsync(h_red, uneven, checked.size() * sizeof(int),
-                               hipMemcpyDeviceToHost, stream);
-            if (e == hipSuccess)
-                e = hipStreamSynchronize(stream);
-            for (size_t i = 0; i < checked.size() && e == hipSuccess; ++i)
-                if (((const int *)h_red)[i])
-                    without_f16(checked[i]->plan);
         }
         // 2. one step for every running request.  A tick whose requests would
         // fill the device twice over with large tiles runs all of them on large
@@ -608,18 +602,35 @@ struct HipExec {
                 e = hipMemcpyAsync(h_red, dev_d, red.size() * sizeof(double),
                                    hipMemcpyDeviceToHost, stream);
         }
+        if (e == hipSuccess && !checked.empty())
+            e = hipMemcpyAsync((void *)h_uneven, uneven, checked.size() * sizeof(int),
+                               hipMemcpyDeviceToHost, stream);
         if (e == hipSuccess)
             e = hipStreamSynchronize(stream);
-        if (e != hipSuccess) {
-            set_error("la_serve: device error %s", hipGetErrorString(e));
-            return LA_ERR_DEVICE;
-        }
         for (size_t i = 0; i < fresh.size(); ++i)
             fro2[i] = h_red[i];
         for (size_t j = fresh.size(); j < red.size(); ++j)
             delta2.push_back(h_red[j]);
         for (serve::Req *r : run)
             ((DevReq *)r->x)->cur ^= 1;
+        // an uneven request's first preconditioning step is not counted: X0 again
+        for (size_t i = 0; i < checked.size() && e == hipSuccess; ++i) {
+            serve::Req *r = checked[i];
+            DevReq *d = (DevReq *)r->x;
+            if (!h_uneven[i])
+                continue;
+            without_f16(r->plan);
+            if (!r->precond())
+                continue;
+            e = launch_scale_by_norm(d->A, r->n, d->X[0], r->n, r->m, r->n, d->scal, stream);
+            d->cur = 0;
+            d->packed = 0;
+            r->info.iters_precond = -1;   // the scheduler counts the step
+        }
+        if (e != hipSuccess) {
+            set_error("la_serve: device error %s", hipGetErrorString(e));
+            return LA_ERR_DEVICE;
+        }
         return LA_OK;
     }
 
@@ -758,7 +769,7 @@ la_status la_serve_create(la_context *ctx, const la_serve_config *cfg, void *are
         if (e == hipSuccess)
             e = hipHostMalloc((void **)&x.h_stage, kBandReserve, hipHostMallocDefault);
         if (e == hipSuccess)
-            e = hipHostMalloc((void **)&x.h_red, 2 * kMaxSlots * sizeof(double),
+            e = hipHostMalloc((void **)&x.h_red, kRedBytes,
                               hipHostMallocDefault);
         bands.push_back(&x);
     }
