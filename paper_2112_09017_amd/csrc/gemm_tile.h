@@ -798,9 +798,10 @@ __device__ __forceinline__ void round_tile_coords(const GemmDesc &d, int &tm, in
 
 // Epilogue of one tile: out = alpha acc + beta E + gamma I, written to C (and
 // mirrored for a full Gram), with the FP64 sum of (out - E)^2 for the step
-// norm.  row0, col0: the first row and column acc holds.  Each 32 x 32 block's 16 addend values per lane are loaded together,
-// before any of the block's stores (C may alias E, so a load placed after a
-// store would have to wait for it), and one explicit wait for them follows:
+// norm.  row0, col0: the first row and column acc holds.  Each 32 x 32 block's
+// 16 addend values per lane are loaded together, before any of the block's
+// stores (C may alias E, so a load placed after a store would have to wait for
+// it), and one explicit wait for them follows:
 // without it the per-element bounds branches make the compiler wait for every
 // outstanding memory operation, stores included, before each element.
 template <int PREC>
@@ -829,13 +830,15 @@ __device__ __forceinline__ void epilogue(const GemmDesc &d,
     constexpr bool ROWS = base_prec(PREC) == PREC_F16X3 && (PREC & kPacked) != 0;
     const bool rowed = ROWS && d.row_max != nullptr;
     uint32_t cmax[G::FN] = {};
-    // A whole tile off the diagonal of a product without addend and step norm only
-    // scales and stores: in the general loop below every element has its bounds,
-    // diagonal, mirror and FP64 terms computed (8000 x 8000 x 91 at 3xBF16 120 ->
-    // 85 us, 16384 x 16384 x 64 446 -> 271)
+    // A whole tile of a product without addend and step norm only scales and stores:
+    // in the general loop below every element has its bounds, diagonal, mirror and
+    // FP64 terms computed (8000 x 8000 x 91 at 3xBF16 120 -> 85 us, 16384 x 16384 x
+    // 64 446 -> 271).  Its elements on the diagonal are stored once more: tiles on it
+    // in the general loop fall behind the others, and the workgroups of an XCD then
+    // no longer read the same panels at the same time (16384^2 x 32768 on packed
+    // operands reads 48 GiB so, 57 otherwise; 4096^3 at 3xBF16 347 us, 367 otherwise)
     if (!ROWS && !d.E && !want_ss && !d.gram && row0 == rlo && col0 == clo &&
-        rspan == (uint32_t)Cfg<PREC>::BM && cspan == (uint32_t)Cfg<PREC>::BN &&
-        (rend <= clo || cend <= rlo)) {
+        rspan == (uint32_t)Cfg<PREC>::BM && cspan == (uint32_t)Cfg<PREC>::BN) {
         auto p = gmem(d.C) + rb * d.ldc + cb;
 #pragma clang loop unroll(full)
         for (int i = 0; i < G::FM; ++i)
@@ -846,6 +849,22 @@ __device__ __forceinline__ void epilogue(const GemmDesc &d,
                     p[j * 32] = d.alpha * acc[i][j][e];
                 p += (e & 3) == 3 ? 5 * d.ldc : d.ldc;
             }
+        if (rend > clo && cend > rlo) {
+#pragma clang fp contract(off)   // rounded as in the general loop
+            int below = (int)(cb - rb);   // rows from this lane's first to the diagonal
+#pragma clang loop unroll(full)
+            for (int i = 0; i < G::FM; ++i)
+#pragma clang loop unroll(full)
+                for (int j = 0; j < G::FN; ++j) {
+                    asm volatile("" : "+v"(below));
+                    const int in = below + 32 * (j - i);
+#pragma clang loop unroll(full)
+                    for (int e = 0; e < 16; ++e)
+                        if (in == (e >> 2) * 8 + (e & 3))
+                            gmem(d.C)[(rb + i * 32 + in) * d.ldc + cb + j * 32] =
+                                d.alpha * acc[i][j][e] + d.gamma;
+                }
+        }
         return;
     }
 #pragma clang loop unroll(full)
@@ -1382,8 +1401,9 @@ __global__ void __launch_bounds__(256) pack_x3_kernel(const float *__restrict__ 
                         cr += few;
                         const uint32_t ck =
                             (uint32_t)__popc(lane < 32 ? (uint32_t)b : (uint32_t)(b >> 32));
+                        uint32_t *col = check.counts + R + k0 + kk + j;
                         if ((lane & 31) == 0 && ck)
-                            bad |= 4 * (int64_t)(atomicAdd(check.counts + R + k0 + kk + j, ck) + ck) > R;
+                            bad |= 4 * (int64_t)(atomicAdd(col, ck) + ck) > R;
                     }
                     if (cr)
                         bad |= 4 * (int64_t)(atomicAdd(check.counts + r0 + r, cr) + cr) > K;
