@@ -298,7 +298,8 @@ la_status la_inverse(la_context *ctx, int64_t n, int64_t m, const float *A, int6
  * entries in each of its rows and columns are at least 2^-17 of the largest beside them),
  * its equivalent of two scaled fp16 terms per operand: the result then depends, within
  * that accuracy, on whether the workspace holds more than the three buffers.  Both run
- * on hip_stream and return after the last kernel has completed.  F must not overlap A or the workspace.
+ * on hip_stream and return after the last kernel has completed.  F must not overlap A or
+ * the workspace.
  * ---------------------------------------------------------------------- */
 size_t la_matfunc_workspace_size(int64_t m, int64_t n);
 

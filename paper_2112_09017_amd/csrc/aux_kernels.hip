@@ -851,8 +851,8 @@ hipError_t launch_uneven(const float *X, int64_t ldx, int64_t m, int64_t n, cons
         return hipErrorInvalidValue;
     const int64_t strips = (m + kEvenRows - 1) / kEvenRows;
     const int64_t gy = std::min<int64_t>(strips, std::max<int64_t>(1, 2048 / gx));
-    hipLaunchKernelGGL(small_count_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(kThreads), 0, s, X,
-                       ldx, m, n, nrm2, counts, flag, st);
+    hipLaunchKernelGGL(small_count_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(kThreads), 0, s,
+                       X, ldx, m, n, nrm2, counts, flag, st);
     return hipGetLastError();
 }
 

@@ -833,7 +833,7 @@ __device__ __forceinline__ void epilogue(const GemmDesc &d,
     // A whole tile of a product without addend and step norm only scales and stores:
     // in the general loop below every element has its bounds, diagonal, mirror and
     // FP64 terms computed (8000 x 8000 x 91 at 3xBF16 120 -> 85 us, 16384 x 16384 x
-    // 64 446 -> 271).  Its elements on the diagonal are stored once more: tiles on it
+    // 64 446 -> 260).  Its elements on the diagonal are stored once more: tiles on it
     // in the general loop fall behind the others, and the workgroups of an XCD then
     // no longer read the same panels at the same time (16384^2 x 32768 on packed
     // operands reads 48 GiB so, 57 otherwise; 4096^3 at 3xBF16 347 us, 367 otherwise)

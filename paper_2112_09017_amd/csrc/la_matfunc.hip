@@ -132,8 +132,8 @@ hipError_t f16_pack_a(const F16 &f, const float *X, int64_t ldx, int kc, int64_t
 // out = alpha op(A) Y + beta E + gamma I with op(A) (M x K) in f.pa and Y (K x N,
 // columns' maxima in f.cb[c]); the columns' maxima of out go to f.cb[c ^ 1].  Nothing is
 // done where f.uneven[w].
-hipError_t f16_product(const F16 &f, int w, int c, const float *Y, int64_t ldy, float *out, int64_t ldo,
-                       int64_t M, int64_t N, int64_t K, float alpha, float beta, const float *E,
+hipError_t f16_product(const F16 &f, int w, int c, const float *Y, int64_t ldy, float *out,
+                       int64_t ldo, int64_t M, int64_t N, int64_t K, float alpha, float beta, const float *E,
                        int64_t lde, float gamma, hipStream_t s)
 {
     GemmDesc d;
@@ -329,13 +329,14 @@ la_status la_matfunc_odd(la_context *ctx, int64_t m, int64_t n, const float *A, 
         cur = 0;
         LA_HIP(launch_affine(G, n, P[0], n, n, coef[d], coef[d - 1], s), "la_matfunc_odd: affine");
         if (f_horner) {
-            LA_HIP(f16_pack_a(f, G, n, 1, n, n, 0, kUnevenG, f.counts[1], s), "la_matfunc_odd: pack");
+            LA_HIP(f16_pack_a(f, G, n, 1, n, n, 0, kUnevenG, f.counts[1], s),
+                   "la_matfunc_odd: pack");
             LA_HIP(launch_absmax(P[0], n, n, n, 0, f.cb[0], s), "la_matfunc_odd: pack");
         }
         for (int j = d - 2; j >= 0; --j) {
             if (f_horner)
-                LA_HIP(f16_product(f, 0, cur, P[cur], n, P[cur ^ 1], n, n, n, n, 1.0f, 0.0f, nullptr,
-                                   0, (float)coef[j], s),
+                LA_HIP(f16_product(f, 0, cur, P[cur], n, P[cur ^ 1], n, n, n, n, 1.0f, 0.0f,
+                                   nullptr, 0, (float)coef[j], s),
                        "la_matfunc_odd: horner");
             else
                 LA_HIP(product(pr, G, n, P[cur], n, P[cur ^ 1], n, n, n, n, 1.0f, 0.0f, nullptr, 0,
